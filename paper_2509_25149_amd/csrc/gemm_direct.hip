@@ -1,0 +1,278 @@
+// Block-scaled GEMM straight from the packed codes for gfx950 (App. B.3 Eq. 5): no scratch, any K that is a multiple of
+// 16.  The form for products that do not fill the chip with 256 x 256 tiles -- few tokens, small layers -- and for
+// contraction lengths that are not a multiple of 64.
+//
+// A wavefront owns MB x NB blocks of 16 x 16 outputs and every WK-th step of 128 k; the WK wavefronts of a workgroup own
+// the same outputs and add their sums through LDS at the end.  No barrier in the loop: a wavefront loads the codes and
+// scales of its own rows into registers one step ahead, passes them through its own piece of LDS, decodes them to FP16
+// (value * block scale, exact) and feeds the 16x16x32 MFMA.
+//   - Through LDS, because a load in the MFMA's lane order (16 consecutive lanes = 16 rows) touches 16 cache lines per 16
+//     lanes; four lanes to a row's 64 bytes touch 4.  64 x 20480 x 5120: 35 us without this detour, 27 with.
+//   - Steps of 128 k rather than 256: half the LDS and the staging registers per wavefront, so that 640 workgroups are
+//     resident at once (27 -> 22 us), and less to lose where K is not a multiple of the step.
+//   - What bounds it is the issue of vector instructions: a 16 x 32 fragment takes 32 of them (cvt + pk_mul per two
+//     values) and serves 4 (MB or NB) MFMAs, so a decoded fragment's k + 1 is spread over the MFMAs of k.  Decoding A once per
+//     workgroup and sharing it through LDS needs a barrier per step and was slower (33 against 22 us, 52 against 38).
+// Measured (us; before = whatever the call took then): 64 x 20480 x 5120 133 -> 22, 16 x 20480 x 5120 131 -> 14.6 (4.0 TB/s of
+// codes), 512 x 5120 x 5120 101 -> 38, 256 x 256 x 512 18 -> 3.4, 1040 x 1296 x 2064 44 -> 15.
+
+#include "nvfp4_internal.h"
+#include "nvfp4_device.h"
+#include "gemm_epilogue.h"
+
+namespace nvfp4 {
+namespace {
+
+constexpr int kStepK = 128;               // k per step: 64 bytes of codes and 8 of scales per row, 1 KiB of codes per 16-row block
+constexpr int kPiece = 1024;              // one 16 x 32 FP16 MFMA fragment
+constexpr int kCodeBytes = 1024, kScaleBytes = 128;   // of a 16-row block and step
+
+struct __attribute__((packed, aligned(8))) Codes16 { uint32_t w[4]; };
+typedef uint16_t u16_any __attribute__((aligned(1)));
+
+// What a lane holds of a 16-row block and step as loaded: row lane / 4, 16-byte chunk lane % 4 (32 codes), its 2 scales.
+struct Loaded {
+  uint4 c;
+  uint32_t s;
+};
+
+__device__ __forceinline__ uint32_t word(const uint4& c, int t) { return t == 0 ? c.x : t == 1 ? c.y : t == 2 ? c.z : c.w; }
+
+// 8 codes of k 8 t .. 8 t + 7 of a 32-code chunk, times the block scale: exact in FP16
+__device__ __forceinline__ half8v decode8(const uint4& c, half2v s2, int t) {
+  const _Float16 sv = (t >> 1) ? s2.y : s2.x;
+  const half2v s = {sv, sv};
+  const uint32_t w = word(c, t);
+  union { half2v h[4]; half8v v; } o;
+  o.h[0] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 0) * s;
+  o.h[1] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 1) * s;
+  o.h[2] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 2) * s;
+  o.h[3] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 3) * s;
+  return o.v;
+}
+__device__ __forceinline__ half2v scales2(uint32_t s) { return __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(static_cast<int>(s), 1.0f, false); }
+
+// MB x NB blocks of 16 x 16 outputs per wavefront, WK wavefronts per workgroup that split K.
+template <int MB, int NB, int WK>
+struct Shape {
+  static constexpr int kTM = MB * 16, kTN = NB * 16, kThreads = WK * 64, kBlocks = MB + NB;
+  static constexpr int kStage = kBlocks * (kCodeBytes + kScaleBytes);       // one step's codes and scales, per wavefront
+  static constexpr int kSum = WK > 1 ? MB * NB * 1024 : 0;
+  static constexpr int kWaveBytes = kStage > kSum ? kStage : kSum;
+  static constexpr int kLdsBytes = WK * kWaveBytes;
+};
+
+template <int MB, int NB, int WK, int kOcc, bool kBf16Out>
+__global__ __launch_bounds__(WK * 64, kOcc) void gemm_direct_kernel(Operand A, Operand B, int K, void* __restrict__ Dv, int64_t ldd,
+                                                                  bool accumulate, int tiles_m, int tiles_n) {
+  using S = Shape<MB, NB, WK>;
+  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+  const int lane = threadIdx.x & 63;
+  const int wk = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  const int num_tiles = tiles_m * tiles_n;
+  int pid = blockIdx.x;
+  if ((num_tiles & 7) == 0) pid = (pid & 7) * (num_tiles >> 3) + (pid >> 3);
+  int tm, tn;
+  tile_coordinates(pid, tiles_m, tiles_n, tm, tn);
+  const int l16 = lane & 15, q = lane >> 4;
+  const int row4 = lane >> 2, c4 = lane & 3;      // loading: row and chunk of the lane
+  const int M = static_cast<int>(A.outer), N = static_cast<int>(B.outer);
+  const int m0 = tm * S::kTM, n0 = tn * S::kTN;
+  uint8_t* const mine = lds + wk * S::kWaveBytes;
+
+  // Wave-uniform bases plus one 32-bit lane offset; blocks 0 .. MB-1 are A's, the others B's.  Blocks past the
+  // end of an operand are replaced by its last (they feed outputs that are never stored).
+  const int code_ld = K / 2, scale_ld = K / 16;
+  const uint8_t *cp[S::kBlocks], *sp[S::kBlocks];
+#pragma unroll
+  for (int i = 0; i < S::kBlocks; ++i) {
+    const int64_t row = i < MB ? min(m0 + i * 16, M - 16) : min(n0 + (i - MB) * 16, N - 16);
+    cp[i] = (i < MB ? A.codes : B.codes) + row * code_ld;
+    sp[i] = (i < MB ? A.scales : B.scales) + row * scale_ld;
+  }
+  const uint32_t code_off = static_cast<uint32_t>(row4 * code_ld + c4 * 16), scale_off = static_cast<uint32_t>(row4 * scale_ld + c4 * 2);
+
+  float4v acc[MB][NB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) acc[i][j] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
+
+  Loaded ld[S::kBlocks];
+  auto load = [&](int i, int step) {
+    const Codes16 c = *reinterpret_cast<const Codes16*>(cp[i] + step * 64 + code_off);
+    ld[i].c = make_uint4(c.w[0], c.w[1], c.w[2], c.w[3]);
+    ld[i].s = *reinterpret_cast<const u16_any*>(sp[i] + step * 8 + scale_off);
+  };
+  // The last, partial step (rest = 16 .. 112 k): a lane's chunk is whole, half there or absent; what is absent is read
+  // from where the row still has bytes and gets scale 0.
+  const int full = K / kStepK, rest = K - full * kStepK;
+  auto load_tail = [&](int i) {
+    const bool in0 = c4 * 32 < rest, in1 = c4 * 32 + 16 < rest;
+    const uint32_t co = in0 ? code_off : code_off - c4 * 16, so = in0 ? scale_off : scale_off - c4 * 2;
+    const uint2 lo = *reinterpret_cast<const uint2*>(cp[i] + full * 64 + co);
+    const uint2 hi = *reinterpret_cast<const uint2*>(cp[i] + full * 64 + co + (in1 ? 8 : 0));
+    const uint32_t s0 = sp[i][full * 8 + so], s1 = sp[i][full * 8 + so + (in1 ? 1 : 0)];
+    ld[i].c = make_uint4(lo.x, lo.y, hi.x, hi.y);
+    ld[i].s = (in0 ? s0 : 0u) | (in1 ? s1 << 8 : 0u);
+  };
+  auto stage_out = [&]() {
+#pragma unroll
+    for (int i = 0; i < S::kBlocks; ++i) {
+      *reinterpret_cast<uint4*>(mine + i * kCodeBytes + (row4 * 4 + (c4 ^ (row4 >> 2))) * 16) = ld[i].c;
+      *reinterpret_cast<uint16_t*>(mine + S::kBlocks * kCodeBytes + i * kScaleBytes + lane * 2) = static_cast<uint16_t>(ld[i].s);
+    }
+  };
+  auto multiply = [&]() {
+    uint4 c[S::kBlocks];
+    half2v sc[S::kBlocks];
+#pragma unroll
+    for (int i = 0; i < S::kBlocks; ++i) {
+      c[i] = *reinterpret_cast<const uint4*>(mine + i * kCodeBytes + (l16 * 4 + (q ^ (l16 >> 2))) * 16);
+      sc[i] = scales2(*reinterpret_cast<const uint16_t*>(mine + S::kBlocks * kCodeBytes + i * kScaleBytes + l16 * 8 + q * 2));
+    }
+    half8v f[2][S::kBlocks];
+#pragma unroll
+    for (int i = 0; i < S::kBlocks; ++i) f[0][i] = decode8(c[i], sc[i], 0);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      if (t < 3) {
+#pragma unroll
+        for (int i = 0; i < S::kBlocks; ++i) f[(t + 1) & 1][i] = decode8(c[i], sc[i], t + 1);
+      }
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(f[t & 1][MB + j], f[t & 1][i], acc[i][j], 0, 0, 0);
+      if (t < 3) {   // the next fragments' decode spread over these MFMAs
+        constexpr int kValu = (S::kBlocks * 8 + MB * NB - 1) / (MB * NB);
+#pragma unroll
+        for (int g = 0; g < MB * NB; ++g) {
+          __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x2, kValu, 0);
+        }
+      }
+    }
+  };
+  const bool tail = rest && full % WK == wk;
+  if (tail) {
+#pragma unroll
+    for (int i = 0; i < S::kBlocks; ++i) load_tail(i);
+    stage_out();
+  }
+  if (wk < full) {
+#pragma unroll
+    for (int i = 0; i < S::kBlocks; ++i) load(i, wk);
+  }
+  if (tail) multiply();
+#pragma unroll 1
+  for (int step = wk; step < full; step += WK) {
+    stage_out();
+#pragma unroll
+    for (int i = 0; i < S::kBlocks; ++i) load(i, step + WK < full ? step + WK : step);
+    multiply();
+  }
+
+  const TensorScales ts{A.ts, B.ts, A.ts_per_row != 0, B.ts_per_row != 0};
+  const bool vec = ts.a_per_row || ts.b_per_row;
+  const float out_scale = vec ? 0.0f : A.ts[0] * B.ts[0];
+  auto store = [&](float4v v, int i, int j) {
+    const int m = m0 + i * 16 + l16, n = n0 + j * 16 + q * 4;
+    if (m < M && n < N) {
+      v *= scale4(ts, out_scale, vec, true, m, n);
+      if (kBf16Out) {
+        uint2 o;
+        o.x = f32x2_to_bf16(v[0], v[1]);
+        o.y = f32x2_to_bf16(v[2], v[3]);
+        *reinterpret_cast<uint2*>(static_cast<uint16_t*>(Dv) + m * ldd + n) = o;
+      } else {
+        float* d = static_cast<float*>(Dv) + m * ldd + n;
+        if (accumulate) v += *reinterpret_cast<const float4v*>(d);
+        *reinterpret_cast<float4v*>(d) = v;
+      }
+    }
+  };
+  if constexpr (WK == 1) {
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) store(acc[i][j], i, j);
+  } else {
+    constexpr int kFrags = MB * NB;
+    __syncthreads();   // everybody is done with the staged operands
+#pragma unroll
+    for (int f = 0; f < kFrags; ++f) reinterpret_cast<float4v*>(mine)[f * 64 + lane] = acc[f / NB][f % NB];
+    __syncthreads();
+    for (int f = wk; f < kFrags; f += WK) {
+      const uint8_t* p = lds + (f * 64 + lane) * 16;
+      float4v v = *reinterpret_cast<const float4v*>(p);
+#pragma unroll
+      for (int w = 1; w < WK; ++w) v += *reinterpret_cast<const float4v*>(p + w * S::kWaveBytes);
+      store(v, f / NB, f % NB);
+    }
+  }
+}
+
+}  // namespace
+
+// The tile shapes the kernel comes in.  `cost`: time of one step (128 k) of one round of 256 tiles, in units of 0.247 us,
+// fitted to the measured times of 13 shapes (it reproduces them within 5 %).  A shape's time is then
+//   3 us + 0.247 us * cost * steps * ceil(tiles / 256),
+// and the smallest wins: large tiles decode less per product, small ones fill the chip.  Both sides of the choice, us:
+// 64 x 20480 x 5120: 4x3 22.3, 4x4 26.7, 2x2 27.2; 512 x 5120 x 5120: 4x4 37.8, 4x3 39.4; 32 x 5120 x 5120: 2x2 7.7, 1x2 8.8, 4x3 > 10.
+struct DirectShape {
+  int mb, nb;
+  double cost;
+};
+constexpr DirectShape kDirectShapes[4] = {{1, 2, 0.30}, {2, 2, 0.46}, {4, 3, 0.96}, {4, 4, 1.19}};
+
+static int64_t direct_tiles(const DirectShape& d, int64_t M, int64_t N) {
+  return ((M + d.mb * 16 - 1) / (d.mb * 16)) * ((N + d.nb * 16 - 1) / (d.nb * 16));
+}
+
+static double direct_shape_us(const DirectShape& d, int64_t M, int64_t N, int64_t K) {
+  const int64_t rounds = (direct_tiles(d, M, N) + 255) / 256, steps = (K + kStepK - 1) / kStepK;
+  return 3.0 + 0.247 * d.cost * static_cast<double>(steps) * static_cast<double>(rounds);
+}
+
+static int pick_direct_shape(int64_t M, int64_t N, int64_t K) {
+  int best = 0;
+  for (int i = 1; i < 4; ++i)
+    if (direct_shape_us(kDirectShapes[i], M, N, K) < direct_shape_us(kDirectShapes[best], M, N, K)) best = i;
+  return best;
+}
+
+double gemm_direct_us(int64_t M, int64_t N, int64_t K) { return direct_shape_us(kDirectShapes[pick_direct_shape(M, N, K)], M, N, K); }
+
+template <int MB, int NB, int WK, bool kBf16Out>
+static hipError_t launch_shape(const GemmArgs& g, hipStream_t s) {
+  using S = Shape<MB, NB, WK>;
+  static PerDeviceOnce once;
+  const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&gemm_direct_kernel<MB, NB, WK, 2, kBf16Out>), S::kLdsBytes, once);
+  if (e != hipSuccess) return e;
+  const int tiles_m = static_cast<int>((g.a.outer + S::kTM - 1) / S::kTM), tiles_n = static_cast<int>((g.b.outer + S::kTN - 1) / S::kTN);
+  hipLaunchKernelGGL((gemm_direct_kernel<MB, NB, WK, 2, kBf16Out>), dim3(static_cast<unsigned>(tiles_m * tiles_n)), dim3(S::kThreads),
+                     S::kLdsBytes, s, g.a, g.b, static_cast<int>(g.K), g.d, g.ldd, g.accumulate, tiles_m, tiles_n);
+  return hipGetLastError();
+}
+
+template <bool kBf16Out>
+static hipError_t launch_direct(const GemmArgs& g, hipStream_t s) {
+  const int shape = pick_direct_shape(g.a.outer, g.b.outer, g.K);
+  switch (shape) {
+    // 16 x 32 tiles: enough of them to fill the chip four times over do better with fewer wavefronts on each (16 x 20480 x
+    // 5120: 14.6 against 15.7 us), few with more (32 x 5120 x 5120 in these tiles: 9.4 against 8.8)
+    case 0: return direct_tiles(kDirectShapes[0], g.a.outer, g.b.outer) >= 512 ? launch_shape<1, 2, 4, kBf16Out>(g, s) : launch_shape<1, 2, 8, kBf16Out>(g, s);
+    case 1: return launch_shape<2, 2, 8, kBf16Out>(g, s);
+    case 2: return launch_shape<4, 3, 4, kBf16Out>(g, s);
+    default: return launch_shape<4, 4, 4, kBf16Out>(g, s);
+  }
+}
+
+hipError_t launch_gemm_direct(const GemmArgs& g, hipStream_t s) {
+  // 32-bit rows, and byte offsets within a 16-row block
+  if (g.a.outer > 0x7fffffff || g.b.outer > 0x7fffffff || g.K > (int64_t{1} << 27)) return hipErrorInvalidValue;
+  return g.out_bf16 ? launch_direct<true>(g, s) : launch_direct<false>(g, s);
+}
+
+}  // namespace nvfp4

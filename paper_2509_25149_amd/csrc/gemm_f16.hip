@@ -524,6 +524,24 @@ bool gemm_two_pass_usable(const GemmArgs& g) {
          reinterpret_cast<uintptr_t>(g.b.scales) % 4 == 0;
 }
 
+// Expected time of this route: what is still to decode (codes and scales in, FP16 out) at 4.7 TB/s, then rounds of 256
+// tiles at 16 ns per k while the chip is partly filled (160 tiles, K = 5120: 83 us) up to 22.5 when it is full (the clock
+// drops with the matrix pipes busy), a split last round counted as the fraction it is.
+double gemm_two_pass_us(const GemmArgs& g) {
+  const int64_t M = g.a.outer, N = g.b.outer;
+  const double k = static_cast<double>(g.K);
+  const int64_t tiles = ((M + TM - 1) / TM) * ((N + TN - 1) / TN);
+  const TailPlan p = plan_tail(M, N, g.K);
+  double rounds = static_cast<double>((tiles - p.tail + kCUs - 1) / kCUs), us = 4.0;
+  if (p.tail) {
+    rounds += 1.0 / p.splits;
+    us += 15.0;
+  }
+  const int64_t rows = (g.a.fp16 ? 0 : M) + (g.b.fp16 ? 0 : N);
+  us += static_cast<double>(rows) * k * 2.5625 / 4.7e6 + (rows ? 2.0 : 0.0);
+  return us + rounds * k * (tiles >= kCUs ? 0.0225 : 0.0160);
+}
+
 #define NVFP4_LAUNCH_F16(BF16, ROWSCALES, SPLIT)                                                                  \
   do {                                                                                                            \
     static PerDeviceOnce once;                                                                                    \

@@ -83,6 +83,10 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);
 bool gemm_two_pass_usable(const GemmArgs& g);
 hipError_t launch_gemm_two_pass(const GemmArgs& g, hipStream_t s);
+double gemm_two_pass_us(const GemmArgs& g);   // expected time, to choose between the routes
+// Straight from the packed codes, without scratch, any K
+hipError_t launch_gemm_direct(const GemmArgs& g, hipStream_t s);
+double gemm_direct_us(int64_t M, int64_t N, int64_t K);
 // Decodes one operand (codes [outer, K/2], scales [outer, K/16]) to FP16 [outer, K]
 hipError_t launch_predecode(const Operand& op, int64_t K, void* fp16_out, hipStream_t s);
 
