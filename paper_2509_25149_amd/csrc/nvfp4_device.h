@@ -60,20 +60,14 @@ __device__ __forceinline__ float e4m3_decode(uint32_t code) {
   return __builtin_amdgcn_cvt_f32_fp8(static_cast<int>(code), 0);
 }
 
-// x / 6 with IEEE round-to-nearest, for finite x >= 0, mostly without the
-// hardware division sequence: one multiply by the rounded reciprocal, then one
-// Newton-style correction with an exact FMA residual.  That is bit-identical to
-// x / 6.0f for every x >= 2^-124 (below, the residual leaves the normal range);
-// if any lane of the wavefront is below, the whole wavefront divides for real.
-// Checked against IEEE division over all finite non-negative inputs by the
-// self-test.  The result feeds the stored block scale of App. B.2 Eq. 2.
-__device__ __forceinline__ float div_by_6(float x) {
-  if (__builtin_amdgcn_ballot_w64(x < 0x1p-124f) != 0) return x / 6.0f;
-  const float c = 0.16666667163372040f;           // RN(1/6)
-  const float q = x * c;
-  const float r = __builtin_fmaf(-q, 6.0f, x);     // exact residual x - 6q
-  return __builtin_fmaf(r, c, q);
-}
+// x / 6 with IEEE round-to-nearest, for x >= 0, without a branch: a binary64 product with the rounded reciprocal, rounded
+// once to binary32.  The two roundings are innocent: the distance of x / 6 from a point half-way between two normal
+// binary32 numbers is at least 2^-27 of it, and where the quotient is subnormal and half-way exactly, the product rounds to
+// that very point.  Checked against IEEE division over all finite non-negative inputs by the self-test.  The result feeds
+// the stored block scale of App. B.2 Eq. 2.
+// (A binary32 form with an FMA correction needs the real division below 2^-124 and so for every all-zero block; the
+// wavefront-wide branch to it cut the row and column passes of a patch into 24 pieces that could not overlap.)
+__device__ __forceinline__ float div_by_6(float x) { return static_cast<float>(static_cast<double>(x) * (1.0 / 6.0)); }
 
 // Stored block scale and the "real" block encode scale (App. B.2):
 //   code    = e4m3(amax_b / 6 * s_enc)

@@ -1,10 +1,10 @@
 // NVFP4 quantizer kernels for gfx950 (App. B Eq. 1-4; Sec. 4.2-4.4; App. C).
 //
 // Work decomposition shared by both passes: a lane owns a 16-row x 8-column
-// patch of the bf16 tensor (sixteen 128-bit loads, one per row); a wavefront
-// owns 16 rows x 512 columns, so each of its loads reads 1 KiB of contiguous
-// memory; a 256-thread workgroup covers 128 rows x 512 columns (four wavefronts,
-// two 16-row groups each).  With this patch
+// patch of the bf16 tensor (sixteen 128-bit loads, one per row).  In the amax
+// pass a wavefront spans 16 rows x 512 columns and walks down the rows; in the
+// cast pass it is one patch per lane, two 16-row groups x 256 columns, and a
+// 256-thread workgroup covers 128 rows x 256 columns.  With this patch
 //   - a 1x16 block of the row copy is split over two neighbouring lanes
 //     (one cross-lane exchange of the half-block amax),
 //   - a 1x16 block of the col copy (16 consecutive rows of one column) sits
@@ -13,8 +13,8 @@
 //   - a 16x16 weight tile is exactly two neighbouring lanes,
 //   - the eight columns of one row are the eight elements served by one
 //     Philox call, whose output is shared by the row and the col copy.
-// Row codes leave as one dword per lane and row (256 contiguous bytes per
-// wavefront).  The transposed col copy, its scales and the row scales are staged
+// Row codes leave as one dword per lane and row (128 contiguous bytes per
+// 16-row group).  The transposed col copy, its scales and the row scales are staged
 // in LDS and written back as contiguous 128-bit / 64-bit pieces: 64 bytes of
 // codes per column per workgroup instead of scattered 8-byte stores.
 #include "nvfp4_internal.h"
@@ -25,10 +25,10 @@ namespace nvfp4 {
 
 // ---------------------------------------------------------------- pass 1: amax (App. B.1)
 // Every workgroup writes its own maxima (raw tensor / rotated tensor) into its
-// slot of the workspace; a one-workgroup kernel folds the slots.  No atomics:
+// slot of the workspace; whoever needs the tensor's folds the slots.  No atomics:
 // thousands of same-address atomics serialise in L2 and cost more than the pass.
 // The raw maximum is always taken, also when only a rotated copy is asked for: it is the one place where a NaN in
-// the input shows (the floating-point maxima of the rotated values skip NaNs), and amax_finalize_kernel carries a
+// the input shows (the floating-point maxima of the rotated values skip NaNs), and the fold carries a
 // non-finite raw maximum over into the rotated one.
 template <int kRht>   // kRht: 0, or the rotation size 2, 4 or 16 (sign_mask: the d signs repeated over 16 bits)
 __global__ __launch_bounds__(kThreads) void amax_kernel(const uint16_t* __restrict__ x, int64_t rows,
@@ -36,13 +36,12 @@ __global__ __launch_bounds__(kThreads) void amax_kernel(const uint16_t* __restri
                                                         uint32_t* __restrict__ ws) {
   __shared__ uint32_t red[2][4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t col0 = static_cast<int64_t>(blockIdx.x) * kWaveCols + lane * 8;
+  const int64_t col0 = static_cast<int64_t>(blockIdx.x) * kWaveCols + lane * 8, ngroups = rows / 16;
   uint32_t m_raw = 0, m_rot = 0;
   float f_rot = 0.0f;
+  if (col0 < cols) {
 #pragma unroll 1
-  for (int gi = 0; gi < kGroupsPerWave; ++gi) {
-    const int64_t group = static_cast<int64_t>(blockIdx.y) * kGroupsPerBlock + wave * kGroupsPerWave + gi;
-    if (col0 < cols && group * 16 < rows) {
+    for (int64_t group = static_cast<int64_t>(blockIdx.y) * 4 + wave; group < ngroups; group += static_cast<int64_t>(gridDim.y) * 4) {
       Patch p;
       load_patch(x, ld, group * 16, col0, p);
       m_raw = max(m_raw, patch_amax_bits(p));
@@ -76,30 +75,65 @@ __global__ __launch_bounds__(kThreads) void amax_kernel(const uint16_t* __restri
 }
 
 // ---------------------------------------------------------------- pass 2: cast
-
-
-
+// A workgroup is four wavefronts with one patch per lane: a wavefront spans two 16-row groups x 256 columns, a workgroup 128
+// rows x 256 columns, which is 64 bytes of codes per column of the col copy and 128 per row of the row copy.  (One
+// patch per lane instead of two 16-row groups one after the other: 256 x 512 22.7 -> 13.1 us per call, 1040 x 2064 49 -> 15.7.
+// Wavefronts of 16 rows x 512 columns leave 32-byte pieces of col codes, 8192 x 5120 47 -> 57 us; 64 x 128 no better than this.)
+// What bounds it: large tensors the memory system (all calls, both passes, bytes over time: W 5120 x 20480 6.2 TB/s where a
+// plain copy of this card runs at 4.6 - 5.1), with stochastic rounding the vector pipe (Philox and one conversion per
+// value), small ones the chain load - amax - scale - table - codes of one patch.
+// maxima: n raw maxima, then n rotated ones (pass 1's slots; n = 1: the tensor's own), folded by every workgroup while its
+// patch is on its way from memory -- a launch of its own for that cost 5 us and two gaps between kernels.
+// Codes leave with non-temporal stores: nothing reads them in this call, and in the memory-side cache they push out the tensor
+// that pass 1 has left there (W 104 -> 86 us, dY 8192 x 20480 SR 223 -> 213, X 8192 x 5120 47.8 -> 46.8).
+using CastTile = Staged<8, 32, true>;
 template <bool kRow, bool kCol, int kRht, bool kSR, bool k2D>   // kRht as in amax_kernel
 __global__ __launch_bounds__(kThreads, 2) void cast_kernel(
     const uint16_t* __restrict__ x, int64_t rows, int64_t cols, int64_t ld,
-    const uint32_t* __restrict__ ws, uint32_t sign_mask, uint32_t key0, uint32_t key1,
+    const uint32_t* __restrict__ maxima, uint32_t n_maxima, uint32_t sign_mask, uint32_t key0, uint32_t key1,
     uint8_t* __restrict__ row_codes, uint8_t* __restrict__ row_scales, float* __restrict__ row_ts,
-    uint8_t* __restrict__ col_codes, uint8_t* __restrict__ col_scales, float* __restrict__ col_ts, int reverse) {
-  __shared__ __attribute__((aligned(16))) uint8_t st_col_codes[kCol ? kColCodesBytes : 16];
-  __shared__ __attribute__((aligned(16))) uint8_t st_col_scales[kCol ? kColScalesBytes : 16];
-  __shared__ __attribute__((aligned(16))) uint8_t st_row_scales[kRow ? kRowScalesBytes : 16];
+    uint8_t* __restrict__ col_codes, uint8_t* __restrict__ col_scales, float* __restrict__ col_ts, int reverse, int stream) {
+  using T = CastTile;
+  __shared__ __attribute__((aligned(16))) uint8_t st_col_codes[kCol ? T::kColCodesBytes : 16];
+  __shared__ __attribute__((aligned(16))) uint8_t st_col_scales[kCol ? T::kColScalesBytes : 16];
+  __shared__ __attribute__((aligned(16))) uint8_t st_row_scales[kRow ? T::kRowScalesBytes : 16];
   __shared__ float lut_row[128], lut_col[128];  // block encode scale per stored E4M3 code
+  __shared__ uint32_t red[2][4];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & (T::kLanes - 1), wave = tid >> 6;
+  const int gl = tid / T::kLanes;                // group index inside the tile
   const unsigned bx = reverse ? gridDim.x - 1 - blockIdx.x : blockIdx.x, by = reverse ? gridDim.y - 1 - blockIdx.y : blockIdx.y;
-  const int64_t colblk = static_cast<int64_t>(bx) * kWaveCols;
+  const int64_t colblk = static_cast<int64_t>(bx) * T::kCols;
   const int64_t col0 = colblk + lane * 8;
-  const int64_t group0 = static_cast<int64_t>(by) * kGroupsPerBlock;
-  const int64_t ngroups = rows / 16;
+  const int64_t group0 = static_cast<int64_t>(by) * T::kGroups, ngroups = rows / 16;
+  const int64_t group = group0 + gl, row0 = group * 16;
+  const bool active = col0 < cols && group < ngroups;
+
+  Patch p;
+  if (active) {
+    if (stream) load_patch<true>(x, ld, row0, col0, p);
+    else load_patch(x, ld, row0, col0, p);
+  }
+
+  uint32_t m_raw = 0, m_rot = 0;
+  for (uint32_t i = tid; i < n_maxima; i += kThreads) {
+    m_raw = max(m_raw, maxima[i]);
+    if (kRht) m_rot = max(m_rot, maxima[n_maxima + i]);
+  }
+  m_raw = wave_max_u32_lane63(m_raw);
+  if (kRht) m_rot = wave_max_u32_lane63(m_rot);
+  if ((tid & 63) == 63) {
+    red[0][wave] = m_raw;
+    red[1][wave] = m_rot;
+  }
+  __syncthreads();
+  m_raw = max(max(red[0][0], red[0][1]), max(red[0][2], red[0][3]));
+  m_rot = max(max(red[1][0], red[1][1]), max(red[1][2], red[1][3]));
+  if (m_raw >= 0x7F800000u) m_rot = max(m_rot, m_raw);   // a non-finite input shows in the rotated amax too
 
   // App. B.1 Eq. 1, from the amax of pass 1.
-  const float amax_raw = __uint_as_float(ws[0]);
-  const float amax_col = kRht ? __uint_as_float(ws[1]) : amax_raw;
+  const float amax_raw = __uint_as_float(m_raw);
+  const float amax_col = kRht ? __uint_as_float(m_rot) : amax_raw;
   float s_enc_r, s_dec_r, s_enc_c, s_dec_c;
   tensor_scales(amax_raw, s_enc_r, s_dec_r);
   tensor_scales(amax_col, s_enc_c, s_dec_c);
@@ -116,19 +150,7 @@ __global__ __launch_bounds__(kThreads, 2) void cast_kernel(
   }
   __syncthreads();
 
-#pragma unroll 1
-  for (int gi = 0; gi < kGroupsPerWave; ++gi) {
-    const int gl = wave * kGroupsPerWave + gi;  // group index inside the tile
-    const int64_t group = group0 + gl;
-    if (col0 >= cols || group >= ngroups) continue;
-    const int64_t row0 = group * 16;
-
-    // (Requesting both patches of the wavefront up front was tried for the kernels without stochastic rounding, which
-    // have the registers: 157 - 173 instead of 113 - 120 cost a wavefront per SIMD, and X / W went from 59 / 122 us per
-    // call to 62 / 130.)
-    Patch p;
-    load_patch(x, ld, row0, col0, p);
-
+  if (active) {
     // Random words: one Philox call per row serves the row's 8 columns.
     uint32_t rnd[16][4];
     if (kSR) {
@@ -148,8 +170,8 @@ __global__ __launch_bounds__(kThreads, 2) void cast_kernel(
     }
 
     if (kRow)
-      row_pass<kSR, k2D>(p, rnd, lane, gl, s_enc_r, lut_row, s_enc_tile, tile_code, row_codes + row0 * (cols / 2) + col0 / 2,
-                         cols / 2, st_row_scales);
+      row_pass<kSR, k2D, T>(p, rnd, lane, gl, s_enc_r, lut_row, s_enc_tile, tile_code, row_codes + row0 * (cols / 2) + col0 / 2,
+                            cols / 2, st_row_scales);
 
     if (kCol) {
 #pragma unroll
@@ -167,15 +189,15 @@ __global__ __launch_bounds__(kThreads, 2) void cast_kernel(
             hi[r] *= rht_norm<kRht>();
           }
         }
-        emit_column<kSR, k2D>(lo, 2 * t, rnd, lane, gl, s_enc_c, lut_col, s_enc_tile, tile_code, st_col_codes, st_col_scales);
-        emit_column<kSR, k2D>(hi, 2 * t + 1, rnd, lane, gl, s_enc_c, lut_col, s_enc_tile, tile_code, st_col_codes, st_col_scales);
+        emit_column<kSR, k2D, T>(lo, 2 * t, rnd, lane, gl, s_enc_c, lut_col, s_enc_tile, tile_code, st_col_codes, st_col_scales);
+        emit_column<kSR, k2D, T>(hi, 2 * t + 1, rnd, lane, gl, s_enc_c, lut_col, s_enc_tile, tile_code, st_col_codes, st_col_scales);
       }
     }
   }
   __syncthreads();
 
-  write_back_tile<kRow, kCol, kThreads>(tid, rows, cols, group0, ngroups, colblk, st_col_codes, st_col_scales,
-                                          st_row_scales, row_scales, col_codes, col_scales);
+  write_back_tile<kRow, kCol, kThreads, T>(tid, rows, cols, group0, ngroups, colblk, st_col_codes, st_col_scales,
+                                           st_row_scales, row_scales, col_codes, col_scales);
 }
 
 // ---------------------------------------------------------------- host side
@@ -188,67 +210,70 @@ size_t quantize_workspace_bytes(int64_t rows, int64_t cols) {
   return (per_tensor > per_row ? per_tensor : per_row) * sizeof(uint32_t);
 }
 
-// The cast pass walks a large tensor from its end: the amax pass has just streamed it front to back, so its tail is
-// what the 256 MB memory-side cache still holds (measured at the 12B shapes: W 124 -> 121 us, dY 250 -> 245 us per
-// call; a tensor that fits the cache whole gains nothing either way).
-static int cast_reverse(const QuantizeArgs& a) { return a.do_amax && a.rows * a.cols * 2 > (int64_t{128} << 20); }
+// How the cast pass reads a tensor that pass 1 has just streamed front to back through the 256 MB memory-side cache:
+//   above 128 MB from its end (what comes last is what the cache still holds; a smaller tensor it holds whole);
+//   above 256 MB, where most of it is gone again, from the front and with non-temporal loads, which leave the tail alone until the
+//   walk gets there (dY 8192 x 20480, 335 MB: RNE 173 -> 154 us, SR 212 -> 203; at 251 MB they are the slower: 145 against 153).
+// With the amax given nothing is in the cache: non-temporal loads only matter to others.
+constexpr int64_t kCacheBytes = int64_t{256} << 20;
+static int cast_streams(const QuantizeArgs& a) { return a.rows * a.cols * 2 > kCacheBytes; }
+static int cast_reverse(const QuantizeArgs& a) { return a.do_amax && a.rows * a.cols * 2 > kCacheBytes / 2 && !cast_streams(a); }
+
+// Workgroups of the amax pass, at most kMaxAmaxWgs (one per 512 columns if that is more): two to a CU keep enough loads in
+// flight, and every workgroup of the cast pass folds their maxima (dY 8192 x 20480: 512 218 us per call, 1024 222, 2048 236).
+// Two words each fit the workspace whatever the shape: it has 2 (rows + cols), and 64-row x 512-column tiles are fewer.
+constexpr int64_t kMaxAmaxWgs = 512;
+static dim3 amax_grid(const QuantizeArgs& a) {
+  const int64_t gx = (a.cols + kWaveCols - 1) / kWaveCols, gy = (a.rows / 16 + 3) / 4;
+  const int64_t cap = kMaxAmaxWgs / gx > 0 ? kMaxAmaxWgs / gx : 1;
+  return dim3(static_cast<unsigned>(gx), static_cast<unsigned>(gy < cap ? gy : cap));
+}
 
 template <bool kRow, bool kCol, int kRht, bool kSR, bool k2D>
-static void launch_cast(const QuantizeArgs& a, dim3 grid, hipStream_t s) {
+static void launch_cast(const QuantizeArgs& a, hipStream_t s) {
+  using T = CastTile;
+  const dim3 grid(static_cast<unsigned>((a.cols + T::kCols - 1) / T::kCols), static_cast<unsigned>((a.rows / 16 + T::kGroups - 1) / T::kGroups));
+  const dim3 ag = amax_grid(a);
+  const uint32_t* maxima = a.do_amax ? a.ws + kWsHeader : a.ws;
   hipLaunchKernelGGL((cast_kernel<kRow, kCol, kRht, kSR, k2D>), grid, dim3(kThreads), 0, s,
-                     static_cast<const uint16_t*>(a.x), a.rows, a.cols, a.ld, a.ws, a.sign_mask, a.key0,
-                     a.key1, a.row_codes, a.row_scales, a.row_ts, a.col_codes, a.col_scales, a.col_ts, cast_reverse(a));
+                     static_cast<const uint16_t*>(a.x), a.rows, a.cols, a.ld, maxima, a.do_amax ? ag.x * ag.y : 1u, a.sign_mask, a.key0,
+                     a.key1, a.row_codes, a.row_scales, a.row_ts, a.col_codes, a.col_scales, a.col_ts, cast_reverse(a), cast_streams(a));
 }
 
 template <bool kRow, bool kCol, int kRht>
-static void dispatch_cast2(const QuantizeArgs& a, dim3 grid, hipStream_t s) {
-  if (a.block2d) {
-    if (a.sr) launch_cast<kRow, kCol, 0, true, true>(a, grid, s);
-    else launch_cast<kRow, kCol, 0, false, true>(a, grid, s);
-  } else {
-    if (a.sr) launch_cast<kRow, kCol, kRht, true, false>(a, grid, s);
-    else launch_cast<kRow, kCol, kRht, false, false>(a, grid, s);
-  }
-}
-
-template <bool kRow, int kRht>
-static void launch_rotated(const QuantizeArgs& a, dim3 grid, hipStream_t s) {
-  const uint16_t* x = static_cast<const uint16_t*>(a.x);
+static void launch_passes(const QuantizeArgs& a, hipStream_t s) {
   if (a.do_amax) {
-    hipLaunchKernelGGL((amax_kernel<kRht>), grid, dim3(kThreads), 0, s, x, a.rows, a.cols, a.ld, a.sign_mask, a.ws);
-    hipLaunchKernelGGL(amax_finalize_kernel, dim3(1), dim3(1024), 0, s, a.ws, grid.x * grid.y, a.amax_copy);
+    const dim3 grid = amax_grid(a);
+    hipLaunchKernelGGL((amax_kernel<kRht>), grid, dim3(kThreads), 0, s, static_cast<const uint16_t*>(a.x), a.rows, a.cols, a.ld,
+                       a.sign_mask, a.ws);
+    // the cast pass folds the maxima itself; only a caller of the amax alone needs them folded
+    if (!a.do_cast) hipLaunchKernelGGL(amax_finalize_kernel, dim3(1), dim3(1024), 0, s, a.ws, grid.x * grid.y, a.amax_copy);
   }
-  if (a.do_cast) dispatch_cast2<kRow, true, kRht>(a, grid, s);
+  if (!a.do_cast) return;
+  if (a.block2d) {
+    if (a.sr) launch_cast<kRow, kCol, 0, true, true>(a, s);
+    else launch_cast<kRow, kCol, 0, false, true>(a, s);
+  } else {
+    if (a.sr) launch_cast<kRow, kCol, kRht, true, false>(a, s);
+    else launch_cast<kRow, kCol, kRht, false, false>(a, s);
+  }
 }
 
 hipError_t launch_quantize(const QuantizeArgs& a, hipStream_t s) {
-  const dim3 grid(static_cast<unsigned>((a.cols + kWaveCols - 1) / kWaveCols),
-                  static_cast<unsigned>((a.rows / 16 + kGroupsPerBlock - 1) / kGroupsPerBlock));
   const int rht = a.want_col ? a.rht_dim : 0;
   if (a.scale_per_row) return launch_quantize_rowscale(a, s);
   if (a.row_rht) return launch_quantize_rowrot(a, s);
   if (rht > 16) return launch_quantize_wide(a, s);
-  if (rht) {
-    if (a.want_row) {
-      if (rht == 16) launch_rotated<true, 16>(a, grid, s);
-      else if (rht == 4) launch_rotated<true, 4>(a, grid, s);
-      else launch_rotated<true, 2>(a, grid, s);
-    } else {
-      if (rht == 16) launch_rotated<false, 16>(a, grid, s);
-      else if (rht == 4) launch_rotated<false, 4>(a, grid, s);
-      else launch_rotated<false, 2>(a, grid, s);
-    }
-    return hipGetLastError();
-  }
-  if (a.do_amax) {
-    hipLaunchKernelGGL((amax_kernel<0>), grid, dim3(kThreads), 0, s, static_cast<const uint16_t*>(a.x), a.rows, a.cols,
-                       a.ld, a.sign_mask, a.ws);
-    hipLaunchKernelGGL(amax_finalize_kernel, dim3(1), dim3(1024), 0, s, a.ws, grid.x * grid.y, a.amax_copy);
-  }
-  if (a.do_cast) {
-    if (a.want_row && a.want_col) dispatch_cast2<true, true, 0>(a, grid, s);
-    else if (a.want_row) dispatch_cast2<true, false, 0>(a, grid, s);
-    else dispatch_cast2<false, true, 0>(a, grid, s);
+  if (rht == 16) {
+    if (a.want_row) launch_passes<true, true, 16>(a, s); else launch_passes<false, true, 16>(a, s);
+  } else if (rht == 4) {
+    if (a.want_row) launch_passes<true, true, 4>(a, s); else launch_passes<false, true, 4>(a, s);
+  } else if (rht == 2) {
+    if (a.want_row) launch_passes<true, true, 2>(a, s); else launch_passes<false, true, 2>(a, s);
+  } else {
+    if (a.want_row && a.want_col) launch_passes<true, true, 0>(a, s);
+    else if (a.want_row) launch_passes<true, false, 0>(a, s);
+    else launch_passes<false, true, 0>(a, s);
   }
   return hipGetLastError();
 }

@@ -22,11 +22,31 @@ __device__ __forceinline__ float patch_elem(const uint4& q, int c) {
   return (c & 1) ? bf16_hi(w) : bf16_lo(w);
 }
 
+typedef uint32_t dword4 __attribute__((ext_vector_type(4)));
+
+// kStream: non-temporal loads, which leave no copy in the memory-side cache.
+template <bool kStream = false>
 __device__ __forceinline__ void load_patch(const uint16_t* __restrict__ x, int64_t ld, int64_t row0,
                                            int64_t col0, Patch& p) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r)
-    p.raw[r] = *reinterpret_cast<const uint4*>(x + (row0 + r) * ld + col0);
+  for (int r = 0; r < 16; ++r) {
+    const dword4* src = reinterpret_cast<const dword4*>(x + (row0 + r) * ld + col0);
+    const dword4 v = kStream ? __builtin_nontemporal_load(src) : *src;
+    p.raw[r] = make_uint4(v[0], v[1], v[2], v[3]);
+  }
+}
+
+// Codes leave with non-temporal stores where a kernel says so (kStream): they are not read again by this call and would push
+// the source tensor out of the memory-side cache.
+template <bool kStream>
+__device__ __forceinline__ void store_codes(uint8_t* dst, uint32_t v) {
+  if (kStream) __builtin_nontemporal_store(v, reinterpret_cast<uint32_t*>(dst));
+  else *reinterpret_cast<uint32_t*>(dst) = v;
+}
+template <bool kStream>
+__device__ __forceinline__ void store_codes(uint8_t* dst, uint4 v) {
+  if (kStream) __builtin_nontemporal_store(dword4{v.x, v.y, v.z, v.w}, reinterpret_cast<dword4*>(dst));
+  else *reinterpret_cast<uint4*>(dst) = v;
 }
 
 typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
@@ -91,10 +111,19 @@ __device__ __forceinline__ constexpr float rht_norm() {
                                                                                         : 0.0883883476483184405f;
 }
 
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t m) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) m = max(m, static_cast<uint32_t>(__shfl_xor(static_cast<int>(m), off, 64)));
+// Maximum over the wavefront, valid in lane 63: shifts within rows of 16 lanes, then row 0 -> 1 and 2 -> 3, then the lower half
+// -> the upper (lanes without a source take 0).
+__device__ __forceinline__ uint32_t wave_max_u32_lane63(uint32_t m) {
+  m = max(m, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(m), 0x111, 0xF, 0xF, false)));   // row_shr:1
+  m = max(m, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(m), 0x112, 0xF, 0xF, false)));   // row_shr:2
+  m = max(m, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(m), 0x114, 0xF, 0xF, false)));   // row_shr:4
+  m = max(m, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(m), 0x118, 0xF, 0xF, false)));   // row_shr:8
+  m = max(m, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(m), 0x142, 0xA, 0xF, false)));   // row_bcast:15
+  m = max(m, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(m), 0x143, 0xC, 0xF, false)));   // row_bcast:31
   return m;
+}
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t m) {
+  return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(wave_max_u32_lane63(m)), 63));
 }
 
 // Eight scaled values of one row -> one dword of eight codes.
@@ -148,15 +177,23 @@ __device__ __forceinline__ uint32_t encode8_col(const float* v, const uint32_t r
   }
 }
 
-// LDS staging of one workgroup tile (128 rows x 512 columns):
-//   col codes : [c 0..7][g 0..7][65 slots of 8 B]  (lane l of group g, column c of its patch)
-//               -- consecutive lanes write consecutive slots; the 65th slot is padding that
+// LDS staging of one workgroup tile of kG 16-row groups x kL lane patches (16 kG rows x 8 kL columns):
+//   col codes : [c 0..7][g][kL + 1 slots of 8 B]  (lane l of group g, column c of its patch)
+//               -- consecutive lanes write consecutive slots; the extra slot is padding that
 //               spreads the transposed read-back over the banks
-//   col scales: [c][g][64] bytes ; row scales: [128 rows][32] bytes
-constexpr int kColSlot = 65;
-constexpr int kColCodesBytes = 8 * kGroupsPerBlock * kColSlot * 8;   // 33280
-constexpr int kColScalesBytes = 8 * kGroupsPerBlock * 64;            // 4096
-constexpr int kRowScalesBytes = 16 * kGroupsPerBlock * 32;           // 4096
+//   col scales: [c][g][kL] bytes ; row scales: [16 kG rows][kL / 2] bytes
+template <int kG, int kL, bool kStreamCodes = false>
+struct Staged {
+  static constexpr bool kStream = kStreamCodes;
+  static constexpr int kGroups = kG, kLanes = kL, kCols = kL * 8, kSlot = kL + 1;
+  static constexpr int kColCodesBytes = 8 * kG * kSlot * 8, kColScalesBytes = 8 * kG * kL, kRowScaleLd = kL / 2;
+  static constexpr int kRowScalesBytes = 16 * kG * kRowScaleLd;
+};
+using WideTile = Staged<kGroupsPerBlock, 64>;   // 128 rows x 512 columns
+constexpr int kColSlot = WideTile::kSlot;
+constexpr int kColCodesBytes = WideTile::kColCodesBytes;     // 33280
+constexpr int kColScalesBytes = WideTile::kColScalesBytes;   // 4096
+constexpr int kRowScalesBytes = WideTile::kRowScalesBytes;   // 4096
 
 // Folds the per-workgroup maxima of pass 1 (nwg raw maxima, then nwg rotated maxima, after the header):
 // ws[0] = amax of the tensor, ws[1] = amax of the rotated tensor, both as FP32 bits (also stored to `copy` if
@@ -192,7 +229,7 @@ static __global__ __launch_bounds__(1024) void amax_finalize_kernel(uint32_t* __
 // Row copy of one patch (App. B.2-B.3): per row, the amax of the 1x16 block (this lane's eight columns and the
 // neighbour's; or the 16x16 tile's scale of Sec. 4.3), Eq. 2-4, one dword of codes straight to memory (dst = the
 // row copy's codes at (first row of the patch, first column of the lane)), the scale byte staged in LDS.
-template <bool kSR, bool k2D>
+template <bool kSR, bool k2D, class T = WideTile>
 __device__ __forceinline__ void row_pass(const Patch& p, const uint32_t (&rnd)[16][4], int lane, int gl, float s_enc_r,
                                          const float* lut_row, float s_enc_tile, uint32_t tile_code,
                                          uint8_t* __restrict__ dst, int64_t code_ld, uint8_t* st_row_scales) {
@@ -217,14 +254,14 @@ __device__ __forceinline__ void row_pass(const Patch& p, const uint32_t (&rnd)[1
 #pragma unroll
     for (int c = 0; c < 8; ++c) v[c] *= s_enc_b;                    // Eq. 4
     const uint32_t d = encode8<kSR>(v, rnd[r]);
-    *reinterpret_cast<uint32_t*>(dst + r * code_ld) = d;
-    if ((lane & 1) == 0) st_row_scales[(gl * 16 + r) * 32 + (lane >> 1)] = static_cast<uint8_t>(code);
+    store_codes<T::kStream>(dst + r * code_ld, d);
+    if ((lane & 1) == 0) st_row_scales[(gl * 16 + r) * T::kRowScaleLd + (lane >> 1)] = static_cast<uint8_t>(code);
   }
 }
 
 // One 1x16 block of the col copy: the 16 (possibly rotated) values of column c of the patch -> scale byte and
 // eight bytes of codes, staged in LDS.
-template <bool kSR, bool k2D>
+template <bool kSR, bool k2D, class T = WideTile>
 __device__ __forceinline__ void emit_column(float (&v)[16], int c, const uint32_t (&rnd)[16][4], int lane, int gl,
                                             float s_enc_c, const float* lut_col, float s_enc_tile, uint32_t tile_code,
                                             uint8_t* st_col_codes, uint8_t* st_col_scales) {
@@ -245,34 +282,39 @@ __device__ __forceinline__ void emit_column(float (&v)[16], int c, const uint32_
   uint2 out;
   out.x = encode8_col<kSR>(v, rnd, 0, c);
   out.y = encode8_col<kSR>(v + 8, rnd, 8, c);
-  *reinterpret_cast<uint2*>(st_col_codes + ((c * kGroupsPerBlock + gl) * kColSlot + lane) * 8) = out;
-  st_col_scales[(c * kGroupsPerBlock + gl) * 64 + lane] = static_cast<uint8_t>(code);
+  *reinterpret_cast<uint2*>(st_col_codes + ((c * T::kGroups + gl) * T::kSlot + lane) * 8) = out;
+  st_col_scales[(c * T::kGroups + gl) * T::kLanes + lane] = static_cast<uint8_t>(code);
 }
 
 // Write-back of one staged workgroup tile with wide, contiguous stores (all kT threads of the workgroup call it
 // after a barrier that follows the last staging write).
-template <bool kRow, bool kCol, int kT>
+template <bool kRow, bool kCol, int kT, class T = WideTile>
 __device__ __forceinline__ void write_back_tile(int tid, int64_t rows, int64_t cols, int64_t group0, int64_t ngroups,
                                                 int64_t colblk, const uint8_t* st_col_codes, const uint8_t* st_col_scales,
                                                 const uint8_t* st_row_scales, uint8_t* __restrict__ row_scales,
                                                 uint8_t* __restrict__ col_codes, uint8_t* __restrict__ col_scales) {
-  const int tile_groups = static_cast<int>(min<int64_t>(kGroupsPerBlock, ngroups - group0));
-  const int tile_cols = static_cast<int>(min<int64_t>(kWaveCols, cols - colblk));
+  constexpr int kG = T::kGroups;
+  const int tile_groups = static_cast<int>(min<int64_t>(kG, ngroups - group0));
+  const int tile_cols = static_cast<int>(min<int64_t>(T::kCols, cols - colblk));
 
   if (kRow) {
     const int64_t scale_ld = cols / 16;
     const int nblk = tile_cols / 16;  // scale bytes per row in this tile
-    if ((scale_ld & 15) == 0 && nblk == 32) {
-      for (int q = tid; q < 256; q += kT) {
-        const int r = q >> 1, half = q & 1;   // 128 rows x two 16-byte halves
-        if (r < tile_groups * 16)
-          *reinterpret_cast<uint4*>(row_scales + (group0 * 16 + r) * scale_ld + colblk / 16 + half * 16) =
-              *reinterpret_cast<const uint4*>(st_row_scales + r * 32 + half * 16);
+    constexpr int kPiece = T::kRowScaleLd < 16 ? T::kRowScaleLd : 16, kPieces = T::kRowScaleLd / kPiece;   // of a full tile row
+    if ((scale_ld & (kPiece - 1)) == 0 && nblk == T::kRowScaleLd) {
+      for (int q = tid; q < 16 * kG * kPieces; q += kT) {
+        const int r = q / kPieces, part = q % kPieces;
+        if (r < tile_groups * 16) {
+          uint8_t* dst = row_scales + (group0 * 16 + r) * scale_ld + colblk / 16 + part * kPiece;
+          const uint8_t* src = st_row_scales + r * T::kRowScaleLd + part * kPiece;
+          if (kPiece == 16) *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(src);
+          else *reinterpret_cast<uint2*>(dst) = *reinterpret_cast<const uint2*>(src);
+        }
       }
     } else {
       for (int i = tid; i < tile_groups * 16 * nblk; i += kT) {
         const int r = i / nblk, b = i - r * nblk;
-        row_scales[(group0 * 16 + r) * scale_ld + colblk / 16 + b] = st_row_scales[r * 32 + b];
+        row_scales[(group0 * 16 + r) * scale_ld + colblk / 16 + b] = st_row_scales[r * T::kRowScaleLd + b];
       }
     }
   }
@@ -281,37 +323,36 @@ __device__ __forceinline__ void write_back_tile(int tid, int64_t rows, int64_t c
     const int64_t code_ld = rows / 2, scale_ld = rows / 16;
     const bool wide = (code_ld & 15) == 0;   // 16-byte aligned column rows
 #pragma unroll 1
-    for (int i = 0; i < 2048 / kT; ++i) {
-      const int q = i * kT + tid;       // 2048 pieces of 16 bytes: column j, group pair pr
-      const int j = q >> 2, pr = q & 3;
+    for (int q = tid; q < T::kCols * (kG / 2); q += kT) {   // pieces of 16 bytes: column j, group pair pr
+      const int j = q / (kG / 2), pr = q % (kG / 2);
       if (j >= tile_cols) continue;
       const int lj = j >> 3, c = j & 7;
-      const uint2 a = *reinterpret_cast<const uint2*>(st_col_codes + ((c * kGroupsPerBlock + 2 * pr) * kColSlot + lj) * 8);
-      const uint2 b = *reinterpret_cast<const uint2*>(st_col_codes + ((c * kGroupsPerBlock + 2 * pr + 1) * kColSlot + lj) * 8);
+      const uint2 a = *reinterpret_cast<const uint2*>(st_col_codes + ((c * kG + 2 * pr) * T::kSlot + lj) * 8);
+      const uint2 b = *reinterpret_cast<const uint2*>(st_col_codes + ((c * kG + 2 * pr + 1) * T::kSlot + lj) * 8);
       uint8_t* dst = col_codes + (colblk + j) * code_ld + (group0 + 2 * pr) * 8;
       if (wide && 2 * pr + 1 < tile_groups) {
-        *reinterpret_cast<uint4*>(dst) = make_uint4(a.x, a.y, b.x, b.y);
+        store_codes<T::kStream>(dst, make_uint4(a.x, a.y, b.x, b.y));
       } else {
         if (2 * pr < tile_groups) *reinterpret_cast<uint2*>(dst) = a;
         if (2 * pr + 1 < tile_groups) *reinterpret_cast<uint2*>(dst + 8) = b;
       }
     }
 #pragma unroll 1
-    for (int i = 0; i < 512 / kT; ++i) {
-      const int j = i * kT + tid;       // one column: 8 scale bytes (one per group)
+    for (int j = tid; j < T::kCols; j += kT) {       // one column: kG scale bytes (one per group)
       if (j >= tile_cols) continue;
       const int lj = j >> 3, c = j & 7;
-      uint8_t sc[8];
+      uint8_t sc[kG];
 #pragma unroll
-      for (int g = 0; g < 8; ++g) sc[g] = st_col_scales[(c * kGroupsPerBlock + g) * 64 + lj];
+      for (int g = 0; g < kG; ++g) sc[g] = st_col_scales[(c * kG + g) * T::kLanes + lj];
       uint8_t* dst = col_scales + (colblk + j) * scale_ld + group0;
-      if (tile_groups == 8 && (scale_ld & 7) == 0) {
-        uint2 o;
-        o.x = sc[0] | (sc[1] << 8) | (sc[2] << 16) | (static_cast<uint32_t>(sc[3]) << 24);
-        o.y = sc[4] | (sc[5] << 8) | (sc[6] << 16) | (static_cast<uint32_t>(sc[7]) << 24);
-        *reinterpret_cast<uint2*>(dst) = o;
+      if (tile_groups == kG && (scale_ld & (kG - 1)) == 0) {
+#pragma unroll
+        for (int w = 0; w < kG / 4; ++w)
+          reinterpret_cast<uint32_t*>(dst)[w] = sc[4 * w] | (sc[4 * w + 1] << 8) | (sc[4 * w + 2] << 16) | (static_cast<uint32_t>(sc[4 * w + 3]) << 24);
       } else {
-        for (int g = 0; g < tile_groups; ++g) dst[g] = sc[g];
+#pragma unroll
+        for (int g = 0; g < kG; ++g)
+          if (g < tile_groups) dst[g] = sc[g];
       }
     }
   }

@@ -1,0 +1,29 @@
+"""GPU parity of the quantizer at the edges of its workgroup tiles (cast pass 128 rows x 256 columns, amax pass 64 rows x 512
+columns) and where an amax workgroup walks over several row groups, bit for bit against the oracle."""
+import pytest
+
+from paper_2509_25149_amd import binding as nv, synth
+from test_gpu_parity import check_quantize
+
+pytestmark = pytest.mark.gpu
+
+RC = nv.LAYOUT_ROW | nv.LAYOUT_COL
+
+
+# inside one tile; exactly one; a 16-row and a 16-column remainder of a second; several tiles, odd scale rows (unaligned
+# scale pieces); more row groups than amax workgroups may be launched (one column block: 512 workgroups of 4 groups)
+@pytest.mark.parametrize("rows,cols", [(112, 240), (128, 256), (144, 272), (656, 784), (32784, 16)])
+@pytest.mark.parametrize("mode", ["activation", "weight", "gradient", "row_only"])
+def test_tile_edges(rows, cols, mode):
+    xb = synth.student_t3(rows, cols, 1e-3, rows + cols) if mode == "gradient" else \
+        synth.normal_with_outliers(rows, cols, 1.0, rows + cols, frac=0.01)
+    xb[-16:, -16:] = 0                                   # an all-zero 16x16 tile: stored scale 0
+    xb[-1, 0] = 0x5000                                   # the tensor's largest magnitude in its last row
+    if mode == "activation":
+        check_quantize(xb, RC, rht=True, rht_seed=11)
+    elif mode == "weight":
+        check_quantize(xb, RC, nv.BLOCK_16x16)
+    elif mode == "gradient":
+        check_quantize(xb, RC, rounding=nv.ROUND_SR, rht=True, rht_seed=12, sr_seed=13)
+    else:
+        check_quantize(xb, nv.LAYOUT_ROW)
