@@ -71,18 +71,20 @@ __device__ __forceinline__ float4v scale4(const TensorScales& ts, float uniform,
 // (m = 16 i + l16) one factor each.  Otherwise the product a[0] * b[0] serves every output.
 // A lane's addresses are one pointer (its row l16, its first column) plus i * 16 rows plus a constant per j, which the
 // stores carry as their immediate offsets.
-template <bool kBf16Out, bool kVec>
+// kNB: how many 16-column blocks a lane holds of its rows (8 for a 128-column block; an odd number's last one is paired with
+// nothing).
+template <bool kBf16Out, bool kVec, int kNB = 8>
 struct WaveBlockStore {
   void* d;
   int64_t ldd, lane_first;
   int l16, nl, rows, cols;
   bool accumulate;
   float out_scale;
-  float4v sb[kVec ? 8 : 1];
+  float4v sb[kVec ? kNB : 1];
 
   __device__ __forceinline__ WaveBlockStore(const TensorScales ts, void* Dv, int64_t ldd_, bool accumulate_, int64_t row0, int64_t col0,
                                             int rows_, int cols_, int lane)
-      : d(Dv), ldd(ldd_), l16(lane & 15), rows(rows_), cols(cols_), accumulate(accumulate_), out_scale(ts.a[0] * ts.b[0]) {
+      : d(Dv), ldd(ldd_), l16(lane & 15), rows(rows_), cols(cols_ < 16 * kNB ? cols_ : 16 * kNB), accumulate(accumulate_), out_scale(ts.a[0] * ts.b[0]) {
     const int lq = lane >> 4;
     // bf16: after the exchange a lane of an even column group holds 8 consecutive columns of block j, a lane of an odd
     // group 8 of block j + 1: column 16 j + nl, nl = 0, 16, 8, 24 for lq = 0 .. 3.
@@ -90,7 +92,7 @@ struct WaveBlockStore {
     lane_first = (row0 + l16) * ldd + col0 + nl;
     if (kVec) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
+      for (int j = 0; j < kNB; ++j) {
         if (ts.b_per_row && j * 16 + lq * 4 < cols) {
           sb[kVec ? j : 0] = *reinterpret_cast<const float4v*>(ts.b + col0 + j * 16 + lq * 4);
         } else {
@@ -107,7 +109,7 @@ struct WaveBlockStore {
   }
 
   // The lane's 8 x 4 sums of 16-row block i: row m = 16 i + l16, columns 16 j + 4 lq + r.
-  __device__ __forceinline__ void store_rows(const float4v (&sums)[8], int i, float sa) const {
+  __device__ __forceinline__ void store_rows(const float4v (&sums)[kNB], int i, float sa) const {
     auto scale = [&](int j) -> float4v {
       if (kVec) return sb[kVec ? j : 0] * sa;
       return float4v{out_scale, out_scale, out_scale, out_scale};
@@ -116,8 +118,8 @@ struct WaveBlockStore {
     if (kBf16Out) {
       uint16_t* d_row = static_cast<uint16_t*>(d) + lane_first + i * 16 * ldd;
 #pragma unroll
-      for (int j = 0; j < 8; j += 2) {
-        const float4v va = sums[j] * scale(j), vb = sums[j + 1] * scale(j + 1);
+      for (int j = 0; j < kNB; j += 2) {
+        const float4v va = sums[j] * scale(j), vb = j + 1 < kNB ? sums[j + 1 < kNB ? j + 1 : j] * scale(j + 1 < kNB ? j + 1 : j) : float4v{0.0f, 0.0f, 0.0f, 0.0f};
         const uint32_t a0 = f32x2_to_bf16(va[0], va[1]), a1 = f32x2_to_bf16(va[2], va[3]);
         const uint32_t b0 = f32x2_to_bf16(vb[0], vb[1]), b1 = f32x2_to_bf16(vb[2], vb[3]);
         // first result: lanes of odd groups now hold the second block's dword of the group below; second result: lanes of
@@ -131,7 +133,7 @@ struct WaveBlockStore {
     } else {
       float* d_row = static_cast<float*>(d) + lane_first + i * 16 * ldd;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
+      for (int j = 0; j < kNB; ++j) {
         if (row_in && j * 16 + nl < cols) {  // columns come in multiples of 16, so the 4 columns are in or out together
           float4v v = sums[j] * scale(j);
           float* p = d_row + j * 16;
@@ -146,10 +148,10 @@ struct WaveBlockStore {
 // A wavefront's whole 128 x 128 block.  (A variant without the predicates for blocks that exist whole measured no
 // faster.)  A kernel should contain this once: where a second use of the sums sits in another branch, the compiler
 // reads all 256 out of the accumulation registers ahead of the branch, into registers it does not have.
-template <bool kBf16Out, bool kVec>
-__device__ __forceinline__ void store_wave_block_impl(float4v (&acc)[8][8], const TensorScales ts, void* __restrict__ Dv, int64_t ldd,
+template <bool kBf16Out, bool kVec, int kNB = 8>
+__device__ __forceinline__ void store_wave_block_impl(float4v (&acc)[8][kNB], const TensorScales ts, void* __restrict__ Dv, int64_t ldd,
                                                       bool accumulate, int64_t row0, int64_t col0, int rows, int cols, int lane) {
-  const WaveBlockStore<kBf16Out, kVec> out(ts, Dv, ldd, accumulate, row0, col0, rows, cols, lane);
+  const WaveBlockStore<kBf16Out, kVec, kNB> out(ts, Dv, ldd, accumulate, row0, col0, rows, cols, lane);
   float sa[kVec ? 8 : 1] = {};
   if (kVec) {
 #pragma unroll
@@ -160,10 +162,10 @@ __device__ __forceinline__ void store_wave_block_impl(float4v (&acc)[8][8], cons
 }
 
 // The per-tensor form, for kernels that have no other.
-template <bool kBf16Out>
-__device__ __forceinline__ void store_wave_block(float4v (&acc)[8][8], const TensorScales ts, void* __restrict__ Dv, int64_t ldd,
+template <bool kBf16Out, int kNB = 8>
+__device__ __forceinline__ void store_wave_block(float4v (&acc)[8][kNB], const TensorScales ts, void* __restrict__ Dv, int64_t ldd,
                                                  bool accumulate, int64_t row0, int64_t col0, int rows, int cols, int lane) {
-  store_wave_block_impl<kBf16Out, false>(acc, ts, Dv, ldd, accumulate, row0, col0, rows, cols, lane);
+  store_wave_block_impl<kBf16Out, false, kNB>(acc, ts, Dv, ldd, accumulate, row0, col0, rows, cols, lane);
 }
 
 }  // namespace nvfp4

@@ -280,15 +280,27 @@ __device__ __forceinline__ void lds_read_2x4_st64(int2v& dst, uint32_t addr) {
   asm volatile("ds_read2st64_b32 %0, %1 offset0:%2 offset1:%3" : "=&v"(dst) : "v"(addr), "n"(kOff0), "n"(kOff1));
 }
 
-// Read number q of the 24 of a fragment set: 0..7 A codes, 8..15 B codes (16-row blocks are 2 KiB apart), 16..19 A
-// scales, 20..23 B scales (16-row blocks are 256 bytes apart).
-template <int q>
+// Read number q of the 16 + kNB of a fragment set: 8 of A codes, kNB of B codes (16-row blocks are 2 KiB apart), 4 of A
+// scales, 4 of B scales (16-row blocks are 256 bytes apart; for kNB < 8 some of them read rows that count for nothing).
+template <int q, int kNB>
 __device__ __forceinline__ void read_frag_wide(Frags& f, RawScales& r, uint32_t a_codes, uint32_t b_codes, uint32_t a_scales,
                                                uint32_t b_scales) {
+  constexpr int s = q - 8 - kNB;
   if constexpr (q < 8) lds_read16<q * 16 * kWideRowBytes>(f.a[q], a_codes);
-  else if constexpr (q < 16) lds_read16<(q - 8) * 16 * kWideRowBytes>(f.b[q - 8], b_codes);
-  else if constexpr (q < 20) lds_read_2x4_st64<(q - 16) * 2, (q - 16) * 2 + 1>(r.a[q - 16], a_scales);
-  else lds_read_2x4_st64<(q - 20) * 2, (q - 20) * 2 + 1>(r.b[q - 20], b_scales);
+  else if constexpr (q < 8 + kNB) lds_read16<(q - 8) * 16 * kWideRowBytes>(f.b[q - 8], b_codes);
+  else if constexpr (s < 4) lds_read_2x4_st64<s * 2, s * 2 + 1>(r.a[s], a_scales);
+  else lds_read_2x4_st64<(s - 4) * 2, (s - 4) * 2 + 1>(r.b[s - 4], b_scales);
+}
+
+// Spreads `total` things evenly over the `slots` places between MFMAs: the number of the one that place n takes, or -1.
+constexpr int spread(int n, int total, int slots) {
+  return (n + 1) * total / slots > n * total / slots ? n * total / slots : -1;
+}
+// Fragment reads: every second place, so that the last are back before the wait that follows (evenly, the 256-column tile
+// is 1-2 % slower), or evenly where there are not enough places.  odd: which of two places.
+constexpr int read_at(int n, int total, int slots, int odd) {
+  if (2 * total > slots) return spread(n, total, slots);
+  return (n & 1) == odd && (n >> 1) < total ? n >> 1 : -1;
 }
 
 // The first instruction on an accumulator in a tile: C = 0, so the 256 accumulation registers are never cleared.
@@ -299,10 +311,10 @@ __device__ __forceinline__ void mfma_first(float4v& acc, const int4v& b, const i
                : "v"(b), "v"(a), "v"(sb), "v"(sa), "n"(kSelB & 1), "n"(kSelA & 1), "n"(kSelB >> 1), "n"(kSelA >> 1));
 }
 
-// A wavefront's output stage issues 32 (bf16) or 64 (FP32) stores for a full tile; three quarters of them may still be
+// A wavefront's output stage issues 8 ceil(kNB / 2) (bf16) or 8 kNB (FP32) stores for a full tile; three quarters of them may still be
 // outstanding when the loads issued before it are needed (memory operations complete in issue order).
-template <bool kBf16Out>
-constexpr int kTileStoresMx = kBf16Out ? 24 : 48;
+template <bool kBf16Out, int kNB>
+constexpr int kTileStoresMx = kBf16Out ? 6 * ((kNB + 1) / 2) : 6 * kNB;
 
 // With more tiles than CUs the host launches one workgroup per CU, which takes tiles blockIdx.x, blockIdx.x +
 // gridDim.x, ... and runs them as ONE stream of stages, as the FP16 kernel of the NVFP4 route does: the loads issued
@@ -310,9 +322,11 @@ constexpr int kTileStoresMx = kBf16Out ? 24 : 48;
 // neither drains nor refills at a tile boundary.  K is a multiple of 512, so every tile is an even number of stages
 // and a whole number of scale chunks: the stage buffers and the scale ring simply keep turning (`gst` below counts
 // stages over all tiles).  The output stage's stores are not waited for.
-template <bool kBf16Out>
+template <bool kBf16Out, int kNB>
 __global__ __launch_bounds__(kThreads) void gemm_mx_kernel_k512(Operand A, Operand B, int64_t K, void* __restrict__ Dv,
                                                                 int64_t ldd, bool accumulate, int tiles_m, int tiles_n) {
+  constexpr int kTN = 32 * kNB;                  // columns of a tile: two wavefronts of kNB 16-column blocks
+  constexpr int kReads = 16 + kNB, kLoads = 8 + kNB, kMfmas = 8 * kNB;
   extern __shared__ __attribute__((aligned(16))) char lds[];
 
   const int num_tiles = tiles_m * tiles_n;
@@ -343,7 +357,7 @@ __global__ __launch_bounds__(kThreads) void gemm_mx_kernel_k512(Operand A, Opera
     lane_odd = static_cast<uint32_t>(lane >> 3) * static_cast<uint32_t>(code_ld) + (c0 ^ 64u);
     lane_srow = static_cast<uint32_t>(wave * 64 + lane);
     const int l16 = lane & 15, kb = lane >> 4;
-    const int arow = (wave >> 1) * 128 + l16, brow = (wave & 1) * 128 + l16;
+    const int arow = (wave >> 1) * 128 + l16, brow = (wave & 1) * (16 * kNB) + l16;
     a_lo = lds0 + swz128(arow, kb);
     a_hi = lds0 + swz128(arow, 4 + kb);
     b_lo = lds0 + kWideOperandBytes + swz128(brow, kb);
@@ -361,11 +375,11 @@ __global__ __launch_bounds__(kThreads) void gemm_mx_kernel_k512(Operand A, Opera
   const uint8_t* base_b = nullptr;
   const uint8_t* base_sa = nullptr;
   const uint8_t* base_sb = nullptr;
-  uint32_t voff[16];   // q 0..7 A, 8..15 B
+  uint32_t voff[8 + kNB];   // q 0..7 A, then B
   uint32_t vsa = 0, vsb = 0;
   // Point the loads at stage `stage` and scale chunk `chunk` of tile (tm, tn).
   auto aim = [&](int tm, int tn, int stage, int chunk) {
-    const int64_t m_first = static_cast<int64_t>(tm) * TM, n_first = static_cast<int64_t>(tn) * TN;
+    const int64_t m_first = static_cast<int64_t>(tm) * TM, n_first = static_cast<int64_t>(tn) * kTN;
     base_a = A.codes + m_first * code_ld + stage * kWideRowBytes;
     base_b = B.codes + n_first * code_ld + stage * kWideRowBytes;
     base_sa = A.scales + m_first * scale_ld + chunk * 16;
@@ -375,15 +389,19 @@ __global__ __launch_bounds__(kThreads) void gemm_mx_kernel_k512(Operand A, Opera
     for (int q = 0; q < 8; ++q) {
       const uint32_t r = static_cast<uint32_t>(wave * 64 + q * 8);
       voff[q] = ((q & 1) ? lane_odd : lane_even) + min(r, last_a) * static_cast<uint32_t>(code_ld);
-      voff[8 + q] = ((q & 1) ? lane_odd : lane_even) + min(r, last_b) * static_cast<uint32_t>(code_ld);
+    }
+#pragma unroll
+    for (int q = 0; q < kNB; ++q) {
+      const uint32_t blk = static_cast<uint32_t>(wave * kNB + q);
+      voff[8 + q] = ((blk & 1) ? lane_odd : lane_even) + min(blk * 8u, last_b) * static_cast<uint32_t>(code_ld);
     }
     vsa = min(lane_srow, last_a + 7) * static_cast<uint32_t>(scale_ld);
     vsb = min(lane_srow, last_b + 7) * static_cast<uint32_t>(scale_ld);
   };
-  // load number q (0..15) of a stage into stage buffer `buf`: 0..7 A, 8..15 B
+  // load number q of a stage into stage buffer `buf`: 0..7 A, then B
   auto issue_codes = [&](auto qc, int buf) {
     constexpr int q = decltype(qc)::value;
-    const uint32_t dst = lds0 + buf * kWideStageBytes + (q < 8 ? 0 : kWideOperandBytes) + wave * 8192 + (q & 7) * 1024;
+    const uint32_t dst = lds0 + buf * kWideStageBytes + (q < 8 ? wave * 8192 + q * 1024 : kWideOperandBytes + (wave * kNB + q - 8) * 1024);
     load16_to_lds(voff[q], q < 8 ? base_a : base_b, dst);
   };
   // the two loads of a scale chunk (four K steps) into ring slot `slot`
@@ -398,17 +416,17 @@ __global__ __launch_bounds__(kThreads) void gemm_mx_kernel_k512(Operand A, Opera
   int tm = 0, tn = 0;
   locate(item, tm, tn);
   aim(tm, tn, 0, 0);
-  static_for<0, 16>([&](auto q) { issue_codes(q, 0); });
+  static_for<0, kLoads>([&](auto q) { issue_codes(q, 0); });
   base_a += kWideRowBytes;
   base_b += kWideRowBytes;
-  static_for<0, 16>([&](auto q) { issue_codes(q, 1); });
+  static_for<0, kLoads>([&](auto q) { issue_codes(q, 1); });
   issue_scales(0);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __builtin_amdgcn_s_barrier();
 
   Frags f0, f1;
   RawScales raw;
-  float4v acc[8][8];
+  float4v acc[8][kNB];
   uint32_t gst = 0;             // stages done so far, over all tiles (even at every tile's start)
   bool stores_behind = false;   // the previous tile's stores were issued after the loads now in flight
   for (;;) {
@@ -416,7 +434,7 @@ __global__ __launch_bounds__(kThreads) void gemm_mx_kernel_k512(Operand A, Opera
     // read again so that the output stage had their registers to work with.)
     {
       const uint32_t cur = (gst & 1) * kWideStageBytes, sc = ((gst >> 1) & 1) * kWideScaleSlotBytes;
-      static_for<0, kFragReads>([&](auto q) { read_frag_wide<decltype(q)::value>(f0, raw, a_lo + cur, b_lo + cur, a_scales + sc, b_scales + sc); });
+      static_for<0, kReads>([&](auto q) { read_frag_wide<decltype(q)::value, kNB>(f0, raw, a_lo + cur, b_lo + cur, a_scales + sc, b_scales + sc); });
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       pack_scales(f0, raw, sel01);
     }
@@ -446,29 +464,30 @@ __global__ __launch_bounds__(kThreads) void gemm_mx_kernel_k512(Operand A, Opera
       } else if (st + 2 > stages && !has_next) {
         code_advance = 0;
       }
-      static_for<0, 64>([&](auto ic) {
-        constexpr int n = decltype(ic)::value;
+      static_for<0, kMfmas>([&](auto ic) {
+        constexpr int n = decltype(ic)::value, i = n / kNB, j = n % kNB, rd = read_at(n, kReads, kMfmas, 1);
         if constexpr (kFirst)
-          mfma_first<(n & 3), ((n >> 3) & 3)>(acc[n >> 3][n & 7], f0.b[n & 7], f0.a[n >> 3], f0.pb[(n & 7) >> 2], f0.pa[n >> 5]);
+          mfma_first<(j & 3), (i & 3)>(acc[i][j], f0.b[j], f0.a[i], f0.pb[j >> 2], f0.pa[i >> 2]);
         else
-          mfma<(n & 3), ((n >> 3) & 3)>(acc[n >> 3][n & 7], f0.b[n & 7], f0.a[n >> 3], f0.pb[(n & 7) >> 2], f0.pa[n >> 5]);
-        if constexpr ((n & 1) == 1 && (n >> 1) < kFragReads)
-          read_frag_wide<(n >> 1)>(f1, raw, a_hi + cur, b_hi + cur, a_scales + sc1, b_scales + sc1);
+          mfma<(j & 3), (i & 3)>(acc[i][j], f0.b[j], f0.a[i], f0.pb[j >> 2], f0.pa[i >> 2]);
+        if constexpr (rd >= 0)
+          read_frag_wide<rd, kNB>(f1, raw, a_hi + cur, b_hi + cur, a_scales + sc1, b_scales + sc1);
         if constexpr (n == 2) {
           base_a += code_advance;
           base_b += code_advance;
         }
       });
-      if (kFirst && stores_behind) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(kTileStoresMx<kBf16Out>) : "memory");
+      if (kFirst && stores_behind) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(kTileStoresMx<kBf16Out, kNB>) : "memory");
       else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
       __builtin_amdgcn_s_barrier();
       pack_scales(f1, raw, sel01);
-      static_for<0, 64>([&](auto ic) {
-        constexpr int n = decltype(ic)::value;
-        mfma<(n & 3), ((n >> 3) & 3)>(acc[n >> 3][n & 7], f1.b[n & 7], f1.a[n >> 3], f1.pb[(n & 7) >> 2], f1.pa[n >> 5]);
-        if constexpr ((n & 1) == 0 && (n >> 1) < kFragReads)
-          read_frag_wide<(n >> 1)>(f0, raw, a_lo + nxt, b_lo + nxt, a_scales + sc2, b_scales + sc2);
-        if constexpr ((n & 3) == 3) issue_codes(std::integral_constant<int, (n >> 2)>{}, static_cast<int>(gst & 1));
+      static_for<0, kMfmas>([&](auto ic) {
+        constexpr int n = decltype(ic)::value, i = n / kNB, j = n % kNB;
+        constexpr int rd = read_at(n, kReads, kMfmas, 0), ld = spread(n, kLoads, kMfmas);
+        mfma<(j & 3), (i & 3)>(acc[i][j], f1.b[j], f1.a[i], f1.pb[j >> 2], f1.pa[i >> 2]);
+        if constexpr (rd >= 0)
+          read_frag_wide<rd, kNB>(f0, raw, a_lo + nxt, b_lo + nxt, a_scales + sc2, b_scales + sc2);
+        if constexpr (ld >= 0) issue_codes(std::integral_constant<int, ld>{}, static_cast<int>(gst & 1));
       });
       // even stages also fetch the scales of the chunk after the next stage's, into the slot its predecessor left
       // at this stage's barrier
@@ -485,18 +504,18 @@ __global__ __launch_bounds__(kThreads) void gemm_mx_kernel_k512(Operand A, Opera
     asm volatile("" : "+s"(wm), "+s"(wn));
     const int lane = lane_id();
     const TensorScales out_scale{A.ts, B.ts, false, false};    // both are 1 for MXFP4 (no tensor-level scale)
-    const int64_t m0 = static_cast<int64_t>(tm) * TM, n0 = static_cast<int64_t>(tn) * TN;
+    const int64_t m0 = static_cast<int64_t>(tm) * TM, n0 = static_cast<int64_t>(tn) * kTN;
     const int Mt = static_cast<int>(A.outer - m0 < TM ? A.outer - m0 : TM);
-    const int Nt = static_cast<int>(B.outer - n0 < TN ? B.outer - n0 : TN);
+    const int Nt = static_cast<int>(B.outer - n0 < kTN ? B.outer - n0 : kTN);
     // The MFMA results must have left the pipe before ordinary instructions read the accumulators (the compiler
     // cannot see into the assembly statements to insert these wait states itself).  With nothing to follow, the
     // trailing global->LDS loads must have landed before the wavefront ends.
     if (has_next) asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
     else asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
-    store_wave_block<kBf16Out>(acc, out_scale, Dv, ldd, accumulate, m0 + wm * 128, n0 + wn * 128, Mt - wm * 128, Nt - wn * 128,
+    store_wave_block<kBf16Out, kNB>(acc, out_scale, Dv, ldd, accumulate, m0 + wm * 128, n0 + wn * (16 * kNB), Mt - wm * 128, Nt - wn * (16 * kNB),
                                lane);
     if (!has_next) break;
-    stores_behind = Mt == TM && Nt == TN;   // every lane stored every block: the count is known
+    stores_behind = Mt == TM && Nt == kTN;   // every lane stored every block: the count is known
     item = next_item;
     tm = next_tm;
     tn = next_tn;
@@ -516,21 +535,54 @@ static hipError_t launch_mx(Kernel kernel, PerDeviceOnce& once, int lds_bytes, c
   return hipGetLastError();
 }
 
+// Width of the k512 kernel's tiles: 32 kNB columns.  256 x 256 tiles move the fewest bytes per product, but a product of a few
+// hundred of them leaves CUs idle: a tile of 5 / 8 of the width takes 0.80 of the time (K = 5120: 37.6, 35.4, 31.5, 26.4 us for kNB =
+// 8, 7, 5, 4), so the width with the smallest rounds-of-256-tiles x time is taken, the wider one at a tie.  Measured, us, at
+// kNB = 8 / 7 / 5 / 4: 4096 x 5120 x 5120 75 / 70 / 63 / 79, 5120 x 5120 x 4096 (FP32) 69.5 / 67 / 80 / 92, 512 x 5120 x 5120 33 / 33 / 27 /
+// 24, 1024 x 1024 x 1024 12.9 / 12.2 / 10.3 / 9.0, 8192 x 20480 x 5120 422 / 461 / 531 / 608.
+static int pick_mx_width(int64_t M, int64_t N) {
+  constexpr int kWidths[4] = {8, 7, 5, 4};
+  constexpr double kTime[4] = {1.0, 0.94, 0.80, 0.71};
+  int best = 8;
+  double best_time = 0.0;
+  for (int i = 0; i < 4; ++i) {
+    const int64_t tiles = ((M + TM - 1) / TM) * ((N + 32 * kWidths[i] - 1) / (32 * kWidths[i]));
+    const double t = static_cast<double>((tiles + 255) / 256) * kTime[i];
+    if (i == 0 || t < best_time) {
+      best = kWidths[i];
+      best_time = t;
+    }
+  }
+  return best;
+}
+
+template <int kNB>
+static hipError_t launch_k512(const GemmArgs& g, int tiles_m, hipStream_t s) {
+  static PerDeviceOnce once_bf16, once_f32;
+  const int tiles_n = static_cast<int>((g.b.outer + 32 * kNB - 1) / (32 * kNB));
+  const int64_t tiles = static_cast<int64_t>(tiles_m) * tiles_n;
+  const dim3 grid(static_cast<unsigned>(tiles < 256 ? tiles : 256));   // one workgroup per CU, each running its tiles as one stream
+  if (g.out_bf16) return launch_mx(gemm_mx_kernel_k512<true, kNB>, once_bf16, kWideLdsBytes, g, grid, tiles_m, tiles_n, s);
+  return launch_mx(gemm_mx_kernel_k512<false, kNB>, once_f32, kWideLdsBytes, g, grid, tiles_m, tiles_n, s);
+}
+
 hipError_t launch_gemm_mx(const GemmArgs& g, hipStream_t s) {
   if (g.K >= (int64_t{1} << 24)) return hipErrorInvalidValue;   // the kernels' 32-bit byte offsets inside a block of rows
   const int tiles_m = static_cast<int>((g.a.outer + TM - 1) / TM), tiles_n = static_cast<int>((g.b.outer + TN - 1) / TN);
-  const unsigned tiles = static_cast<unsigned>(tiles_m) * static_cast<unsigned>(tiles_n);
-  const dim3 grid(tiles);
-  const dim3 grid_cus(tiles < 256u ? tiles : 256u);   // the k512 kernel: one workgroup per CU, each running its tiles as one stream
   // 16-byte pieces of scale rows need K / 32 to be a multiple of 16 and the scale arrays 16-byte aligned
   const bool wide = g.K % 512 == 0 && reinterpret_cast<uintptr_t>(g.a.scales) % 16 == 0 && reinterpret_cast<uintptr_t>(g.b.scales) % 16 == 0;
-  static PerDeviceOnce set[4];
   if (wide) {
-    if (g.out_bf16) return launch_mx(gemm_mx_kernel_k512<true>, set[0], kWideLdsBytes, g, grid_cus, tiles_m, tiles_n, s);
-    return launch_mx(gemm_mx_kernel_k512<false>, set[1], kWideLdsBytes, g, grid_cus, tiles_m, tiles_n, s);
+    switch (pick_mx_width(g.a.outer, g.b.outer)) {
+      case 4: return launch_k512<4>(g, tiles_m, s);
+      case 5: return launch_k512<5>(g, tiles_m, s);
+      case 7: return launch_k512<7>(g, tiles_m, s);
+      default: return launch_k512<8>(g, tiles_m, s);
+    }
   }
-  if (g.out_bf16) return launch_mx(gemm_mx_kernel_any_k<true>, set[2], kLdsBytes, g, grid, tiles_m, tiles_n, s);
-  return launch_mx(gemm_mx_kernel_any_k<false>, set[3], kLdsBytes, g, grid, tiles_m, tiles_n, s);
+  const dim3 grid(static_cast<unsigned>(tiles_m) * static_cast<unsigned>(tiles_n));
+  static PerDeviceOnce set[2];
+  if (g.out_bf16) return launch_mx(gemm_mx_kernel_any_k<true>, set[0], kLdsBytes, g, grid, tiles_m, tiles_n, s);
+  return launch_mx(gemm_mx_kernel_any_k<false>, set[1], kLdsBytes, g, grid, tiles_m, tiles_n, s);
 }
 
 }  // namespace nvfp4

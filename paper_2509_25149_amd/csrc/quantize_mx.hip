@@ -85,7 +85,8 @@ template <bool kRow, bool kCol, bool kRht, bool kSR>
 __global__ __launch_bounds__(kThreads) void quantize_mx_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
                                                                int64_t ld, uint32_t sign_mask, uint32_t key0, uint32_t key1,
                                                                uint8_t* __restrict__ row_codes, uint8_t* __restrict__ row_scales,
-                                                               uint8_t* __restrict__ col_codes, uint8_t* __restrict__ col_scales) {
+                                                               float* __restrict__ row_ts, uint8_t* __restrict__ col_codes,
+                                                               uint8_t* __restrict__ col_scales, float* __restrict__ col_ts) {
   __shared__ __attribute__((aligned(16))) uint8_t st_col_codes[8 * 4 * kSlot * 16];   // [column of the lane][wavefront][lane] x 16 bytes
   __shared__ uint8_t st_col_scales[8 * 4 * 64];                                       // [column of the lane][wavefront][lane]
   __shared__ __attribute__((aligned(16))) uint8_t st_row_scales[4 * kRowsPerWave * 16];   // [wavefront][row][16 blocks]
@@ -95,6 +96,11 @@ __global__ __launch_bounds__(kThreads) void quantize_mx_kernel(const uint16_t* _
   const int64_t col0 = colblk + lane * 8;
   const int64_t rowblk = static_cast<int64_t>(blockIdx.y) * kRowsPerBlock;
   const int64_t row0 = rowblk + wave * kRowsPerWave;
+  if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) {
+    // MXFP4 has no tensor-level scale: s_dec = 1; the amax slot is not computed.
+    if (kRow) { row_ts[0] = 1.0f; row_ts[1] = 0.0f; }
+    if (kCol) { col_ts[0] = 1.0f; col_ts[1] = 0.0f; }
+  }
   const bool active = col0 < cols && row0 < rows;   // cols and rows are multiples of 32: whole patches only
 
   uint4 raw[32];
@@ -221,16 +227,10 @@ void dispatch(const QuantizeArgs& a, dim3 grid, hipStream_t s) {
   const uint16_t* x = static_cast<const uint16_t*>(a.x);
   if (a.sr)
     hipLaunchKernelGGL((quantize_mx_kernel<kRow, kCol, kRht, true>), grid, dim3(kThreads), 0, s, x, a.rows, a.cols, a.ld,
-                       a.sign_mask, a.key0, a.key1, a.row_codes, a.row_scales, a.col_codes, a.col_scales);
+                       a.sign_mask, a.key0, a.key1, a.row_codes, a.row_scales, a.row_ts, a.col_codes, a.col_scales, a.col_ts);
   else
     hipLaunchKernelGGL((quantize_mx_kernel<kRow, kCol, kRht, false>), grid, dim3(kThreads), 0, s, x, a.rows, a.cols, a.ld,
-                       a.sign_mask, a.key0, a.key1, a.row_codes, a.row_scales, a.col_codes, a.col_scales);
-}
-
-__global__ void mx_tensor_scale_kernel(float* row_ts, float* col_ts) {
-  // MXFP4 has no tensor-level scale: s_dec = 1; the amax slot is not computed.
-  if (row_ts) { row_ts[0] = 1.0f; row_ts[1] = 0.0f; }
-  if (col_ts) { col_ts[0] = 1.0f; col_ts[1] = 0.0f; }
+                       a.sign_mask, a.key0, a.key1, a.row_codes, a.row_scales, a.row_ts, a.col_codes, a.col_scales, a.col_ts);
 }
 
 }  // namespace
@@ -238,8 +238,6 @@ __global__ void mx_tensor_scale_kernel(float* row_ts, float* col_ts) {
 hipError_t launch_quantize_mx(const QuantizeArgs& a, hipStream_t s) {
   const dim3 grid(static_cast<unsigned>((a.cols + kWaveCols - 1) / kWaveCols),
                   static_cast<unsigned>((a.rows + kRowsPerBlock - 1) / kRowsPerBlock));
-  hipLaunchKernelGGL(mx_tensor_scale_kernel, dim3(1), dim3(1), 0, s, a.want_row ? a.row_ts : nullptr,
-                     a.want_col ? a.col_ts : nullptr);
   if (a.want_row && a.want_col) {
     if (a.rht) dispatch<true, true, true>(a, grid, s); else dispatch<true, true, false>(a, grid, s);
   } else if (a.want_row) {
