@@ -149,6 +149,13 @@ constexpr int kStageBytes = 2 * kOperandBytes;          // 32 KiB
 constexpr int kStages = 4;
 constexpr int kLdsBytes = kStages * kStageBytes;
 
+// Spreads `total` things evenly over the `slots` places between MFMAs, half a distance in: the number of the one that
+// place n takes, or -1.
+constexpr int spread(int n, int total, int slots) {
+  const int at = n * total + slots / 2;
+  return (at + total) / slots > at / slots ? at / slots : -1;
+}
+
 // Fragments of one 32-wide half of a K step for a 128 x 128 wave tile.  A 16x16x32 MFMA operand
 // is 16 rows x 32 k: lane l holds the 8 consecutive k of 16-byte chunk (l >> 4) of row (l & 15).
 struct Frags {
@@ -177,7 +184,7 @@ __device__ __forceinline__ void lds_read16(half8v& dst, uint32_t addr) {
   asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(dst) : "v"(addr), "n"(kOff));
 }
 
-// Fragment q of a 16-fragment set: 0..7 = A rows i * 16, 8..15 = B rows j * 16: one piece each.
+// Fragment q of a set: 0..7 = A rows i * 16, the others B rows j * 16: one piece each.
 template <int q>
 __device__ __forceinline__ void read_frag(Frags& f, uint32_t a_addr, uint32_t b_addr) {
   if constexpr (q < 8) lds_read16<q * kPieceBytes>(f.a[q], a_addr);
@@ -202,11 +209,11 @@ __device__ __forceinline__ void mfma_first(float4v& acc, const half8v& b, const 
   asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, 0" : "=a"(acc) : "v"(b), "v"(a));
 }
 
-// A wavefront's output stage issues 32 (bf16) or 64 (FP32) stores for a full 256 x 256 tile (store_wave_block: 16 bytes
+// A wavefront's output stage issues 8 ceil(kNB / 2) (bf16) or 8 kNB (FP32) stores for a full tile (store_wave_block: 16 bytes
 // per lane and instruction).  Three quarters of them: the number of its memory operations that may still be
 // outstanding when the loads issued before it are needed, with a margin against a store more or less.
-template <bool kBf16Out>
-constexpr int kTileStores = kBf16Out ? 24 : 48;
+template <bool kBf16Out, int kNB>
+constexpr int kTileStores = kBf16Out ? 6 * ((kNB + 1) / 2) : 6 * kNB;
 
 // Tiles [tile_begin, tile_begin + tile_count) of the 256x256 tiling are covered.
 //
@@ -228,13 +235,17 @@ constexpr int kTileStores = kBf16Out ? 24 : 48;
 // 1 MiB that four XCDs had written 50 -- with 16 loads in flight per thread, and 90 with 64.)
 // kRowScales: an operand carries a tensor-level scale per row (uniform over a launch, and a different output stage).
 // kSplit: k_splits > 1; the output stage is the store of the partial tile (kBf16Out and kRowScales are false then).
-template <bool kBf16Out, bool kRowScales, bool kSplit>
+// kNB: 16-column blocks per wavefront; a tile is 256 rows x 32 kNB columns (8: the 256 x 256 of the description above).  The
+// narrower tiles are for products whose rounds of 256 x 256 tiles come out badly (see pick_width).
+template <bool kBf16Out, bool kRowScales, bool kSplit, int kNB>
 __global__ __launch_bounds__(kThreads) void gemm_f16_kernel(const _Float16* __restrict__ A, const _Float16* __restrict__ B,
                                                             int64_t M, int64_t N, int64_t K, const float* __restrict__ a_ts,
                                                             const float* __restrict__ b_ts, void* __restrict__ Dv,
                                                             int64_t ldd, bool accumulate, int tiles_m, int tiles_n,
                                                             int tile_begin, int tile_count, int k_splits, float* partials,
                                                             bool a_ts_per_row, bool b_ts_per_row) {
+  constexpr int kTN = 32 * kNB, kMfmas = 8 * kNB, kReads = 8 + kNB;
+  constexpr int kBLoads = (2 * kNB + 3) / 4, kLoads = 4 + kBLoads;   // a wavefront's loads per stage: 4 pieces of A, 2 - 4 of B's 2 kNB (some of the last wavefront's are not needed)
   extern __shared__ __attribute__((aligned(16))) char lds[];
 
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
@@ -270,33 +281,32 @@ __global__ __launch_bounds__(kThreads) void gemm_f16_kernel(const _Float16* __re
   auto lane_setup = [&]() {
     lane_bytes = static_cast<uint32_t>(lane_id()) * 16u;
     a_frag = lds0 + (wave >> 1) * (8 * kPieceBytes) + lane_bytes;
-    b_frag = lds0 + kOperandBytes + (wave & 1) * (8 * kPieceBytes) + lane_bytes;
+    b_frag = lds0 + kOperandBytes + (wave & 1) * (kNB * kPieceBytes) + lane_bytes;
   };
   lane_setup();
   const char* base_a = nullptr;
   const char* base_b = nullptr;
-  uint32_t voff[8];   // q 0..3 A, 4..7 B
+  uint32_t voff[kLoads];   // q 0..3 A, then B
   // Point the loads at stage st (32 k) of tile (tm, tn).
   auto aim = [&](int tm, int tn, int st) {
-    const int64_t m_first = static_cast<int64_t>(tm) * TM, n_first = static_cast<int64_t>(tn) * TN;
+    const int64_t m_first = static_cast<int64_t>(tm) * TM, n_first = static_cast<int64_t>(tn) * kTN;
     base_a = reinterpret_cast<const char*>(A) + m_first * K * 2 + (st - 3) * kPieceBytes;
     base_b = reinterpret_cast<const char*>(B) + n_first * K * 2 + (st - 3) * kPieceBytes;
     // 16-row blocks counted from the tile's first; a block's stages are K / 32 KiB
     const uint32_t last_a = static_cast<uint32_t>(M - 16 - m_first) >> 4, last_b = static_cast<uint32_t>(N - 16 - n_first) >> 4;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const uint32_t blk = static_cast<uint32_t>(wave * 4 + q);
       const uint32_t fixed = static_cast<uint32_t>(3 - q) * 1024u;
-      voff[q] = lane_bytes + min(blk, last_a) * static_cast<uint32_t>(K * 32) + fixed;
-      voff[4 + q] = lane_bytes + min(blk, last_b) * static_cast<uint32_t>(K * 32) + fixed;
+      voff[q] = lane_bytes + min(static_cast<uint32_t>(wave * 4 + q), last_a) * static_cast<uint32_t>(K * 32) + fixed;
+      if (q < kBLoads) voff[4 + q] = lane_bytes + min(static_cast<uint32_t>(wave * kBLoads + q), last_b) * static_cast<uint32_t>(K * 32) + fixed;
     }
   };
-  const uint32_t fill0 = lds0 + wave * (4 * kPieceBytes);   // this wavefront's 4 KiB of each operand tile
-  // load q of the wavefront's 8 that fill ring buffer `buf`
+  const uint32_t fill_a = lds0 + wave * (4 * kPieceBytes), fill_b = lds0 + kOperandBytes + wave * (kBLoads * kPieceBytes);   // this wavefront's pieces of each operand tile
+  // load q of the wavefront's that fill ring buffer `buf`
   auto issue = [&](auto qc, uint32_t buf) {
     constexpr int q = decltype(qc)::value;
     const char* base = q < 4 ? base_a : base_b;
-    if constexpr ((q & 3) == 0) load_1k_to_lds(voff[q], base, fill0 + buf * kStageBytes + (q < 4 ? 0 : kOperandBytes));
+    if constexpr ((q & 3) == 0) load_1k_to_lds(voff[q], base, (q < 4 ? fill_a : fill_b) + buf * kStageBytes);
     else load_1k_to_lds_next<(q & 3) * 1024>(voff[q], base);
   };
 
@@ -311,7 +321,7 @@ __global__ __launch_bounds__(kThreads) void gemm_f16_kernel(const _Float16* __re
   // The stage the loads were last pointed at: they run four stages ahead of the MFMAs.
   int fetch_st = 2 * kt_begin;
   aim(tm, tn, fetch_st);
-  static_for<0, 8>([&](auto q) { issue(q, 0); });
+  static_for<0, kLoads>([&](auto q) { issue(q, 0); });
 #pragma unroll
   for (uint32_t buf = 1; buf < kStages; ++buf) {
     if (fetch_st + 1 < 2 * kt_end) {   // (an item of two stages fetches its last three times)
@@ -319,13 +329,13 @@ __global__ __launch_bounds__(kThreads) void gemm_f16_kernel(const _Float16* __re
       base_a += kPieceBytes;
       base_b += kPieceBytes;
     }
-    static_for<0, 8>([&](auto q) { issue(q, buf); });
+    static_for<0, kLoads>([&](auto q) { issue(q, buf); });
   }
-  asm volatile("s_waitcnt vmcnt(16)" ::: "memory");   // the first two stages
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kLoads) : "memory");   // the first two stages
   __builtin_amdgcn_s_barrier();
 
   Frags f0, f1;
-  float4v acc[8][8];
+  float4v acc[8][kNB];
   uint32_t g = 0;               // stages done so far; stage g lives in ring buffer g % 4
   bool stores_behind = false;   // the previous tile's kTileStores stores were issued after the loads now in flight
   for (;;) {
@@ -334,7 +344,7 @@ __global__ __launch_bounds__(kThreads) void gemm_f16_kernel(const _Float16* __re
     // buffer these came from.
     {
       const uint32_t cur = (g & 3u) * kStageBytes;
-      static_for<0, 16>([&](auto q) { read_frag<decltype(q)::value>(f0, a_frag + cur, b_frag + cur); });
+      static_for<0, kReads>([&](auto q) { read_frag<decltype(q)::value>(f0, a_frag + cur, b_frag + cur); });
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
@@ -363,20 +373,20 @@ __global__ __launch_bounds__(kThreads) void gemm_f16_kernel(const _Float16* __re
           aim(next_tm, next_tn, 0);
         }
       }
-      static_for<0, 64>([&](auto ic) {
-        constexpr int n = decltype(ic)::value;
-        if constexpr (kFirst) mfma_first(acc[n >> 3][n & 7], fc.b[n & 7], fc.a[n >> 3]);
-        else mfma(acc[n >> 3][n & 7], fc.b[n & 7], fc.a[n >> 3]);
-        if constexpr ((n & 3) == 1) read_frag<(n >> 2)>(fn, a_frag + nxt, b_frag + nxt);
-        if constexpr (n == 3) base_a += advance;
-        if constexpr (n == 35) base_b += advance;
-        if constexpr ((n & 7) == 3) issue(std::integral_constant<int, (n >> 3)>{}, buf);
+      static_for<0, kMfmas>([&](auto ic) {
+        constexpr int n = decltype(ic)::value, i = n / kNB, j = n % kNB, rd = spread(n, kReads, kMfmas), ld = spread(n, kLoads, kMfmas);
+        if constexpr (kFirst) mfma_first(acc[i][j], fc.b[j], fc.a[i]);
+        else mfma(acc[i][j], fc.b[j], fc.a[i]);
+        if constexpr (rd >= 0) read_frag<rd>(fn, a_frag + nxt, b_frag + nxt);
+        if constexpr (ld == 0) base_a += advance;
+        if constexpr (ld == 4) base_b += advance;
+        if constexpr (ld >= 0) issue(std::integral_constant<int, ld>{}, buf);
       });
       // Memory operations complete in issue order.  Behind the loads of stage g + 2 this wavefront has issued those of
-      // g + 3 and g + 4, 8 each, and, across a tile boundary, the stores of the tile before.
+      // g + 3 and g + 4, kLoads each, and, across a tile boundary, the stores of the tile before.
       if (kRelaxed && stores_behind)
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(16 + kTileStores<kBf16Out> > 63 ? 63 : 16 + kTileStores<kBf16Out>) : "memory");
-      else asm volatile("s_waitcnt vmcnt(16) lgkmcnt(0)" ::: "memory");
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * kLoads + kTileStores<kBf16Out, kNB> > 63 ? 63 : 2 * kLoads + kTileStores<kBf16Out, kNB>) : "memory");
+      else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * kLoads) : "memory");
       __builtin_amdgcn_s_barrier();
       ++g;
     };
@@ -395,9 +405,9 @@ __global__ __launch_bounds__(kThreads) void gemm_f16_kernel(const _Float16* __re
     const int lane = lane_id(), tid = (wm * 2 + wn) * 64 + lane;
     // Tensor-level decode scales on the finished sums (App. B.3, after Eq. 5).
     const TensorScales out_scale{a_ts, b_ts, a_ts_per_row, b_ts_per_row};
-    const int64_t m0 = static_cast<int64_t>(tm) * TM, n0 = static_cast<int64_t>(tn) * TN;
+    const int64_t m0 = static_cast<int64_t>(tm) * TM, n0 = static_cast<int64_t>(tn) * kTN;
     const int Mt = static_cast<int>(M - m0 < TM ? M - m0 : TM);
-    const int Nt = static_cast<int>(N - n0 < TN ? N - n0 : TN);
+    const int Nt = static_cast<int>(N - n0 < kTN ? N - n0 : kTN);
     // The MFMA results must have left the pipe before ordinary instructions read the accumulators (the compiler
     // cannot see into the assembly statements to insert these wait states itself).  With nothing to follow, the
     // trailing global->LDS loads must have landed before the wavefront ends; otherwise the next
@@ -410,20 +420,21 @@ __global__ __launch_bounds__(kThreads) void gemm_f16_kernel(const _Float16* __re
     }
 
     if constexpr (kSplit) {   // has_next is false
+      static_assert(kNB == 8, "the partial tiles are 256 x 256");
       // Partial tile in fragment order: float4 number (i * 8 + j) * 256 + tid.
       float4v* mine = reinterpret_cast<float4v*>(partials) +
                       (static_cast<int64_t>(tile_local) * k_splits + split) * (TM * TN / 4) + tid;
 #pragma unroll
       for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int j = 0; j < 8; ++j) mine[(i * 8 + j) * kThreads] = acc[i][j];
+        for (int j = 0; j < kNB; ++j) mine[(i * kNB + j) * kThreads] = acc[i][j];
       return;
     } else {
-      store_wave_block_impl<kBf16Out, kRowScales>(acc, out_scale, Dv, ldd, accumulate, m0 + wm * 128, n0 + wn * 128,
-                                                  Mt - wm * 128, Nt - wn * 128, lane);
+      store_wave_block_impl<kBf16Out, kRowScales, kNB>(acc, out_scale, Dv, ldd, accumulate, m0 + wm * 128, n0 + wn * (16 * kNB),
+                                                       Mt - wm * 128, Nt - wn * (16 * kNB), lane);
     }
     if (!has_next) break;
-    stores_behind = Mt == TM && Nt == TN;   // every lane stored every block: the count is known
+    stores_behind = Mt == TM && Nt == kTN;   // every lane stored every block: the count is known
     item = next_item;
     tm = next_tm;
     tn = next_tn;
@@ -494,6 +505,31 @@ static TailPlan plan_tail(int64_t M, int64_t N, int64_t K) {
   return p;
 }
 
+// Tile width (32 nb columns) of the whole product, and how long it takes in rounds of 256 x 256 tiles.  A narrower tile takes
+// 0.90, 0.80, 0.68 of the time for nb = 7, 6, 5 (fewer products per byte moved), but rounds come out better for some
+// products; the widest wins a tie.  A split last round costs its share of a round and 0.15 for the partial tiles.  Measured,
+// us per call with nb = 8 / 7 / 6 / 5: 5120 x 5120 x 4096 (FP32) 179 / 172 / 211 / 190, 2048 x 5120 x 5120 105 / 99 / 93 / 89, 4096 x 5120 x 5120
+// 171 (split) / 189 / 170 / 160, 3072 x 5120 x 5120 118 / 187 / 166 / 147, 8192 x 5120 x 20480 1165 (split) / 1225 / 1337 / 1337.
+struct Width {
+  int nb;
+  double rounds;
+  int64_t tiles;
+};
+static Width pick_width(int64_t M, int64_t N, const TailPlan& p) {
+  constexpr double kTime[4] = {1.0, 0.90, 0.80, 0.68};
+  const int64_t tiles_m = (M + TM - 1) / TM;
+  Width best{8, 0.0, 0};
+  for (int i = 0; i < 4; ++i) {
+    const int nb = 8 - i;
+    const int64_t tiles = tiles_m * ((N + 32 * nb - 1) / (32 * nb));
+    double rounds = static_cast<double>((tiles + kCUs - 1) / kCUs);
+    if (i == 0 && p.tail) rounds = static_cast<double>((tiles - p.tail) / kCUs) + 1.0 / p.splits + 0.15;
+    rounds *= kTime[i];
+    if (i == 0 || rounds < best.rounds) best = Width{nb, rounds, tiles};
+  }
+  return best;
+}
+
 // FP16 bytes of the operands that still have to be decoded into the workspace (rows_a / rows_b: 0 for an operand the
 // caller has decoded beforehand)
 static size_t operand_bytes(int64_t rows_a, int64_t rows_b, int64_t K) {
@@ -525,34 +561,28 @@ bool gemm_two_pass_usable(const GemmArgs& g) {
 }
 
 // Expected time of this route: what is still to decode (codes and scales in, FP16 out) at 4.7 TB/s, then rounds of 256
-// tiles at 16 ns per k while the chip is partly filled (160 tiles, K = 5120: 83 us) up to 22.5 when it is full (the clock
-// drops with the matrix pipes busy), a split last round counted as the fraction it is.
+// tiles at 18.5 ns per k while there are fewer (3072 x 5120 x 5120, 240 tiles: 118 us in all) and 22.5 when the chip is full (the clock
+// drops with the matrix pipes busy).
 double gemm_two_pass_us(const GemmArgs& g) {
   const int64_t M = g.a.outer, N = g.b.outer;
   const double k = static_cast<double>(g.K);
-  const int64_t tiles = ((M + TM - 1) / TM) * ((N + TN - 1) / TN);
-  const TailPlan p = plan_tail(M, N, g.K);
-  double rounds = static_cast<double>((tiles - p.tail + kCUs - 1) / kCUs), us = 4.0;
-  if (p.tail) {
-    rounds += 1.0 / p.splits;
-    us += 15.0;
-  }
+  const Width w = pick_width(M, N, plan_tail(M, N, g.K));
   const int64_t rows = (g.a.fp16 ? 0 : M) + (g.b.fp16 ? 0 : N);
-  us += static_cast<double>(rows) * k * 2.5625 / 4.7e6 + (rows ? 2.0 : 0.0);
-  return us + rounds * k * (tiles >= kCUs ? 0.0225 : 0.0160);
+  return 4.0 + static_cast<double>(rows) * k * 2.5625 / 4.7e6 + (rows ? 2.0 : 0.0) + w.rounds * k * (w.tiles >= kCUs ? 0.0225 : 0.0185);
 }
 
-#define NVFP4_LAUNCH_F16(BF16, ROWSCALES, SPLIT)                                                                  \
+#define NVFP4_LAUNCH_F16(BF16, ROWSCALES, SPLIT, NB)                                                                  \
   do {                                                                                                            \
     static PerDeviceOnce once;                                                                                    \
-    const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&gemm_f16_kernel<BF16, ROWSCALES, SPLIT>), kLdsBytes, once); \
+    const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&gemm_f16_kernel<BF16, ROWSCALES, SPLIT, NB>), kLdsBytes, once); \
     if (e != hipSuccess) return e;                                                                                \
-    hipLaunchKernelGGL((gemm_f16_kernel<BF16, ROWSCALES, SPLIT>), dim3(wgs), dim3(kThreads), kLdsBytes, s, a16, b16, \
+    hipLaunchKernelGGL((gemm_f16_kernel<BF16, ROWSCALES, SPLIT, NB>), dim3(wgs), dim3(kThreads), kLdsBytes, s, a16, b16, \
                        g.a.outer, g.b.outer, g.K, g.a.ts, g.b.ts, g.d, g.ldd, g.accumulate, tiles_m, tiles_n,     \
                        tile_begin, tile_count, k_splits, partials, g.a.ts_per_row != 0, g.b.ts_per_row != 0);      \
   } while (0)
 
 // Tiles [tile_begin, tile_begin + tile_count); k_splits > 1: each shared by that many workgroups, summed by a second launch.
+template <int kNB>
 static hipError_t launch_f16(bool bf16_out, const _Float16* a16, const _Float16* b16, const GemmArgs& g, int tiles_m,
                              int tiles_n, int tile_begin, int tile_count, int k_splits, float* partials, hipStream_t s) {
   // More whole tiles than CUs: one workgroup per CU, each running its tiles as one stream of K steps.
@@ -560,7 +590,7 @@ static hipError_t launch_f16(bool bf16_out, const _Float16* a16, const _Float16*
   if (k_splits == 1 && g.K / TK >= 2 && wgs > static_cast<unsigned>(kCUs)) wgs = kCUs;
   const bool row_scales = g.a.ts_per_row != 0 || g.b.ts_per_row != 0;
   if (k_splits > 1) {
-    NVFP4_LAUNCH_F16(false, false, true);
+    NVFP4_LAUNCH_F16(false, false, true, 8);
     const dim3 grid(static_cast<unsigned>(tile_count) * 32);   // tile, 128 x 128 block, 16 rows
 #define NVFP4_LAUNCH_SUM(BF16, ROWSCALES)                                                                              \
   hipLaunchKernelGGL((splitk_sum_kernel<BF16, ROWSCALES>), grid, dim3(64), 0, s, partials, k_splits, g.a.outer, g.b.outer, \
@@ -573,9 +603,9 @@ static hipError_t launch_f16(bool bf16_out, const _Float16* a16, const _Float16*
     }
 #undef NVFP4_LAUNCH_SUM
   } else if (row_scales) {
-    if (bf16_out) NVFP4_LAUNCH_F16(true, true, false); else NVFP4_LAUNCH_F16(false, true, false);
+    if (bf16_out) NVFP4_LAUNCH_F16(true, true, false, kNB); else NVFP4_LAUNCH_F16(false, true, false, kNB);
   } else {
-    if (bf16_out) NVFP4_LAUNCH_F16(true, false, false); else NVFP4_LAUNCH_F16(false, false, false);
+    if (bf16_out) NVFP4_LAUNCH_F16(true, false, false, kNB); else NVFP4_LAUNCH_F16(false, false, false, kNB);
   }
   return hipGetLastError();
 }
@@ -597,6 +627,13 @@ hipError_t launch_predecode(const Operand& op, int64_t K, void* fp16_out, hipStr
                      static_cast<int>(op.outer / 16), static_cast<_Float16*>(fp16_out), op.codes, op.scales, 0,
                      static_cast<_Float16*>(fp16_out), K);
   return hipGetLastError();
+}
+
+// Every tile in one launch of the kernel with 32 kNB columns per tile.
+template <int kNB>
+static hipError_t launch_all(const GemmArgs& g, const _Float16* a16, const _Float16* b16, int tiles_m, hipStream_t s) {
+  const int tiles_n = static_cast<int>((g.b.outer + 32 * kNB - 1) / (32 * kNB));
+  return launch_f16<kNB>(g.out_bf16, a16, b16, g, tiles_m, tiles_n, 0, tiles_m * tiles_n, 1, nullptr, s);
 }
 
 hipError_t launch_gemm_two_pass(const GemmArgs& g, hipStream_t s) {
@@ -621,11 +658,17 @@ hipError_t launch_gemm_two_pass(const GemmArgs& g, hipStream_t s) {
   // One 256x256 tile keeps one CU busy (its LDS fits one workgroup).  Whole rounds of kCUs tiles
   // run as they are; a last partial round that fills at most half the chip is split along K.
   const TailPlan p = plan_tail(M, N, K);
+  switch (pick_width(M, N, p).nb) {
+    case 7: return launch_all<7>(g, a16, b16, tiles_m, s);
+    case 6: return launch_all<6>(g, a16, b16, tiles_m, s);
+    case 5: return launch_all<5>(g, a16, b16, tiles_m, s);
+    default: break;
+  }
   const int full = tiles - p.tail;
   hipError_t e = hipSuccess;
-  if (full > 0) e = launch_f16(g.out_bf16, a16, b16, g, tiles_m, tiles_n, 0, full, 1, nullptr, s);
+  if (full > 0) e = launch_f16<8>(g.out_bf16, a16, b16, g, tiles_m, tiles_n, 0, full, 1, nullptr, s);
   if (e == hipSuccess && p.tail > 0)
-    e = launch_f16(g.out_bf16, a16, b16, g, tiles_m, tiles_n, full, p.tail, p.splits, partials, s);
+    e = launch_f16<8>(g.out_bf16, a16, b16, g, tiles_m, tiles_n, full, p.tail, p.splits, partials, s);
   return e;
 }
 
