@@ -87,12 +87,14 @@ __global__ __launch_bounds__(kThreads) void amax_kernel(const uint16_t* __restri
 // Codes leave with non-temporal stores: nothing reads them in this call, and in the memory-side cache they push out the tensor
 // that pass 1 has left there (W 104 -> 86 us, dY 8192 x 20480 SR 223 -> 213, X 8192 x 5120 47.8 -> 46.8).
 using CastTile = Staged<8, 32, true>;
-template <bool kRow, bool kCol, int kRht, bool kSR, bool k2D>   // kRht as in amax_kernel
+// kStream: the source is read with non-temporal loads (cast_streams; a template argument because a branch around the patch's loads
+// makes every one of them wait at its end: dY 8192 x 20480 SR 232 us).
+template <bool kRow, bool kCol, int kRht, bool kSR, bool k2D, bool kStream>   // kRht as in amax_kernel
 __global__ __launch_bounds__(kThreads, 2) void cast_kernel(
     const uint16_t* __restrict__ x, int64_t rows, int64_t cols, int64_t ld,
     const uint32_t* __restrict__ maxima, uint32_t n_maxima, uint32_t sign_mask, uint32_t key0, uint32_t key1,
     uint8_t* __restrict__ row_codes, uint8_t* __restrict__ row_scales, float* __restrict__ row_ts,
-    uint8_t* __restrict__ col_codes, uint8_t* __restrict__ col_scales, float* __restrict__ col_ts, int reverse, int stream) {
+    uint8_t* __restrict__ col_codes, uint8_t* __restrict__ col_scales, float* __restrict__ col_ts, int reverse) {
   using T = CastTile;
   __shared__ __attribute__((aligned(16))) uint8_t st_col_codes[kCol ? T::kColCodesBytes : 16];
   __shared__ __attribute__((aligned(16))) uint8_t st_col_scales[kCol ? T::kColScalesBytes : 16];
@@ -108,12 +110,11 @@ __global__ __launch_bounds__(kThreads, 2) void cast_kernel(
   const int64_t group0 = static_cast<int64_t>(by) * T::kGroups, ngroups = rows / 16;
   const int64_t group = group0 + gl, row0 = group * 16;
   const bool active = col0 < cols && group < ngroups;
+  // A small tensor's two copies are made by two sets of workgroups (see launch_cast).
+  const bool do_row = kRow && (gridDim.z == 1 || blockIdx.z == 0), do_col = kCol && (gridDim.z == 1 || blockIdx.z == 1);
 
   Patch p;
-  if (active) {
-    if (stream) load_patch<true>(x, ld, row0, col0, p);
-    else load_patch(x, ld, row0, col0, p);
-  }
+  if (active) load_patch<kStream>(x, ld, row0, col0, p);
 
   uint32_t m_raw = 0, m_rot = 0;
   for (uint32_t i = tid; i < n_maxima; i += kThreads) {
@@ -138,8 +139,8 @@ __global__ __launch_bounds__(kThreads, 2) void cast_kernel(
   tensor_scales(amax_raw, s_enc_r, s_dec_r);
   tensor_scales(amax_col, s_enc_c, s_dec_c);
   if (bx == 0 && by == 0 && tid == 0) {
-    if (kRow) { row_ts[0] = s_dec_r; row_ts[1] = amax_raw; }
-    if (kCol) { col_ts[0] = s_dec_c; col_ts[1] = amax_col; }
+    if (do_row) { row_ts[0] = s_dec_r; row_ts[1] = amax_raw; }
+    if (do_col) { col_ts[0] = s_dec_c; col_ts[1] = amax_col; }
   }
   // "real" block encode scale 1 / (fp32(code) * s_dec) for each of the 127 codes (App. B.2)
   {
@@ -169,11 +170,11 @@ __global__ __launch_bounds__(kThreads, 2) void cast_kernel(
       s_enc_tile = lut_row[tile_code];
     }
 
-    if (kRow)
+    if (do_row)
       row_pass<kSR, k2D, T>(p, rnd, lane, gl, s_enc_r, lut_row, s_enc_tile, tile_code, row_codes + row0 * (cols / 2) + col0 / 2,
                             cols / 2, st_row_scales);
 
-    if (kCol) {
+    if (do_col) {
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         float lo[16], hi[16];
@@ -197,7 +198,7 @@ __global__ __launch_bounds__(kThreads, 2) void cast_kernel(
   __syncthreads();
 
   write_back_tile<kRow, kCol, kThreads, T>(tid, rows, cols, group0, ngroups, colblk, st_col_codes, st_col_scales,
-                                           st_row_scales, row_scales, col_codes, col_scales);
+                                           st_row_scales, row_scales, col_codes, col_scales, do_row, do_col);
 }
 
 // ---------------------------------------------------------------- host side
@@ -232,12 +233,17 @@ static dim3 amax_grid(const QuantizeArgs& a) {
 template <bool kRow, bool kCol, int kRht, bool kSR, bool k2D>
 static void launch_cast(const QuantizeArgs& a, hipStream_t s) {
   using T = CastTile;
-  const dim3 grid(static_cast<unsigned>((a.cols + T::kCols - 1) / T::kCols), static_cast<unsigned>((a.rows / 16 + T::kGroups - 1) / T::kGroups));
+  const unsigned gx = static_cast<unsigned>((a.cols + T::kCols - 1) / T::kCols), gy = static_cast<unsigned>((a.rows / 16 + T::kGroups - 1) / T::kGroups);
+  // Up to 256 workgroups (one per CU) the call takes as long as one patch does: each copy gets workgroups of its own, though the
+  // patch is then read twice.  us, one set / two: X 256 x 512 12.9 / 10.6, dY SR 256 x 512 15.7 / 11.9, X 2048 x 4096 (256 workgroups)
+  // 15.0 / 12.9, dY 4096 x 4096 (512) 28.4 / 31.8.  16x16 blocks have little work per patch: 2048 x 4096 10.3 / 10.8.
+  const dim3 grid(gx, gy, kRow && kCol && !k2D && static_cast<int64_t>(gx) * gy <= 256 ? 2 : 1);
   const dim3 ag = amax_grid(a);
   const uint32_t* maxima = a.do_amax ? a.ws + kWsHeader : a.ws;
-  hipLaunchKernelGGL((cast_kernel<kRow, kCol, kRht, kSR, k2D>), grid, dim3(kThreads), 0, s,
+  const auto kernel = cast_streams(a) ? &cast_kernel<kRow, kCol, kRht, kSR, k2D, true> : &cast_kernel<kRow, kCol, kRht, kSR, k2D, false>;
+  hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s,
                      static_cast<const uint16_t*>(a.x), a.rows, a.cols, a.ld, maxima, a.do_amax ? ag.x * ag.y : 1u, a.sign_mask, a.key0,
-                     a.key1, a.row_codes, a.row_scales, a.row_ts, a.col_codes, a.col_scales, a.col_ts, cast_reverse(a), cast_streams(a));
+                     a.key1, a.row_codes, a.row_scales, a.row_ts, a.col_codes, a.col_scales, a.col_ts, cast_reverse(a));
 }
 
 template <bool kRow, bool kCol, int kRht>

@@ -292,12 +292,13 @@ template <bool kRow, bool kCol, int kT, class T = WideTile>
 __device__ __forceinline__ void write_back_tile(int tid, int64_t rows, int64_t cols, int64_t group0, int64_t ngroups,
                                                 int64_t colblk, const uint8_t* st_col_codes, const uint8_t* st_col_scales,
                                                 const uint8_t* st_row_scales, uint8_t* __restrict__ row_scales,
-                                                uint8_t* __restrict__ col_codes, uint8_t* __restrict__ col_scales) {
+                                                uint8_t* __restrict__ col_codes, uint8_t* __restrict__ col_scales,
+                                                bool do_row = true, bool do_col = true) {
   constexpr int kG = T::kGroups;
   const int tile_groups = static_cast<int>(min<int64_t>(kG, ngroups - group0));
   const int tile_cols = static_cast<int>(min<int64_t>(T::kCols, cols - colblk));
 
-  if (kRow) {
+  if (kRow && do_row) {
     const int64_t scale_ld = cols / 16;
     const int nblk = tile_cols / 16;  // scale bytes per row in this tile
     constexpr int kPiece = T::kRowScaleLd < 16 ? T::kRowScaleLd : 16, kPieces = T::kRowScaleLd / kPiece;   // of a full tile row
@@ -319,7 +320,7 @@ __device__ __forceinline__ void write_back_tile(int tid, int64_t rows, int64_t c
     }
   }
 
-  if (kCol) {
+  if (kCol && do_col) {
     const int64_t code_ld = rows / 2, scale_ld = rows / 16;
     const bool wide = (code_ld & 15) == 0;   // 16-byte aligned column rows
 #pragma unroll 1
