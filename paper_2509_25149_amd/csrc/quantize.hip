@@ -87,10 +87,15 @@ __global__ __launch_bounds__(kThreads) void amax_kernel(const uint16_t* __restri
 // Codes leave with non-temporal stores: nothing reads them in this call, and in the memory-side cache they push out the tensor
 // that pass 1 has left there (W 104 -> 86 us, dY 8192 x 20480 SR 223 -> 213, X 8192 x 5120 47.8 -> 46.8).
 using CastTile = Staged<8, 32, true>;
+__device__ __forceinline__ float to_scalar(float v) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v))); }
+
 // kStream: the source is read with non-temporal loads (cast_streams; a template argument because a branch around the patch's loads
 // makes every one of them wait at its end: dY 8192 x 20480 SR 232 us).
 template <bool kRow, bool kCol, int kRht, bool kSR, bool k2D, bool kStream>   // kRht as in amax_kernel
-__global__ __launch_bounds__(kThreads, 2) void cast_kernel(
+// With stochastic rounding the draws of a patch (64 registers beside its own 64) left room for two wavefronts per SIMD, which did
+// not cover each other's loads and stores; columns one at a time instead of in pairs bring both copies under 168 registers (with
+// eight parked in LDS), i.e. to three: dY 8192 x 20480 209 -> 189 us, 8192 x 5120 61 -> 57.
+__global__ __launch_bounds__(kThreads, kSR && kRow && kCol && !k2D ? 3 : 2) void cast_kernel(
     const uint16_t* __restrict__ x, int64_t rows, int64_t cols, int64_t ld,
     const uint32_t* __restrict__ maxima, uint32_t n_maxima, uint32_t sign_mask, uint32_t key0, uint32_t key1,
     uint8_t* __restrict__ row_codes, uint8_t* __restrict__ row_scales, float* __restrict__ row_ts,
@@ -101,6 +106,7 @@ __global__ __launch_bounds__(kThreads, 2) void cast_kernel(
   __shared__ __attribute__((aligned(16))) uint8_t st_row_scales[kRow ? T::kRowScalesBytes : 16];
   __shared__ float lut_row[128], lut_col[128];  // block encode scale per stored E4M3 code
   __shared__ uint32_t red[2][4];
+  __shared__ __attribute__((aligned(16))) uint4 stash[kSR && kRow && kCol ? 2 * kThreads : 1];
 
   const int tid = threadIdx.x, lane = tid & (T::kLanes - 1), wave = tid >> 6;
   const int gl = tid / T::kLanes;                // group index inside the tile
@@ -138,6 +144,8 @@ __global__ __launch_bounds__(kThreads, 2) void cast_kernel(
   float s_enc_r, s_dec_r, s_enc_c, s_dec_c;
   tensor_scales(amax_raw, s_enc_r, s_dec_r);
   tensor_scales(amax_col, s_enc_c, s_dec_c);
+  s_enc_r = to_scalar(s_enc_r);   // the same in every lane: no vector register for them
+  s_enc_c = to_scalar(s_enc_c);
   if (bx == 0 && by == 0 && tid == 0) {
     if (do_row) { row_ts[0] = s_dec_r; row_ts[1] = amax_raw; }
     if (do_col) { col_ts[0] = s_dec_c; col_ts[1] = amax_col; }
@@ -175,23 +183,50 @@ __global__ __launch_bounds__(kThreads, 2) void cast_kernel(
                             cols / 2, st_row_scales);
 
     if (do_col) {
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        float lo[16], hi[16];
-        // Without a rotation sign_mask is 0 at run time; it is still applied, so that these values are not
-        // recognised as the row pass's: keeping all 128 of those alive costs more registers than there are.
-        signed_column_pair(p, t, sign_mask, lo, hi);
-        if (kRht) {
-          butterfly_rows<kRht>(lo);
-          butterfly_rows<kRht>(hi);
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            lo[r] *= rht_norm<kRht>();
-            hi[r] *= rht_norm<kRht>();
-          }
+      if (kSR) {
+        // one column at a time, in order: with the draws in registers there is no room for two, and eight of the words that
+        // hold columns 6 and 7 wait in LDS meanwhile (the assembly statement keeps the compiler from remembering them)
+        if (kRow) {
+          stash[tid] = make_uint4(p.raw[0].w, p.raw[1].w, p.raw[2].w, p.raw[3].w);
+          stash[kThreads + tid] = make_uint4(p.raw[4].w, p.raw[5].w, p.raw[6].w, p.raw[7].w);
+          asm volatile("" ::"v"(stash + tid) : "memory");
         }
-        emit_column<kSR, k2D, T>(lo, 2 * t, rnd, lane, gl, s_enc_c, lut_col, s_enc_tile, tile_code, st_col_codes, st_col_scales);
-        emit_column<kSR, k2D, T>(hi, 2 * t + 1, rnd, lane, gl, s_enc_c, lut_col, s_enc_tile, tile_code, st_col_codes, st_col_scales);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          if (kRow && c == 6) {
+            const uint4 a = stash[tid], b = stash[kThreads + tid];
+            p.raw[0].w = a.x, p.raw[1].w = a.y, p.raw[2].w = a.z, p.raw[3].w = a.w;
+            p.raw[4].w = b.x, p.raw[5].w = b.y, p.raw[6].w = b.z, p.raw[7].w = b.w;
+          }
+          float v[16];
+          signed_column(p, c, sign_mask, v);
+          if (kRht) {
+            butterfly_rows<kRht>(v);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) v[r] *= rht_norm<kRht>();
+          }
+          emit_column<kSR, k2D, T>(v, c, rnd, lane, gl, s_enc_c, lut_col, s_enc_tile, tile_code, st_col_codes, st_col_scales);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      } else {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          float lo[16], hi[16];
+          // Without a rotation sign_mask is 0 at run time; it is still applied, so that these values are not
+          // recognised as the row pass's: keeping all 128 of those alive costs more registers than there are.
+          signed_column_pair(p, t, sign_mask, lo, hi);
+          if (kRht) {
+            butterfly_rows<kRht>(lo);
+            butterfly_rows<kRht>(hi);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              lo[r] *= rht_norm<kRht>();
+              hi[r] *= rht_norm<kRht>();
+            }
+          }
+          emit_column<kSR, k2D, T>(lo, 2 * t, rnd, lane, gl, s_enc_c, lut_col, s_enc_tile, tile_code, st_col_codes, st_col_scales);
+          emit_column<kSR, k2D, T>(hi, 2 * t + 1, rnd, lane, gl, s_enc_c, lut_col, s_enc_tile, tile_code, st_col_codes, st_col_scales);
+        }
       }
     }
   }

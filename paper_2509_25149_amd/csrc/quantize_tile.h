@@ -86,6 +86,15 @@ __device__ __forceinline__ void signed_column_pair(const Patch& p, int t, uint32
   }
 }
 
+// The 16 values of one column, likewise.
+__device__ __forceinline__ void signed_column(const Patch& p, int c, uint32_t sign_mask, float v[16]) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const uint32_t w = (c < 2 ? p.raw[r].x : c < 4 ? p.raw[r].y : c < 6 ? p.raw[r].z : p.raw[r].w) ^ (((sign_mask >> r) & 1u) * 0x80008000u);
+    v[r] = (c & 1) ? bf16_hi(w) : bf16_lo(w);
+  }
+}
+
 // Unnormalised Walsh-Hadamard butterfly over the 16 rows a lane holds, stages h = 1, 2, ... < kStagesBelow
 // (App. C).  kStagesBelow = 16 is the whole 16-point transform; 2 and 4 rotate every aligned pair / group of
 // four on its own; the first four stages of a 32- or 128-point transform are the 16-point one.
@@ -256,6 +265,7 @@ __device__ __forceinline__ void row_pass(const Patch& p, const uint32_t (&rnd)[1
     const uint32_t d = encode8<kSR>(v, rnd[r]);
     store_codes<T::kStream>(dst + r * code_ld, d);
     if ((lane & 1) == 0) st_row_scales[(gl * 16 + r) * T::kRowScaleLd + (lane >> 1)] = static_cast<uint8_t>(code);
+    if (kSR && T::kStream) __builtin_amdgcn_sched_barrier(0);   // one row at a time: see cast_kernel
   }
 }
 
