@@ -10,7 +10,9 @@
 // (two cross-lane maxima); a col-copy block (32 rows of one column) and the whole
 // 32-point butterfly live in one lane's registers.  Row codes leave as one dword
 // per lane and row; everything else is staged in LDS and written back as
-// contiguous pieces (64 bytes of codes per column per workgroup).
+// contiguous pieces (64 bytes of codes per column per workgroup).  (Non-temporal stores of the codes made
+// the calls by themselves faster -- X 8192 x 5120 47 -> 41 us -- but the GEMM behind them, which reads the codes as they are, slower by
+// more: training step 4096 x 5120 x 5120 289 -> 302 us.)
 //
 // Random draws: the row copy uses the NVFP4 draws (counter (j / 8, i, 0, 0)); the
 // col copy draws its own, counter (i / 8, j, 1, 0), word (i % 8) / 2, low half for
@@ -81,7 +83,8 @@ __device__ __forceinline__ float elem(const uint4& q, int c) {
   return (c & 1) ? bf16_hi(w) : bf16_lo(w);
 }
 
-template <bool kRow, bool kCol, bool kRht, bool kSR>
+// kSplit: the two copies are made by two sets of workgroups (blockIdx.z).
+template <bool kRow, bool kCol, bool kRht, bool kSR, bool kSplit>
 __global__ __launch_bounds__(kThreads) void quantize_mx_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
                                                                int64_t ld, uint32_t sign_mask, uint32_t key0, uint32_t key1,
                                                                uint8_t* __restrict__ row_codes, uint8_t* __restrict__ row_scales,
@@ -112,7 +115,8 @@ __global__ __launch_bounds__(kThreads) void quantize_mx_kernel(const uint16_t* _
     for (int r = 0; r < 32; ++r) raw[r] = make_uint4(0u, 0u, 0u, 0u);
   }
 
-  if (kRow) {
+  const bool do_row = kRow && (!kSplit || blockIdx.z == 0), do_col = kCol && (!kSplit || blockIdx.z == 1);
+  if (do_row) {
 #pragma unroll   // fully: a partly unrolled loop indexes raw[] at run time, which puts the whole patch in scratch memory
     for (int r = 0; r < 32; ++r) {
       float v[8];
@@ -145,7 +149,7 @@ __global__ __launch_bounds__(kThreads) void quantize_mx_kernel(const uint16_t* _
 #pragma unroll
     for (int r = 0; r < 32; ++r) asm volatile("" : "+v"(raw[r].x), "+v"(raw[r].y), "+v"(raw[r].z), "+v"(raw[r].w));
   }
-  if (kCol) {
+  if (do_col) {
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
       float w[32];
@@ -176,7 +180,7 @@ __global__ __launch_bounds__(kThreads) void quantize_mx_kernel(const uint16_t* _
 
   const int tile_cols = static_cast<int>(cols - colblk < kWaveCols ? cols - colblk : kWaveCols);
   const int tile_groups = static_cast<int>((rows - rowblk < kRowsPerBlock ? rows - rowblk : kRowsPerBlock) / 32);   // 32-row groups in this tile
-  if (kRow) {
+  if (do_row) {
     // 128 rows x (tile_cols / 32) scale bytes; a full tile row is 16 contiguous bytes
     const int r = tid & 127, half = tid >> 7;   // two threads per row, 8 bytes each
     const int64_t row = rowblk + r;
@@ -191,7 +195,7 @@ __global__ __launch_bounds__(kThreads) void quantize_mx_kernel(const uint16_t* _
       }
     }
   }
-  if (kCol) {
+  if (do_col) {
     const int64_t code_ld = rows / 2, scale_ld = rows / 32;
     const bool wide = (code_ld & 15) == 0;
 #pragma unroll 1
@@ -224,13 +228,15 @@ __global__ __launch_bounds__(kThreads) void quantize_mx_kernel(const uint16_t* _
 
 template <bool kRow, bool kCol, bool kRht>
 void dispatch(const QuantizeArgs& a, dim3 grid, hipStream_t s) {
-  const uint16_t* x = static_cast<const uint16_t*>(a.x);
-  if (a.sr)
-    hipLaunchKernelGGL((quantize_mx_kernel<kRow, kCol, kRht, true>), grid, dim3(kThreads), 0, s, x, a.rows, a.cols, a.ld,
-                       a.sign_mask, a.key0, a.key1, a.row_codes, a.row_scales, a.row_ts, a.col_codes, a.col_scales, a.col_ts);
-  else
-    hipLaunchKernelGGL((quantize_mx_kernel<kRow, kCol, kRht, false>), grid, dim3(kThreads), 0, s, x, a.rows, a.cols, a.ld,
-                       a.sign_mask, a.key0, a.key1, a.row_codes, a.row_scales, a.row_ts, a.col_codes, a.col_scales, a.col_ts);
+  // Up to 256 workgroups (one per CU) the call takes as long as one patch does: each copy gets workgroups of its own, though the
+  // patch is then read twice.  us, one set / two: X 256 x 512 15.8 / 12.7, X 1024 x 2048 16.4 / 12.4, dY SR 1024 x 2048 23.1 / 14.0.
+  constexpr bool kBoth = kRow && kCol;
+  const bool split = kBoth && static_cast<int64_t>(grid.x) * grid.y <= 256;
+  if (split) grid.z = 2;
+  const auto kernel = a.sr ? (split ? &quantize_mx_kernel<kRow, kCol, kRht, true, kBoth> : &quantize_mx_kernel<kRow, kCol, kRht, true, false>)
+                           : (split ? &quantize_mx_kernel<kRow, kCol, kRht, false, kBoth> : &quantize_mx_kernel<kRow, kCol, kRht, false, false>);
+  hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, static_cast<const uint16_t*>(a.x), a.rows, a.cols, a.ld, a.sign_mask, a.key0,
+                     a.key1, a.row_codes, a.row_scales, a.row_ts, a.col_codes, a.col_scales, a.col_ts);
 }
 
 }  // namespace
