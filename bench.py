@@ -608,7 +608,7 @@ def main() -> int:
                      "note": "peak is the published FP16 dense MFMA rate; what a register-only MFMA loop sustains on this "
                              "box under its power limit is measured in `matrix_pipe_context`; traffic and mfma_util are "
                              "rocprofv3 --pmc figures of this script read back from profiles/measured_counters.json"},
-        "roofline_quantize": {"kernel": "three nvfp4_quantize calls = amax_kernel + amax_finalize_kernel + cast_kernel each",
+        "roofline_quantize": {"kernel": "three nvfp4_quantize calls = amax_kernel + cast_kernel each",
                               "bound": "hbm", "achieved": q_total_gbps2,
                               "peak": PEAK_HBM_GBPS, "unit": "GB/s", "frac": q_total_gbps2 / PEAK_HBM_GBPS,
                               "traffic": pc.get("quantize_calls_traffic_bytes"),

@@ -228,11 +228,13 @@ int nvfp4_quantize_with_amax(const void* x, int64_t rows, int64_t cols, int64_t 
  * NVFP4_OUT_F32_ACCUMULATE, D is FP32 and is read: every element becomes
  * fp32(D_old + result), one FP32 addition after the FP32 result is formed.
  * workspace: optional device scratch, 256-byte aligned.  With at least
- * nvfp4_gemm_workspace_bytes(M, N, K) bytes (and K a multiple of 64) the call
- * first decodes both operands to FP16 (value * block scale, exact) into it and
- * then runs an FP16 MFMA GEMM with no decode work in its loop; with NULL or
- * too little room it runs a fused kernel that decodes inside the GEMM loop
- * (slower, no scratch).  Both give the same result up to FP32 summation order.
+ * nvfp4_gemm_workspace_bytes(M, N, K) bytes (and K a multiple of 64) a call that is
+ * large enough to gain from it first decodes both operands to FP16 (value * block
+ * scale, exact) into it and then runs an FP16 MFMA GEMM with no decode work in its
+ * loop; with NULL or too little room it decodes inside the GEMM loop (slower for
+ * large products, no scratch).  Products of few tokens, small layers and every K
+ * that is not a multiple of 64 are computed straight from the codes in any case.
+ * All give the same result up to FP32 summation order.
  * (With both operands decoded beforehand by nvfp4_predecode and no split last
  * round of tiles the FP16 GEMM needs nothing of the workspace and runs without.)
  * The workspace contents are scratch: undefined afterwards, free for reuse once
