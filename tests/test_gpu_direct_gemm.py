@@ -12,9 +12,10 @@ pytestmark = pytest.mark.gpu
 
 
 # tile shape the dispatch takes for it: 16x32 tiles (8 wavefronts; 4 for many tiles), 32x32, 64x48, 64x64.
-# K: shorter than a step of 128; a step and a rest of one 16-block; whole steps; more steps than wavefronts, with a rest.
+# K: shorter than a step of 128; a step and a rest of one 16-block; whole steps; more steps than wavefronts, with a rest (the
+# last three: every wavefront stages, reads back and stages again, and the sums of all of them are added).
 @pytest.mark.parametrize("M,N,K", [(16, 16, 16), (48, 80, 112), (16, 16400, 272), (32, 5136, 400), (64, 9232, 128),
-                                   (80, 8208, 144), (144, 5200, 1040)])
+                                   (80, 8208, 144), (144, 5200, 1040), (32, 5136, 2192), (64, 9232, 1168)])
 @pytest.mark.parametrize("per_row", [False, True], ids=["tensor_scale", "row_scales"])
 def test_direct_gemm(M, N, K, per_row):
     xb = synth.normal_with_outliers(M, K, 1.0, 7000 + M + K, frac=0.01)
