@@ -10,9 +10,11 @@
 // the product exactly (11 bits; range 2^-10 .. 2688 is inside FP16's normal
 // range), so each operand tile is decoded ONCE per workgroup to
 // value * block_scale in FP16 while it is staged into LDS, and the
-// contraction runs on v_mfma_f32_16x16x32_f16: every product is exact and the
+// contraction runs on the FP16 matrix instructions: every product is exact and the
 // accumulation is FP32, which is Eq. 5 up to FP32 summation order.  The two
 // tensor-level decode scales are applied to the finished sums.
+#include <cmath>
+
 #include "nvfp4_internal.h"
 #include "nvfp4_device.h"
 #include "gemm_epilogue.h"
@@ -20,6 +22,10 @@
 namespace nvfp4 {
 
 namespace {
+
+constexpr int BM = 128, BN = 128, BK = 64;
+constexpr int LDS_LD = BK + 8;  // halfs per LDS row; the 16-byte pad keeps 128-bit reads conflict free
+constexpr int kGemmThreads = 256;
 
 template <int kByte>
 __device__ __forceinline__ half2v decode_pair(uint32_t codes, half2v scale) {
@@ -45,6 +51,116 @@ __device__ __forceinline__ half2v scale_to_half2(uint32_t e4m3_byte) {
   r.x = s;
   r.y = s;
   return r;
+}
+
+// ---------------------------------------------------------------- 128 x 128 kernel
+// 128 x 128 outputs per workgroup of 4 wavefronts, K step 64, one buffer, any K and alignment: for large results of a
+// short contraction, where storing the result is the work (see plan_route).  Three workgroups fit a CU.  5120 x 20480 x 16: FP32 80 us
+// (5.2 TB/s of result), bf16 71.
+
+// Stage 32 elements (two 16-blocks) of one operand row into LDS as FP16.
+__device__ __forceinline__ void stage_row(const Operand& op, int64_t K, int64_t row, int64_t k,
+                                          _Float16* lds_row) {
+  uint2 c01 = make_uint2(0u, 0u), c23 = make_uint2(0u, 0u);
+  uint32_t s0 = 0, s1 = 0;
+  if (row < op.outer) {
+    const uint8_t* cp = op.codes + row * (K / 2) + k / 2;
+    const uint8_t* sp = op.scales + row * (K / 16) + k / 16;
+    if (k < K) {
+      c01 = *reinterpret_cast<const uint2*>(cp);
+      s0 = sp[0];
+    }
+    if (k + 16 < K) {
+      c23 = *reinterpret_cast<const uint2*>(cp + 8);
+      s1 = sp[1];
+    }
+  }
+  const half2v h0 = scale_to_half2(s0), h1 = scale_to_half2(s1);
+  uint4* dst = reinterpret_cast<uint4*>(lds_row);
+  dst[0] = decode8(c01.x, h0);
+  dst[1] = decode8(c01.y, h0);
+  dst[2] = decode8(c23.x, h1);
+  dst[3] = decode8(c23.y, h1);
+}
+
+template <bool kBf16Out>
+__global__ __launch_bounds__(kGemmThreads) void gemm_kernel(Operand A, Operand B, int64_t K,
+                                                            void* __restrict__ Dv, int64_t ldd, bool accumulate) {
+  __shared__ __attribute__((aligned(16))) _Float16 As[BM * LDS_LD];
+  __shared__ __attribute__((aligned(16))) _Float16 Bs[BN * LDS_LD];
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave >> 1, wn = wave & 1;  // 2 x 2 wavefronts, 64 x 64 outputs each
+  const int64_t m0 = static_cast<int64_t>(blockIdx.y) * BM, n0 = static_cast<int64_t>(blockIdx.x) * BN;
+
+  // acc[i][j]: 32x32 block with n-rows (B operand rows) as the MFMA's M index
+  // and m-rows as its N index, so a lane ends up with 4 consecutive n.
+  float16v acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+
+  const int srow = tid >> 1, shalf = tid & 1;
+  const int l32 = lane & 31, kq = (lane >> 5) * 8;
+
+  for (int64_t k0 = 0; k0 < K; k0 += BK) {
+    stage_row(A, K, m0 + srow, k0 + shalf * 32, As + srow * LDS_LD + shalf * 32);
+    stage_row(B, K, n0 + srow, k0 + shalf * 32, Bs + srow * LDS_LD + shalf * 32);
+    __syncthreads();
+#pragma unroll
+    for (int kk = 0; kk < BK; kk += 16) {
+      half8v af[2], bf[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        af[i] = *reinterpret_cast<const half8v*>(As + (wm * 64 + i * 32 + l32) * LDS_LD + kk + kq);
+        bf[i] = *reinterpret_cast<const half8v*>(Bs + (wn * 64 + i * 32 + l32) * LDS_LD + kk + kq);
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bf[j], af[i], acc[i][j], 0, 0, 0);
+    }
+    __syncthreads();
+  }
+
+  // Tensor-level decode scales on the finished sums (App. B.3, after Eq. 5).
+  const TensorScales ts{A.ts, B.ts, A.ts_per_row != 0, B.ts_per_row != 0};
+  const bool vec = ts.a_per_row || ts.b_per_row;
+  const float out_scale = vec ? 0.0f : A.ts[0] * B.ts[0];
+  const int M = static_cast<int>(A.outer - m0 < BM ? A.outer - m0 : BM);
+  const int N = static_cast<int>(B.outer - n0 < BN ? B.outer - n0 : BN);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int m = wm * 64 + i * 32 + l32;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int n = wn * 64 + j * 32 + q * 8 + (lane >> 5) * 4;
+        if (m < M && n < N) {  // N is a multiple of 16, so the 4 columns are in or out together
+          const float4v sc = scale4(ts, out_scale, vec, true, m0 + m, n0 + n);
+          float4v v;
+#pragma unroll
+          for (int t = 0; t < 4; ++t) v[t] = acc[i][j][q * 4 + t] * sc[t];
+          if (kBf16Out) {
+            uint16_t* d = static_cast<uint16_t*>(Dv) + (m0 + m) * ldd + n0 + n;
+            uint2 o;
+            o.x = f32x2_to_bf16(v[0], v[1]);
+            o.y = f32x2_to_bf16(v[2], v[3]);
+            *reinterpret_cast<uint2*>(d) = o;
+          } else {
+            float* d = static_cast<float*>(Dv) + (m0 + m) * ldd + n0 + n;
+            if (accumulate) v += *reinterpret_cast<const float4v*>(d);
+            *reinterpret_cast<float4v*>(d) = v;
+          }
+        }
+      }
+    }
+  }
 }
 
 // ---------------------------------------------------------------- large-tile kernel
@@ -245,21 +361,36 @@ static double fused_us(int64_t M, int64_t N, int64_t K) {
   return 4.0 + static_cast<double>((tiles + 255) / 256) * static_cast<double>(K) * (tiles > 1024 ? 0.031 : 0.0265);
 }
 
-hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
-  const int64_t M = g.a.outer, N = g.b.outer;
-  const double direct = gemm_direct_us(M, N, g.K);
-  // With a workspace: decode pass + FP16 GEMM, unless the product is too small to fill its 256 x 256 tiles.
-  if (gemm_two_pass_usable(g) && gemm_two_pass_us(g) <= direct) return launch_gemm_two_pass(g, s);
-  // Without (or where that is slower): the fused kernel below for large products -- it needs whole K steps of 64 and
-  // 16-byte aligned code rows --, the direct one for all others.
-  const bool big = (g.K % TK == 0) && (reinterpret_cast<uintptr_t>(g.a.codes) % 16 == 0) &&
-                   (reinterpret_cast<uintptr_t>(g.b.codes) % 16 == 0) && fused_us(M, N, g.K) <= direct;
-  if (!big) return launch_gemm_direct(g, s);
+double small_tile_us(const SmallTileCost& c, const GemmArgs& g, int64_t tile_m, int64_t tile_n, int64_t steps) {
+  const int64_t tiles = ((g.a.outer + tile_m - 1) / tile_m) * ((g.b.outer + tile_n - 1) / tile_n);
+  const int64_t wave = int64_t{256} * c.resident, whole = tiles / wave, last = (tiles - whole * wave + 255) / 256;   // tiles of a CU in the last wave
+  double rounds = static_cast<double>(whole * c.resident);
+  if (last) rounds += c.alone + static_cast<double>(last - 1) * (c.resident - c.alone) / (c.resident - 1);
+  const double loop = rounds * (c.tile + c.step * static_cast<double>(steps));
+  // accumulate: the result is read first; beyond what the caches hold nothing hides that (5120 x 20480: 1.6 times plain bytes)
+  const double elements = static_cast<double>(g.a.outer) * static_cast<double>(g.b.outer);
+  const double bytes = elements * (g.out_bf16 ? 2 : !g.accumulate ? 4 : elements < 8e6 ? 8 : 16);
+  return c.call + std::hypot(loop, c.result * bytes * 1e-6);
+}
+
+// The 128 x 128 kernel, in the same terms (steps of 64 k; three workgroups fit a CU).
+static constexpr SmallTileCost kTile128Cost{3, 3.47, 1.45, 1.14, 0.788, 0.151};
+
+static hipError_t launch_tile128(const GemmArgs& g, hipStream_t s) {
+  const dim3 grid(static_cast<unsigned>((g.b.outer + BN - 1) / BN), static_cast<unsigned>((g.a.outer + BM - 1) / BM));
+  if (g.out_bf16)
+    hipLaunchKernelGGL(gemm_kernel<true>, grid, dim3(kGemmThreads), 0, s, g.a, g.b, g.K, g.d, g.ldd, g.accumulate);
+  else
+    hipLaunchKernelGGL(gemm_kernel<false>, grid, dim3(kGemmThreads), 0, s, g.a, g.b, g.K, g.d, g.ldd, g.accumulate);
+  return hipGetLastError();
+}
+
+static hipError_t launch_fused256(const GemmArgs& g, hipStream_t s) {
   static PerDeviceOnce once_bf16, once_f32;
   const hipError_t e = g.out_bf16 ? ensure_dynamic_lds(reinterpret_cast<const void*>(&gemm_kernel_256<true>), 2 * kStageBytes, once_bf16)
                                   : ensure_dynamic_lds(reinterpret_cast<const void*>(&gemm_kernel_256<false>), 2 * kStageBytes, once_f32);
   if (e != hipSuccess) return e;
-  const int tiles_m = static_cast<int>((M + TM - 1) / TM), tiles_n = static_cast<int>((N + TN - 1) / TN);
+  const int tiles_m = static_cast<int>((g.a.outer + TM - 1) / TM), tiles_n = static_cast<int>((g.b.outer + TN - 1) / TN);
   const dim3 grid(static_cast<unsigned>(tiles_m * tiles_n));
   if (g.out_bf16)
     hipLaunchKernelGGL(gemm_kernel_256<true>, grid, dim3(kBigThreads), 2 * kStageBytes, s, g.a, g.b, g.K, g.d, g.ldd, g.accumulate, tiles_m, tiles_n);
@@ -268,4 +399,72 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Which kernel a product takes.
+enum GemmRoute { kTwoPass, kFused256, kTile128, kDirect };
+struct GemmPlan {
+  GemmRoute route;
+  int shape;   // kDirect: the tile shape
+};
+
+static GemmPlan plan_route(const GemmArgs& g) {
+  const double direct = gemm_direct_compute_us(g);
+  // With a workspace: decode pass + FP16 GEMM, unless the product is too small to fill its 256-row tiles.
+  if (gemm_two_pass_usable(g) && gemm_two_pass_us(g) <= direct) return {kTwoPass, 0};
+  // Without (or where that is slower): the fused kernel for large products -- it needs whole K steps of 64 and 16-byte aligned
+  // code rows.
+  const bool big = (g.K % TK == 0) && (reinterpret_cast<uintptr_t>(g.a.codes) % 16 == 0) &&
+                   (reinterpret_cast<uintptr_t>(g.b.codes) % 16 == 0);
+  if (big && fused_us(g.a.outer, g.b.outer, g.K) <= direct) return {kFused256, 0};
+  // All others: the direct kernel with K split among the wavefronts of a workgroup, where the tiles are few for the length of K;
+  // else 128 x 128 tiles.  These the direct kernel with a tile per wavefront does faster from K of some 250 on (no barrier), the
+  // kernel that decodes a tile once per workgroup below (three workgroups per CU keep more stores in flight, steps of 64 waste
+  // less).  us, split K / own tiles / 128 x 128: 5120 x 20480 x 16 (FP32) 193 / 87 / 80, x 144 197 / 112 / 107, x 400 228 / 159 / 177,
+  // x 2064 677 / 623 / 768; 8176 x 1296 x 1040 45 / 40 / 49; 1040 x 1296 x 1040 11.4 / 17.5 / 24.7.  Where K ends in a partial step
+  // of 128, own tiles have to promise 8 %: nearer than that the estimates do not tell the two apart.  Where the result is read too,
+  // 20 % (two workgroups per CU hide those reads worse than three: 5120 x 20480 x 400 324 / 290), and the 128 x 128 kernel, which reads
+  // it 16 bytes here and there, 1.5 us more for a small one (1040 x 1296 x 16 9.1 against 7.8 with K split).
+  const int split = pick_direct_shape(g);
+  const double tile128 = small_tile_us(kTile128Cost, g, BM, BN, (g.K + BK - 1) / BK) + (g.accumulate ? 1.5 : 0.0), own = gemm_direct_us(g, kDirectOwnTiles);
+  const bool take_own = own < (g.accumulate ? 0.8 : g.K % 128 ? 0.92 : 1.0) * tile128;
+  if (gemm_direct_us(g, split) <= (take_own ? own : tile128)) return {kDirect, split};
+  return take_own ? GemmPlan{kDirect, kDirectOwnTiles} : GemmPlan{kTile128, 0};
+}
+
+hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
+  const GemmPlan p = plan_route(g);
+  switch (p.route) {
+    case kTwoPass: return launch_gemm_two_pass(g, s);
+    case kFused256: return launch_fused256(g, s);
+    case kTile128: return launch_tile128(g, s);
+    default: return launch_gemm_direct(g, p.shape, s);
+  }
+}
+
 }  // namespace nvfp4
+
+// For the tests, not part of the ABI: which kernel an NVFP4 product of these sizes takes with aligned operands.  decoded: bit 0 A, bit 1 B
+// decoded beforehand.  out: route (0 two-pass, 1 fused 256 x 256, 2 128 x 128, 3 direct); two-pass: 32-column units of a tile, tiles of a split
+// last round, workgroups that share each; direct: the tile shape.
+extern "C" void nvfp4_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int bf16_out, int accumulate, size_t workspace_bytes, int decoded, int* out) {
+  using namespace nvfp4;
+  GemmArgs g{};
+  const uint8_t* const some = reinterpret_cast<const uint8_t*>(uintptr_t{4096});
+  g.a = Operand{some, some, nullptr, M, 0, decoded & 1 ? some : nullptr};
+  g.b = Operand{some, some, nullptr, N, 0, decoded & 2 ? some : nullptr};
+  g.K = K;
+  g.out_bf16 = bf16_out != 0;
+  g.accumulate = accumulate != 0;
+  g.workspace = workspace_bytes ? const_cast<uint8_t*>(some) : nullptr;
+  g.workspace_bytes = workspace_bytes;
+  const GemmPlan p = plan_route(g);
+  out[0] = p.route;
+  out[1] = p.shape;
+  out[2] = 0;
+  out[3] = 1;
+  if (p.route == kTwoPass) {
+    const TwoPassShape t = gemm_two_pass_shape(g);
+    out[1] = t.units;
+    out[2] = t.tail;
+    out[3] = t.splits;
+  }
+}

@@ -60,23 +60,25 @@ __device__ __forceinline__ void wavefront_exchange() {
 }
 __device__ __forceinline__ half2v scales2(uint32_t s) { return __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(static_cast<int>(s), 1.0f, false); }
 
-// MB x NB blocks of 16 x 16 outputs per wavefront, WK wavefronts per workgroup that split K.
+// MB x NB blocks of 16 x 16 outputs per wavefront, WK wavefronts per workgroup that split K.  WK = 1: a workgroup of 2 x 2
+// wavefronts that own a tile each.
 template <int MB, int NB, int WK>
 struct Shape {
-  static constexpr int kTM = MB * 16, kTN = NB * 16, kThreads = WK * 64, kBlocks = MB + NB;
+  static constexpr int kOwn = WK == 1 ? 2 : 1, kWaves = WK * kOwn * kOwn;
+  static constexpr int kTM = MB * 16 * kOwn, kTN = NB * 16 * kOwn, kThreads = kWaves * 64, kBlocks = MB + NB;
   static constexpr int kStage = kBlocks * (kCodeBytes + kScaleBytes);       // one step's codes and scales, per wavefront
   static constexpr int kSum = WK > 1 ? MB * NB * 1024 : 0;
   static constexpr int kWaveBytes = kStage > kSum ? kStage : kSum;
-  static constexpr int kLdsBytes = WK * kWaveBytes;
+  static constexpr int kLdsBytes = kWaves * kWaveBytes;
 };
 
-template <int MB, int NB, int WK, int kOcc, bool kBf16Out>
-__global__ __launch_bounds__(WK * 64, kOcc) void gemm_direct_kernel(Operand A, Operand B, int K, void* __restrict__ Dv, int64_t ldd,
+template <int MB, int NB, int WK, bool kBf16Out>
+__global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, 2) void gemm_direct_kernel(Operand A, Operand B, int K, void* __restrict__ Dv, int64_t ldd,
                                                                   bool accumulate, int tiles_m, int tiles_n) {
   using S = Shape<MB, NB, WK>;
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   const int lane = threadIdx.x & 63;
-  const int wk = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6), wk = WK == 1 ? 0 : wave;
   const int num_tiles = tiles_m * tiles_n;
   int pid = blockIdx.x;
   if ((num_tiles & 7) == 0) pid = (pid & 7) * (num_tiles >> 3) + (pid >> 3);
@@ -85,8 +87,8 @@ __global__ __launch_bounds__(WK * 64, kOcc) void gemm_direct_kernel(Operand A, O
   const int l16 = lane & 15, q = lane >> 4;
   const int row4 = lane >> 2, c4 = lane & 3;      // loading: row and chunk of the lane
   const int M = static_cast<int>(A.outer), N = static_cast<int>(B.outer);
-  const int m0 = tm * S::kTM, n0 = tn * S::kTN;
-  uint8_t* const mine = lds + wk * S::kWaveBytes;
+  const int m0 = tm * S::kTM + (WK == 1 ? (wave >> 1) * (MB * 16) : 0), n0 = tn * S::kTN + (WK == 1 ? (wave & 1) * (NB * 16) : 0);
+  uint8_t* const mine = lds + wave * S::kWaveBytes;
 
   // Wave-uniform bases plus one 32-bit lane offset; blocks 0 .. MB-1 are A's, the others B's.  Blocks past the
   // end of an operand are replaced by its last (they feed outputs that are never stored).
@@ -230,19 +232,31 @@ __global__ __launch_bounds__(WK * 64, kOcc) void gemm_direct_kernel(Operand A, O
 
 }  // namespace
 
-// The tile shapes the kernel comes in.  `cost`: time of one step (128 k) of one round of 256 tiles, in units of 0.247 us,
-// fitted to the measured times of 13 shapes (it reproduces them within 5 %).  A shape's time is then
+// The tile shapes the kernel comes in.  In the first four the wavefronts of a workgroup split K.  Which of these: `cost` is the time
+// of one step (128 k) of one round of 256 tiles, in units of 0.247 us, fitted to the measured times of 13 shapes (it reproduces them
+// within 5 %); a shape's time is then
 //   3 us + 0.247 us * cost * steps * ceil(tiles / 256),
 // and the smallest wins: large tiles decode less per product, small ones fill the chip.  Both sides of the choice, us:
 // 64 x 20480 x 5120: 4x3 22.3, 4x4 26.7, 2x2 27.2; 512 x 5120 x 5120: 4x4 37.8, 4x3 39.4; 32 x 5120 x 5120: 2x2 7.7, 1x2 8.8, 4x3 > 10.
+// The last has a tile per wavefront, 128 x 128 outputs per workgroup: for results that fill the chip without a split of K, where the
+// others' wavefronts have too few steps to share and pay the sum through LDS per 64 x 64 tile.  Which of the two: `us`, fitted to
+// 930 measured calls of 16 .. 8192 rows, 256 .. 20480 columns, K 16 .. 20496, FP32 and bf16 (its 5th and 95th percentile are 0.85 and 1.12
+// of the measured time).  us, 4x4 split / own: 5120 x 20480 x 16 193 / 87, x 400 228 / 159, x 2064 677 / 623; 2048 x 5120 x 2064 the split.
 struct DirectShape {
-  int mb, nb;
+  int mb, nb, wk;
   double cost;
+  SmallTileCost us;
 };
-constexpr DirectShape kDirectShapes[4] = {{1, 2, 0.30}, {2, 2, 0.46}, {4, 3, 0.96}, {4, 4, 1.19}};
+constexpr DirectShape kDirectShapes[5] = {{1, 2, 8, 0.30, {3, 4.02, 1.23, 0.0, 0.647, 0.203}},
+                                          {2, 2, 8, 0.46, {2, 3.53, 1.0, 0.0, 1.02, 0.214}},
+                                          {4, 3, 4, 0.96, {2, 4.01, 1.15, 0.591, 0.936, 0.194}},
+                                          {4, 4, 4, 1.19, {2, 4.09, 1.03, 0.653, 1.17, 0.186}},
+                                          {4, 4, 1, 0.0, {2, 3.72, 1.13, 1.56, 1.14, 0.141}}};
 
+static int tile_m(const DirectShape& d) { return d.mb * (d.wk == 1 ? 32 : 16); }
+static int tile_n(const DirectShape& d) { return d.nb * (d.wk == 1 ? 32 : 16); }
 static int64_t direct_tiles(const DirectShape& d, int64_t M, int64_t N) {
-  return ((M + d.mb * 16 - 1) / (d.mb * 16)) * ((N + d.nb * 16 - 1) / (d.nb * 16));
+  return ((M + tile_m(d) - 1) / tile_m(d)) * ((N + tile_n(d) - 1) / tile_n(d));
 }
 
 static double direct_shape_us(const DirectShape& d, int64_t M, int64_t N, int64_t K) {
@@ -250,44 +264,50 @@ static double direct_shape_us(const DirectShape& d, int64_t M, int64_t N, int64_
   return 3.0 + 0.247 * d.cost * static_cast<double>(steps) * static_cast<double>(rounds);
 }
 
-static int pick_direct_shape(int64_t M, int64_t N, int64_t K) {
+int pick_direct_shape(const GemmArgs& g) {
   int best = 0;
-  for (int i = 1; i < 4; ++i)
-    if (direct_shape_us(kDirectShapes[i], M, N, K) < direct_shape_us(kDirectShapes[best], M, N, K)) best = i;
+  for (int i = 1; i < kDirectOwnTiles; ++i)
+    if (direct_shape_us(kDirectShapes[i], g.a.outer, g.b.outer, g.K) < direct_shape_us(kDirectShapes[best], g.a.outer, g.b.outer, g.K)) best = i;
   return best;
 }
 
-double gemm_direct_us(int64_t M, int64_t N, int64_t K) { return direct_shape_us(kDirectShapes[pick_direct_shape(M, N, K)], M, N, K); }
+double gemm_direct_compute_us(const GemmArgs& g) { return direct_shape_us(kDirectShapes[pick_direct_shape(g)], g.a.outer, g.b.outer, g.K); }
+
+double gemm_direct_us(const GemmArgs& g, int shape) {
+  const DirectShape& d = kDirectShapes[shape];
+  const int64_t steps = (g.K + kStepK - 1) / kStepK;
+  return small_tile_us(d.us, g, tile_m(d), tile_n(d), (steps + d.wk - 1) / d.wk);
+}
 
 template <int MB, int NB, int WK, bool kBf16Out>
 static hipError_t launch_shape(const GemmArgs& g, hipStream_t s) {
   using S = Shape<MB, NB, WK>;
   static PerDeviceOnce once;
-  const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&gemm_direct_kernel<MB, NB, WK, 2, kBf16Out>), S::kLdsBytes, once);
+  const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&gemm_direct_kernel<MB, NB, WK, kBf16Out>), S::kLdsBytes, once);
   if (e != hipSuccess) return e;
   const int tiles_m = static_cast<int>((g.a.outer + S::kTM - 1) / S::kTM), tiles_n = static_cast<int>((g.b.outer + S::kTN - 1) / S::kTN);
-  hipLaunchKernelGGL((gemm_direct_kernel<MB, NB, WK, 2, kBf16Out>), dim3(static_cast<unsigned>(tiles_m * tiles_n)), dim3(S::kThreads),
+  hipLaunchKernelGGL((gemm_direct_kernel<MB, NB, WK, kBf16Out>), dim3(static_cast<unsigned>(tiles_m * tiles_n)), dim3(S::kThreads),
                      S::kLdsBytes, s, g.a, g.b, static_cast<int>(g.K), g.d, g.ldd, g.accumulate, tiles_m, tiles_n);
   return hipGetLastError();
 }
 
 template <bool kBf16Out>
-static hipError_t launch_direct(const GemmArgs& g, hipStream_t s) {
-  const int shape = pick_direct_shape(g.a.outer, g.b.outer, g.K);
+static hipError_t launch_direct(const GemmArgs& g, int shape, hipStream_t s) {
   switch (shape) {
     // 16 x 32 tiles: enough of them to fill the chip four times over do better with fewer wavefronts on each (16 x 20480 x
     // 5120: 14.6 against 15.7 us), few with more (32 x 5120 x 5120 in these tiles: 9.4 against 8.8)
     case 0: return direct_tiles(kDirectShapes[0], g.a.outer, g.b.outer) >= 512 ? launch_shape<1, 2, 4, kBf16Out>(g, s) : launch_shape<1, 2, 8, kBf16Out>(g, s);
     case 1: return launch_shape<2, 2, 8, kBf16Out>(g, s);
     case 2: return launch_shape<4, 3, 4, kBf16Out>(g, s);
-    default: return launch_shape<4, 4, 4, kBf16Out>(g, s);
+    case 3: return launch_shape<4, 4, 4, kBf16Out>(g, s);
+    default: return launch_shape<4, 4, 1, kBf16Out>(g, s);
   }
 }
 
-hipError_t launch_gemm_direct(const GemmArgs& g, hipStream_t s) {
+hipError_t launch_gemm_direct(const GemmArgs& g, int shape, hipStream_t s) {
   // 32-bit rows, and byte offsets within a 16-row block
   if (g.a.outer > 0x7fffffff || g.b.outer > 0x7fffffff || g.K > (int64_t{1} << 27)) return hipErrorInvalidValue;
-  return g.out_bf16 ? launch_direct<true>(g, s) : launch_direct<false>(g, s);
+  return g.out_bf16 ? launch_direct<true>(g, shape, s) : launch_direct<false>(g, shape, s);
 }
 
 }  // namespace nvfp4

@@ -515,7 +515,9 @@ struct Width {
   double rounds;
   int64_t tiles;
 };
-static Width pick_width(int64_t M, int64_t N, const TailPlan& p) {
+// A product that is accumulated into its result takes longer over the result the more tiles there are (5120 x 20480, K = 64 / 256 / 512: nb = 8
+// 283 / 299 / 333, nb = 5 306 / 313 / 345): there a narrower tile has to promise 4 % while K is short.
+static Width pick_width(int64_t M, int64_t N, int64_t K, const TailPlan& p, bool accumulate) {
   constexpr double kTime[4] = {1.0, 0.90, 0.80, 0.68};
   const int64_t tiles_m = (M + TM - 1) / TM;
   Width best{8, 0.0, 0};
@@ -525,7 +527,7 @@ static Width pick_width(int64_t M, int64_t N, const TailPlan& p) {
     double rounds = static_cast<double>((tiles + kCUs - 1) / kCUs);
     if (i == 0 && p.tail) rounds = static_cast<double>((tiles - p.tail) / kCUs) + 1.0 / p.splits + 0.15;
     rounds *= kTime[i];
-    if (i == 0 || rounds < best.rounds) best = Width{nb, rounds, tiles};
+    if (i == 0 || rounds < (accumulate && K < 1024 && best.nb == 8 ? 0.96 : 1.0) * best.rounds) best = Width{nb, rounds, tiles};
   }
   return best;
 }
@@ -566,9 +568,15 @@ bool gemm_two_pass_usable(const GemmArgs& g) {
 double gemm_two_pass_us(const GemmArgs& g) {
   const int64_t M = g.a.outer, N = g.b.outer;
   const double k = static_cast<double>(g.K);
-  const Width w = pick_width(M, N, plan_tail(M, N, g.K));
+  const Width w = pick_width(M, N, g.K, plan_tail(M, N, g.K), g.accumulate);
   const int64_t rows = (g.a.fp16 ? 0 : M) + (g.b.fp16 ? 0 : N);
   return 4.0 + static_cast<double>(rows) * k * 2.5625 / 4.7e6 + (rows ? 2.0 : 0.0) + w.rounds * k * (w.tiles >= kCUs ? 0.0225 : 0.0185);
+}
+
+TwoPassShape gemm_two_pass_shape(const GemmArgs& g) {
+  const TailPlan p = plan_tail(g.a.outer, g.b.outer, g.K);
+  const int nb = pick_width(g.a.outer, g.b.outer, g.K, p, g.accumulate).nb;
+  return nb == 8 ? TwoPassShape{8, p.tail, p.splits} : TwoPassShape{nb, 0, 1};
 }
 
 #define NVFP4_LAUNCH_F16(BF16, ROWSCALES, SPLIT, NB)                                                                  \
@@ -658,7 +666,7 @@ hipError_t launch_gemm_two_pass(const GemmArgs& g, hipStream_t s) {
   // One 256x256 tile keeps one CU busy (its LDS fits one workgroup).  Whole rounds of kCUs tiles
   // run as they are; a last partial round that fills at most half the chip is split along K.
   const TailPlan p = plan_tail(M, N, K);
-  switch (pick_width(M, N, p).nb) {
+  switch (pick_width(M, N, K, p, g.accumulate).nb) {
     case 7: return launch_all<7>(g, a16, b16, tiles_m, s);
     case 6: return launch_all<6>(g, a16, b16, tiles_m, s);
     case 5: return launch_all<5>(g, a16, b16, tiles_m, s);

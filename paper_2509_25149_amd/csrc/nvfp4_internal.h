@@ -84,9 +84,25 @@ size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);
 bool gemm_two_pass_usable(const GemmArgs& g);
 hipError_t launch_gemm_two_pass(const GemmArgs& g, hipStream_t s);
 double gemm_two_pass_us(const GemmArgs& g);   // expected time, to choose between the routes
-// Straight from the packed codes, without scratch, any K
-hipError_t launch_gemm_direct(const GemmArgs& g, hipStream_t s);
-double gemm_direct_us(int64_t M, int64_t N, int64_t K);
+// 32-column units of this route's tile, and how many tiles of the last round are split along K over how many workgroups
+struct TwoPassShape {
+  int units, tail, splits;
+};
+TwoPassShape gemm_two_pass_shape(const GemmArgs& g);
+// Straight from the packed codes, without scratch, any K.  `shape`: number of a tile shape, see gemm_direct.hip.
+hipError_t launch_gemm_direct(const GemmArgs& g, int shape, hipStream_t s);
+constexpr int kDirectOwnTiles = 4;                        // the shape whose wavefronts own different tiles
+int pick_direct_shape(const GemmArgs& g);                 // the best of the others
+double gemm_direct_compute_us(const GemmArgs& g);         // its time, the result's bytes left out
+double gemm_direct_us(const GemmArgs& g, int shape);      // any shape's time
+// Expected time of a kernel on small tiles: `call`, then rounds of 256 tiles of `tile` us and `step` us per step of the loop,
+// or, where that is more, the result's bytes at `result` us per MB (added in quadrature: neither hides the other fully).  A
+// CU holds `resident` workgroups; a round in which only one of them has a tile takes `alone` rounds, not 1.
+struct SmallTileCost {
+  int resident;
+  double call, alone, tile, step, result;
+};
+double small_tile_us(const SmallTileCost& c, const GemmArgs& g, int64_t tile_m, int64_t tile_n, int64_t steps);
 // Decodes one operand (codes [outer, K/2], scales [outer, K/16]) to FP16 [outer, K]
 hipError_t launch_predecode(const Operand& op, int64_t K, void* fp16_out, hipStream_t s);
 

@@ -1,0 +1,64 @@
+"""Which kernel an NVFP4 product takes (host code only): the library's own plan, asked through the query that it exports for tests.
+Here: each class of products takes the kernel that was measured to be the faster one for it."""
+import ctypes
+import os
+
+import pytest
+
+from paper_2509_25149_amd import binding as nv
+
+TWO_PASS, FUSED_256, TILE_128, DIRECT = range(4)
+OWN_TILES = 4                        # the direct kernel's shape without a split of K
+
+
+@pytest.fixture(scope="module", autouse=True)
+def library():
+    if not os.path.exists(nv.LIB_PATH):
+        pytest.skip("libnvfp4_hip.so not built")
+
+
+def plan(M, N, K, bf16=False, accumulate=False, workspace=0, decoded=0):
+    """(route, shape, tiles of a split last round, splits); workspace: bytes, or True for what the library asks for."""
+    out = (ctypes.c_int * 4)()
+    if workspace is True:
+        workspace = nv.gemm_workspace_bytes(M, N, K)
+    i64 = ctypes.c_int64
+    nv.load_library().nvfp4_internal_gemm_plan(i64(M), i64(N), i64(K), int(bf16), int(accumulate), ctypes.c_size_t(workspace), decoded, out)
+    return tuple(out)
+
+
+@pytest.mark.parametrize("M,N", [(2048, 2048), (2048, 8192), (5120, 20480), (4096, 5120), (8176, 1296)])
+@pytest.mark.parametrize("K", [16, 48, 80, 144, 208, 272, 336, 400])
+@pytest.mark.parametrize("bf16,accumulate", [(False, False), (True, False), (False, True)], ids=["f32", "bf16", "accumulate"])
+def test_short_contractions_with_a_large_result_do_not_split_k(M, N, K, bf16, accumulate):
+    """The result's bytes are the work: no wavefront may wait for others that have no step of K.  5120 x 20480 x 16 (FP32) took 193 us
+    with K split over four wavefronts, 80 in 128 x 128 tiles."""
+    for workspace in (0, True):
+        route, shape = plan(M, N, K, bf16, accumulate, workspace)[:2]
+        assert route == TILE_128 or (route, shape) == (DIRECT, OWN_TILES)
+    if K <= 48:
+        assert route == TILE_128
+
+
+@pytest.mark.parametrize("M,N,K", [(5120, 20480, 1040), (5120, 20480, 2064), (4096, 5120, 1040), (8176, 1296, 1040), (8176, 20464, 5136)])
+def test_large_products_of_a_ragged_contraction_keep_whole_tiles(M, N, K):
+    assert plan(M, N, K)[:2] == (DIRECT, OWN_TILES)      # 5120 x 20480 x 1040: 314 us; 385 with K split, 369 in the 128 x 128 kernel
+
+
+@pytest.mark.parametrize("M,N,K,shape", [(16, 20480, 5136, 0), (32, 5120, 5136, 1), (64, 20480, 5136, 2), (512, 5120, 5136, 3),
+                                         (64, 20480, 5120, 2), (512, 5120, 5120, 3), (1040, 1296, 2064, 2), (256, 256, 512, 0)])
+def test_few_tokens_and_small_layers_split_k(M, N, K, shape):
+    for workspace in (0, True):
+        assert plan(M, N, K, True, False, workspace)[:2] == (DIRECT, shape)
+
+
+@pytest.mark.parametrize("M,N,K,units", [(8192, 20480, 5120, 8), (8192, 5120, 20480, 8), (5120, 20480, 8192, 8), (5120, 5120, 4096, 7),
+                                         (2048, 5120, 5120, 5), (4096, 5120, 5120, 5)])
+def test_large_products_take_the_two_pass_route(M, N, K, units):
+    assert plan(M, N, K, workspace=True)[:2] == (TWO_PASS, units)
+    assert plan(M, N, K, workspace=0)[0] in (FUSED_256, DIRECT)
+
+
+def test_accumulating_products_keep_the_widest_tile_unless_a_narrower_one_saves_rounds():
+    assert plan(5120, 20480, 256, accumulate=True, workspace=True)[:2] == (TWO_PASS, 8)      # 299 us; 160 columns 313
+    assert plan(5120, 20480, 256, bf16=True, workspace=True)[:2] == (TWO_PASS, 5)            # 83 us; 256 columns 88

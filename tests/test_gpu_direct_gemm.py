@@ -1,23 +1,30 @@
 """GPU parity of the GEMM straight from the packed codes (few tokens, small layers, K not a multiple of 64): each of its
-tile shapes at ragged edges of M, N and K, against the oracle's binary64 product."""
+tile shapes, and the 128 x 128 kernel of short contractions, at ragged edges of M, N and K, against the oracle's binary64 product."""
 import numpy as np
 import pytest
 import torch
 
 import oracle
 from paper_2509_25149_amd import binding as nv, synth
+from test_gemm_routes import DIRECT, OWN_TILES, TILE_128, plan
 from test_gpu_parity import GEMM_TOL, check_quantize, to_dev
 
 pytestmark = pytest.mark.gpu
 
 
-# tile shape the dispatch takes for it: 16x32 tiles (8 wavefronts; 4 for many tiles), 32x32, 64x48, 64x64.
-# K: shorter than a step of 128; a step and a rest of one 16-block; whole steps; more steps than wavefronts, with a rest (the
-# last three: every wavefront stages, reads back and stages again, and the sums of all of them are added).
-@pytest.mark.parametrize("M,N,K", [(16, 16, 16), (48, 80, 112), (16, 16400, 272), (32, 5136, 400), (64, 9232, 128),
-                                   (80, 8208, 144), (144, 5200, 1040), (32, 5136, 2192), (64, 9232, 1168)])
+# tile shape the dispatch takes for it: 16x32 tiles (8 wavefronts; 4 for many tiles), 32x32, 64x48, 64x64 with K split among the
+# wavefronts; 128x128 with a tile per wavefront; the 128x128 kernel.
+# K: shorter than a step of 128; a step and a rest of one 16-block; whole steps; more steps than wavefronts, with a rest (every
+# wavefront stages, reads back and stages again, and the sums of all of them are added).  The last six: many rounds of tiles.
+@pytest.mark.parametrize("M,N,K,kernel", [
+    (16, 16, 16, (DIRECT, 0)), (48, 80, 112, (DIRECT, 0)), (16, 16400, 272, (DIRECT, 0)), (32, 5136, 400, (DIRECT, 1)),
+    (64, 9232, 128, (DIRECT, 2)), (80, 8208, 144, (DIRECT, 0)), (144, 5200, 1040, (DIRECT, 3)), (32, 5136, 2192, (DIRECT, 1)),
+    (64, 9232, 1168, (DIRECT, 2)), (16, 16400, 1040, (DIRECT, 0)), (528, 5136, 1104, (DIRECT, 3)),
+    (2064, 8208, 16, (TILE_128, 0)), (2064, 4112, 80, (TILE_128, 0)), (1040, 8208, 208, (TILE_128, 0)),
+    (2064, 8208, 528, (DIRECT, OWN_TILES)), (4112, 4112, 400, (DIRECT, OWN_TILES)), (2064, 2064, 128, (DIRECT, OWN_TILES))])
 @pytest.mark.parametrize("per_row", [False, True], ids=["tensor_scale", "row_scales"])
-def test_direct_gemm(M, N, K, per_row):
+def test_direct_gemm(M, N, K, kernel, per_row):
+    assert plan(M, N, K)[:2] == kernel
     xb = synth.normal_with_outliers(M, K, 1.0, 7000 + M + K, frac=0.01)
     wb = synth.normal(K, N, 0.02, 7100 + N)
     qw, rw = check_quantize(wb, nv.LAYOUT_COL, nv.BLOCK_16x16)
