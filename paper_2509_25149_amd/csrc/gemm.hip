@@ -424,7 +424,9 @@ static GemmPlan plan_route(const GemmArgs& g) {
   // 20 % (two workgroups per CU hide those reads worse than three: 5120 x 20480 x 400 324 / 290), and the 128 x 128 kernel, which reads
   // it 16 bytes here and there, 1.5 us more for a small one (1040 x 1296 x 16 9.1 against 7.8 with K split).
   const int split = pick_direct_shape(g);
-  const double tile128 = small_tile_us(kTile128Cost, g, BM, BN, (g.K + BK - 1) / BK) + (g.accumulate ? 1.5 : 0.0), own = gemm_direct_us(g, kDirectOwnTiles);
+  const double tile128 = g.a.outer > int64_t{65535} * BM ? HUGE_VAL   // its tile rows are the launch's second dimension
+                                                         : small_tile_us(kTile128Cost, g, BM, BN, (g.K + BK - 1) / BK) + (g.accumulate ? 1.5 : 0.0);
+  const double own = gemm_direct_us(g, kDirectOwnTiles);
   const bool take_own = own < (g.accumulate ? 0.8 : g.K % 128 ? 0.92 : 1.0) * tile128;
   if (gemm_direct_us(g, split) <= (take_own ? own : tile128)) return {kDirect, split};
   return take_own ? GemmPlan{kDirect, kDirectOwnTiles} : GemmPlan{kTile128, 0};

@@ -16,6 +16,8 @@
 // Measured (us; before = whatever the call took then): 64 x 20480 x 5120 133 -> 22, 16 x 20480 x 5120 131 -> 14.6 (4.0 TB/s of
 // codes), 512 x 5120 x 5120 101 -> 38, 256 x 256 x 512 18 -> 3.4, 1040 x 1296 x 2064 44 -> 15.
 
+#include <cmath>
+
 #include "nvfp4_internal.h"
 #include "nvfp4_device.h"
 #include "gemm_epilogue.h"
@@ -259,7 +261,13 @@ static int64_t direct_tiles(const DirectShape& d, int64_t M, int64_t N) {
   return ((M + tile_m(d) - 1) / tile_m(d)) * ((N + tile_n(d) - 1) / tile_n(d));
 }
 
+// What the kernel's 32-bit rows, byte offsets within a 16-row block and launch size allow; others take other kernels.
+static bool fits(const DirectShape& d, int64_t M, int64_t N, int64_t K) {
+  return M <= 0x7fffffff && N <= 0x7fffffff && K <= (int64_t{1} << 27) && direct_tiles(d, M, N) * (d.wk == 1 ? 256 : d.wk * 64) <= 0xffffffff;
+}
+
 static double direct_shape_us(const DirectShape& d, int64_t M, int64_t N, int64_t K) {
+  if (!fits(d, M, N, K)) return HUGE_VAL;
   const int64_t rounds = (direct_tiles(d, M, N) + 255) / 256, steps = (K + kStepK - 1) / kStepK;
   return 3.0 + 0.247 * d.cost * static_cast<double>(steps) * static_cast<double>(rounds);
 }
@@ -275,6 +283,7 @@ double gemm_direct_compute_us(const GemmArgs& g) { return direct_shape_us(kDirec
 
 double gemm_direct_us(const GemmArgs& g, int shape) {
   const DirectShape& d = kDirectShapes[shape];
+  if (!fits(d, g.a.outer, g.b.outer, g.K)) return HUGE_VAL;
   const int64_t steps = (g.K + kStepK - 1) / kStepK;
   return small_tile_us(d.us, g, tile_m(d), tile_n(d), (steps + d.wk - 1) / d.wk);
 }
@@ -305,8 +314,7 @@ static hipError_t launch_direct(const GemmArgs& g, int shape, hipStream_t s) {
 }
 
 hipError_t launch_gemm_direct(const GemmArgs& g, int shape, hipStream_t s) {
-  // 32-bit rows, and byte offsets within a 16-row block
-  if (g.a.outer > 0x7fffffff || g.b.outer > 0x7fffffff || g.K > (int64_t{1} << 27)) return hipErrorInvalidValue;
+  if (!fits(kDirectShapes[shape], g.a.outer, g.b.outer, g.K)) return hipErrorInvalidValue;
   return g.out_bf16 ? launch_direct<true>(g, shape, s) : launch_direct<false>(g, shape, s);
 }
 

@@ -62,3 +62,21 @@ def test_large_products_take_the_two_pass_route(M, N, K, units):
 def test_accumulating_products_keep_the_widest_tile_unless_a_narrower_one_saves_rounds():
     assert plan(5120, 20480, 256, accumulate=True, workspace=True)[:2] == (TWO_PASS, 8)      # 299 us; 160 columns 313
     assert plan(5120, 20480, 256, bf16=True, workspace=True)[:2] == (TWO_PASS, 5)            # 83 us; 256 columns 88
+
+
+@pytest.mark.parametrize("K", [2 ** 27 + 16, 2 ** 29, 2 ** 31 + 16, 2 ** 33 + 64])
+def test_contractions_beyond_the_direct_kernels_offsets_take_a_kernel_that_has_none(K):
+    """The direct kernel's byte offsets within 16 rows are 32 bits wide (K <= 2^27); the other two count K in 64."""
+    for M, N in ((16, 16), (16, 4096), (512, 512)):
+        assert plan(M, N, K)[0] == (TILE_128 if K % 64 else FUSED_256)
+    assert plan(16, 16, 2 ** 27)[0] == DIRECT
+
+
+def test_results_too_large_for_one_launch_of_a_kernel_take_another():
+    # tile rows of the 128 x 128 kernel are the launch's second dimension: 65535 of them at the most
+    assert plan(65535 * 128, 128, 16)[0] == TILE_128
+    assert plan(65535 * 128 + 16, 128, 16)[0] == DIRECT
+    # 16 x 32 tiles: 256 threads each, under 2^32 in all
+    assert plan(2 ** 26, 128, 16)[:2] != (DIRECT, 0)
+    # 32-bit rows of the direct kernel
+    assert plan(16, 2 ** 31, 16)[0] == TILE_128
