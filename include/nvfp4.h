@@ -235,8 +235,8 @@ int nvfp4_quantize_with_amax(const void* x, int64_t rows, int64_t cols, int64_t 
  * large products, no scratch).  Products of few tokens, small layers and every K
  * that is not a multiple of 64 are computed straight from the codes in any case.
  * All give the same result up to FP32 summation order.
- * (With both operands decoded beforehand by nvfp4_predecode and no split last
- * round of tiles the FP16 GEMM needs nothing of the workspace and runs without.)
+ * (With both operands decoded beforehand by nvfp4_predecode the FP16 GEMM runs without
+ * a workspace too; room for the partial tiles of a split last round makes some faster.)
  * The workspace contents are scratch: undefined afterwards, free for reuse once
  * the call's kernels have run.
  */
@@ -260,9 +260,10 @@ int nvfp4_gemm(const nvfp4_qtensor* a, const nvfp4_qtensor* b, int op, void* d, 
  */
 int nvfp4_predecode(nvfp4_qtensor* q, int which_copy, void* fp16_out, size_t fp16_bytes, nvfp4_stream_t stream);
 
-/* Scratch bytes that let nvfp4_gemm take its faster two-pass route (host pointer out):
- * (M + N) * K * 2 for the FP16 operands and up to 64 MiB of FP32 partial tiles when the last
- * round of 256x256 output tiles is partial and gets split along K.
+/* Scratch bytes with which nvfp4_gemm takes the fastest of its routes (host pointer out):
+ * (M + N) * K * 2 for the FP16 operands of the two-pass route and up to 64 MiB of FP32 partial
+ * tiles when the last round of 256x256 output tiles is partial and may get split along K.
+ * With room for the operands only, that route runs without the split.
  * Two calls that overlap in time on one GPU need a workspace each. */
 int nvfp4_gemm_workspace_bytes(int64_t m, int64_t n, int64_t k, size_t* workspace_bytes);
 
@@ -288,7 +289,7 @@ int nvfp4_gemm_workspace_bytes(int64_t m, int64_t n, int64_t k, size_t* workspac
  * workspace: device, 256-byte aligned, shared by all steps of a call.  At least
  *   the quantizer's need (nvfp4_quantized_sizes) is required; with
  *   nvfp4_linear_workspace_bytes(tokens, d_in, d_out) bytes every GEMM takes
- *   its faster two-pass route.
+ *   its fastest route.
  */
 int nvfp4_linear_workspace_bytes(int64_t tokens, int64_t d_in, int64_t d_out, size_t* workspace_bytes);
 int nvfp4_linear_forward(const void* x, int64_t tokens, int64_t d_in, int64_t ldx, const nvfp4_qtensor* qw,

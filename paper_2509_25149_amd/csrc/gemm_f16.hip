@@ -539,20 +539,35 @@ static size_t operand_bytes(int64_t rows_a, int64_t rows_b, int64_t K) {
   return (b + 255) & ~static_cast<size_t>(255);
 }
 
+static size_t partial_bytes(const TailPlan& p) { return static_cast<size_t>(p.tail) * p.splits * kPartialTileBytes; }
+
+// Enough for every way in which the operands may come; a call may use less (plan_two_pass).
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) {
   const TailPlan p = plan_tail(M, N, K);
-  return operand_bytes(M, N, K) + static_cast<size_t>(p.tail) * p.splits * kPartialTileBytes;
+  return operand_bytes(M, N, K) + partial_bytes(p);
 }
 
-static size_t workspace_need(const GemmArgs& g) {
-  const TailPlan p = plan_tail(g.a.outer, g.b.outer, g.K);
-  return operand_bytes(g.a.fp16 ? 0 : g.a.outer, g.b.fp16 ? 0 : g.b.outer, g.K) +
-         static_cast<size_t>(p.tail) * p.splits * kPartialTileBytes;
+// What a call does: tile width, split of the last round, expected rounds.  One answer for the estimate, the room asked of the
+// workspace and the launch: the partial tiles of a split count only where tiles are 256 columns wide, and a workspace
+// without room for them (workspace_bytes: what it holds) makes the last round an ordinary one.
+struct TwoPassPlan {
+  Width width;
+  TailPlan tail;
+  size_t need;   // workspace bytes
+};
+static TwoPassPlan plan_two_pass(const GemmArgs& g) {
+  const int64_t M = g.a.outer, N = g.b.outer;
+  const size_t operands = operand_bytes(g.a.fp16 ? 0 : M, g.b.fp16 ? 0 : N, g.K);
+  TailPlan tail = plan_tail(M, N, g.K);
+  if (operands + partial_bytes(tail) > g.workspace_bytes) tail = TailPlan{0, 1};
+  const Width w = pick_width(M, N, g.K, tail, g.accumulate);
+  if (w.nb != 8) tail = TailPlan{0, 1};
+  return TwoPassPlan{w, tail, operands + partial_bytes(tail)};
 }
 
 bool gemm_two_pass_usable(const GemmArgs& g) {
-  // (With both operands decoded beforehand and no partial last round of tiles nothing is needed of the workspace.)
-  const size_t need = workspace_need(g);
+  // (With both operands decoded beforehand nothing is needed of the workspace.)
+  const size_t need = plan_two_pass(g).need;
   const bool room = need == 0 || (g.workspace && g.workspace_bytes >= need && reinterpret_cast<uintptr_t>(g.workspace) % 256 == 0);
   return room && (g.K % TK) == 0 &&
          reinterpret_cast<uintptr_t>(g.a.fp16) % 16 == 0 && reinterpret_cast<uintptr_t>(g.b.fp16) % 16 == 0 &&
@@ -568,15 +583,14 @@ bool gemm_two_pass_usable(const GemmArgs& g) {
 double gemm_two_pass_us(const GemmArgs& g) {
   const int64_t M = g.a.outer, N = g.b.outer;
   const double k = static_cast<double>(g.K);
-  const Width w = pick_width(M, N, g.K, plan_tail(M, N, g.K), g.accumulate);
+  const Width w = plan_two_pass(g).width;
   const int64_t rows = (g.a.fp16 ? 0 : M) + (g.b.fp16 ? 0 : N);
   return 4.0 + static_cast<double>(rows) * k * 2.5625 / 4.7e6 + (rows ? 2.0 : 0.0) + w.rounds * k * (w.tiles >= kCUs ? 0.0225 : 0.0185);
 }
 
 TwoPassShape gemm_two_pass_shape(const GemmArgs& g) {
-  const TailPlan p = plan_tail(g.a.outer, g.b.outer, g.K);
-  const int nb = pick_width(g.a.outer, g.b.outer, g.K, p, g.accumulate).nb;
-  return nb == 8 ? TwoPassShape{8, p.tail, p.splits} : TwoPassShape{nb, 0, 1};
+  const TwoPassPlan p = plan_two_pass(g);
+  return TwoPassShape{p.width.nb, p.tail.tail, p.tail.splits};
 }
 
 #define NVFP4_LAUNCH_F16(BF16, ROWSCALES, SPLIT, NB)                                                                  \
@@ -665,8 +679,9 @@ hipError_t launch_gemm_two_pass(const GemmArgs& g, hipStream_t s) {
   const int tiles = tiles_m * tiles_n;
   // One 256x256 tile keeps one CU busy (its LDS fits one workgroup).  Whole rounds of kCUs tiles
   // run as they are; a last partial round that fills at most half the chip is split along K.
-  const TailPlan p = plan_tail(M, N, K);
-  switch (pick_width(M, N, K, p, g.accumulate).nb) {
+  const TwoPassPlan plan = plan_two_pass(g);
+  const TailPlan& p = plan.tail;
+  switch (plan.width.nb) {
     case 7: return launch_all<7>(g, a16, b16, tiles_m, s);
     case 6: return launch_all<6>(g, a16, b16, tiles_m, s);
     case 5: return launch_all<5>(g, a16, b16, tiles_m, s);

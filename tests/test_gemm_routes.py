@@ -80,3 +80,19 @@ def test_results_too_large_for_one_launch_of_a_kernel_take_another():
     assert plan(2 ** 26, 128, 16)[:2] != (DIRECT, 0)
     # 32-bit rows of the direct kernel
     assert plan(16, 2 ** 31, 16)[0] == TILE_128
+
+
+def test_workspace_without_room_for_partial_tiles_still_serves_the_two_pass_route():
+    M, N, K = 4352, 4096, 4096                                   # 272 tiles: the last 16 split 8 ways
+    operands = (M + N) * K * 2
+    assert plan(M, N, K, workspace=True) == (TWO_PASS, 8, 16, 8)
+    assert nv.gemm_workspace_bytes(M, N, K) == operands + 16 * 8 * 2 ** 18
+    route, units, tail, splits = plan(M, N, K, workspace=operands)
+    assert (route, tail, splits) == (TWO_PASS, 0, 1) and units < 8    # two whole rounds of 256 columns or fewer of narrower tiles
+    assert plan(M, N, K, workspace=operands - 256)[0] != TWO_PASS
+    # narrower tiles ask for no partial ones: 4096 x 5120 x 5120 (320 tiles) runs 160 columns wide
+    assert plan(4096, 5120, 5120, workspace=(4096 + 5120) * 5120 * 2) == (TWO_PASS, 5, 0, 1)
+    # with both operands decoded nothing is needed; with room for the partial tiles alone the split is back
+    assert plan(M, N, K, decoded=3) == (TWO_PASS, units, 0, 1)
+    assert plan(M, N, K, workspace=16 * 8 * 2 ** 18, decoded=3) == (TWO_PASS, 8, 16, 8)
+    assert plan(M, N, K, workspace=N * K * 2, decoded=1)[0] == TWO_PASS
