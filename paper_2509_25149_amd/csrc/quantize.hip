@@ -2,7 +2,7 @@
 //
 // Work decomposition shared by both passes: a lane owns a 16-row x 8-column
 // patch of the bf16 tensor (sixteen 128-bit loads, one per row).  In the amax
-// pass a wavefront spans 16 rows x 512 columns and walks down the rows; in the
+// pass a wavefront spans 16 rows x 512 columns (more rows of a narrower tensor) at a time; in the
 // cast pass it is one patch per lane, two 16-row groups x 256 columns, and a
 // 256-thread workgroup covers 128 rows x 256 columns.  With this patch
 //   - a 1x16 block of the row copy is split over two neighbouring lanes
@@ -30,18 +30,25 @@ namespace nvfp4 {
 // The raw maximum is always taken, also when only a rotated copy is asked for: it is the one place where a NaN in
 // the input shows (the floating-point maxima of the rotated values skip NaNs), and the fold carries a
 // non-finite raw maximum over into the rotated one.
+// A piece of work is 4 wavefronts x 64 lanes; `lanes` = 1 << lane_bits of a wavefront (64, fewer for a tensor narrower than 512
+// columns) span the columns of one 16-row group.  Pieces are numbered column by column, then down the rows, and dealt to the
+// workgroups in turn, so that a tensor of any proportions keeps every one of them and every lane at work.  (With whole column
+// blocks to a workgroup 1024 x 133120 took 57 us, 1048576 x 16 208.)
 template <int kRht>   // kRht: 0, or the rotation size 2, 4 or 16 (sign_mask: the d signs repeated over 16 bits)
 __global__ __launch_bounds__(kThreads) void amax_kernel(const uint16_t* __restrict__ x, int64_t rows,
-                                                        int64_t cols, int64_t ld, uint32_t sign_mask,
-                                                        uint32_t* __restrict__ ws) {
+                                                        int64_t cols, int64_t ld, uint32_t sign_mask, int lane_bits, uint32_t col_blocks,
+                                                        uint32_t pieces, uint32_t* __restrict__ ws) {
   __shared__ uint32_t red[2][4];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t col0 = static_cast<int64_t>(blockIdx.x) * kWaveCols + lane * 8, ngroups = rows / 16;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, groups_per_wave = 64 >> lane_bits;
+  const int64_t ngroups = rows / 16;
   uint32_t m_raw = 0, m_rot = 0;
   float f_rot = 0.0f;
-  if (col0 < cols) {
 #pragma unroll 1
-    for (int64_t group = static_cast<int64_t>(blockIdx.y) * 4 + wave; group < ngroups; group += static_cast<int64_t>(gridDim.y) * 4) {
+  for (uint32_t piece = blockIdx.x; piece < pieces; piece += gridDim.x) {
+    const uint32_t down = piece / col_blocks, across = piece - down * col_blocks;
+    const int64_t group = (static_cast<int64_t>(down) * 4 + wave) * groups_per_wave + (lane >> lane_bits);
+    const int64_t col0 = (static_cast<int64_t>(across) << (lane_bits + 3)) + (lane & ((1 << lane_bits) - 1)) * 8;
+    if (col0 < cols && group < ngroups) {
       Patch p;
       load_patch(x, ld, group * 16, col0, p);
       m_raw = max(m_raw, patch_amax_bits(p));
@@ -68,7 +75,7 @@ __global__ __launch_bounds__(kThreads) void amax_kernel(const uint16_t* __restri
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    const uint32_t nwg = gridDim.x * gridDim.y, wg = blockIdx.y * gridDim.x + blockIdx.x;
+    const uint32_t nwg = gridDim.x, wg = blockIdx.x;
     ws[kWsHeader + wg] = max(max(red[0][0], red[0][1]), max(red[0][2], red[0][3]));
     ws[kWsHeader + nwg + wg] = max(max(red[1][0], red[1][1]), max(red[1][2], red[1][3]));
   }
@@ -255,14 +262,23 @@ constexpr int64_t kCacheBytes = int64_t{256} << 20;
 static int cast_streams(const QuantizeArgs& a) { return a.rows * a.cols * 2 > kCacheBytes; }
 static int cast_reverse(const QuantizeArgs& a) { return a.do_amax && a.rows * a.cols * 2 > kCacheBytes / 2 && !cast_streams(a); }
 
-// Workgroups of the amax pass, at most kMaxAmaxWgs (one per 512 columns if that is more): two to a CU keep enough loads in
-// flight, and every workgroup of the cast pass folds their maxima (dY 8192 x 20480: 512 218 us per call, 1024 222, 2048 236).
-// Two words each fit the workspace whatever the shape: it has 2 (rows + cols), and 64-row x 512-column tiles are fewer.
-constexpr int64_t kMaxAmaxWgs = 512;
-static dim3 amax_grid(const QuantizeArgs& a) {
-  const int64_t gx = (a.cols + kWaveCols - 1) / kWaveCols, gy = (a.rows / 16 + 3) / 4;
-  const int64_t cap = kMaxAmaxWgs / gx > 0 ? kMaxAmaxWgs / gx : 1;
-  return dim3(static_cast<unsigned>(gx), static_cast<unsigned>(gy < cap ? gy : cap));
+// Workgroups of the amax pass, at most 512: two to a CU keep enough loads in flight, and every workgroup of the cast pass
+// folds their maxima (dY 8192 x 20480: 512 218 us per call, 1024 222, 2048 236).
+// Two words each fit the workspace whatever the shape: it has 2 (rows + cols), and pieces of 64 rows x 512 columns, or of more
+// rows of a narrower tensor, are fewer.
+struct AmaxWork {
+  int lane_bits;
+  uint32_t col_blocks, pieces, workgroups;
+};
+static AmaxWork amax_work(const QuantizeArgs& a) {
+  constexpr uint32_t kMaxAmaxWgs = 512;
+  AmaxWork w{6, 0, 0, 0};
+  while (w.lane_bits > 1 && a.cols <= (int64_t{4} << w.lane_bits)) --w.lane_bits;   // half the lanes span it
+  const int64_t rows = int64_t{64} << (6 - w.lane_bits);                             // of a piece
+  w.col_blocks = static_cast<uint32_t>((a.cols + (int64_t{8} << w.lane_bits) - 1) >> (w.lane_bits + 3));
+  w.pieces = static_cast<uint32_t>(w.col_blocks * ((a.rows + rows - 1) / rows));
+  w.workgroups = w.pieces < kMaxAmaxWgs ? w.pieces : kMaxAmaxWgs;
+  return w;
 }
 
 template <bool kRow, bool kCol, int kRht, bool kSR, bool k2D>
@@ -273,22 +289,21 @@ static void launch_cast(const QuantizeArgs& a, hipStream_t s) {
   // patch is then read twice.  us, one set / two: X 256 x 512 12.9 / 10.6, dY SR 256 x 512 15.7 / 11.9, X 2048 x 4096 (256 workgroups)
   // 15.0 / 12.9, dY 4096 x 4096 (512) 28.4 / 31.8.  16x16 blocks have little work per patch: 2048 x 4096 10.3 / 10.8.
   const dim3 grid(gx, gy, kRow && kCol && !k2D && static_cast<int64_t>(gx) * gy <= 256 ? 2 : 1);
-  const dim3 ag = amax_grid(a);
   const uint32_t* maxima = a.do_amax ? a.ws + kWsHeader : a.ws;
   const auto kernel = cast_streams(a) ? &cast_kernel<kRow, kCol, kRht, kSR, k2D, true> : &cast_kernel<kRow, kCol, kRht, kSR, k2D, false>;
   hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s,
-                     static_cast<const uint16_t*>(a.x), a.rows, a.cols, a.ld, maxima, a.do_amax ? ag.x * ag.y : 1u, a.sign_mask, a.key0,
+                     static_cast<const uint16_t*>(a.x), a.rows, a.cols, a.ld, maxima, a.do_amax ? amax_work(a).workgroups : 1u, a.sign_mask, a.key0,
                      a.key1, a.row_codes, a.row_scales, a.row_ts, a.col_codes, a.col_scales, a.col_ts, cast_reverse(a));
 }
 
 template <bool kRow, bool kCol, int kRht>
 static void launch_passes(const QuantizeArgs& a, hipStream_t s) {
   if (a.do_amax) {
-    const dim3 grid = amax_grid(a);
-    hipLaunchKernelGGL((amax_kernel<kRht>), grid, dim3(kThreads), 0, s, static_cast<const uint16_t*>(a.x), a.rows, a.cols, a.ld,
-                       a.sign_mask, a.ws);
+    const AmaxWork w = amax_work(a);
+    hipLaunchKernelGGL((amax_kernel<kRht>), dim3(w.workgroups), dim3(kThreads), 0, s, static_cast<const uint16_t*>(a.x), a.rows, a.cols,
+                       a.ld, a.sign_mask, w.lane_bits, w.col_blocks, w.pieces, a.ws);
     // the cast pass folds the maxima itself; only a caller of the amax alone needs them folded
-    if (!a.do_cast) hipLaunchKernelGGL(amax_finalize_kernel, dim3(1), dim3(1024), 0, s, a.ws, grid.x * grid.y, a.amax_copy);
+    if (!a.do_cast) hipLaunchKernelGGL(amax_finalize_kernel, dim3(1), dim3(1024), 0, s, a.ws, w.workgroups, a.amax_copy);
   }
   if (!a.do_cast) return;
   if (a.block2d) {
