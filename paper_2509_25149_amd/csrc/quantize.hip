@@ -93,12 +93,16 @@ __global__ __launch_bounds__(kThreads) void amax_kernel(const uint16_t* __restri
 // patch is on its way from memory -- a launch of its own for that cost 5 us and two gaps between kernels.
 // Codes leave with non-temporal stores: nothing reads them in this call, and in the memory-side cache they push out the tensor
 // that pass 1 has left there (W 104 -> 86 us, dY 8192 x 20480 SR 223 -> 213, X 8192 x 5120 47.8 -> 46.8).
-using CastTile = Staged<8, 32, true>;
+// (After a pass 1, that is; for calls with the amax given see cast_memory.)
+enum CastMemory { kCachedLoads = 0, kStreamedLoads = 1, kStreamedLoadsCachedStores = 2 };
+template <int kMemory>
+using CastTile = Staged<8, 32, kMemory != kStreamedLoadsCachedStores>;
+enum { kWalkReverse = 1, kWalkBands = 2 };   // see cast_walk
 __device__ __forceinline__ float to_scalar(float v) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v))); }
 
-// kStream: the source is read with non-temporal loads (cast_streams; a template argument because a branch around the patch's loads
-// makes every one of them wait at its end: dY 8192 x 20480 SR 232 us).
-template <bool kRow, bool kCol, int kRht, bool kSR, bool k2D, bool kStream>   // kRht as in amax_kernel
+// kMemory: see cast_memory (a template argument because a branch around the patch's loads makes every one of them wait at
+// its end: dY 8192 x 20480 SR 232 us).
+template <bool kRow, bool kCol, int kRht, bool kSR, bool k2D, int kMemory>   // kRht as in amax_kernel
 // With stochastic rounding the draws of a patch (64 registers beside its own 64) left room for two wavefronts per SIMD, which did
 // not cover each other's loads and stores; columns one at a time instead of in pairs bring both copies under 168 registers (with
 // eight parked in LDS), i.e. to three: dY 8192 x 20480 209 -> 189 us, 8192 x 5120 61 -> 57.
@@ -106,8 +110,8 @@ __global__ __launch_bounds__(kThreads, kSR && kRow && kCol && !k2D ? 3 : 2) void
     const uint16_t* __restrict__ x, int64_t rows, int64_t cols, int64_t ld,
     const uint32_t* __restrict__ maxima, uint32_t n_maxima, uint32_t sign_mask, uint32_t key0, uint32_t key1,
     uint8_t* __restrict__ row_codes, uint8_t* __restrict__ row_scales, float* __restrict__ row_ts,
-    uint8_t* __restrict__ col_codes, uint8_t* __restrict__ col_scales, float* __restrict__ col_ts, int reverse) {
-  using T = CastTile;
+    uint8_t* __restrict__ col_codes, uint8_t* __restrict__ col_scales, float* __restrict__ col_ts, int walk) {
+  using T = CastTile<kMemory>;
   __shared__ __attribute__((aligned(16))) uint8_t st_col_codes[kCol ? T::kColCodesBytes : 16];
   __shared__ __attribute__((aligned(16))) uint8_t st_col_scales[kCol ? T::kColScalesBytes : 16];
   __shared__ __attribute__((aligned(16))) uint8_t st_row_scales[kRow ? T::kRowScalesBytes : 16];
@@ -117,7 +121,17 @@ __global__ __launch_bounds__(kThreads, kSR && kRow && kCol && !k2D ? 3 : 2) void
 
   const int tid = threadIdx.x, lane = tid & (T::kLanes - 1), wave = tid >> 6;
   const int gl = tid / T::kLanes;                // group index inside the tile
-  const unsigned bx = reverse ? gridDim.x - 1 - blockIdx.x : blockIdx.x, by = reverse ? gridDim.y - 1 - blockIdx.y : blockIdx.y;
+  unsigned bx = blockIdx.x, by = blockIdx.y;
+  if (walk & kWalkBands) {
+    const unsigned id = by * gridDim.x + bx, band = gridDim.x * gridDim.y >> 3;
+    const unsigned to = id < band * 8 ? (id & 7) * band + (id >> 3) : id;
+    by = to / gridDim.x;
+    bx = to - by * gridDim.x;
+  }
+  if (walk & kWalkReverse) {
+    bx = gridDim.x - 1 - bx;
+    by = gridDim.y - 1 - by;
+  }
   const int64_t colblk = static_cast<int64_t>(bx) * T::kCols;
   const int64_t col0 = colblk + lane * 8;
   const int64_t group0 = static_cast<int64_t>(by) * T::kGroups, ngroups = rows / 16;
@@ -127,7 +141,7 @@ __global__ __launch_bounds__(kThreads, kSR && kRow && kCol && !k2D ? 3 : 2) void
   const bool do_row = kRow && (gridDim.z == 1 || blockIdx.z == 0), do_col = kCol && (gridDim.z == 1 || blockIdx.z == 1);
 
   Patch p;
-  if (active) load_patch<kStream>(x, ld, row0, col0, p);
+  if (active) load_patch<kMemory != kCachedLoads>(x, ld, row0, col0, p);
 
   uint32_t m_raw = 0, m_rot = 0;
   for (uint32_t i = tid; i < n_maxima; i += kThreads) {
@@ -253,14 +267,32 @@ size_t quantize_workspace_bytes(int64_t rows, int64_t cols) {
   return (per_tensor > per_row ? per_tensor : per_row) * sizeof(uint32_t);
 }
 
-// How the cast pass reads a tensor that pass 1 has just streamed front to back through the 256 MB memory-side cache:
+// How the cast pass goes over memory.  After pass 1, which has just streamed the tensor front to back through the 256 MB
+// memory-side cache:
 //   above 128 MB from its end (what comes last is what the cache still holds; a smaller tensor it holds whole);
 //   above 256 MB, where most of it is gone again, from the front and with non-temporal loads, which leave the tail alone until the
-//   walk gets there (dY 8192 x 20480, 335 MB: RNE 173 -> 154 us, SR 212 -> 203; at 251 MB they are the slower: 145 against 153).
-// With the amax given nothing is in the cache: non-temporal loads only matter to others.
+//   walk gets there (dY 8192 x 20480, 335 MB: RNE 173 -> 154 us, SR 212 -> 203; at 251 MB they are the slower: 145 against 153).  Where rows
+//   do not start on 128-byte lines, two workgroups fetch each border line and the cache has to hold it between them: there from
+//   304 MB on (8208 x 16400, 269 MB: X 185 us streamed, 178 from the end; 8176 x 19472, 318 MB: 222 / 223).
+// With the amax given: non-temporal loads above 256 MB, and where rows do not start on 128-byte lines ordinary stores of the codes --
+// nothing of the tensor is to be kept in the cache, and it puts the pieces of border lines together (15552 x 13648 259 -> 178 us, 8176 x
+// 20464 149 either way; on 128-byte lines it depends on the shape: 8192 x 20480 126 -> 107, 4096 x 76800 213 -> 231).
+// The row copy alone, rows not on 128-byte lines: neighbouring tiles, which share those lines and the border lines of the codes, go to
+// workgroups of one XCD (they are dealt out round robin), an eighth of the grid to each: 5104 x 20464 91 -> 80 us, 8176 x 5104 38.8 -> 35.1,
+// 1920 x 31504 56 -> 50.  With both copies it loses above 200 MB (5104 x 20464 129 -> 137), with few rows too (272 x 131088 36 -> 37).
 constexpr int64_t kCacheBytes = int64_t{256} << 20;
-static int cast_streams(const QuantizeArgs& a) { return a.rows * a.cols * 2 > kCacheBytes; }
-static int cast_reverse(const QuantizeArgs& a) { return a.do_amax && a.rows * a.cols * 2 > kCacheBytes / 2 && !cast_streams(a); }
+static bool lines_aligned(const QuantizeArgs& a) { return a.ld % 64 == 0 && reinterpret_cast<uintptr_t>(a.x) % 128 == 0; }
+static CastMemory cast_memory(const QuantizeArgs& a) {
+  const int64_t bytes = a.rows * a.cols * 2;
+  if (lines_aligned(a)) return bytes > kCacheBytes ? kStreamedLoads : kCachedLoads;
+  if (!a.do_amax) return bytes > kCacheBytes ? kStreamedLoadsCachedStores : kCachedLoads;
+  return bytes > kCacheBytes / 16 * 19 ? kStreamedLoads : kCachedLoads;
+}
+static int cast_walk(const QuantizeArgs& a) {
+  const bool reverse = a.do_amax && a.rows * a.cols * 2 > kCacheBytes / 2 && cast_memory(a) == kCachedLoads;
+  const bool bands = !a.want_col && !lines_aligned(a) && a.rows >= 1024;
+  return (reverse ? kWalkReverse : 0) | (bands ? kWalkBands : 0);
+}
 
 // Workgroups of the amax pass, at most 512: two to a CU keep enough loads in flight, and every workgroup of the cast pass
 // folds their maxima (dY 8192 x 20480: 512 218 us per call, 1024 222, 2048 236).
@@ -283,17 +315,20 @@ static AmaxWork amax_work(const QuantizeArgs& a) {
 
 template <bool kRow, bool kCol, int kRht, bool kSR, bool k2D>
 static void launch_cast(const QuantizeArgs& a, hipStream_t s) {
-  using T = CastTile;
+  using T = CastTile<kCachedLoads>;   // the tile is the same for all
   const unsigned gx = static_cast<unsigned>((a.cols + T::kCols - 1) / T::kCols), gy = static_cast<unsigned>((a.rows / 16 + T::kGroups - 1) / T::kGroups);
   // Up to 256 workgroups (one per CU) the call takes as long as one patch does: each copy gets workgroups of its own, though the
   // patch is then read twice.  us, one set / two: X 256 x 512 12.9 / 10.6, dY SR 256 x 512 15.7 / 11.9, X 2048 x 4096 (256 workgroups)
   // 15.0 / 12.9, dY 4096 x 4096 (512) 28.4 / 31.8.  16x16 blocks have little work per patch: 2048 x 4096 10.3 / 10.8.
   const dim3 grid(gx, gy, kRow && kCol && !k2D && static_cast<int64_t>(gx) * gy <= 256 ? 2 : 1);
   const uint32_t* maxima = a.do_amax ? a.ws + kWsHeader : a.ws;
-  const auto kernel = cast_streams(a) ? &cast_kernel<kRow, kCol, kRht, kSR, k2D, true> : &cast_kernel<kRow, kCol, kRht, kSR, k2D, false>;
+  const CastMemory m = cast_memory(a);
+  const auto kernel = m == kCachedLoads     ? &cast_kernel<kRow, kCol, kRht, kSR, k2D, kCachedLoads>
+                      : m == kStreamedLoads ? &cast_kernel<kRow, kCol, kRht, kSR, k2D, kStreamedLoads>
+                                            : &cast_kernel<kRow, kCol, kRht, kSR, k2D, kStreamedLoadsCachedStores>;
   hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s,
                      static_cast<const uint16_t*>(a.x), a.rows, a.cols, a.ld, maxima, a.do_amax ? amax_work(a).workgroups : 1u, a.sign_mask, a.key0,
-                     a.key1, a.row_codes, a.row_scales, a.row_ts, a.col_codes, a.col_scales, a.col_ts, cast_reverse(a));
+                     a.key1, a.row_codes, a.row_scales, a.row_ts, a.col_codes, a.col_scales, a.col_ts, cast_walk(a));
 }
 
 template <bool kRow, bool kCol, int kRht>

@@ -265,7 +265,7 @@ __device__ __forceinline__ void row_pass(const Patch& p, const uint32_t (&rnd)[1
     const uint32_t d = encode8<kSR>(v, rnd[r]);
     store_codes<T::kStream>(dst + r * code_ld, d);
     if ((lane & 1) == 0) st_row_scales[(gl * 16 + r) * T::kRowScaleLd + (lane >> 1)] = static_cast<uint8_t>(code);
-    if (kSR && T::kStream) __builtin_amdgcn_sched_barrier(0);   // one row at a time: see cast_kernel
+    if (kSR && T::kLanes == 32) __builtin_amdgcn_sched_barrier(0);   // one row at a time: see cast_kernel
   }
 }
 

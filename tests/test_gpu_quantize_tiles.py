@@ -1,9 +1,11 @@
 """GPU parity of the quantizer at the edges of its workgroup tiles (cast pass 128 rows x 256 columns, amax pass 64 rows x 512
 columns or more rows of a narrower tensor) and where an amax workgroup takes several pieces, bit for bit against the oracle."""
 import pytest
+import torch
 
+import oracle
 from paper_2509_25149_amd import binding as nv, synth
-from test_gpu_parity import check_quantize
+from test_gpu_parity import check_quantize, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -31,3 +33,41 @@ def test_tile_edges(rows, cols, mode):
         check_quantize(xb, RC, rounding=nv.ROUND_SR, rht=True, rht_seed=12, sr_seed=13)
     else:
         check_quantize(xb, nv.LAYOUT_ROW)
+
+
+# a row copy alone whose rows do not start on 128-byte lines: tiles dealt out in bands, one per XCD, with a remainder of the 8 and without
+@pytest.mark.parametrize("rows,cols", [(1040, 2064), (1024, 2064), (2064, 784)])
+def test_row_copy_in_bands(rows, cols):
+    check_quantize(synth.normal_with_outliers(rows, cols, 1.0, 8100 + rows, frac=0.01), nv.LAYOUT_ROW)
+
+
+@pytest.mark.parametrize("cols,ld,mode", [
+    (16400, 16448, dict(layout_mask=RC, block_dim=nv.BLOCK_16x16)),          # rows on 128-byte lines by their padding: streamed
+    (16400, 16400, dict(layout_mask=RC, rht_on_col=2, rht_seed=21)),         # rows anywhere, 269 MB: from the end
+    (19504, 19504, dict(layout_mask=RC, rht_on_col=4, rht_seed=22)),         # 320 MB: streamed
+    (19504, 19504, dict(layout_mask=nv.LAYOUT_ROW)),                         # the row copy alone, streamed and in bands
+    (16400, 16400, dict(layout_mask=nv.LAYOUT_ROW)),                         # from the end and in bands
+], ids=["16x16_padded", "d2", "d4", "row", "row_from_the_end"])
+def test_beyond_the_memory_side_cache(cols, ld, mode):
+    """Tensors of more than 256 MB: 144 rows repeated 57 times, so that the oracle's bytes for those repeat as well (same maximum, same
+    blocks; nothing is drawn).  With the amax given, too: there the codes of rows that start anywhere leave by ordinary stores."""
+    base, reps = 144, 57
+    xb = synth.normal_with_outliers(base, cols, 1.0, 8200 + cols, frac=0.01)
+    big = torch.zeros((base * reps, ld), dtype=torch.bfloat16, device="cuda")
+    x = big[:, :cols]
+    x.copy_(to_dev(xb).repeat(reps, 1))
+    q = nv.nvfp4_quantize(x, **mode)
+    given = nv.nvfp4_quantize_with_amax(x, nv.nvfp4_amax(x, mode.get("rht_on_col", 0), mode.get("rht_seed", 0)), **mode)
+    ob = mode.get("block_dim", nv.BLOCK_1x16)
+    ob = oracle.BLOCK_16x16 if ob == nv.BLOCK_16x16 else oracle.BLOCK_1x16
+    for t in (q, given):
+        r = oracle.quantize(xb, oracle.ROW, ob)
+        assert torch.equal(t.row_codes.view(reps, base, -1), torch.from_numpy(r.codes).cuda().expand(reps, -1, -1))
+        assert torch.equal(t.row_scales.view(reps, base, -1), torch.from_numpy(r.scales).cuda().expand(reps, -1, -1))
+        assert t.row_ts.cpu().numpy()[1] == r.amax
+        if mode["layout_mask"] & nv.LAYOUT_COL:
+            d = mode.get("rht_on_col", 0)
+            c = oracle.quantize(xb, oracle.COL, ob, oracle.RNE, d > 0, mode.get("rht_seed", 0), rht_dim=d or 16)
+            assert torch.equal(t.col_codes.view(cols, reps, -1), torch.from_numpy(c.codes).cuda().unsqueeze(1).expand(-1, reps, -1))
+            assert torch.equal(t.col_scales.view(cols, reps, -1), torch.from_numpy(c.scales).cuda().unsqueeze(1).expand(-1, reps, -1))
+            assert t.col_ts.cpu().numpy()[1] == c.amax
