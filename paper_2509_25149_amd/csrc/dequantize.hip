@@ -64,8 +64,9 @@ __global__ __launch_bounds__(256) void dequantize_kernel(Operand q, int64_t K, b
 
 // bf16 without a rotation: one thread per 8 elements (a dword of codes; two threads share a scale byte), so that a store
 // instruction of a wavefront writes 1 KiB of consecutive bytes and can be non-temporal.  Bound by the memory system: 8192 x 5120
-// (107 MB) 18.6 us with a thread per 16-block (two 16-byte stores 32 bytes apart from lane to lane), 17.1 so, 13.7 with
-// non-temporal stores (7.8 TB/s); with those the two-store form takes 30.
+// (107 MB), repeated on the same buffers, 18.6 us with a thread per 16-block (two 16-byte stores 32 bytes apart from lane to lane),
+// 17.1 so, 13.7 with non-temporal stores; with those the two-store form takes 30.  (Above a plain copy's 4.6 - 5.1 TB/s because the
+// memory-side cache still holds the codes; with cold buffers 23.7 us, a thread per 16-block 24.2.)
 __global__ __launch_bounds__(256) void dequantize8_kernel(Operand q, int64_t K, void* __restrict__ outv, int64_t ld_out) {
   const int64_t n8 = K / 8;
   const int64_t idx = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
@@ -252,8 +253,20 @@ hipError_t launch_dequantize(const DequantArgs& d, hipStream_t s) {
     return hipGetLastError();
   }
   if (!d.undo_rht && d.out_bf16) {
-    hipLaunchKernelGGL(dequantize8_kernel, dim3(static_cast<unsigned>((total * 2 + 255) / 256)), dim3(256), 0, s, d.q, d.K, d.out, d.ld_out);
-    return hipGetLastError();
+    // A launch holds fewer than 2^32 threads: 2^35 elements and more go in pieces of whole rows.
+    const int64_t rows_at_once = ((int64_t{1} << 32) - 256) / (d.K / 8);
+    for (int64_t r = 0; r < d.q.outer; r += rows_at_once) {
+      Operand q = d.q;
+      q.outer = d.q.outer - r < rows_at_once ? d.q.outer - r : rows_at_once;
+      q.codes += r * (d.K / 2);
+      q.scales += r * (d.K / 16);
+      if (q.ts_per_row) q.ts += r;
+      hipLaunchKernelGGL(dequantize8_kernel, dim3(static_cast<unsigned>((q.outer * (d.K / 8) + 255) / 256)), dim3(256), 0, s, q, d.K,
+                         static_cast<uint16_t*>(d.out) + r * d.ld_out, d.ld_out);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
   }
   const dim3 grid(static_cast<unsigned>((total + 255) / 256));
   if (d.out_bf16)
