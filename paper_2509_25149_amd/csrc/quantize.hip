@@ -28,8 +28,8 @@ namespace nvfp4 {
 // slot of the workspace; whoever needs the tensor's folds the slots.  No atomics:
 // thousands of same-address atomics serialise in L2 and cost more than the pass.
 // The raw maximum is always taken, also when only a rotated copy is asked for: it is the one place where a NaN in
-// the input shows (the floating-point maxima of the rotated values skip NaNs), and the fold carries a
-// non-finite raw maximum over into the rotated one.
+// the input shows (the floating-point maxima of the rotated values skip NaNs), and a non-finite one is carried over into
+// the rotated maximum -- here, not where the maxima are folded: there the two words may be a caller's, who gives each for itself.
 // A piece of work is 4 wavefronts x 64 lanes; `lanes` = 1 << lane_bits of a wavefront (64, fewer for a tensor narrower than 512
 // columns) span the columns of one 16-row group.  Pieces are numbered column by column, then down the rows, and dealt to the
 // workgroups in turn, so that a tensor of any proportions keeps every one of them and every lane at work.  (With whole column
@@ -76,8 +76,11 @@ __global__ __launch_bounds__(kThreads) void amax_kernel(const uint16_t* __restri
   __syncthreads();
   if (threadIdx.x == 0) {
     const uint32_t nwg = gridDim.x, wg = blockIdx.x;
-    ws[kWsHeader + wg] = max(max(red[0][0], red[0][1]), max(red[0][2], red[0][3]));
-    ws[kWsHeader + nwg + wg] = max(max(red[1][0], red[1][1]), max(red[1][2], red[1][3]));
+    const uint32_t raw = max(max(red[0][0], red[0][1]), max(red[0][2], red[0][3]));
+    uint32_t rot = max(max(red[1][0], red[1][1]), max(red[1][2], red[1][3]));
+    if (raw >= 0x7F800000u) rot = max(rot, raw);
+    ws[kWsHeader + wg] = raw;
+    ws[kWsHeader + nwg + wg] = rot;
   }
 }
 
@@ -157,7 +160,6 @@ __global__ __launch_bounds__(kThreads, kSR && kRow && kCol && !k2D ? 3 : 2) void
   __syncthreads();
   m_raw = max(max(red[0][0], red[0][1]), max(red[0][2], red[0][3]));
   m_rot = max(max(red[1][0], red[1][1]), max(red[1][2], red[1][3]));
-  if (m_raw >= 0x7F800000u) m_rot = max(m_rot, m_raw);   // a non-finite input shows in the rotated amax too
 
   // App. B.1 Eq. 1, from the amax of pass 1.
   const float amax_raw = __uint_as_float(m_raw);

@@ -431,6 +431,18 @@ def test_quantize_with_a_supplied_amax_matches_the_oracle(factor):
                       oracle.quantize(xb, oracle.COL, use_rht=True, rht_seed=5, amax=float(g[1])), "col copy")
 
 
+@pytest.mark.parametrize("raw", [-0.0, 0.0])
+def test_the_two_supplied_maxima_are_independent(raw):
+    """A raw maximum of zero (of either sign: its bits are no larger than others' as a number) leaves the rotated copy to its own."""
+    rows, cols = 64, 272
+    xb = synth.normal_with_outliers(rows, cols, 1.0, 4444, frac=0.01)
+    x = to_dev(xb)
+    own = nv.nvfp4_amax(x, 16, 5).cpu().numpy()
+    given = torch.tensor([raw, own[1]], dtype=torch.float32, device="cuda")
+    q = nv.nvfp4_quantize_with_amax(x, given, nv.LAYOUT_COL, rht_on_col=16, rht_seed=5)
+    assert_copy_equal(q.col_codes, q.col_scales, q.col_ts, oracle.quantize(xb, oracle.COL, use_rht=True, rht_seed=5, amax=float(own[1])), "col copy")
+
+
 def test_predecoded_operands_give_the_same_bits():
     """nvfp4_predecode: a weight decoded to FP16 once serves Fprop and Dgrad of every micro-batch (Sec. 4.3, Sec. 4.1);
     the GEMM on the decoded copy runs the same kernel on the same FP16 values, so the results are identical.  Shapes
