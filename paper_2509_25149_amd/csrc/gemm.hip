@@ -367,10 +367,10 @@ double small_tile_us(const SmallTileCost& c, const GemmArgs& g, int64_t tile_m, 
   double rounds = static_cast<double>(whole * c.resident);
   if (last) rounds += c.alone + static_cast<double>(last - 1) * (c.resident - c.alone) / (c.resident - 1);
   const double loop = rounds * (c.tile + c.step * static_cast<double>(steps));
-  // accumulate: the result is read first; beyond what the caches hold nothing hides that (5120 x 20480: 1.6 times plain bytes)
+  // Bytes of an FP32 result, whatever leaves: the choice of the kernel must not depend on the output type, since bf16 and accumulated
+  // results are defined by the FP32 ones, to the last bit of whose sums the order of summation counts.
   const double elements = static_cast<double>(g.a.outer) * static_cast<double>(g.b.outer);
-  const double bytes = elements * (g.out_bf16 ? 2 : !g.accumulate ? 4 : elements < 8e6 ? 8 : 16);
-  return c.call + std::hypot(loop, c.result * bytes * 1e-6);
+  return c.call + std::hypot(loop, c.result * elements * 4e-6);
 }
 
 // The 128 x 128 kernel, in the same terms (steps of 64 k; three workgroups fit a CU).
@@ -420,14 +420,16 @@ static GemmPlan plan_route(const GemmArgs& g) {
   // kernel that decodes a tile once per workgroup below (three workgroups per CU keep more stores in flight, steps of 64 waste
   // less).  us, split K / own tiles / 128 x 128: 5120 x 20480 x 16 (FP32) 193 / 87 / 80, x 144 197 / 112 / 107, x 400 228 / 159 / 177,
   // x 2064 677 / 623 / 768; 8176 x 1296 x 1040 45 / 40 / 49; 1040 x 1296 x 1040 11.4 / 17.5 / 24.7.  Where K ends in a partial step
-  // of 128, own tiles have to promise 8 %: nearer than that the estimates do not tell the two apart.  Where the result is read too,
-  // 20 % (two workgroups per CU hide those reads worse than three: 5120 x 20480 x 400 324 / 290), and the 128 x 128 kernel, which reads
-  // it 16 bytes here and there, 1.5 us more for a small one (1040 x 1296 x 16 9.1 against 7.8 with K split).
+  // of 128, own tiles have to promise 8 %: nearer than that the estimates do not tell the two apart.  Accumulated results move both lines
+  // (and the choice is one for all, see small_tile_us): where a large result is read too, two workgroups per CU hide that worse than three
+  // (5120 x 20480 x 400 324 / 290, 4096 x 5120 x 400 75 / 73), so from 3e7 elements on own tiles have to promise 17 % (K of some 800); and the 128 x 128 kernel
+  // reads a small one 16 bytes here and there, 1.5 us more (1040 x 1296 x 16 9.1, 7.8 with K split; FP32 7.6 / 7.7).
   const int split = pick_direct_shape(g);
+  const double elements = static_cast<double>(g.a.outer) * static_cast<double>(g.b.outer);
   const double tile128 = g.a.outer > int64_t{65535} * BM ? HUGE_VAL   // its tile rows are the launch's second dimension
-                                                         : small_tile_us(kTile128Cost, g, BM, BN, (g.K + BK - 1) / BK) + (g.accumulate ? 1.5 : 0.0);
+                                                         : small_tile_us(kTile128Cost, g, BM, BN, (g.K + BK - 1) / BK) + (elements < 8e6 ? 1.5 : 0.0);
   const double own = gemm_direct_us(g, kDirectOwnTiles);
-  const bool take_own = own < (g.accumulate ? 0.8 : g.K % 128 ? 0.92 : 1.0) * tile128;
+  const bool take_own = own < (elements > 3e7 ? 0.83 : g.K % 128 ? 0.92 : 1.0) * tile128;
   if (gemm_direct_us(g, split) <= (take_own ? own : tile128)) return {kDirect, split};
   return take_own ? GemmPlan{kDirect, kDirectOwnTiles} : GemmPlan{kTile128, 0};
 }

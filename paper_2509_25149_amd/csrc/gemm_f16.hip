@@ -516,7 +516,7 @@ struct Width {
   int64_t tiles;
 };
 // A product that is accumulated into its result takes longer over the result the more tiles there are (5120 x 20480, K = 64 / 256 / 512: nb = 8
-// 283 / 299 / 333, nb = 5 306 / 313 / 345): there a narrower tile has to promise 4 % while K is short.
+// 283 / 299 / 333, nb = 5 306 / 313 / 345): there a narrower tile has to promise 4 % while K is short (no last round is split then, so the sums are the same).
 static Width pick_width(int64_t M, int64_t N, int64_t K, const TailPlan& p, bool accumulate) {
   constexpr double kTime[4] = {1.0, 0.90, 0.80, 0.68};
   const int64_t tiles_m = (M + TM - 1) / TM;
@@ -583,7 +583,9 @@ bool gemm_two_pass_usable(const GemmArgs& g) {
 double gemm_two_pass_us(const GemmArgs& g) {
   const int64_t M = g.a.outer, N = g.b.outer;
   const double k = static_cast<double>(g.K);
-  const Width w = plan_two_pass(g).width;
+  GemmArgs plain = g;   // one choice of the route for all output types (see small_tile_us)
+  plain.accumulate = false;
+  const Width w = plan_two_pass(plain).width;
   const int64_t rows = (g.a.fp16 ? 0 : M) + (g.b.fp16 ? 0 : N);
   return 4.0 + static_cast<double>(rows) * k * 2.5625 / 4.7e6 + (rows ? 2.0 : 0.0) + w.rounds * k * (w.tiles >= kCUs ? 0.0225 : 0.0185);
 }

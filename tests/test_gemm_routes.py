@@ -2,6 +2,7 @@
 Here: each class of products takes the kernel that was measured to be the faster one for it."""
 import ctypes
 import os
+import random
 
 import pytest
 
@@ -36,7 +37,7 @@ def test_short_contractions_with_a_large_result_do_not_split_k(M, N, K, bf16, ac
     for workspace in (0, True):
         route, shape = plan(M, N, K, bf16, accumulate, workspace)[:2]
         assert route == TILE_128 or (route, shape) == (DIRECT, OWN_TILES)
-    if K <= 48:
+    if K <= 48 and M * N > 8e6:
         assert route == TILE_128
 
 
@@ -80,6 +81,21 @@ def test_results_too_large_for_one_launch_of_a_kernel_take_another():
     assert plan(2 ** 26, 128, 16)[:2] != (DIRECT, 0)
     # 32-bit rows of the direct kernel
     assert plan(16, 2 ** 31, 16)[0] == TILE_128
+
+
+def test_one_kernel_for_all_output_types():
+    """bf16 results are the FP32 ones rounded, accumulated ones the FP32 ones added: to the last bit only if the same sums are taken in the
+    same order.  (Two-pass tiles of any width take them in the same order unless the last round is split, which needs K >= 1024.)"""
+    rng = random.Random(7)
+    size = lambda lo, hi: max(16, int(lo * (hi / lo) ** rng.random()) // 16 * 16)
+    for _ in range(4000):
+        M, N, K = size(16, 20480), size(16, 20480), size(16, 20480)
+        K = K if rng.random() < 0.5 else max(64, K // 64 * 64)
+        for workspace, decoded in ((0, 0), (0, 3), (True, 0), (True, 2)):
+            f32 = plan(M, N, K, False, False, workspace, decoded)
+            assert plan(M, N, K, True, False, workspace, decoded) == f32
+            accumulated = plan(M, N, K, False, True, workspace, decoded)
+            assert accumulated == f32 or (f32[0] == accumulated[0] == TWO_PASS and f32[2:] == accumulated[2:] == (0, 1) and K < 1024)
 
 
 def test_workspace_without_room_for_partial_tiles_still_serves_the_two_pass_route():
