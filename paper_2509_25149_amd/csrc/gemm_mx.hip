@@ -586,3 +586,6 @@ hipError_t launch_gemm_mx(const GemmArgs& g, hipStream_t s) {
 }
 
 }  // namespace nvfp4
+
+// For the tests, not part of the ABI: 32-column units of the tile that an MXFP4 product of these sizes takes where K is a multiple of 512.
+extern "C" int nvfp4_internal_mx_gemm_units(int64_t M, int64_t N) { return nvfp4::pick_mx_width(M, N); }

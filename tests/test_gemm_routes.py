@@ -28,6 +28,11 @@ def plan(M, N, K, bf16=False, accumulate=False, workspace=0, decoded=0):
     return tuple(out)
 
 
+def mx_units(M, N):
+    i64 = ctypes.c_int64
+    return nv.load_library().nvfp4_internal_mx_gemm_units(i64(M), i64(N))
+
+
 @pytest.mark.parametrize("M,N", [(2048, 2048), (2048, 8192), (5120, 20480), (4096, 5120), (8176, 1296)])
 @pytest.mark.parametrize("K", [16, 48, 80, 144, 208, 272, 336, 400])
 @pytest.mark.parametrize("bf16,accumulate", [(False, False), (True, False), (False, True)], ids=["f32", "bf16", "accumulate"])
@@ -58,6 +63,11 @@ def test_few_tokens_and_small_layers_split_k(M, N, K, shape):
 def test_large_products_take_the_two_pass_route(M, N, K, units):
     assert plan(M, N, K, workspace=True)[:2] == (TWO_PASS, units)
     assert plan(M, N, K, workspace=0)[0] in (FUSED_256, DIRECT)
+
+
+@pytest.mark.parametrize("M,N,units", [(8192, 20480, 8), (4096, 5120, 5), (5120, 5120, 7), (512, 5120, 4)])
+def test_mxfp4_tile_widths(M, N, units):
+    assert mx_units(M, N) == units
 
 
 def test_accumulating_products_keep_the_widest_tile_unless_a_narrower_one_saves_rounds():

@@ -13,6 +13,7 @@ import torch
 
 import oracle
 from paper_2509_25149_amd import binding as nv, synth
+from test_gemm_routes import FUSED_256, TWO_PASS, plan
 
 pytestmark = pytest.mark.gpu
 
@@ -266,10 +267,8 @@ def test_gemm_ragged_shapes_all_ops(mnk):
 
 @pytest.mark.parametrize("K", [64, 128, 192])
 def test_gemm_with_more_tiles_than_compute_units(K):
-    """17 x 18 tiles of 256 x 256, the last row and column of them ragged: with a workspace the FP16 kernel is launched
-    with one workgroup per CU, 50 of which run two tiles as one stream of K steps (K = 128: the shortest tile that
-    allows it; K = 192: an odd number of steps, so the LDS stage parity differs from tile to tile; K = 64: one step,
-    launched with a workgroup per tile instead)."""
+    """17 x 18 tiles of 256 x 256, the last row and column of them ragged, at a short K: with a workspace 17 x 28 tiles of 160 columns
+    (K = 192: two to a CU as one stream of K steps) or 128 x 128 ones (K = 128), without one the fused kernel or 128 x 128 ones."""
     M, N = 4112, 4368
     xb = synth.normal_with_outliers(M, K, 1.0, 900 + K, frac=0.01)
     wb = synth.normal(K, N, 0.02, 901 + K)
@@ -277,6 +276,29 @@ def test_gemm_with_more_tiles_than_compute_units(K):
     qw, rw = check_quantize(wb, nv.LAYOUT_COL, nv.BLOCK_16x16)
     y = gemm_both_routes(qx, qw, nv.OP_FPROP, oracle.gemm_f64(rx["row"], rw["col"]))
     assert y.shape == (M, N)
+
+
+@pytest.mark.parametrize("K", [64, 128, 192, 320])
+def test_gemm_with_two_ragged_tiles_per_compute_unit(K):
+    """16 x 32 tiles of 256 x 256, the last row and column of them ragged: with a workspace one workgroup per CU runs two tiles as one
+    stream of K steps (K = 128: the shortest tile that allows it; K = 192, 320: an odd number of steps, so the LDS stage parity
+    differs from tile to tile; K = 64: one step, launched with a workgroup per tile instead), without one the fused kernel decodes
+    as it goes.  K = 128 takes the first of these only with both operands decoded beforehand."""
+    M, N = 4080, 8176
+    decoded = 3 if K == 128 else 0
+    assert plan(M, N, K, workspace=True, decoded=decoded) == (TWO_PASS, 8, 0, 1) and plan(M, N, K)[0] == FUSED_256
+    xb = synth.normal_with_outliers(M, K, 1.0, 930 + K, frac=0.01)
+    wb = synth.normal(K, N, 0.02, 931 + K)
+    qx, rx = check_quantize(xb, nv.LAYOUT_ROW)
+    qw, rw = check_quantize(wb, nv.LAYOUT_COL, nv.BLOCK_16x16)
+    ref = oracle.gemm_f64(rx["row"], rw["col"])
+    gemm_both_routes(qx, qw, nv.OP_FPROP, ref)
+    if decoded:
+        nv.nvfp4_predecode(qx, nv.COPY_ROW)
+        nv.nvfp4_predecode(qw, nv.COPY_COL)
+        for ws in (None, gemm_ws(M, N, K)):
+            y = nv.nvfp4_gemm(qx, qw, nv.OP_FPROP, nv.OUT_F32, workspace=ws)
+            assert rel_fro(y.cpu().numpy(), ref) <= GEMM_TOL
 
 
 def test_gemm_output_with_leading_dimension():
@@ -337,11 +359,13 @@ def test_linear_layer_calls_equal_the_call_sequence():
     assert e.value.status == -3
 
 
-def test_layer_step_replays_from_a_hip_graph():
+@pytest.mark.parametrize("tokens,d_in,d_out", [(4352, 1024, 4096), (4352, 4096, 4096)])
+def test_layer_step_replays_from_a_hip_graph(tokens, d_in, d_out):
     """A whole layer step (quantize + three GEMMs through the per-layer entry points, caller-owned buffers only) is
     captured into a HIP graph and replayed with eager work in between; every replay must reproduce the eager
-    result bit for bit.  Shapes with a split-K last round."""
-    tokens, d_in, d_out = 4352, 1024, 4096          # Fprop: 17 x 16 = 272 tiles -> the last 16 are split along K
+    result bit for bit.  d_in = 1024: narrower tiles and the direct kernel; 4096: a split-K last round."""
+    if d_in == 4096:                                 # Fprop, Dgrad: 17 x 16 = 272 tiles, the last 16 split along K
+        assert plan(tokens, d_out, d_in, bf16=True, workspace=True) == (TWO_PASS, 8, 16, 8)
     wb = synth.normal(d_in, d_out, 0.02, 951)
     xb = synth.normal_with_outliers(tokens, d_in, 1.0, 952)
     dyb = synth.student_t3(tokens, d_out, 1e-3, 953)
@@ -443,11 +467,18 @@ def test_the_two_supplied_maxima_are_independent(raw):
     assert_copy_equal(q.col_codes, q.col_scales, q.col_ts, oracle.quantize(xb, oracle.COL, use_rht=True, rht_seed=5, amax=float(own[1])), "col copy")
 
 
-def test_predecoded_operands_give_the_same_bits():
+@pytest.mark.parametrize("tokens,d_in,d_out", [(4352, 1024, 4096), (4352, 4096, 4096)])
+def test_predecoded_operands_give_the_same_bits(tokens, d_in, d_out):
     """nvfp4_predecode: a weight decoded to FP16 once serves Fprop and Dgrad of every micro-batch (Sec. 4.3, Sec. 4.1);
-    the GEMM on the decoded copy runs the same kernel on the same FP16 values, so the results are identical.  Shapes
-    with a split-K last round; a workspace sized only for the operands still to decode must be enough."""
-    tokens, d_in, d_out = 4352, 1024, 4096
+    the GEMM on the decoded copy runs the same kernel on the same FP16 values, so the results are identical.  d_in = 4096: all
+    three products on the two-pass route, Fprop and Dgrad with a split-K last round (d_in = 1024: Fprop alone, in narrower tiles; the
+    others read the codes); a workspace sized only for the operands still to decode must be enough."""
+    if d_in == 4096:
+        for decoded in (0, 2):
+            assert plan(tokens, d_out, d_in, workspace=True, decoded=decoded) == (TWO_PASS, 8, 16, 8)
+            assert plan(tokens, d_in, d_out, workspace=True, decoded=decoded) == (TWO_PASS, 8, 16, 8)
+        for decoded in (0, 3):
+            assert plan(d_in, d_out, tokens, workspace=True, decoded=decoded) == (TWO_PASS, 8, 0, 1)
     wb = synth.normal(d_in, d_out, 0.02, 2101)
     qw = nv.nvfp4_quantize(to_dev(wb), nv.LAYOUT_ROW | nv.LAYOUT_COL, nv.BLOCK_16x16)
     qx = nv.nvfp4_quantize(to_dev(synth.normal_with_outliers(tokens, d_in, 1.0, 2102)), nv.LAYOUT_ROW | nv.LAYOUT_COL,
@@ -482,8 +513,12 @@ def test_predecoded_operands_give_the_same_bits():
     nv.nvfp4_predecode(qdy, nv.COPY_COL)
     tiny = torch.empty(nv.gemm_workspace_bytes(d_in, d_out, tokens) - (d_in + d_out) * tokens * 2, dtype=torch.uint8, device="cuda")
     assert torch.equal(nv.nvfp4_gemm(qx, qdy, nv.OP_WGRAD, nv.OUT_F32, workspace=tiny), dw0)
-    # the fused route ignores decoded copies
-    assert torch.equal(nv.nvfp4_gemm(qx, qw, nv.OP_FPROP, nv.OUT_F32), nv.nvfp4_gemm(qx, qw, nv.OP_FPROP, nv.OUT_F32))
+    # both decoded and no workspace at all: the two-pass route without a split
+    nv.nvfp4_predecode(qx, nv.COPY_ROW)
+    y3 = nv.nvfp4_gemm(qx, qw, nv.OP_FPROP, nv.OUT_F32)
+    assert plan(tokens, d_out, d_in, decoded=3)[0] == TWO_PASS and plan(tokens, d_out, d_in, decoded=3)[2:] == (0, 1)
+    assert float((y3 - y0).double().norm() / y0.double().norm()) <= 2e-6
+    qx.desc.row_fp16 = None
     # requantizing into the descriptor drops the decoded copies (they would be stale)
     nv.nvfp4_quantize(to_dev(wb), nv.LAYOUT_ROW | nv.LAYOUT_COL, nv.BLOCK_16x16, out=qw)
     assert qw.desc.row_fp16 is None and qw.desc.col_fp16 is None and qw.row_fp16 is None

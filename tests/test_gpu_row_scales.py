@@ -9,6 +9,7 @@ import torch
 
 import oracle
 from paper_2509_25149_amd import binding as nv, synth
+from test_gemm_routes import DIRECT, FUSED_256, TWO_PASS, plan
 
 pytestmark = pytest.mark.gpu
 
@@ -138,18 +139,30 @@ def test_gemm_with_row_scales_all_ops(mnk):
     gemm_all_routes(qd, qw1, nv.OP_DGRAD, oracle.gemm_f64(rd["row"], rw1["row"]))
 
 
-@pytest.mark.parametrize("mnk", [(4112, 4368, 128), (4352, 4096, 1024)])
-def test_gemm_with_row_scales_and_more_tiles_than_compute_units(mnk):
-    """The per-row output stage in the two launch forms the small shapes above do not reach: 306 tiles (ragged last
-    row and column) run as streams of tiles by one workgroup per CU; 272 tiles = one whole round + 16 tiles split
-    two ways along K, whose partial tiles the sum launch scales per row."""
-    M, N, K = mnk
-    x = synth.bf16_bits_to_f32(synth.normal_with_outliers(M, K, 1.0, 1700 + M, frac=0.01))
-    x *= np.exp2(-(np.arange(M) % 12))[:, None].astype(np.float32)             # rows of different magnitude
-    qx, rx = check(synth.f32_to_bf16_bits(x), nv.LAYOUT_ROW, nv.ROUND_RNE, False)
-    wb = synth.normal(K, N, 0.02, 1800 + N)
-    qw = nv.nvfp4_quantize(to_dev(wb), nv.LAYOUT_COL, nv.BLOCK_16x16)
-    gemm_all_routes(qx, qw, nv.OP_FPROP, oracle.gemm_f64(rx["row"], oracle.quantize(wb, oracle.COL, oracle.BLOCK_16x16)))
+@pytest.mark.parametrize("scales_on", ["A", "B", "both"])
+@pytest.mark.parametrize("M,N,K,with_ws,without", [
+    (4112, 4368, 128, (DIRECT, 4, 0, 1), (DIRECT, 4, 0, 1)),
+    (4352, 4096, 1024, (TWO_PASS, 5, 0, 1), (DIRECT, 3, 0, 1)),
+    (4080, 8176, 192, (TWO_PASS, 8, 0, 1), (FUSED_256, 0, 0, 1)),
+    (8176, 5104, 1088, (TWO_PASS, 8, 128, 2), None),
+    (4336, 4080, 4096, (TWO_PASS, 8, 16, 8), None)])
+def test_gemm_with_row_scales_and_more_tiles_than_compute_units(M, N, K, with_ws, without, scales_on):
+    """The per-row output stage in the launch forms that the small shapes above do not reach, ragged at both edges: the direct kernel
+    with a tile per wavefront; 160-column tiles run as streams by one workgroup per CU; 256-column tiles likewise, and the fused kernel
+    without a workspace; a last round split along K two and eight ways, whose partial tiles the sum launch scales per row."""
+    assert plan(M, N, K, workspace=True) == with_ws
+    assert without is None or plan(M, N, K) == without
+    def operand(rows, seed, per_row):
+        x = synth.bf16_bits_to_f32(synth.normal_with_outliers(rows, K, 1.0, seed, frac=0.01))
+        x *= np.exp2(-(np.arange(rows) % 12))[:, None].astype(np.float32)          # rows of different magnitude
+        xb = synth.f32_to_bf16_bits(x)
+        if per_row:
+            q, r = check(xb, nv.LAYOUT_ROW, nv.ROUND_RNE, False)
+            return q, r["row"]
+        return nv.nvfp4_quantize(to_dev(xb), nv.LAYOUT_ROW), oracle.quantize(xb, oracle.ROW)
+    qa, ra = operand(M, 1700 + M, scales_on != "B")
+    qb, rb = operand(N, 1800 + N, scales_on != "A")
+    gemm_all_routes(qa, qb, nv.OP_DGRAD, oracle.gemm_f64(ra, rb))
 
 
 def test_bad_combinations_are_refused():
