@@ -27,32 +27,6 @@ constexpr int BM = 128, BN = 128, BK = 64;
 constexpr int LDS_LD = BK + 8;  // halfs per LDS row; the 16-byte pad keeps 128-bit reads conflict free
 constexpr int kGemmThreads = 256;
 
-template <int kByte>
-__device__ __forceinline__ half2v decode_pair(uint32_t codes, half2v scale) {
-  return __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(codes, 1.0f, kByte) * scale;
-}
-
-// 8 codes (one dword) -> 8 FP16 values, each value * block scale.
-__device__ __forceinline__ uint4 decode8(uint32_t codes, half2v scale) {
-  union {
-    half2v h[4];
-    uint4 u;
-  } o;
-  o.h[0] = decode_pair<0>(codes, scale);
-  o.h[1] = decode_pair<1>(codes, scale);
-  o.h[2] = decode_pair<2>(codes, scale);
-  o.h[3] = decode_pair<3>(codes, scale);
-  return o.u;
-}
-
-__device__ __forceinline__ half2v scale_to_half2(uint32_t e4m3_byte) {
-  const _Float16 s = static_cast<_Float16>(e4m3_decode(e4m3_byte));  // exact: 4 significant bits
-  half2v r;
-  r.x = s;
-  r.y = s;
-  return r;
-}
-
 // ---------------------------------------------------------------- 128 x 128 kernel
 // 128 x 128 outputs per workgroup of 4 wavefronts, K step 64, one buffer, any K and alignment: for large results of a
 // short contraction, where storing the result is the work (see plan_route).  Three workgroups fit a CU.  5120 x 20480 x 16: FP32 80 us
@@ -75,12 +49,12 @@ __device__ __forceinline__ void stage_row(const Operand& op, int64_t K, int64_t 
       s1 = sp[1];
     }
   }
-  const half2v h0 = scale_to_half2(s0), h1 = scale_to_half2(s1);
-  uint4* dst = reinterpret_cast<uint4*>(lds_row);
-  dst[0] = decode8(c01.x, h0);
-  dst[1] = decode8(c01.y, h0);
-  dst[2] = decode8(c23.x, h1);
-  dst[3] = decode8(c23.y, h1);
+  const half2v h0 = e4m3_decode_f16x2(s0), h1 = e4m3_decode_f16x2(s1);
+  half8v* dst = reinterpret_cast<half8v*>(lds_row);
+  dst[0] = decode8_f16(c01.x, h0);
+  dst[1] = decode8_f16(c01.y, h0);
+  dst[2] = decode8_f16(c23.x, h1);
+  dst[3] = decode8_f16(c23.y, h1);
 }
 
 template <bool kBf16Out>
@@ -208,16 +182,16 @@ __device__ __forceinline__ void fetch_row(Prefetch& p, const Operand& op, int64_
 }
 
 __device__ __forceinline__ void stage_decoded(const Prefetch& p, char* tile, int row) {
-  const half2v h0 = scale_to_half2(p.scales & 0xFFu), h1 = scale_to_half2((p.scales >> 8) & 0xFFu);
-  const half2v h2 = scale_to_half2((p.scales >> 16) & 0xFFu), h3 = scale_to_half2(p.scales >> 24);
-  *reinterpret_cast<uint4*>(tile + swz(row, 0)) = decode8(p.lo.x, h0);
-  *reinterpret_cast<uint4*>(tile + swz(row, 1)) = decode8(p.lo.y, h0);
-  *reinterpret_cast<uint4*>(tile + swz(row, 2)) = decode8(p.lo.z, h1);
-  *reinterpret_cast<uint4*>(tile + swz(row, 3)) = decode8(p.lo.w, h1);
-  *reinterpret_cast<uint4*>(tile + swz(row, 4)) = decode8(p.hi.x, h2);
-  *reinterpret_cast<uint4*>(tile + swz(row, 5)) = decode8(p.hi.y, h2);
-  *reinterpret_cast<uint4*>(tile + swz(row, 6)) = decode8(p.hi.z, h3);
-  *reinterpret_cast<uint4*>(tile + swz(row, 7)) = decode8(p.hi.w, h3);
+  const half2v h0 = e4m3_decode_f16x2(p.scales & 0xFFu), h1 = e4m3_decode_f16x2((p.scales >> 8) & 0xFFu);
+  const half2v h2 = e4m3_decode_f16x2((p.scales >> 16) & 0xFFu), h3 = e4m3_decode_f16x2(p.scales >> 24);
+  *reinterpret_cast<half8v*>(tile + swz(row, 0)) = decode8_f16(p.lo.x, h0);
+  *reinterpret_cast<half8v*>(tile + swz(row, 1)) = decode8_f16(p.lo.y, h0);
+  *reinterpret_cast<half8v*>(tile + swz(row, 2)) = decode8_f16(p.lo.z, h1);
+  *reinterpret_cast<half8v*>(tile + swz(row, 3)) = decode8_f16(p.lo.w, h1);
+  *reinterpret_cast<half8v*>(tile + swz(row, 4)) = decode8_f16(p.hi.x, h2);
+  *reinterpret_cast<half8v*>(tile + swz(row, 5)) = decode8_f16(p.hi.y, h2);
+  *reinterpret_cast<half8v*>(tile + swz(row, 6)) = decode8_f16(p.hi.z, h3);
+  *reinterpret_cast<half8v*>(tile + swz(row, 7)) = decode8_f16(p.hi.w, h3);
 }
 
 // Fragments of one 32-wide half of a K step for a 128 x 64 wave tile.  A 16x16x32 MFMA operand is

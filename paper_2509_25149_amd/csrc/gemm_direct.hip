@@ -3,18 +3,19 @@
 // contraction lengths that are not a multiple of 64.
 //
 // A wavefront owns MB x NB blocks of 16 x 16 outputs and every WK-th step of 128 k; the WK wavefronts of a workgroup own
-// the same outputs and add their sums through LDS at the end.  No barrier in the loop: a wavefront loads the codes and
+// the same outputs and add their sums through LDS at the end (WK = 1: they own different ones).  No barrier in the loop: a wavefront loads the codes and
 // scales of its own rows into registers one step ahead, passes them through its own piece of LDS, decodes them to FP16
 // (value * block scale, exact) and feeds the 16x16x32 MFMA.
 //   - Through LDS, because a load in the MFMA's lane order (16 consecutive lanes = 16 rows) touches 16 cache lines per 16
 //     lanes; four lanes to a row's 64 bytes touch 4.  64 x 20480 x 5120: 35 us without this detour, 27 with.
-//   - Steps of 128 k rather than 256: half the LDS and the staging registers per wavefront, so that 640 workgroups are
-//     resident at once (27 -> 22 us), and less to lose where K is not a multiple of the step.
-//   - What bounds it is the issue of vector instructions: a 16 x 32 fragment takes 32 of them (cvt + pk_mul per two
-//     values) and serves 4 (MB or NB) MFMAs, so a decoded fragment's k + 1 is spread over the MFMAs of k.  Decoding A once per
+//   - Steps of 128 k rather than 256: half the LDS and the staging registers per wavefront, so that two workgroups of four
+//     wavefronts fit a CU and the 427 of this shape are resident at once (27 -> 22 us), and less to lose where K is not a
+//     multiple of the step.
+//   - What bounds it is the issue of vector instructions: a 16 x 32 fragment takes 8 of them (4 cvt, 4 pk_mul) and serves MB or
+//     NB (3 or 4) MFMAs, so the decode of the next fragments is spread over the MFMAs of these.  Decoding A once per
 //     workgroup and sharing it through LDS needs a barrier per step and was slower (33 against 22 us, 52 against 38).
-// Measured (us; before = whatever the call took then): 64 x 20480 x 5120 133 -> 22, 16 x 20480 x 5120 131 -> 14.6 (4.0 TB/s of
-// codes), 512 x 5120 x 5120 101 -> 38, 256 x 256 x 512 18 -> 3.4, 1040 x 1296 x 2064 44 -> 15.
+// Measured (us; before = whatever the call took then): 64 x 20480 x 5120 133 -> 23, 16 x 20480 x 5120 131 -> 14.6 (4.0 TB/s of
+// codes), 512 x 5120 x 5120 101 -> 38, 256 x 256 x 512 18 -> 3.4, 1040 x 1296 x 2064 44 -> 14.4.
 
 #include <cmath>
 
@@ -26,7 +27,6 @@ namespace nvfp4 {
 namespace {
 
 constexpr int kStepK = 128;               // k per step: 64 bytes of codes and 8 of scales per row, 1 KiB of codes per 16-row block
-constexpr int kPiece = 1024;              // one 16 x 32 FP16 MFMA fragment
 constexpr int kCodeBytes = 1024, kScaleBytes = 128;   // of a 16-row block and step
 
 struct __attribute__((packed, aligned(8))) Codes16 { uint32_t w[4]; };
@@ -40,17 +40,10 @@ struct Loaded {
 
 __device__ __forceinline__ uint32_t word(const uint4& c, int t) { return t == 0 ? c.x : t == 1 ? c.y : t == 2 ? c.z : c.w; }
 
-// 8 codes of k 8 t .. 8 t + 7 of a 32-code chunk, times the block scale: exact in FP16
-__device__ __forceinline__ half8v decode8(const uint4& c, half2v s2, int t) {
-  const _Float16 sv = (t >> 1) ? s2.y : s2.x;
-  const half2v s = {sv, sv};
-  const uint32_t w = word(c, t);
-  union { half2v h[4]; half8v v; } o;
-  o.h[0] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 0) * s;
-  o.h[1] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 1) * s;
-  o.h[2] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 2) * s;
-  o.h[3] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 3) * s;
-  return o.v;
+// 8 codes of k 8 t .. 8 t + 7 of a 32-code chunk, times the scale of their block
+__device__ __forceinline__ half8v decode_part(const uint4& c, half2v scales, int t) {
+  const _Float16 s = (t >> 1) ? scales.y : scales.x;
+  return decode8_f16(word(c, t), half2v{s, s});
 }
 // Between lanes that exchange data through their wavefront's own piece of LDS: the hardware executes a wavefront's LDS
 // instructions in order, so nothing has to be waited for, but the compiler must not move a read above the other lanes' writes
@@ -152,12 +145,12 @@ __global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, 2) void gemm_direct_kernel
   auto multiply = [&]() {
     half8v f[2][S::kBlocks];
 #pragma unroll
-    for (int i = 0; i < S::kBlocks; ++i) f[0][i] = decode8(c[i], sc[i], 0);
+    for (int i = 0; i < S::kBlocks; ++i) f[0][i] = decode_part(c[i], sc[i], 0);
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       if (t < 3) {
 #pragma unroll
-        for (int i = 0; i < S::kBlocks; ++i) f[(t + 1) & 1][i] = decode8(c[i], sc[i], t + 1);
+        for (int i = 0; i < S::kBlocks; ++i) f[(t + 1) & 1][i] = decode_part(c[i], sc[i], t + 1);
       }
 #pragma unroll
       for (int i = 0; i < MB; ++i)

@@ -28,31 +28,6 @@ namespace nvfp4 {
 namespace {
 
 // ---------------------------------------------------------------- pass 1: decode
-template <int kByte>
-__device__ __forceinline__ half2v dec_pair(uint32_t codes, half2v scale) {
-  return __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(codes, 1.0f, kByte) * scale;
-}
-
-__device__ __forceinline__ uint4 dec8(uint32_t codes, half2v scale) {
-  union {
-    half2v h[4];
-    uint4 u;
-  } o;
-  o.h[0] = dec_pair<0>(codes, scale);
-  o.h[1] = dec_pair<1>(codes, scale);
-  o.h[2] = dec_pair<2>(codes, scale);
-  o.h[3] = dec_pair<3>(codes, scale);
-  return o.u;
-}
-
-__device__ __forceinline__ half2v scale_h2(uint32_t e4m3_byte) {
-  const _Float16 s = static_cast<_Float16>(e4m3_decode(e4m3_byte));
-  half2v r;
-  r.x = s;
-  r.y = s;
-  return r;
-}
-
 // Layout of a decoded operand ([outer, K] elements, outer a multiple of 16, K of 64): the piece the GEMM loads with
 // one instruction and reads back as one MFMA fragment -- 16 rows x 32 k = 1 KiB -- is contiguous, the K steps of a
 // 16-row block follow each other, and inside a piece the 16-byte chunks (8 k of one row) are in fragment order, the
@@ -88,7 +63,7 @@ __global__ __launch_bounds__(256) void decode_f16_kernel(const uint8_t* __restri
   if (!in_a && blk >= b_blocks) return;
   const uint8_t* codes = in_a ? a_codes : b_codes;
   const uint8_t* scales = in_a ? a_scales : b_scales;
-  uint4* out = reinterpret_cast<uint4*>(in_a ? a_out : b_out);
+  half8v* out = reinterpret_cast<half8v*>(in_a ? a_out : b_out);
   const int t = static_cast<int>(threadIdx.x);
   const int64_t k0 = static_cast<int64_t>(k_group) * kDecodeK;
   {
@@ -117,7 +92,7 @@ __global__ __launch_bounds__(256) void decode_f16_kernel(const uint8_t* __restri
     const uint32_t c = *reinterpret_cast<const uint32_t*>(lds_codes + r16 * kDecodeCodeRow + piece * 16 + chunk * 4);
     const uint32_t s4 = *reinterpret_cast<const uint32_t*>(lds_scales + r16 * kDecodeScaleRow + (piece >> 1) * 4);
     const uint32_t scale = (s4 >> ((((piece & 1) * 2) + (chunk >> 1)) * 8)) & 0xffu;
-    out[(static_cast<int64_t>(blk) * pieces_per_block + k0 / 32 + piece) * 64 + chunk * 16 + r16] = dec8(c, scale_h2(scale));
+    out[(static_cast<int64_t>(blk) * pieces_per_block + k0 / 32 + piece) * 64 + chunk * 16 + r16] = decode8_f16(c, e4m3_decode_f16x2(scale));
   }
 }
 

@@ -17,6 +17,19 @@ typedef _Float16 half8v __attribute__((ext_vector_type(8)));
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
+// 8 codes (a dword) -> 8 FP16 values, each value * block scale: exact.  scale: the block scale in both halves.
+__device__ __forceinline__ half8v decode8_f16(uint32_t codes, half2v scale) {
+  union {
+    half2v h[4];
+    half8v v;
+  } o;
+  o.h[0] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(codes, 1.0f, 0) * scale;
+  o.h[1] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(codes, 1.0f, 1) * scale;
+  o.h[2] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(codes, 1.0f, 2) * scale;
+  o.h[3] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(codes, 1.0f, 3) * scale;
+  return o.v;
+}
+
 // FP32 -> bf16, round to nearest even (finite inputs; NaN stays NaN).
 __device__ __forceinline__ uint32_t f32_to_bf16(float f) {
   uint32_t w = __float_as_uint(f);
@@ -58,6 +71,12 @@ __device__ __forceinline__ uint32_t e4m3_encode(float u) {
 
 __device__ __forceinline__ float e4m3_decode(uint32_t code) {
   return __builtin_amdgcn_cvt_f32_fp8(static_cast<int>(code), 0);
+}
+
+// A stored block scale in both halves, as decode8_f16 takes it: exact, 4 significant bits.
+__device__ __forceinline__ half2v e4m3_decode_f16x2(uint32_t code) {
+  const _Float16 s = static_cast<_Float16>(e4m3_decode(code));
+  return half2v{s, s};
 }
 
 // x / 6 with IEEE round-to-nearest, for x >= 0, without a branch: a binary64 product with the rounded reciprocal, rounded
