@@ -335,18 +335,6 @@ static double fused_us(int64_t M, int64_t N, int64_t K) {
   return 4.0 + static_cast<double>((tiles + 255) / 256) * static_cast<double>(K) * (tiles > 1024 ? 0.031 : 0.0265);
 }
 
-double small_tile_us(const SmallTileCost& c, const GemmArgs& g, int64_t tile_m, int64_t tile_n, int64_t steps) {
-  const int64_t tiles = ((g.a.outer + tile_m - 1) / tile_m) * ((g.b.outer + tile_n - 1) / tile_n);
-  const int64_t wave = int64_t{256} * c.resident, whole = tiles / wave, last = (tiles - whole * wave + 255) / 256;   // tiles of a CU in the last wave
-  double rounds = static_cast<double>(whole * c.resident);
-  if (last) rounds += c.alone + static_cast<double>(last - 1) * (c.resident - c.alone) / (c.resident - 1);
-  const double loop = rounds * (c.tile + c.step * static_cast<double>(steps));
-  // Bytes of an FP32 result, whatever leaves: the choice of the kernel must not depend on the output type, since bf16 and accumulated
-  // results are defined by the FP32 ones, to the last bit of whose sums the order of summation counts.
-  const double elements = static_cast<double>(g.a.outer) * static_cast<double>(g.b.outer);
-  return c.call + std::hypot(loop, c.result * elements * 4e-6);
-}
-
 // The 128 x 128 kernel, in the same terms (steps of 64 k; three workgroups fit a CU).
 static constexpr SmallTileCost kTile128Cost{3, 3.47, 1.45, 1.14, 0.788, 0.151};
 
@@ -377,41 +365,47 @@ static hipError_t launch_fused256(const GemmArgs& g, hipStream_t s) {
 enum GemmRoute { kTwoPass, kFused256, kTile128, kDirect };
 struct GemmPlan {
   GemmRoute route;
-  int shape;   // kDirect: the tile shape
+  int shape;             // kDirect: the tile shape
+  TwoPassPlan two_pass;  // kTwoPass
 };
 
 static GemmPlan plan_route(const GemmArgs& g) {
-  const double direct = gemm_direct_compute_us(g);
+  const DirectPick direct = pick_direct_shape(g);
   // With a workspace: decode pass + FP16 GEMM, unless the product is too small to fill its 256-row tiles.
-  if (gemm_two_pass_usable(g) && gemm_two_pass_us(g) <= direct) return {kTwoPass, 0};
+  const TwoPassPlan two_pass = plan_two_pass(g);
+  if (two_pass.usable && two_pass.us <= direct.compute_us) return {kTwoPass, 0, two_pass};
   // Without (or where that is slower): the fused kernel for large products -- it needs whole K steps of 64 and 16-byte aligned
   // code rows.
   const bool big = (g.K % TK == 0) && (reinterpret_cast<uintptr_t>(g.a.codes) % 16 == 0) &&
                    (reinterpret_cast<uintptr_t>(g.b.codes) % 16 == 0);
-  if (big && fused_us(g.a.outer, g.b.outer, g.K) <= direct) return {kFused256, 0};
+  if (big && fused_us(g.a.outer, g.b.outer, g.K) <= direct.compute_us) return {kFused256, 0, {}};
   // All others: the direct kernel with K split among the wavefronts of a workgroup, where the tiles are few for the length of K;
   // else 128 x 128 tiles.  These the direct kernel with a tile per wavefront does faster from K of some 250 on (no barrier), the
   // kernel that decodes a tile once per workgroup below (three workgroups per CU keep more stores in flight, steps of 64 waste
   // less).  us, split K / own tiles / 128 x 128: 5120 x 20480 x 16 (FP32) 193 / 87 / 80, x 144 197 / 112 / 107, x 400 228 / 159 / 177,
   // x 2064 677 / 623 / 768; 8176 x 1296 x 1040 45 / 40 / 49; 1040 x 1296 x 1040 11.4 / 17.5 / 24.7.  Where K ends in a partial step
-  // of 128, own tiles have to promise 8 %: nearer than that the estimates do not tell the two apart.  Accumulated results move both lines
-  // (and the choice is one for all, see small_tile_us): where a large result is read too, two workgroups per CU hide that worse than three
-  // (5120 x 20480 x 400 324 / 290, 4096 x 5120 x 400 75 / 73), so from 3e7 elements on own tiles have to promise 17 % (K of some 800); and the 128 x 128 kernel
-  // reads a small one 16 bytes here and there, 1.5 us more (1040 x 1296 x 16 9.1, 7.8 with K split; FP32 7.6 / 7.7).
-  const int split = pick_direct_shape(g);
+  // of 128, own tiles have to promise 8 %: nearer than that the estimates do not tell the two apart.  Accumulated results move that line
+  // (and the choice is one for all, see SmallTileCost): where a large result is read too, two workgroups per CU hide that worse than three
+  // (5120 x 20480 x 400 324 / 290, 4096 x 5120 x 400 75 / 73), so from 3e7 elements on own tiles have to promise 17 % (K of some 800).
+  // Split K wherever its workgroups are on the chip all at once, two to a CU: the others then gain nothing worth a decision (5 % at 8 us), and
+  // lose where the result is read too (768 x 2128 x 64 8.0 split, 10.9 in own tiles).
+  if (direct.tiles <= 512 && direct.compute_us != HUGE_VAL) return {kDirect, direct.shape, {}};
   const double elements = static_cast<double>(g.a.outer) * static_cast<double>(g.b.outer);
+  const int64_t tiles128 = ((g.a.outer + BM - 1) / BM) * ((g.b.outer + BN - 1) / BN);
   const double tile128 = g.a.outer > int64_t{65535} * BM ? HUGE_VAL   // its tile rows are the launch's second dimension
-                                                         : small_tile_us(kTile128Cost, g, BM, BN, (g.K + BK - 1) / BK) + (elements < 8e6 ? 1.5 : 0.0);
+                                                         : small_tile_us(kTile128Cost, tiles128, elements, (g.K + BK - 1) / BK);
   const double own = gemm_direct_us(g, kDirectOwnTiles);
   const bool take_own = own < (elements > 3e7 ? 0.83 : g.K % 128 ? 0.92 : 1.0) * tile128;
-  if (gemm_direct_us(g, split) <= (take_own ? own : tile128)) return {kDirect, split};
-  return take_own ? GemmPlan{kDirect, kDirectOwnTiles} : GemmPlan{kTile128, 0};
+  // (Over a long K own tiles have to promise 8 % against split K too: 512 workgroups at as many places of the operands find less in the
+  // caches than the estimate thinks.  Split / own: 3792 x 18032 x 6576 1237 / 1331 us, 8176 x 5104 x 5136 590 / 580, 8176 x 20464 x 2064 1111 / 1025.)
+  if (gemm_direct_us(g, direct.shape) <= (g.K > 2048 ? 1.08 : 1.0) * (take_own ? own : tile128)) return {kDirect, direct.shape, {}};
+  return take_own ? GemmPlan{kDirect, kDirectOwnTiles, {}} : GemmPlan{kTile128, 0, {}};
 }
 
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
   const GemmPlan p = plan_route(g);
   switch (p.route) {
-    case kTwoPass: return launch_gemm_two_pass(g, s);
+    case kTwoPass: return launch_gemm_two_pass(g, p.two_pass, s);
     case kFused256: return launch_fused256(g, s);
     case kTile128: return launch_tile128(g, s);
     default: return launch_gemm_direct(g, p.shape, s);
@@ -440,9 +434,8 @@ extern "C" void nvfp4_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int bf
   out[2] = 0;
   out[3] = 1;
   if (p.route == kTwoPass) {
-    const TwoPassShape t = gemm_two_pass_shape(g);
-    out[1] = t.units;
-    out[2] = t.tail;
-    out[3] = t.splits;
+    out[1] = p.two_pass.units;
+    out[2] = p.two_pass.tail;
+    out[3] = p.two_pass.splits;
   }
 }

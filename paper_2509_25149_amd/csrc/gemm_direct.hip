@@ -248,37 +248,55 @@ constexpr DirectShape kDirectShapes[5] = {{1, 2, 8, 0.30, {3, 4.02, 1.23, 0.0, 0
                                           {4, 4, 4, 1.19, {2, 4.09, 1.03, 0.653, 1.17, 0.186}},
                                           {4, 4, 1, 0.0, {2, 3.72, 1.13, 1.56, 1.14, 0.141}}};
 
-static int tile_m(const DirectShape& d) { return d.mb * (d.wk == 1 ? 32 : 16); }
-static int tile_n(const DirectShape& d) { return d.nb * (d.wk == 1 ? 32 : 16); }
-static int64_t direct_tiles(const DirectShape& d, int64_t M, int64_t N) {
-  return ((M + tile_m(d) - 1) / tile_m(d)) * ((N + tile_n(d) - 1) / tile_n(d));
+// (Shapes as template arguments: every division is by a constant.)
+template <int I>
+static int64_t direct_tiles(int64_t M, int64_t N) {
+  constexpr DirectShape d = kDirectShapes[I];
+  constexpr int tm = d.mb * (d.wk == 1 ? 32 : 16), tn = d.nb * (d.wk == 1 ? 32 : 16);
+  return ((M + tm - 1) / tm) * ((N + tn - 1) / tn);
 }
 
 // What the kernel's 32-bit rows, byte offsets within a 16-row block and launch size allow; others take other kernels.
-static bool fits(const DirectShape& d, int64_t M, int64_t N, int64_t K) {
-  return M <= 0x7fffffff && N <= 0x7fffffff && K <= (int64_t{1} << 27) && direct_tiles(d, M, N) * (d.wk == 1 ? 256 : d.wk * 64) <= 0xffffffff;
+template <int I>
+static bool fits(int64_t M, int64_t N, int64_t K) {
+  constexpr int wk = kDirectShapes[I].wk;
+  return M <= 0x7fffffff && N <= 0x7fffffff && K <= (int64_t{1} << 27) && direct_tiles<I>(M, N) * (wk == 1 ? 256 : wk * 64) <= 0xffffffff;
 }
 
-static double direct_shape_us(const DirectShape& d, int64_t M, int64_t N, int64_t K) {
-  if (!fits(d, M, N, K)) return HUGE_VAL;
-  const int64_t rounds = (direct_tiles(d, M, N) + 255) / 256, steps = (K + kStepK - 1) / kStepK;
-  return 3.0 + 0.247 * d.cost * static_cast<double>(steps) * static_cast<double>(rounds);
+template <int I>
+static void consider(int64_t M, int64_t N, int64_t K, DirectPick& best) {
+  if (!fits<I>(M, N, K)) return;
+  const int64_t tiles = direct_tiles<I>(M, N), rounds = (tiles + 255) / 256, steps = (K + kStepK - 1) / kStepK;
+  const double us = 3.0 + 0.247 * kDirectShapes[I].cost * static_cast<double>(steps) * static_cast<double>(rounds);
+  if (us < best.compute_us) best = DirectPick{I, tiles, us};
 }
 
-int pick_direct_shape(const GemmArgs& g) {
-  int best = 0;
-  for (int i = 1; i < kDirectOwnTiles; ++i)
-    if (direct_shape_us(kDirectShapes[i], g.a.outer, g.b.outer, g.K) < direct_shape_us(kDirectShapes[best], g.a.outer, g.b.outer, g.K)) best = i;
+DirectPick pick_direct_shape(const GemmArgs& g) {
+  DirectPick best{0, 0, HUGE_VAL};
+  consider<0>(g.a.outer, g.b.outer, g.K, best);
+  consider<1>(g.a.outer, g.b.outer, g.K, best);
+  consider<2>(g.a.outer, g.b.outer, g.K, best);
+  consider<3>(g.a.outer, g.b.outer, g.K, best);
   return best;
 }
 
-double gemm_direct_compute_us(const GemmArgs& g) { return direct_shape_us(kDirectShapes[pick_direct_shape(g)], g.a.outer, g.b.outer, g.K); }
+template <int I>
+static double shape_us(const GemmArgs& g) {
+  if (!fits<I>(g.a.outer, g.b.outer, g.K)) return HUGE_VAL;
+  constexpr DirectShape d = kDirectShapes[I];
+  const int64_t steps = (g.K + kStepK - 1) / kStepK;
+  return small_tile_us(d.us, direct_tiles<I>(g.a.outer, g.b.outer), static_cast<double>(g.a.outer) * static_cast<double>(g.b.outer),
+                       (steps + d.wk - 1) / d.wk);
+}
 
 double gemm_direct_us(const GemmArgs& g, int shape) {
-  const DirectShape& d = kDirectShapes[shape];
-  if (!fits(d, g.a.outer, g.b.outer, g.K)) return HUGE_VAL;
-  const int64_t steps = (g.K + kStepK - 1) / kStepK;
-  return small_tile_us(d.us, g, tile_m(d), tile_n(d), (steps + d.wk - 1) / d.wk);
+  switch (shape) {
+    case 0: return shape_us<0>(g);
+    case 1: return shape_us<1>(g);
+    case 2: return shape_us<2>(g);
+    case 3: return shape_us<3>(g);
+    default: return shape_us<kDirectOwnTiles>(g);
+  }
 }
 
 template <int MB, int NB, int WK, bool kBf16Out>
@@ -298,7 +316,7 @@ static hipError_t launch_direct(const GemmArgs& g, int shape, hipStream_t s) {
   switch (shape) {
     // 16 x 32 tiles: enough of them to fill the chip four times over do better with fewer wavefronts on each (16 x 20480 x
     // 5120: 14.6 against 15.7 us), few with more (32 x 5120 x 5120 in these tiles: 9.4 against 8.8)
-    case 0: return direct_tiles(kDirectShapes[0], g.a.outer, g.b.outer) >= 512 ? launch_shape<1, 2, 4, kBf16Out>(g, s) : launch_shape<1, 2, 8, kBf16Out>(g, s);
+    case 0: return direct_tiles<0>(g.a.outer, g.b.outer) >= 512 ? launch_shape<1, 2, 4, kBf16Out>(g, s) : launch_shape<1, 2, 8, kBf16Out>(g, s);
     case 1: return launch_shape<2, 2, 8, kBf16Out>(g, s);
     case 2: return launch_shape<4, 3, 4, kBf16Out>(g, s);
     case 3: return launch_shape<4, 4, 4, kBf16Out>(g, s);
@@ -307,7 +325,7 @@ static hipError_t launch_direct(const GemmArgs& g, int shape, hipStream_t s) {
 }
 
 hipError_t launch_gemm_direct(const GemmArgs& g, int shape, hipStream_t s) {
-  if (!fits(kDirectShapes[shape], g.a.outer, g.b.outer, g.K)) return hipErrorInvalidValue;
+  if (gemm_direct_us(g, shape) == HUGE_VAL) return hipErrorInvalidValue;   // beyond its offsets or a launch
   return g.out_bf16 ? launch_direct<true>(g, shape, s) : launch_direct<false>(g, shape, s);
 }
 

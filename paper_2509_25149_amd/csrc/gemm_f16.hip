@@ -17,6 +17,7 @@
 // (measured: the fused kernel runs at 1.0-1.07 PFLOP/s, this route at 1.5-1.6
 // in the GEMM proper, the decode pass adding 5-8 % of its time).
 // The results are identical to the fused kernel's up to FP32 summation order.
+#include <cmath>
 #include <type_traits>
 
 #include "nvfp4_internal.h"
@@ -491,8 +492,9 @@ struct Width {
   int64_t tiles;
 };
 // A product that is accumulated into its result takes longer over the result the more tiles there are (5120 x 20480, K = 64 / 256 / 512: nb = 8
-// 283 / 299 / 333, nb = 5 306 / 313 / 345): there a narrower tile has to promise 4 % while K is short (no last round is split then, so the sums are the same).
-static Width pick_width(int64_t M, int64_t N, int64_t K, const TailPlan& p, bool accumulate) {
+// 283 / 299 / 333, nb = 5 306 / 313 / 345): there a narrower tile has to promise 4 % while K is short (`reluctant`; no last round is split
+// then, so the sums are the same).
+static Width pick_width(int64_t M, int64_t N, const TailPlan& p, bool reluctant) {
   constexpr double kTime[4] = {1.0, 0.90, 0.80, 0.68};
   const int64_t tiles_m = (M + TM - 1) / TM;
   Width best{8, 0.0, 0};
@@ -502,7 +504,7 @@ static Width pick_width(int64_t M, int64_t N, int64_t K, const TailPlan& p, bool
     double rounds = static_cast<double>((tiles + kCUs - 1) / kCUs);
     if (i == 0 && p.tail) rounds = static_cast<double>((tiles - p.tail) / kCUs) + 1.0 / p.splits + 0.15;
     rounds *= kTime[i];
-    if (i == 0 || rounds < (accumulate && K < 1024 && best.nb == 8 ? 0.96 : 1.0) * best.rounds) best = Width{nb, rounds, tiles};
+    if (i == 0 || rounds < (reluctant && best.nb == 8 ? 0.96 : 1.0) * best.rounds) best = Width{nb, rounds, tiles};
   }
   return best;
 }
@@ -522,52 +524,34 @@ size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) {
   return operand_bytes(M, N, K) + partial_bytes(p);
 }
 
-// What a call does: tile width, split of the last round, expected rounds.  One answer for the estimate, the room asked of the
-// workspace and the launch: the partial tiles of a split count only where tiles are 256 columns wide, and a workspace
-// without room for them (workspace_bytes: what it holds) makes the last round an ordinary one.
-struct TwoPassPlan {
-  Width width;
-  TailPlan tail;
-  size_t need;   // workspace bytes
-};
-static TwoPassPlan plan_two_pass(const GemmArgs& g) {
+// What a call does: one answer for the estimate, the room asked of the workspace and the launch.  The partial tiles of a split
+// count only where tiles are 256 columns wide, and a workspace without room for them makes the last round an ordinary one.
+// Expected time: what is still to decode (codes and scales in, FP16 out) at 4.7 TB/s, then rounds of 256 tiles at 18.5 ns per k
+// while there are fewer (3072 x 5120 x 5120, 240 tiles: 118 us in all) and 22.5 when the chip is full (the clock drops with the matrix
+// pipes busy) -- of a plain result, for all output types (see SmallTileCost).
+TwoPassPlan plan_two_pass(const GemmArgs& g) {
+  TwoPassPlan plan{false, HUGE_VAL, 8, 0, 1};
   const int64_t M = g.a.outer, N = g.b.outer;
-  const size_t operands = operand_bytes(g.a.fp16 ? 0 : M, g.b.fp16 ? 0 : N, g.K);
+  if (g.K % TK != 0 || g.K >= (int64_t{1} << 21)) return plan;   // (the kernel's 32-bit byte offsets inside a 256-row tile)
+  const int64_t rows = (g.a.fp16 ? 0 : M) + (g.b.fp16 ? 0 : N);
+  const size_t operands = operand_bytes(rows, 0, g.K);
+  if (operands > g.workspace_bytes) return plan;
   TailPlan tail = plan_tail(M, N, g.K);
   if (operands + partial_bytes(tail) > g.workspace_bytes) tail = TailPlan{0, 1};
-  const Width w = pick_width(M, N, g.K, tail, g.accumulate);
+  Width w = pick_width(M, N, tail, false);
+  plan.us = 4.0 + static_cast<double>(rows) * static_cast<double>(g.K) * 2.5625 / 4.7e6 + (rows ? 2.0 : 0.0) +
+            w.rounds * static_cast<double>(g.K) * (w.tiles >= kCUs ? 0.0225 : 0.0185);
+  if (g.accumulate && g.K < 1024) w = pick_width(M, N, tail, true);
   if (w.nb != 8) tail = TailPlan{0, 1};
-  return TwoPassPlan{w, tail, operands + partial_bytes(tail)};
-}
-
-bool gemm_two_pass_usable(const GemmArgs& g) {
+  plan.units = w.nb;
+  plan.tail = tail.tail;
+  plan.splits = tail.splits;
   // (With both operands decoded beforehand nothing is needed of the workspace.)
-  const size_t need = plan_two_pass(g).need;
-  const bool room = need == 0 || (g.workspace && g.workspace_bytes >= need && reinterpret_cast<uintptr_t>(g.workspace) % 256 == 0);
-  return room && (g.K % TK) == 0 &&
-         reinterpret_cast<uintptr_t>(g.a.fp16) % 16 == 0 && reinterpret_cast<uintptr_t>(g.b.fp16) % 16 == 0 &&
-         g.K < (int64_t{1} << 21) &&   // the kernel's 32-bit byte offsets inside a 256-row tile
-         reinterpret_cast<uintptr_t>(g.a.codes) % 16 == 0 &&
-         reinterpret_cast<uintptr_t>(g.b.codes) % 16 == 0 && reinterpret_cast<uintptr_t>(g.a.scales) % 4 == 0 &&
-         reinterpret_cast<uintptr_t>(g.b.scales) % 4 == 0;
-}
-
-// Expected time of this route: what is still to decode (codes and scales in, FP16 out) at 4.7 TB/s, then rounds of 256
-// tiles at 18.5 ns per k while there are fewer (3072 x 5120 x 5120, 240 tiles: 118 us in all) and 22.5 when the chip is full (the clock
-// drops with the matrix pipes busy).
-double gemm_two_pass_us(const GemmArgs& g) {
-  const int64_t M = g.a.outer, N = g.b.outer;
-  const double k = static_cast<double>(g.K);
-  GemmArgs plain = g;   // one choice of the route for all output types (see small_tile_us)
-  plain.accumulate = false;
-  const Width w = plan_two_pass(plain).width;
-  const int64_t rows = (g.a.fp16 ? 0 : M) + (g.b.fp16 ? 0 : N);
-  return 4.0 + static_cast<double>(rows) * k * 2.5625 / 4.7e6 + (rows ? 2.0 : 0.0) + w.rounds * k * (w.tiles >= kCUs ? 0.0225 : 0.0185);
-}
-
-TwoPassShape gemm_two_pass_shape(const GemmArgs& g) {
-  const TwoPassPlan p = plan_two_pass(g);
-  return TwoPassShape{p.width.nb, p.tail.tail, p.tail.splits};
+  const bool room = operands + partial_bytes(tail) == 0 || (g.workspace && reinterpret_cast<uintptr_t>(g.workspace) % 256 == 0);
+  plan.usable = room && reinterpret_cast<uintptr_t>(g.a.fp16) % 16 == 0 && reinterpret_cast<uintptr_t>(g.b.fp16) % 16 == 0 &&
+                reinterpret_cast<uintptr_t>(g.a.codes) % 16 == 0 && reinterpret_cast<uintptr_t>(g.b.codes) % 16 == 0 &&
+                reinterpret_cast<uintptr_t>(g.a.scales) % 4 == 0 && reinterpret_cast<uintptr_t>(g.b.scales) % 4 == 0;
+  return plan;
 }
 
 #define NVFP4_LAUNCH_F16(BF16, ROWSCALES, SPLIT, NB)                                                                  \
@@ -635,7 +619,7 @@ static hipError_t launch_all(const GemmArgs& g, const _Float16* a16, const _Floa
   return launch_f16<kNB>(g.out_bf16, a16, b16, g, tiles_m, tiles_n, 0, tiles_m * tiles_n, 1, nullptr, s);
 }
 
-hipError_t launch_gemm_two_pass(const GemmArgs& g, hipStream_t s) {
+hipError_t launch_gemm_two_pass(const GemmArgs& g, const TwoPassPlan& plan, hipStream_t s) {
   const int64_t M = g.a.outer, N = g.b.outer, K = g.K;
   // Workspace: [A as FP16 unless decoded beforehand][B likewise][partial tiles]
   char* ws = static_cast<char*>(g.workspace);
@@ -656,19 +640,17 @@ hipError_t launch_gemm_two_pass(const GemmArgs& g, hipStream_t s) {
   const int tiles = tiles_m * tiles_n;
   // One 256x256 tile keeps one CU busy (its LDS fits one workgroup).  Whole rounds of kCUs tiles
   // run as they are; a last partial round that fills at most half the chip is split along K.
-  const TwoPassPlan plan = plan_two_pass(g);
-  const TailPlan& p = plan.tail;
-  switch (plan.width.nb) {
+  switch (plan.units) {
     case 7: return launch_all<7>(g, a16, b16, tiles_m, s);
     case 6: return launch_all<6>(g, a16, b16, tiles_m, s);
     case 5: return launch_all<5>(g, a16, b16, tiles_m, s);
     default: break;
   }
-  const int full = tiles - p.tail;
+  const int full = tiles - plan.tail;
   hipError_t e = hipSuccess;
   if (full > 0) e = launch_f16<8>(g.out_bf16, a16, b16, g, tiles_m, tiles_n, 0, full, 1, nullptr, s);
-  if (e == hipSuccess && p.tail > 0)
-    e = launch_f16<8>(g.out_bf16, a16, b16, g, tiles_m, tiles_n, full, p.tail, p.splits, partials, s);
+  if (e == hipSuccess && plan.tail > 0)
+    e = launch_f16<8>(g.out_bf16, a16, b16, g, tiles_m, tiles_n, full, plan.tail, plan.splits, partials, s);
   return e;
 }
 

@@ -81,28 +81,42 @@ struct GemmArgs {
 };
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);
-bool gemm_two_pass_usable(const GemmArgs& g);
-hipError_t launch_gemm_two_pass(const GemmArgs& g, hipStream_t s);
-double gemm_two_pass_us(const GemmArgs& g);   // expected time, to choose between the routes
-// 32-column units of this route's tile, and how many tiles of the last round are split along K over how many workgroups
-struct TwoPassShape {
+// What the two-pass route does with a product: 32-column units of its tile, how many tiles of the last round are split along K over
+// how many workgroups, what it is expected to take; usable: shape, alignment and workspace allow it.
+struct TwoPassPlan {
+  bool usable;
+  double us;
   int units, tail, splits;
 };
-TwoPassShape gemm_two_pass_shape(const GemmArgs& g);
+TwoPassPlan plan_two_pass(const GemmArgs& g);
+hipError_t launch_gemm_two_pass(const GemmArgs& g, const TwoPassPlan& plan, hipStream_t s);
 // Straight from the packed codes, without scratch, any K.  `shape`: number of a tile shape, see gemm_direct.hip.
 hipError_t launch_gemm_direct(const GemmArgs& g, int shape, hipStream_t s);
 constexpr int kDirectOwnTiles = 4;                        // the shape whose wavefronts own different tiles
-int pick_direct_shape(const GemmArgs& g);                 // the best of the others
-double gemm_direct_compute_us(const GemmArgs& g);         // its time, the result's bytes left out
+struct DirectPick {
+  int shape;             // the best of the others
+  int64_t tiles;
+  double compute_us;     // its time, the result's bytes left out
+};
+DirectPick pick_direct_shape(const GemmArgs& g);
 double gemm_direct_us(const GemmArgs& g, int shape);      // any shape's time
 // Expected time of a kernel on small tiles: `call`, then rounds of 256 tiles of `tile` us and `step` us per step of the loop,
 // or, where that is more, the result's bytes at `result` us per MB (added in quadrature: neither hides the other fully).  A
 // CU holds `resident` workgroups; a round in which only one of them has a tile takes `alone` rounds, not 1.
+// Bytes of an FP32 result, whatever leaves: the choice of the kernel must not depend on the output type, since bf16 and accumulated
+// results are defined by the FP32 ones, to the last bit of whose sums the order of summation counts.
 struct SmallTileCost {
   int resident;
   double call, alone, tile, step, result;
 };
-double small_tile_us(const SmallTileCost& c, const GemmArgs& g, int64_t tile_m, int64_t tile_n, int64_t steps);
+// (Always inlined with constants: a launch that takes 7 us to issue should not spend one on divisions by tile sizes.)
+__attribute__((always_inline)) inline double small_tile_us(const SmallTileCost& c, int64_t tiles, double elements, int64_t steps) {
+  const int64_t wave = int64_t{256} * c.resident, whole = tiles / wave, last = (tiles - whole * wave + 255) / 256;   // tiles of a CU in the last wave
+  double rounds = static_cast<double>(whole * c.resident);
+  if (last) rounds += c.alone + static_cast<double>(last - 1) * (c.resident - c.alone) / (c.resident - 1);
+  const double loop = rounds * (c.tile + c.step * static_cast<double>(steps)), result = c.result * elements * 4e-6;
+  return c.call + __builtin_sqrt(loop * loop + result * result);
+}
 // Decodes one operand (codes [outer, K/2], scales [outer, K/16]) to FP16 [outer, K]
 hipError_t launch_predecode(const Operand& op, int64_t K, void* fp16_out, hipStream_t s);
 

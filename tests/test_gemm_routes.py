@@ -58,6 +58,15 @@ def test_few_tokens_and_small_layers_split_k(M, N, K, shape):
         assert plan(M, N, K, True, False, workspace)[:2] == (DIRECT, shape)
 
 
+@pytest.mark.parametrize("M,N,K", [(768, 2128, 64), (2240, 816, 32), (1040, 1296, 16), (320, 5680, 64), (1024, 1024, 80)])
+def test_small_results_split_k_while_all_workgroups_are_resident(M, N, K):
+    """768 x 2128 x 64 accumulated: 8.0 us with K split, 10.9 in 128 x 128 tiles of four wavefronts' own; FP32 alike."""
+    for accumulate in (False, True):
+        for workspace in (0, True):
+            route, shape = plan(M, N, K, False, accumulate, workspace)[:2]
+            assert route == DIRECT and shape < OWN_TILES
+
+
 @pytest.mark.parametrize("M,N,K,units", [(8192, 20480, 5120, 8), (8192, 5120, 20480, 8), (5120, 20480, 8192, 8), (5120, 5120, 4096, 7),
                                          (2048, 5120, 5120, 5), (4096, 5120, 5120, 5)])
 def test_large_products_take_the_two_pass_route(M, N, K, units):
