@@ -396,9 +396,12 @@ static GemmPlan plan_route(const GemmArgs& g) {
                                                          : small_tile_us(kTile128Cost, tiles128, elements, (g.K + BK - 1) / BK);
   const double own = gemm_direct_us(g, kDirectOwnTiles);
   const bool take_own = own < (elements > 3e7 ? 0.83 : g.K % 128 ? 0.92 : 1.0) * tile128;
-  // (Over a long K own tiles have to promise 8 % against split K too: 512 workgroups at as many places of the operands find less in the
-  // caches than the estimate thinks.  Split / own: 3792 x 18032 x 6576 1237 / 1331 us, 8176 x 5104 x 5136 590 / 580, 8176 x 20464 x 2064 1111 / 1025.)
-  if (gemm_direct_us(g, direct.shape) <= (g.K > 2048 ? 1.08 : 1.0) * (take_own ? own : tile128)) return {kDirect, direct.shape, {}};
+  // Split K against these: below K = 1024 and with more than a round of 128 x 128 tiles it has to promise 8 % (a step or two per wavefront cost more than the estimate thinks: 4096 x 5120 x
+  // 400 48 us split, 36 own, 40 in 128 x 128); from there on they have to, 4 % (496 x 18016 x 1136 40 / 43 own: rounds of unequal tiles), and above
+  // 2048 8 % (512 workgroups at as many places of the operands find less in the caches: 3792 x 18032 x 6576 1237 / 1331, 8176 x 5104 x 5136
+  // 590 / 580, 8176 x 20464 x 2064 1111 / 1025).
+  const double margin = g.K > 2048 ? 1.08 : g.K >= 1024 || tiles128 <= 256 ? 1.04 : 0.92;
+  if (gemm_direct_us(g, direct.shape) <= margin * (take_own ? own : tile128)) return {kDirect, direct.shape, {}};
   return take_own ? GemmPlan{kDirect, kDirectOwnTiles, {}} : GemmPlan{kTile128, 0, {}};
 }
 

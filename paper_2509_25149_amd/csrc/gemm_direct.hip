@@ -121,26 +121,42 @@ __global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, 2) void gemm_direct_kernel
     ld[i].c = make_uint4(lo.x, lo.y, hi.x, hi.y);
     ld[i].s = (in0 ? s0 : 0u) | (in1 ? s1 << 8 : 0u);
   };
-  // The step in hand through LDS, block by block: stored as loaded, read back in the MFMA's lane order two blocks later (all
-  // stored before the first is read: 64 x 20480 x 5120 24.3 us instead of 23.7, the loads of the last blocks being waited for by all).
-  constexpr int kLag = 2;
+  // The step in hand through LDS: stored as loaded, read back in the MFMA's lane order.
   uint4 c[S::kBlocks];
   half2v sc[S::kBlocks];
+  auto stage = [&](int i) {
+    *reinterpret_cast<uint4*>(mine + i * kCodeBytes + (row4 * 4 + (c4 ^ (row4 >> 2))) * 16) = ld[i].c;
+    *reinterpret_cast<uint16_t*>(mine + S::kBlocks * kCodeBytes + i * kScaleBytes + lane * 2) = static_cast<uint16_t>(ld[i].s);
+  };
   auto read_back = [&](int i) {
     c[i] = *reinterpret_cast<const uint4*>(mine + i * kCodeBytes + (l16 * 4 + (q ^ (l16 >> 2))) * 16);
     sc[i] = scales2(*reinterpret_cast<const uint16_t*>(mine + S::kBlocks * kCodeBytes + i * kScaleBytes + l16 * 8 + q * 2));
   };
-  auto turn = [&]() {
+  // then: what else to issue on the way (the next step's loads).  With 8 blocks it goes between all the stores and all the reads (3328 x
+  // 15856 x 4368 634 us, 660 block by block); with fewer a block is read back two blocks behind the stores, so that the first do not wait for the
+  // last loads (64 x 20480 x 5120 23.7 us, 24.3 the other way).
+  auto turn = [&](auto then) {
+    if constexpr (S::kBlocks == 8) {
 #pragma unroll
-    for (int i = 0; i < S::kBlocks + kLag; ++i) {
-      if (i < S::kBlocks) {
-        *reinterpret_cast<uint4*>(mine + i * kCodeBytes + (row4 * 4 + (c4 ^ (row4 >> 2))) * 16) = ld[i].c;
-        *reinterpret_cast<uint16_t*>(mine + S::kBlocks * kCodeBytes + i * kScaleBytes + lane * 2) = static_cast<uint16_t>(ld[i].s);
-        wavefront_exchange();
+      for (int i = 0; i < S::kBlocks; ++i) stage(i);
+      wavefront_exchange();
+      then();
+#pragma unroll
+      for (int i = 0; i < S::kBlocks; ++i) read_back(i);
+      wavefront_exchange();   // the next step's stores come after these reads
+    } else {
+      constexpr int kLag = 2;
+#pragma unroll
+      for (int i = 0; i < S::kBlocks + kLag; ++i) {
+        if (i < S::kBlocks) {
+          stage(i);
+          wavefront_exchange();
+        }
+        if (i >= kLag) read_back(i - kLag);
       }
-      if (i >= kLag) read_back(i - kLag);
+      wavefront_exchange();
+      then();
     }
-    wavefront_exchange();   // the next step's stores come after these reads
   };
   auto multiply = [&]() {
     half8v f[2][S::kBlocks];
@@ -170,7 +186,7 @@ __global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, 2) void gemm_direct_kernel
   if (tail) {
 #pragma unroll
     for (int i = 0; i < S::kBlocks; ++i) load_tail(i);
-    turn();
+    turn([] {});
   }
   if (wk < full) {
 #pragma unroll
@@ -179,9 +195,10 @@ __global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, 2) void gemm_direct_kernel
   if (tail) multiply();
 #pragma unroll 1
   for (int step = wk; step < full; step += WK) {
-    turn();
+    turn([&] {
 #pragma unroll
-    for (int i = 0; i < S::kBlocks; ++i) load(i, step + WK < full ? step + WK : step);
+      for (int i = 0; i < S::kBlocks; ++i) load(i, step + WK < full ? step + WK : step);
+    });
     multiply();
   }
 

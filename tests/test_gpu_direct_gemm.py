@@ -21,7 +21,7 @@ pytestmark = pytest.mark.gpu
     (64, 9232, 128, (DIRECT, 2)), (80, 8208, 144, (DIRECT, 0)), (144, 5200, 1040, (DIRECT, 3)), (32, 5136, 2192, (DIRECT, 1)),
     (64, 9232, 1168, (DIRECT, 2)), (16, 16400, 1040, (DIRECT, 0)), (528, 5136, 1104, (DIRECT, 3)),
     (2064, 8208, 16, (TILE_128, 0)), (2064, 4112, 80, (TILE_128, 0)), (1040, 8208, 208, (TILE_128, 0)),
-    (2064, 8208, 528, (DIRECT, OWN_TILES)), (4112, 4112, 400, (DIRECT, OWN_TILES)), (2064, 2064, 128, (DIRECT, OWN_TILES))])
+    (2064, 8208, 528, (DIRECT, OWN_TILES)), (4112, 4112, 528, (DIRECT, OWN_TILES)), (2064, 2064, 128, (DIRECT, OWN_TILES))])
 @pytest.mark.parametrize("per_row", [False, True], ids=["tensor_scale", "row_scales"])
 def test_direct_gemm(M, N, K, kernel, per_row):
     assert plan(M, N, K)[:2] == kernel
