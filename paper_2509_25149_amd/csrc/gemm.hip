@@ -379,6 +379,9 @@ static GemmPlan plan_route(const GemmArgs& g) {
   const bool big = (g.K % TK == 0) && (reinterpret_cast<uintptr_t>(g.a.codes) % 16 == 0) &&
                    (reinterpret_cast<uintptr_t>(g.b.codes) % 16 == 0);
   if (big && fused_us(g.a.outer, g.b.outer, g.K) <= direct.compute_us) return {kFused256, 0, {}};
+  // Over more than 12 rounds of its tiles and a long K the direct kernel takes some 20 % longer than its estimate, the clock being lower: there
+  // the two-pass route has the call after all (960 x 18016 x 2560 127 us direct, 103 estimated, 110 two-pass).
+  if (two_pass.usable && g.K >= 2048 && direct.tiles > 12 * 256 && two_pass.us <= 1.2 * direct.compute_us) return {kTwoPass, 0, two_pass};
   // All others: the direct kernel with K split among the wavefronts of a workgroup, where the tiles are few for the length of K;
   // else 128 x 128 tiles.  These the direct kernel with a tile per wavefront does faster from K of some 250 on (no barrier), the
   // kernel that decodes a tile once per workgroup below (three workgroups per CU keep more stores in flight, steps of 64 waste

@@ -68,7 +68,7 @@ def test_small_results_split_k_while_all_workgroups_are_resident(M, N, K):
 
 
 @pytest.mark.parametrize("M,N,K,units", [(8192, 20480, 5120, 8), (8192, 5120, 20480, 8), (5120, 20480, 8192, 8), (5120, 5120, 4096, 7),
-                                         (2048, 5120, 5120, 5), (4096, 5120, 5120, 5)])
+                                         (2048, 5120, 5120, 5), (4096, 5120, 5120, 5), (960, 18016, 2560, 5)])
 def test_large_products_take_the_two_pass_route(M, N, K, units):
     assert plan(M, N, K, workspace=True)[:2] == (TWO_PASS, units)
     assert plan(M, N, K, workspace=0)[0] in (FUSED_256, DIRECT)
