@@ -484,7 +484,7 @@ static TailPlan plan_tail(int64_t M, int64_t N, int64_t K) {
 // Tile width (32 nb columns) of the whole product, and how long it takes in rounds of 256 x 256 tiles.  A narrower tile takes
 // 0.90, 0.80, 0.68 of the time for nb = 7, 6, 5 (fewer products per byte moved), but rounds come out better for some
 // products; the widest wins a tie.  A split last round costs its share of a round and 0.15 for the partial tiles.  Measured,
-// us per call with nb = 8 / 7 / 6 / 5: 5120 x 5120 x 4096 (FP32) 179 / 172 / 211 / 190, 2048 x 5120 x 5120 105 / 99 / 93 / 89, 4096 x 5120 x 5120
+// us per call with nb = 8 / 7 / 6 / 5: 5120 x 5120 x 4096 (FP32) 192 / 179 / 216 / 193, 2048 x 5120 x 5120 113 / 104 / 95 / 93, 4096 x 5120 x 5120
 // 171 (split) / 189 / 170 / 160, 3072 x 5120 x 5120 118 / 187 / 166 / 147, 8192 x 5120 x 20480 1165 (split) / 1225 / 1337 / 1337.
 struct Width {
   int nb;
