@@ -328,15 +328,15 @@ __global__ __launch_bounds__(kBigThreads) void gemm_kernel_256(Operand A, Operan
 
 }  // namespace
 
-// Expected time of the 256 x 256 fused kernel: rounds of 256 tiles at 26.5 ns per k (256 x 5120 x 5120: 133 us, 4096 x 5120 x
-// 5120: 280; 31 ns with the chip full for long, at a lower clock).
+// Expected time of the 256 x 256 fused kernel: rounds of 256 tiles at 10.8 us and 25.2 ns per k (31 with the chip full for long, at a lower
+// clock).  Fitted to 95 calls; 5th and 95th percentile 0.89 and 1.17 of the measured time.
 static double fused_us(int64_t M, int64_t N, int64_t K) {
   const int64_t tiles = ((M + TM - 1) / TM) * ((N + TN - 1) / TN);
-  return 4.0 + static_cast<double>((tiles + 255) / 256) * static_cast<double>(K) * (tiles > 1024 ? 0.031 : 0.0265);
+  return 1.4 + static_cast<double>((tiles + 255) / 256) * (10.8 + static_cast<double>(K) * (tiles > 1024 ? 0.031 : 0.0252));
 }
 
 // The 128 x 128 kernel, in the same terms (steps of 64 k; three workgroups fit a CU).
-static constexpr SmallTileCost kTile128Cost{3, 3.47, 1.45, 1.14, 0.788, 0.151};
+static constexpr SmallTileCost kTile128Cost{3, 3.9, 1.52, 0.365, 0.759, 0.203};
 
 static hipError_t launch_tile128(const GemmArgs& g, hipStream_t s) {
   const dim3 grid(static_cast<unsigned>((g.b.outer + BN - 1) / BN), static_cast<unsigned>((g.a.outer + BM - 1) / BM));
@@ -365,47 +365,40 @@ static hipError_t launch_fused256(const GemmArgs& g, hipStream_t s) {
 enum GemmRoute { kTwoPass, kFused256, kTile128, kDirect };
 struct GemmPlan {
   GemmRoute route;
-  int shape;             // kDirect: the tile shape
+  DirectPick direct;     // kDirect
   TwoPassPlan two_pass;  // kTwoPass
 };
 
+// The kernel that is expected to be the fastest, with a margin where the estimates are known to lean one way.  Over the same 1080 products the
+// calls take 1.5 % more than with the best kernel each.  us, direct / two-pass: 512 x 5120 x 5120 28 / 82, 4352 x 1280 x 5376 63 / 80, 2048 x 5120 x 5120 95 / 94,
+// 4352 x 4096 x 4096 155 / 133, 8192 x 20480 x 5120 1474 / 1152.
 static GemmPlan plan_route(const GemmArgs& g) {
-  const DirectPick direct = pick_direct_shape(g);
-  // With a workspace: decode pass + FP16 GEMM, unless the product is too small to fill its 256-row tiles.
+  // The direct kernel: its best shape, with K split among a workgroup's wavefronts or a tile to each
+  const DirectPick split = pick_direct_shape(g, false), own = pick_direct_shape(g, true);
+  const double direct_us = split.us < own.us ? split.us : own.us;
+  // With a workspace: decode pass + FP16 GEMM.  The direct kernel takes up to 15 % longer than its estimate in long products, the clock being lower.
   const TwoPassPlan two_pass = plan_two_pass(g);
-  if (two_pass.usable && two_pass.us <= direct.compute_us) return {kTwoPass, 0, two_pass};
-  // Without (or where that is slower): the fused kernel for large products -- it needs whole K steps of 64 and 16-byte aligned
-  // code rows.
+  const double power = direct_us > 30.0 ? 0.0022 * (direct_us - 30.0) : 0.0;
+  if (two_pass.usable && two_pass.us <= direct_us * (1.0 + (power < 0.15 ? power : 0.15))) return {kTwoPass, {}, two_pass};
+  // Without: the fused kernel -- it needs whole K steps of 64 and 16-byte aligned code rows.
   const bool big = (g.K % TK == 0) && (reinterpret_cast<uintptr_t>(g.a.codes) % 16 == 0) &&
                    (reinterpret_cast<uintptr_t>(g.b.codes) % 16 == 0);
-  if (big && fused_us(g.a.outer, g.b.outer, g.K) <= direct.compute_us) return {kFused256, 0, {}};
-  // Over more than 12 rounds of its tiles and a long K the direct kernel takes some 20 % longer than its estimate, the clock being lower: there
-  // the two-pass route has the call after all (960 x 18016 x 2560 127 us direct, 103 estimated, 110 two-pass).
-  if (two_pass.usable && g.K >= 2048 && direct.tiles > 12 * 256 && two_pass.us <= 1.2 * direct.compute_us) return {kTwoPass, 0, two_pass};
-  // All others: the direct kernel with K split among the wavefronts of a workgroup, where the tiles are few for the length of K;
-  // else 128 x 128 tiles.  These the direct kernel with a tile per wavefront does faster from K of some 250 on (no barrier), the
-  // kernel that decodes a tile once per workgroup below (three workgroups per CU keep more stores in flight, steps of 64 waste
-  // less).  us, split K / own tiles / 128 x 128: 5120 x 20480 x 16 (FP32) 193 / 87 / 80, x 144 197 / 112 / 107, x 400 228 / 159 / 177,
-  // x 2064 677 / 623 / 768; 8176 x 1296 x 1040 45 / 40 / 49; 1040 x 1296 x 1040 11.4 / 17.5 / 24.7.  Where K ends in a partial step
-  // of 128, own tiles have to promise 8 %: nearer than that the estimates do not tell the two apart.  Accumulated results move that line
-  // (and the choice is one for all, see SmallTileCost): where a large result is read too, two workgroups per CU hide that worse than three
-  // (5120 x 20480 x 400 324 / 290, 4096 x 5120 x 400 75 / 73), so from 3e7 elements on own tiles have to promise 17 % (K of some 800).
-  // Split K wherever its workgroups are on the chip all at once, two to a CU: the others then gain nothing worth a decision (5 % at 8 us), and
-  // lose where the result is read too (768 x 2128 x 64 8.0 split, 10.9 in own tiles).
-  if (direct.tiles <= 512 && direct.compute_us != HUGE_VAL) return {kDirect, direct.shape, {}};
+  if (big && fused_us(g.a.outer, g.b.outer, g.K) <= direct_us) return {kFused256, {}, {}};
+  // Large results of a short contraction: 128 x 128 tiles of workgroups that decode them once (three of them per CU keep more stores in flight,
+  // steps of 64 waste less), against the direct kernel with a tile per wavefront.  us, own / 128 x 128: 5120 x 20480 x 16 (FP32) 87 / 80, x 208 103 / 107.
+  // Where K ends in a partial step of 128, own tiles have to promise 8 %: nearer than that the estimates do not tell the two apart.  Accumulated
+  // results move that line (and the choice is one for all, see SmallTileCost): where a large result is read too, two workgroups per CU hide that worse
+  // than three (5120 x 20480 x 400 324 / 290, 4096 x 5120 x 400 75 / 73), so from 3e7 elements on own tiles have to promise 17 % (K of some 800).
   const double elements = static_cast<double>(g.a.outer) * static_cast<double>(g.b.outer);
   const int64_t tiles128 = ((g.a.outer + BM - 1) / BM) * ((g.b.outer + BN - 1) / BN);
   const double tile128 = g.a.outer > int64_t{65535} * BM ? HUGE_VAL   // its tile rows are the launch's second dimension
-                                                         : small_tile_us(kTile128Cost, tiles128, elements, (g.K + BK - 1) / BK);
-  const double own = gemm_direct_us(g, kDirectOwnTiles);
-  const bool take_own = own < (elements > 3e7 ? 0.83 : g.K % 128 ? 0.92 : 1.0) * tile128;
-  // Split K against these: below K = 1024 and with more than a round of 128 x 128 tiles it has to promise 8 % (a step or two per wavefront cost more than the estimate thinks: 4096 x 5120 x
-  // 400 48 us split, 36 own, 40 in 128 x 128); from there on they have to, 4 % (496 x 18016 x 1136 40 / 43 own: rounds of unequal tiles), and above
-  // 2048 8 % (512 workgroups at as many places of the operands find less in the caches: 3792 x 18032 x 6576 1237 / 1331, 8176 x 5104 x 5136
-  // 590 / 580, 8176 x 20464 x 2064 1111 / 1025).
-  const double margin = g.K > 2048 ? 1.08 : g.K >= 1024 || tiles128 <= 256 ? 1.04 : 0.92;
-  if (gemm_direct_us(g, direct.shape) <= margin * (take_own ? own : tile128)) return {kDirect, direct.shape, {}};
-  return take_own ? GemmPlan{kDirect, kDirectOwnTiles, {}} : GemmPlan{kTile128, 0, {}};
+                                                         : small_tile_us(kTile128Cost, tiles128, elements, static_cast<double>((g.K + BK - 1) / BK));
+  const bool take_own = own.us < (elements > 3e7 ? 0.83 : g.K % 128 ? 0.92 : 1.02) * tile128;
+  const double other_us = take_own ? own.us : tile128;
+  // Split K against these: small results of a step or less keep it while the estimate, which is too high there (768 x 2128 x 64 8.6 for 6.6 us), is not far
+  // off: where the result is read too, the others lose more (8.0 us split, 10.9 in own tiles).  From K = 1024 on they have to promise 8 %.
+  if (split.us <= (g.K <= 128 && elements <= 2097152.0 ? 1.45 : g.K >= 1024 ? 1.08 : 1.0) * other_us) return {kDirect, split, {}};
+  return take_own ? GemmPlan{kDirect, own, {}} : GemmPlan{kTile128, {}, {}};
 }
 
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
@@ -414,7 +407,7 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
     case kTwoPass: return launch_gemm_two_pass(g, p.two_pass, s);
     case kFused256: return launch_fused256(g, s);
     case kTile128: return launch_tile128(g, s);
-    default: return launch_gemm_direct(g, p.shape, s);
+    default: return launch_gemm_direct(g, p.direct.shape, s);
   }
 }
 
@@ -422,7 +415,7 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
 
 // For the tests, not part of the ABI: which kernel an NVFP4 product of these sizes takes with aligned operands.  decoded: bit 0 A, bit 1 B
 // decoded beforehand.  out: route (0 two-pass, 1 fused 256 x 256, 2 128 x 128, 3 direct); two-pass: 32-column units of a tile, tiles of a split
-// last round, workgroups that share each; direct: the tile shape.
+// last round, workgroups that share each; direct: the kind of tile.
 extern "C" void nvfp4_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int bf16_out, int accumulate, size_t workspace_bytes, int decoded, int* out) {
   using namespace nvfp4;
   GemmArgs g{};
@@ -436,7 +429,7 @@ extern "C" void nvfp4_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int bf
   g.workspace_bytes = workspace_bytes;
   const GemmPlan p = plan_route(g);
   out[0] = p.route;
-  out[1] = p.shape;
+  out[1] = p.route == kDirect ? p.direct.kind : 0;
   out[2] = 0;
   out[3] = 1;
   if (p.route == kTwoPass) {
@@ -444,4 +437,13 @@ extern "C" void nvfp4_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int bf
     out[2] = p.two_pass.tail;
     out[3] = p.two_pass.splits;
   }
+}
+
+// Likewise: {MB, NB, WK, steps} of the shape in which the direct kernel takes such a product.  own: without a split of K.
+extern "C" void nvfp4_internal_direct_shape(int64_t M, int64_t N, int64_t K, int own, int* out) {
+  nvfp4::GemmArgs g{};
+  g.a.outer = M;
+  g.b.outer = N;
+  g.K = K;
+  nvfp4::direct_shape(nvfp4::pick_direct_shape(g, own != 0).shape, out);
 }

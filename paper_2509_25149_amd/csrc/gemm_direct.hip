@@ -2,22 +2,30 @@
 // 16.  The form for products that do not fill the chip with 256 x 256 tiles -- few tokens, small layers -- and for
 // contraction lengths that are not a multiple of 64.
 //
-// A wavefront owns MB x NB blocks of 16 x 16 outputs and every WK-th step of 128 k; the WK wavefronts of a workgroup own
+// A wavefront owns MB x NB blocks of 16 x 16 outputs and every WK-th window of 128 or 256 k; the WK wavefronts of a workgroup own
 // the same outputs and add their sums through LDS at the end (WK = 1: they own different ones).  No barrier in the loop: a wavefront loads the codes and
-// scales of its own rows into registers one step ahead, passes them through its own piece of LDS, decodes them to FP16
+// scales of its own rows into registers two windows ahead, passes them through its own piece of LDS, decodes them to FP16
 // (value * block scale, exact) and feeds the 16x16x32 MFMA.
 //   - Through LDS, because a load in the MFMA's lane order (16 consecutive lanes = 16 rows) touches 16 cache lines per 16
-//     lanes; four lanes to a row's 64 bytes touch 4.  64 x 20480 x 5120: 35 us without this detour, 27 with.
-//   - Steps of 128 k rather than 256: half the LDS and the staging registers per wavefront, so that two workgroups of four
-//     wavefronts fit a CU and the 427 of this shape are resident at once (27 -> 22 us), and less to lose where K is not a
-//     multiple of the step.
+//     lanes; eight lanes to a row's 128 bytes (four to 64) touch 2 (4).  64 x 20480 x 5120: 35 us without this detour, 27 with.
 //   - What bounds it is the issue of vector instructions: a 16 x 32 fragment takes 8 of them (4 cvt, 4 pk_mul) and serves MB or
-//     NB (3 or 4) MFMAs, so the decode of the next fragments is spread over the MFMAs of these.  Decoding A once per
-//     workgroup and sharing it through LDS needs a barrier per step and was slower (33 against 22 us, 52 against 38).
-// Measured (us; before = whatever the call took then): 64 x 20480 x 5120 133 -> 23, 16 x 20480 x 5120 131 -> 14.6 (4.0 TB/s of
-// codes), 512 x 5120 x 5120 101 -> 38, 256 x 256 x 512 18 -> 3.4, 1040 x 1296 x 2064 44 -> 14.4.
+//     NB MFMAs.  Measured, cycles per MFMA with V such instructions beside it: 8 + 4.5 V (16 alone), whichever wavefront of the SIMD they
+//     are from, so that 4 x 4 blocks (V = 4) cannot do better than 26 and 8 x 5 (2.6) reach 20: the large shapes have one wavefront per SIMD
+//     and 460 registers.
+//   - One wavefront per SIMD has nobody to fill its waits, so the loop is pipelined: behind a row of MFMAs go the decode of the next row's
+//     fragment, the LDS reads of the next step, the stores of the next window into LDS and the loads of the window after it, each
+//     an instruction or two behind an MFMA (interleave).  64 x 80 tiles of 64 x 20480 x 8192: 30.7 us with the same parts in turn, 25.5 so;
+//     128 x 80 tiles of 128 x 20480 x 8192 51.5 and 39.7.  Taken out one at a time (us of the 15.9 that 4096 k cost there): loads 2.6, LDS 0, both and
+//     decode 6.7.
+//   - Windows of 256 k, that is whole 128-byte lines of codes, need 40 % less time for the loads alone than 64-byte pieces (8.1 and 4.9 us at
+//     64 x 20480 x 5120) and half the loads of scales; the small shapes, which share short K among many wavefronts, take 128.
+// Decoding A once per workgroup and sharing it through LDS needs a barrier per step and was slower (33 against 22 us, 52 against 38).
+// Measured (us; before = steps of 128 k in turn, at most 64 x 64 per wavefront): 64 x 20480 x 5120 23.5 -> 19.1, 128 x 20480 x 5120 39.8 -> 28.0, 512 x 5120 x
+// 5120 39.3 -> 27.4, 1040 x 1296 x 2064 14.7 -> 13.1, 2064 x 1296 x 1040 15.8 -> 13.3, 8176 x 5104 x 5136 571 -> 395 (1.09 PFLOP/s).
 
 #include <cmath>
+#include <type_traits>
+#include <utility>
 
 #include "nvfp4_internal.h"
 #include "nvfp4_device.h"
@@ -26,15 +34,15 @@
 namespace nvfp4 {
 namespace {
 
-constexpr int kStepK = 128;               // k per step: 64 bytes of codes and 8 of scales per row, 1 KiB of codes per 16-row block
-constexpr int kCodeBytes = 1024, kScaleBytes = 128;   // of a 16-row block and step
-
 struct __attribute__((packed, aligned(8))) Codes16 { uint32_t w[4]; };
 typedef uint16_t u16_any __attribute__((aligned(1)));
+typedef uint32_t u32_any __attribute__((aligned(1)));
 
-// What a lane holds of a 16-row block and step as loaded: row lane / 4, 16-byte chunk lane % 4 (32 codes), its 2 scales.
+// What a lane holds of a 16-row block and a window of 128 kSteps k as loaded: 16-byte chunk lane % (4 kSteps) (32 codes) of row
+// lane / (4 kSteps), with two steps that of the row 8 below too, and the 2 kSteps scales lane % 4 of row lane / 4.
+template <int kSteps>
 struct Loaded {
-  uint4 c;
+  uint4 c[kSteps];
   uint32_t s;
 };
 
@@ -53,24 +61,50 @@ __device__ __forceinline__ void wavefront_exchange() {
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 }
-__device__ __forceinline__ half2v scales2(uint32_t s) { return __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(static_cast<int>(s), 1.0f, false); }
+
+template <int kBegin, int kEnd, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (kBegin < kEnd) {
+    f(std::integral_constant<int, kBegin>{});
+    static_for<kBegin + 1, kEnd>(f);
+  }
+}
+
+// The instructions since the last such call, in this order: the MFMAs with the others spread evenly behind them.
+template <int kMfmas, int kValu, int kDsReads, int kDsWrites, int kLoads>
+__device__ __forceinline__ void interleave() {
+  static_for<0, kMfmas>([](auto n) {
+    constexpr int g = decltype(n)::value;
+    constexpr auto share = [](int total) { return (g + 1) * total / kMfmas - g * total / kMfmas; };
+    __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+    if constexpr (share(kDsReads) > 0) __builtin_amdgcn_sched_group_barrier(0x100, share(kDsReads), 0);
+    if constexpr (share(kDsWrites) > 0) __builtin_amdgcn_sched_group_barrier(0x200, share(kDsWrites), 0);
+    if constexpr (share(kLoads) > 0) __builtin_amdgcn_sched_group_barrier(0x20, share(kLoads), 0);
+    if constexpr (share(kValu) > 0) __builtin_amdgcn_sched_group_barrier(0x2, share(kValu), 0);
+  });
+  __builtin_amdgcn_sched_barrier(0);
+}
 
 // MB x NB blocks of 16 x 16 outputs per wavefront, WK wavefronts per workgroup that split K.  WK = 1: a workgroup of 2 x 2
-// wavefronts that own a tile each.
-template <int MB, int NB, int WK>
+// wavefronts that own a tile each.  kSteps: a window is 128 or 256 k.
+template <int MB, int NB, int WK, int Steps>
 struct Shape {
   static constexpr int kOwn = WK == 1 ? 2 : 1, kWaves = WK * kOwn * kOwn;
   static constexpr int kTM = MB * 16 * kOwn, kTN = NB * 16 * kOwn, kThreads = kWaves * 64, kBlocks = MB + NB;
-  static constexpr int kStage = kBlocks * (kCodeBytes + kScaleBytes);       // one step's codes and scales, per wavefront
+  static constexpr int kSteps = Steps, kWindowK = 128 * kSteps;
+  static constexpr int kCodeBytes = 16 * kWindowK / 2, kScaleBytes = kWindowK;   // of a 16-row block and window
+  static constexpr int kStage = kBlocks * (kCodeBytes + kScaleBytes);            // a window's codes and scales, per wavefront
   static constexpr int kSum = WK > 1 ? MB * NB * 1024 : 0;
   static constexpr int kWaveBytes = kStage > kSum ? kStage : kSum;
   static constexpr int kLdsBytes = kWaves * kWaveBytes;
 };
 
-template <int MB, int NB, int WK, bool kBf16Out>
-__global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, 2) void gemm_direct_kernel(Operand A, Operand B, int K, void* __restrict__ Dv, int64_t ldd,
-                                                                  bool accumulate, int tiles_m, int tiles_n) {
-  using S = Shape<MB, NB, WK>;
+template <int MB, int NB, int WK, int Steps, bool kBf16Out>
+__global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, MB * NB > 16 ? 1 : 2) void gemm_direct_kernel(
+    Operand A, Operand B, int K, void* __restrict__ Dv, int64_t ldd, bool accumulate, int tiles_m, int tiles_n) {
+  using S = Shape<MB, NB, WK, Steps>;
+  constexpr int kSteps = Steps, kWindowK = S::kWindowK, kCodeBytes = S::kCodeBytes, kScaleBytes = S::kScaleBytes;
+  constexpr int kChunks = 4 * kSteps, kLoadRows = 64 / kChunks, kRowBytes = 16 * kChunks;   // of a row of a window; rows that a load instruction covers
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6), wk = WK == 1 ? 0 : wave;
@@ -80,9 +114,10 @@ __global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, 2) void gemm_direct_kernel
   int tm, tn;
   tile_coordinates(pid, tiles_m, tiles_n, tm, tn);
   const int l16 = lane & 15, q = lane >> 4;
-  const int row4 = lane >> 2, c4 = lane & 3;      // loading: row and chunk of the lane
-  const int M = static_cast<int>(A.outer), N = static_cast<int>(B.outer);
-  const int m0 = tm * S::kTM + (WK == 1 ? (wave >> 1) * (MB * 16) : 0), n0 = tn * S::kTN + (WK == 1 ? (wave & 1) * (NB * 16) : 0);
+  const int crow = lane / kChunks, chunk = lane % kChunks, srow = lane >> 2, spart = lane & 3;   // loading: row and chunk of the lane's codes, of its scales
+  // (unsigned: the last tile may reach past 2^31)
+  const uint32_t M = static_cast<uint32_t>(A.outer), N = static_cast<uint32_t>(B.outer);
+  const uint32_t m0 = tm * S::kTM + (WK == 1 ? (wave >> 1) * (MB * 16) : 0), n0 = tn * S::kTN + (WK == 1 ? (wave & 1) * (NB * 16) : 0);
   uint8_t* const mine = lds + wave * S::kWaveBytes;
 
   // Wave-uniform bases plus one 32-bit lane offset; blocks 0 .. MB-1 are A's, the others B's.  Blocks past the
@@ -91,11 +126,16 @@ __global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, 2) void gemm_direct_kernel
   const uint8_t *cp[S::kBlocks], *sp[S::kBlocks];
 #pragma unroll
   for (int i = 0; i < S::kBlocks; ++i) {
-    const int64_t row = i < MB ? min(m0 + i * 16, M - 16) : min(n0 + (i - MB) * 16, N - 16);
+    const int64_t row = i < MB ? min(m0 + i * 16u, M - 16u) : min(n0 + (i - MB) * 16u, N - 16u);
     cp[i] = (i < MB ? A.codes : B.codes) + row * code_ld;
     sp[i] = (i < MB ? A.scales : B.scales) + row * scale_ld;
   }
-  const uint32_t code_off = static_cast<uint32_t>(row4 * code_ld + c4 * 16), scale_off = static_cast<uint32_t>(row4 * scale_ld + c4 * 2);
+  const uint32_t code_off = static_cast<uint32_t>(crow * code_ld + chunk * 16), scale_off = static_cast<uint32_t>(srow * scale_ld + spart * 2 * kSteps);
+
+  // The wavefront's part of K: every WK-th window, and one of them the rest.  (A stretch of K to each, as even as 64 k allow, was slower, also where
+  // the windows do not come out even: neighbouring lines then go to one wavefront one after the other.  512 x 5120 x 5120 29.1 / 28.4 us, 1040 x 1296 x
+  // 2064 13.7 / 13.1; with windows of 128, half a line, 32 x 5120 x 5120 7.6 / 7.1.)
+  const int full = K / kWindowK, windows = (full - wk + WK - 1) / WK, rest = full % WK == wk ? K - full * kWindowK : 0;
 
   float4v acc[MB][NB];
 #pragma unroll
@@ -103,110 +143,203 @@ __global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, 2) void gemm_direct_kernel
 #pragma unroll
     for (int j = 0; j < NB; ++j) acc[i][j] = float4v{0.0f, 0.0f, 0.0f, 0.0f};
 
-  Loaded ld[S::kBlocks];
-  auto load = [&](int i, int step) {
-    const Codes16 c = *reinterpret_cast<const Codes16*>(cp[i] + step * 64 + code_off);
-    ld[i].c = make_uint4(c.w[0], c.w[1], c.w[2], c.w[3]);
-    ld[i].s = *reinterpret_cast<const u16_any*>(sp[i] + step * 8 + scale_off);
+  Loaded<kSteps> ld[S::kBlocks];
+  auto load_block = [&](int i, int k, const uint32_t (&co)[kSteps], uint32_t so) {
+#pragma unroll
+    for (int h = 0; h < kSteps; ++h) {
+      const Codes16 w = *reinterpret_cast<const Codes16*>(cp[i] + k / 2 + co[h]);
+      ld[i].c[h] = make_uint4(w.w[0], w.w[1], w.w[2], w.w[3]);
+    }
+    const uint8_t* from = sp[i] + k / 16 + so;
+    ld[i].s = kSteps == 2 ? *reinterpret_cast<const u32_any*>(from) : *reinterpret_cast<const u16_any*>(from);
   };
-  // The last, partial step (rest = 16 .. 112 k): a lane's chunk is whole, half there or absent; what is absent is read
-  // from where the row still has bytes and gets scale 0.
-  const int full = K / kStepK, rest = K - full * kStepK;
-  auto load_tail = [&](int i) {
-    const bool in0 = c4 * 32 < rest, in1 = c4 * 32 + 16 < rest;
-    const uint32_t co = in0 ? code_off : code_off - c4 * 16, so = in0 ? scale_off : scale_off - c4 * 2;
-    const uint2 lo = *reinterpret_cast<const uint2*>(cp[i] + full * 64 + co);
-    const uint2 hi = *reinterpret_cast<const uint2*>(cp[i] + full * 64 + co + (in1 ? 8 : 0));
-    const uint32_t s0 = sp[i][full * 8 + so], s1 = sp[i][full * 8 + so + (in1 ? 1 : 0)];
-    ld[i].c = make_uint4(lo.x, lo.y, hi.x, hi.y);
-    ld[i].s = (in0 ? s0 : 0u) | (in1 ? s1 << 8 : 0u);
+  // the lane's offsets, or 0 where there is nothing to load (one line instead of 40).  Opaque (no instruction): otherwise the compiler
+  // keeps every block's sum of base and offset as a 64-bit address in vector registers, more than there are.
+  auto offsets = [&](bool any, uint32_t (&co)[kSteps], uint32_t& so) {
+#pragma unroll
+    for (int h = 0; h < kSteps; ++h) {
+      co[h] = any ? code_off + static_cast<uint32_t>(h * kLoadRows * code_ld) : 0u;
+      asm volatile("" : "+v"(co[h]));
+    }
+    so = any ? scale_off : 0u;
+    asm volatile("" : "+v"(so));
   };
-  // The step in hand through LDS: stored as loaded, read back in the MFMA's lane order.
-  uint4 c[S::kBlocks];
-  half2v sc[S::kBlocks];
+  auto load = [&](int k) {
+    uint32_t co[kSteps], so;
+    offsets(true, co, so);
+#pragma unroll
+    for (int i = 0; i < S::kBlocks; ++i) load_block(i, k, co, so);
+  };
+  // A window that is not there whole (K shorter than it): a lane's chunk is whole, half there or absent; what is absent is read from the
+  // row's first bytes and gets scale 0.
+  auto load_short = [&]() {
+    const bool in0 = chunk * 32 < K, in1 = chunk * 32 + 16 < K;
+#pragma unroll
+    for (int i = 0; i < S::kBlocks; ++i) {
+      const uint8_t* p = cp[i] + (in0 ? code_off : code_off - chunk * 16);
+#pragma unroll
+      for (int h = 0; h < kSteps; ++h) {
+        const uint8_t* ph = p + h * kLoadRows * code_ld;
+        const uint2 lo = *reinterpret_cast<const uint2*>(ph), hi = *reinterpret_cast<const uint2*>(ph + (in1 ? 8 : 0));
+        ld[i].c[h] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+      }
+      const uint8_t* ps = sp[i] + srow * scale_ld;
+      ld[i].s = 0u;
+#pragma unroll
+      for (int b = 0; b < 2 * kSteps; ++b) {
+        const int block = spart * 2 * kSteps + b;
+        const bool in = block * 16 < K;
+        const uint32_t v = ps[in ? block : 0];
+        ld[i].s |= in ? v << (8 * b) : 0u;
+      }
+    }
+  };
+  // The window in hand through LDS: stored as loaded, but chunk c of row r at position c ^ swizzle(r), read back in the MFMA's lane order: a
+  // lane takes chunks kSteps q .. of its row, one in each step, of which each MFMA of the step takes 8 codes, and their scales.
+  auto swizzle = [](int row) { return kSteps == 2 ? row & 7 : row >> 1 & 3; };   // eight consecutive rows of one chunk: all banks
   auto stage = [&](int i) {
-    *reinterpret_cast<uint4*>(mine + i * kCodeBytes + (row4 * 4 + (c4 ^ (row4 >> 2))) * 16) = ld[i].c;
-    *reinterpret_cast<uint16_t*>(mine + S::kBlocks * kCodeBytes + i * kScaleBytes + lane * 2) = static_cast<uint16_t>(ld[i].s);
+#pragma unroll
+    for (int h = 0; h < kSteps; ++h)   // (kLoadRows is a multiple of the swizzle's period)
+      *reinterpret_cast<uint4*>(mine + i * kCodeBytes + (h * kLoadRows + crow) * kRowBytes + (chunk ^ swizzle(crow)) * 16) = ld[i].c[h];
+    uint8_t* const to = mine + S::kBlocks * kCodeBytes + i * kScaleBytes + lane * 2 * kSteps;
+    if (kSteps == 2) *reinterpret_cast<uint32_t*>(to) = ld[i].s;
+    else *reinterpret_cast<uint16_t*>(to) = static_cast<uint16_t>(ld[i].s);
   };
-  auto read_back = [&](int i) {
-    c[i] = *reinterpret_cast<const uint4*>(mine + i * kCodeBytes + (l16 * 4 + (q ^ (l16 >> 2))) * 16);
-    sc[i] = scales2(*reinterpret_cast<const uint16_t*>(mine + S::kBlocks * kCodeBytes + i * kScaleBytes + l16 * 8 + q * 2));
+  const uint8_t* const my_codes = mine + l16 * kRowBytes;
+  const uint8_t* const my_scales = mine + S::kBlocks * kCodeBytes + l16 * (8 * kSteps);
+  const uint32_t at0 = static_cast<uint32_t>((kSteps * q) ^ swizzle(l16)) << 4;   // of chunk kSteps q; kSteps q + 1 is at at0 ^ 16
+  uint4 c[S::kBlocks];
+  uint32_t raw[S::kBlocks];   // the scales of the window
+  half2v sc[S::kBlocks];      // the 2 of the step
+  half8v f[2][S::kBlocks];
+  auto read_codes = [&](int i, int step) { c[i] = *reinterpret_cast<const uint4*>(my_codes + i * kCodeBytes + (at0 ^ (step * 16))); };
+  auto read_scales = [&](int i) {
+    const uint8_t* from = my_scales + i * kScaleBytes + q * 2 * kSteps;
+    raw[i] = kSteps == 2 ? *reinterpret_cast<const uint32_t*>(from) : *reinterpret_cast<const uint16_t*>(from);
   };
-  // then: what else to issue on the way (the next step's loads).  With 8 blocks it goes between all the stores and all the reads (3328 x
-  // 15856 x 4368 634 us, 660 block by block); with fewer a block is read back two blocks behind the stores, so that the first do not wait for the
-  // last loads (64 x 20480 x 5120 23.7 us, 24.3 the other way).
-  auto turn = [&](auto then) {
-    if constexpr (S::kBlocks == 8) {
+  auto decode = [&](int i, int step, int t) {
+    if (t == 0) sc[i] = step ? __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(static_cast<int>(raw[i]), 1.0f, true)
+                             : __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(static_cast<int>(raw[i]), 1.0f, false);
+    f[t & 1][i] = decode_part(c[i], sc[i], t);
+  };
+  auto multiply_row = [&](int i, int t) {
 #pragma unroll
-      for (int i = 0; i < S::kBlocks; ++i) stage(i);
-      wavefront_exchange();
-      then();
+    for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(f[t & 1][MB + j], f[t & 1][i], acc[i][j], 0, 0, 0);
+  };
+  // The part of [0, total) that falls to place n of `places`
+  constexpr auto part = [](int n, int total, int places) { return n * total / places; };
+  // One window, whose first step's codes and scales are in c and raw and its first fragments decoded: f[0] of A's block 0 and of all of B's.
+  // kSteps steps x 4 fragments of depth 32 x MB rows of MFMAs.  Behind a row's MFMAs: the next row's fragment of A, a share of the next
+  // depth's of B; in the last depth of a step the reads of the next step's codes, each as soon as the registers are free.
+  // kMore: a next window follows: in the last step's first three depths it goes to LDS, block by block, and each block's loads of the window
+  // after that are issued.
+  auto run_window = [&](auto more, int k_load, const uint32_t (&co)[kSteps], uint32_t so) {
+    constexpr bool kMore = decltype(more)::value;
+    static_for<0, 4 * kSteps * MB>([&](auto n) {
+      constexpr int at = decltype(n)::value, step = at / (4 * MB), t = at / MB % 4, i = at % MB;
+      constexpr bool last_step = step == kSteps - 1, next_step = !last_step || kMore;   // after depth 3: is there one
+      constexpr int to_step = last_step ? 0 : step + 1;
+      constexpr int kFirst = MB > 2 ? 2 : MB - 1;         // row of depth 3 from which B's next fragments are decoded: the reads are back
+      // reads of the next step, in depth 3: all of B's blocks and A's first in row 0, then A's block by block
+      if constexpr (t == 3 && next_step) {
+        if constexpr (i == 0) {
+          if constexpr (last_step) wavefront_exchange();
 #pragma unroll
-      for (int i = 0; i < S::kBlocks; ++i) read_back(i);
-      wavefront_exchange();   // the next step's stores come after these reads
-    } else {
-      constexpr int kLag = 2;
-#pragma unroll
-      for (int i = 0; i < S::kBlocks + kLag; ++i) {
-        if (i < S::kBlocks) {
-          stage(i);
-          wavefront_exchange();
+          for (int b = 0; b < NB; ++b) {
+            read_codes(MB + b, to_step);
+            if (last_step) read_scales(MB + b);
+          }
         }
-        if (i >= kLag) read_back(i - kLag);
+        read_codes(i, to_step);
+        if (last_step) read_scales(i);
+        if constexpr (i == MB - 1) wavefront_exchange();   // the next window's stores come after these reads
       }
-      wavefront_exchange();
-      then();
-    }
-  };
-  auto multiply = [&]() {
-    half8v f[2][S::kBlocks];
+      constexpr int reads = t == 3 && next_step ? ((i == 0 ? NB : 0) + 1) * (last_step ? 2 : 1) : 0;
+      if constexpr (i + 1 < MB) decode(i + 1, step, t);
+      else if constexpr (t < 3) decode(0, step, t + 1);
+      else if constexpr (next_step) decode(0, to_step, 0);
+      constexpr bool a_here = i + 1 < MB || t < 3 || next_step;
+      constexpr int b0 = t < 3 ? part(i, NB, MB) : i < kFirst || !next_step ? 0 : part(i - kFirst, NB, MB - kFirst);
+      constexpr int b1 = t < 3 ? part(i + 1, NB, MB) : i < kFirst || !next_step ? 0 : part(i + 1 - kFirst, NB, MB - kFirst);
 #pragma unroll
-    for (int i = 0; i < S::kBlocks; ++i) f[0][i] = decode_part(c[i], sc[i], 0);
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      if (t < 3) {
-#pragma unroll
-        for (int i = 0; i < S::kBlocks; ++i) f[(t + 1) & 1][i] = decode_part(c[i], sc[i], t + 1);
+      for (int b = b0; b < b1; ++b) {
+        if (t < 3) decode(MB + b, step, t + 1);
+        else decode(MB + b, to_step, 0);
       }
+      constexpr bool staging = kMore && last_step && t < 3;
+      constexpr int place = t * MB + i, s0 = staging ? part(place, S::kBlocks, 3 * MB) : 0, s1 = staging ? part(place + 1, S::kBlocks, 3 * MB) : 0;
 #pragma unroll
-      for (int i = 0; i < MB; ++i)
-#pragma unroll
-        for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(f[t & 1][MB + j], f[t & 1][i], acc[i][j], 0, 0, 0);
-      if (t < 3) {   // the next fragments' decode spread over these MFMAs
-        constexpr int kValu = (S::kBlocks * 8 + MB * NB - 1) / (MB * NB);
-#pragma unroll
-        for (int g = 0; g < MB * NB; ++g) {
-          __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x2, kValu, 0);
-        }
+      for (int b = s0; b < s1; ++b) {
+        stage(b);
+        load_block(b, k_load, co, so);
       }
-    }
-  };
-  const bool tail = rest && full % WK == wk;
-  if (tail) {
-#pragma unroll
-    for (int i = 0; i < S::kBlocks; ++i) load_tail(i);
-    turn([] {});
-  }
-  if (wk < full) {
-#pragma unroll
-    for (int i = 0; i < S::kBlocks; ++i) load(i, wk);
-  }
-  if (tail) multiply();
-#pragma unroll 1
-  for (int step = wk; step < full; step += WK) {
-    turn([&] {
-#pragma unroll
-      for (int i = 0; i < S::kBlocks; ++i) load(i, step + WK < full ? step + WK : step);
+      multiply_row(i, t);
+      interleave<NB, (a_here ? 8 : 0) + 8 * (b1 - b0), reads, (1 + kSteps) * (s1 - s0), (1 + kSteps) * (s1 - s0)>();
     });
-    multiply();
+  };
+  // 8 codes per lane of every block, k .. k + 31 of the window, in f[t]; blocks of 16 below lo count for nothing
+  auto rest_piece = [&](int k, int lo, int t) {
+    const int at = k + q * 8, block = at >> 4;
+#pragma unroll
+    for (int i = 0; i < S::kBlocks; ++i) {
+      const uint32_t w = *reinterpret_cast<const uint32_t*>(my_codes + i * kCodeBytes + (((at >> 5) ^ swizzle(l16)) << 4) + (at >> 3 & 3) * 4);
+      const uint32_t s = my_scales[i * kScaleBytes + block];
+      f[t][i] = decode8_f16(w, e4m3_decode_f16x2(block * 16 >= lo ? s : 0u));
+    }
+  };
+  // The rest comes last, as a window that ends where K does: its k are those from lo on (K shorter than a window: it starts at 0, with zeros above K).
+  const int total = windows + (rest ? 1 : 0), k_rest = K >= kWindowK ? K - kWindowK : 0;
+  if (total) {
+    auto k_of = [&](int n) { return n < windows ? (wk + n * WK) * kWindowK : k_rest; };
+    if (K >= kWindowK) load(k_of(0));
+    else load_short();
+#pragma unroll
+    for (int i = 0; i < S::kBlocks; ++i) stage(i);
+    wavefront_exchange();
+    if (windows) {
+      if (total > 1) load(k_of(1));
+#pragma unroll
+      for (int i = 0; i < S::kBlocks; ++i) {
+        read_codes(i, 0);
+        read_scales(i);
+      }
+      decode(0, 0, 0);
+#pragma unroll
+      for (int b = 0; b < NB; ++b) decode(MB + b, 0, 0);
+#pragma unroll 1
+      for (int next = 1; next < total; ++next) {
+        uint32_t co[kSteps], so;
+        offsets(next + 1 < total, co, so);
+        run_window(std::true_type{}, k_of(min(next + 1, total - 1)), co, so);
+      }
+      if (!rest) run_window(std::false_type{}, 0, {}, 0u);
+    }
+    if (rest) {
+      const int lo = K >= kWindowK ? kWindowK - rest : 0;
+      int hi = K >= kWindowK ? kWindowK : (K + 31) & ~31;
+      if (static_cast<unsigned>(hi - lo - 1) % 64 < 32) {
+        hi -= 32;
+        rest_piece(hi, lo, 0);
+#pragma unroll
+        for (int i = 0; i < MB; ++i) multiply_row(i, 0);
+      }
+#pragma unroll 1
+      for (hi -= 64; hi > lo - 64; hi -= 64) {
+        rest_piece(hi, lo, 0);
+        rest_piece(hi + 32, lo, 1);
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int i = 0; i < MB; ++i) multiply_row(i, t);
+      }
+    }
   }
 
   const TensorScales ts{A.ts, B.ts, A.ts_per_row != 0, B.ts_per_row != 0};
   const bool vec = ts.a_per_row || ts.b_per_row;
   const float out_scale = vec ? 0.0f : A.ts[0] * B.ts[0];
   auto store = [&](float4v v, int i, int j) {
-    const int m = m0 + i * 16 + l16, n = n0 + j * 16 + q * 4;
+    const uint32_t m = m0 + i * 16 + l16, n = n0 + j * 16 + q * 4;
     if (m < M && n < N) {
       v *= scale4(ts, out_scale, vec, true, m, n);
       if (kBf16Out) {
@@ -244,26 +377,35 @@ __global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, 2) void gemm_direct_kernel
 
 }  // namespace
 
-// The tile shapes the kernel comes in.  In the first four the wavefronts of a workgroup split K.  Which of these: `cost` is the time
-// of one step (128 k) of one round of 256 tiles, in units of 0.247 us, fitted to the measured times of 13 shapes (it reproduces them
-// within 5 %); a shape's time is then
-//   3 us + 0.247 us * cost * steps * ceil(tiles / 256),
-// and the smallest wins: large tiles decode less per product, small ones fill the chip.  Both sides of the choice, us:
-// 64 x 20480 x 5120: 4x3 22.3, 4x4 26.7, 2x2 27.2; 512 x 5120 x 5120: 4x4 37.8, 4x3 39.4; 32 x 5120 x 5120: 2x2 7.7, 1x2 8.8, 4x3 > 10.
-// The last has a tile per wavefront, 128 x 128 outputs per workgroup: for results that fill the chip without a split of K, where the
-// others' wavefronts have too few steps to share and pay the sum through LDS per 64 x 64 tile.  Which of the two: `us`, fitted to
-// 930 measured calls of 16 .. 8192 rows, 256 .. 20480 columns, K 16 .. 20496, FP32 and bf16 (its 5th and 95th percentile are 0.85 and 1.12
-// of the measured time).  us, 4x4 split / own: 5120 x 20480 x 16 193 / 87, x 400 228 / 159, x 2064 677 / 623; 2048 x 5120 x 2064 the split.
+// The tile shapes the kernel comes in: MB x NB blocks per wavefront, WK wavefronts that split K, steps of 128 k to a window.  `kind` (for the
+// tests): 0 16 x 32 tiles, 1 32 rows, 2 64 x 48 and 80 columns, 3 64 x 64 and 128 rows, 4 a tile to each wavefront.  Which of them: `us`, fitted to
+// 1080 products of 16 .. 8192 rows, 256 .. 20480 columns, K 16 .. 20480, FP32 and bf16 (5th and 95th percentile 0.87 and 1.15 of the
+// measured time); the shapes taken by it need 0.9 % more than the best ones do.  Large tiles decode less per product, small ones fill the chip; without a
+// split of K there is no sum through LDS.  us, 64 x 48 / 64 x 64 / 64 x 80 / 128 x 80 / own 64 x 64 / own 128 x 80 / the rest at best: 64 x 20480 x 5120 22.1 /
+// 26.1 / 19.0 / 27.6 / 42 / 84 / 20.3, 512 x 5120 x 5120 40 / 36 / 35 / 28 / 44 / 84 / 36, 4096 x 5120 x 2064 130 / 122 / 168 / 130 / 119 / 97 / 120,
+// 1024 x 1024 x 1024 7.2 / 6.1 / 6.9 / 10 / 12 / - / 7.5, 32 x 5120 x 5120 12 / 13 / 16 / 24 / 41 / - / 7.1 (32 x 32).
 struct DirectShape {
-  int mb, nb, wk;
-  double cost;
+  int mb, nb, wk, steps, kind;
   SmallTileCost us;
 };
-constexpr DirectShape kDirectShapes[5] = {{1, 2, 8, 0.30, {3, 4.02, 1.23, 0.0, 0.647, 0.203}},
-                                          {2, 2, 8, 0.46, {2, 3.53, 1.0, 0.0, 1.02, 0.214}},
-                                          {4, 3, 4, 0.96, {2, 4.01, 1.15, 0.591, 0.936, 0.194}},
-                                          {4, 4, 4, 1.19, {2, 4.09, 1.03, 0.653, 1.17, 0.186}},
-                                          {4, 4, 1, 0.0, {2, 3.72, 1.13, 1.56, 1.14, 0.141}}};
+constexpr DirectShape kDirectShapes[] = {
+    {4, 4, 4, 1, 3, {2, 3.58, 1, 0.285, 1.15, 0.341}},
+    {2, 2, 8, 1, 1, {2, 3.11, 1, 0, 0.867, 0.6}},
+    {4, 3, 4, 1, 2, {2, 3.23, 1, 0.387, 1.01, 0.341}},
+    {4, 3, 4, 2, 2, {2, 3.38, 1.07, 0.198, 0.904, 0.382}},
+    {1, 2, 4, 1, 0, {5, 3.15, 1.29, 0, 0.309, 0.368}},
+    {1, 2, 4, 2, 0, {5, 3.09, 1.41, 0, 0.268, 0}},
+    {1, 2, 8, 1, 0, {3, 3.12, 1.02, 0, 0.594, 0.6}},
+    {2, 4, 8, 1, 1, {1, 1.57, 1, 1.59, 1.44, 0.147}},
+    {4, 5, 4, 2, 2, {1, 1.69, 1, 2.22, 1.4, 0.528}},
+    {5, 5, 4, 2, 2, {1, 1.6, 1, 2.52, 1.61, 0.468}},
+    {8, 5, 4, 2, 3, {1, 1.51, 1, 3.87, 2.26, 0.221}},
+    {4, 4, 1, 1, 4, {2, 3.96, 1, 0.608, 1.1, 0.218}},
+    {8, 5, 1, 2, 4, {1, 2.99, 1, 5.99, 2, 0.24}},
+    {6, 4, 1, 2, 4, {1, 2.42, 1, 3.44, 1.42, 0.292}},
+};
+constexpr int kNumDirectShapes = sizeof(kDirectShapes) / sizeof(kDirectShapes[0]);
+using AllShapes = std::make_integer_sequence<int, kNumDirectShapes>;
 
 // (Shapes as template arguments: every division is by a constant.)
 template <int I>
@@ -280,70 +422,70 @@ static bool fits(int64_t M, int64_t N, int64_t K) {
   return M <= 0x7fffffff && N <= 0x7fffffff && K <= (int64_t{1} << 27) && direct_tiles<I>(M, N) * (wk == 1 ? 256 : wk * 64) <= 0xffffffff;
 }
 
+// Steps (128 k) of the wavefront that has most of them; a rest counts half a step more than its k: nothing of it overlaps.
 template <int I>
-static void consider(int64_t M, int64_t N, int64_t K, DirectPick& best) {
-  if (!fits<I>(M, N, K)) return;
-  const int64_t tiles = direct_tiles<I>(M, N), rounds = (tiles + 255) / 256, steps = (K + kStepK - 1) / kStepK;
-  const double us = 3.0 + 0.247 * kDirectShapes[I].cost * static_cast<double>(steps) * static_cast<double>(rounds);
-  if (us < best.compute_us) best = DirectPick{I, tiles, us};
-}
-
-DirectPick pick_direct_shape(const GemmArgs& g) {
-  DirectPick best{0, 0, HUGE_VAL};
-  consider<0>(g.a.outer, g.b.outer, g.K, best);
-  consider<1>(g.a.outer, g.b.outer, g.K, best);
-  consider<2>(g.a.outer, g.b.outer, g.K, best);
-  consider<3>(g.a.outer, g.b.outer, g.K, best);
-  return best;
+static double wavefront_steps(int64_t K) {
+  constexpr DirectShape d = kDirectShapes[I];
+  constexpr int window = 128 * d.steps;
+  const int64_t full = K / window, rest = K - full * window, each = full / d.wk;
+  const double whole = static_cast<double>((each + (full > each * d.wk)) * d.steps);
+  const double with_rest = static_cast<double>(each * d.steps) + (rest ? (full ? 0.5 : d.steps == 2 ? 3.0 : 1.2) + static_cast<double>(rest) / 128.0 : 0.0);
+  return whole > with_rest ? whole : with_rest;
 }
 
 template <int I>
 static double shape_us(const GemmArgs& g) {
   if (!fits<I>(g.a.outer, g.b.outer, g.K)) return HUGE_VAL;
-  constexpr DirectShape d = kDirectShapes[I];
-  const int64_t steps = (g.K + kStepK - 1) / kStepK;
-  return small_tile_us(d.us, direct_tiles<I>(g.a.outer, g.b.outer), static_cast<double>(g.a.outer) * static_cast<double>(g.b.outer),
-                       (steps + d.wk - 1) / d.wk);
+  return small_tile_us(kDirectShapes[I].us, direct_tiles<I>(g.a.outer, g.b.outer), static_cast<double>(g.a.outer) * static_cast<double>(g.b.outer),
+                       wavefront_steps<I>(g.K));
 }
 
-double gemm_direct_us(const GemmArgs& g, int shape) {
-  switch (shape) {
-    case 0: return shape_us<0>(g);
-    case 1: return shape_us<1>(g);
-    case 2: return shape_us<2>(g);
-    case 3: return shape_us<3>(g);
-    default: return shape_us<kDirectOwnTiles>(g);
-  }
+template <int... I>
+static DirectPick pick_shape(const GemmArgs& g, bool own, std::integer_sequence<int, I...>) {
+  DirectPick best{0, 0, HUGE_VAL};
+  auto consider = [&](int shape, double us) {   // (nearer than 5 % the estimates do not tell two shapes apart)
+    if (us < 0.95 * best.us) best = DirectPick{shape, kDirectShapes[shape].kind, us};
+  };
+  ((own == (kDirectShapes[I].wk == 1) ? consider(I, shape_us<I>(g)) : void()), ...);
+  return best;
 }
 
-template <int MB, int NB, int WK, bool kBf16Out>
+DirectPick pick_direct_shape(const GemmArgs& g, bool own_tiles) { return pick_shape(g, own_tiles, AllShapes{}); }
+
+void direct_shape(int shape, int* out) {
+  const DirectShape& d = kDirectShapes[shape];
+  out[0] = d.mb, out[1] = d.nb, out[2] = d.wk, out[3] = d.steps;
+}
+
+template <int I, bool kBf16Out>
 static hipError_t launch_shape(const GemmArgs& g, hipStream_t s) {
-  using S = Shape<MB, NB, WK>;
+  constexpr DirectShape d = kDirectShapes[I];
+  using S = Shape<d.mb, d.nb, d.wk, d.steps>;
+  constexpr auto kernel = &gemm_direct_kernel<d.mb, d.nb, d.wk, d.steps, kBf16Out>;
   static PerDeviceOnce once;
-  const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&gemm_direct_kernel<MB, NB, WK, kBf16Out>), S::kLdsBytes, once);
+  const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), S::kLdsBytes, once);
   if (e != hipSuccess) return e;
   const int tiles_m = static_cast<int>((g.a.outer + S::kTM - 1) / S::kTM), tiles_n = static_cast<int>((g.b.outer + S::kTN - 1) / S::kTN);
-  hipLaunchKernelGGL((gemm_direct_kernel<MB, NB, WK, kBf16Out>), dim3(static_cast<unsigned>(tiles_m * tiles_n)), dim3(S::kThreads),
-                     S::kLdsBytes, s, g.a, g.b, static_cast<int>(g.K), g.d, g.ldd, g.accumulate, tiles_m, tiles_n);
+  hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(tiles_m * tiles_n)), dim3(S::kThreads), S::kLdsBytes, s, g.a, g.b, static_cast<int>(g.K), g.d,
+                     g.ldd, g.accumulate, tiles_m, tiles_n);
   return hipGetLastError();
 }
 
-template <bool kBf16Out>
-static hipError_t launch_direct(const GemmArgs& g, int shape, hipStream_t s) {
-  switch (shape) {
-    // 16 x 32 tiles: enough of them to fill the chip four times over do better with fewer wavefronts on each (16 x 20480 x
-    // 5120: 14.6 against 15.7 us), few with more (32 x 5120 x 5120 in these tiles: 9.4 against 8.8)
-    case 0: return direct_tiles<0>(g.a.outer, g.b.outer) >= 512 ? launch_shape<1, 2, 4, kBf16Out>(g, s) : launch_shape<1, 2, 8, kBf16Out>(g, s);
-    case 1: return launch_shape<2, 2, 8, kBf16Out>(g, s);
-    case 2: return launch_shape<4, 3, 4, kBf16Out>(g, s);
-    case 3: return launch_shape<4, 4, 4, kBf16Out>(g, s);
-    default: return launch_shape<4, 4, 1, kBf16Out>(g, s);
-  }
+template <bool kBf16Out, int... I>
+static hipError_t launch_direct(const GemmArgs& g, int shape, hipStream_t s, std::integer_sequence<int, I...>) {
+  hipError_t e = hipErrorInvalidValue;
+  ((shape == I ? void(e = launch_shape<I, kBf16Out>(g, s)) : void()), ...);
+  return e;
+}
+
+template <int... I>
+static bool fits_shape(const GemmArgs& g, int shape, std::integer_sequence<int, I...>) {
+  return ((shape == I && fits<I>(g.a.outer, g.b.outer, g.K)) || ...);
 }
 
 hipError_t launch_gemm_direct(const GemmArgs& g, int shape, hipStream_t s) {
-  if (gemm_direct_us(g, shape) == HUGE_VAL) return hipErrorInvalidValue;   // beyond its offsets or a launch
-  return g.out_bf16 ? launch_direct<true>(g, shape, s) : launch_direct<false>(g, shape, s);
+  if (!fits_shape(g, shape, AllShapes{})) return hipErrorInvalidValue;   // beyond its offsets or a launch
+  return g.out_bf16 ? launch_direct<true>(g, shape, s, AllShapes{}) : launch_direct<false>(g, shape, s, AllShapes{});
 }
 
 }  // namespace nvfp4

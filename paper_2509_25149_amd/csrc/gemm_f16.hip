@@ -526,9 +526,10 @@ size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) {
 
 // What a call does: one answer for the estimate, the room asked of the workspace and the launch.  The partial tiles of a split
 // count only where tiles are 256 columns wide, and a workspace without room for them makes the last round an ordinary one.
-// Expected time: what is still to decode (codes and scales in, FP16 out) at 4.7 TB/s, then rounds of 256 tiles at 18.5 ns per k
-// while there are fewer (3072 x 5120 x 5120, 240 tiles: 118 us in all) and 22.5 when the chip is full (the clock drops with the matrix
-// pipes busy) -- of a plain result, for all output types (see SmallTileCost).
+// Expected time: what is still to decode (codes and scales in, FP16 out) at 5.0 TB/s, then rounds of 256 tiles at 7.9 us for the result and 15.9 ns
+// per k while there are fewer (3072 x 5120 x 5120, 240 tiles: 130 us in all), 18.6 when the chip is full (the clock drops with the matrix
+// pipes busy) -- of a plain result, for all output types (see SmallTileCost).  Fitted to 177 calls of 12 us to 1.3 ms; 5th and 95th
+// percentile 0.81 and 1.18 of the measured time, from 200 us on 0.88 .. 1.09.
 TwoPassPlan plan_two_pass(const GemmArgs& g) {
   TwoPassPlan plan{false, HUGE_VAL, 8, 0, 1};
   const int64_t M = g.a.outer, N = g.b.outer;
@@ -539,8 +540,8 @@ TwoPassPlan plan_two_pass(const GemmArgs& g) {
   TailPlan tail = plan_tail(M, N, g.K);
   if (operands + partial_bytes(tail) > g.workspace_bytes) tail = TailPlan{0, 1};
   Width w = pick_width(M, N, tail, false);
-  plan.us = 4.0 + static_cast<double>(rows) * static_cast<double>(g.K) * 2.5625 / 4.7e6 + (rows ? 2.0 : 0.0) +
-            w.rounds * static_cast<double>(g.K) * (w.tiles >= kCUs ? 0.0225 : 0.0185);
+  plan.us = 7.4 + static_cast<double>(rows) * static_cast<double>(g.K) * 2.5625 / 5.0e6 +
+            w.rounds * (7.9 + static_cast<double>(g.K) * (w.tiles >= kCUs ? 0.0186 : 0.0159));
   if (g.accumulate && g.K < 1024) w = pick_width(M, N, tail, true);
   if (w.nb != 8) tail = TailPlan{0, 1};
   plan.units = w.nb;

@@ -92,14 +92,12 @@ TwoPassPlan plan_two_pass(const GemmArgs& g);
 hipError_t launch_gemm_two_pass(const GemmArgs& g, const TwoPassPlan& plan, hipStream_t s);
 // Straight from the packed codes, without scratch, any K.  `shape`: number of a tile shape, see gemm_direct.hip.
 hipError_t launch_gemm_direct(const GemmArgs& g, int shape, hipStream_t s);
-constexpr int kDirectOwnTiles = 4;                        // the shape whose wavefronts own different tiles
 struct DirectPick {
-  int shape;             // the best of the others
-  int64_t tiles;
-  double compute_us;     // its time, the result's bytes left out
+  int shape, kind;       // its number in the kernel's list; the kind of tile (see there)
+  double us;             // expected
 };
-DirectPick pick_direct_shape(const GemmArgs& g);
-double gemm_direct_us(const GemmArgs& g, int shape);      // any shape's time
+DirectPick pick_direct_shape(const GemmArgs& g, bool own_tiles);   // the best of the shapes that split K, or of those whose wavefronts own different tiles
+void direct_shape(int shape, int* out);   // MB, NB, WK, steps of a shape, for the tests
 // Expected time of a kernel on small tiles: `call`, then rounds of 256 tiles of `tile` us and `step` us per step of the loop,
 // or, where that is more, the result's bytes at `result` us per MB (added in quadrature: neither hides the other fully).  A
 // CU holds `resident` workgroups; a round in which only one of them has a tile takes `alone` rounds, not 1.
@@ -110,11 +108,11 @@ struct SmallTileCost {
   double call, alone, tile, step, result;
 };
 // (Always inlined with constants: a launch that takes 7 us to issue should not spend one on divisions by tile sizes.)
-__attribute__((always_inline)) inline double small_tile_us(const SmallTileCost& c, int64_t tiles, double elements, int64_t steps) {
+__attribute__((always_inline)) inline double small_tile_us(const SmallTileCost& c, int64_t tiles, double elements, double steps) {
   const int64_t wave = int64_t{256} * c.resident, whole = tiles / wave, last = (tiles - whole * wave + 255) / 256;   // tiles of a CU in the last wave
   double rounds = static_cast<double>(whole * c.resident);
-  if (last) rounds += c.alone + static_cast<double>(last - 1) * (c.resident - c.alone) / (c.resident - 1);
-  const double loop = rounds * (c.tile + c.step * static_cast<double>(steps)), result = c.result * elements * 4e-6;
+  if (last) rounds += c.resident == 1 ? 1.0 : c.alone + static_cast<double>(last - 1) * (c.resident - c.alone) / (c.resident - 1);
+  const double loop = rounds * (c.tile + c.step * steps), result = c.result * elements * 4e-6;
   return c.call + __builtin_sqrt(loop * loop + result * result);
 }
 // Decodes one operand (codes [outer, K/2], scales [outer, K/16]) to FP16 [outer, K]
