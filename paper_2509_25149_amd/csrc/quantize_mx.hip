@@ -4,15 +4,20 @@
 // Sec. 5: a 32-point random Hadamard rotation on the Wgrad operands).
 //
 // There is no tensor-level scale, so one pass over the tensor is enough.
-// Work decomposition: a lane owns 32 rows x 8 columns (thirty-two 128-bit loads);
-// a wavefront owns 32 rows x 512 columns; a 256-thread workgroup 128 rows x 512
-// columns.  A row-copy block (32 columns of one row) is four neighbouring lanes
-// (two cross-lane maxima); a col-copy block (32 rows of one column) and the whole
-// 32-point butterfly live in one lane's registers.  Row codes leave as one dword
-// per lane and row; everything else is staged in LDS and written back as
+// Work decomposition: a lane owns 16 rows x 8 columns (sixteen 128-bit loads); a wavefront 32 rows x 256 columns,
+// rows 0 - 15 in its lower half and 16 - 31 in its upper; a 256-thread workgroup 128 rows x 256 columns.  A row-copy
+// block (32 columns of one row) is four neighbouring lanes (two cross-lane maxima).  A col-copy block (32 rows of one
+// column) is a lane and its counterpart 32 lanes on: stages h = 1 .. 8 of the 32-point butterfly run in each, then
+// v_permlane32_swap_b32 exchanges half of the values -- after it a lane holds both partners of eight pairs (i, i + 16), rows
+// i = 0 - 7 and 16 - 23 in the lower half, 8 - 15 and 24 - 31 in the upper -- and stage 16 runs in each again.  Row codes leave as
+// one dword per lane and row; everything else is staged in LDS and written back as
 // contiguous pieces (64 bytes of codes per column per workgroup).  (Non-temporal stores of the codes made
 // the calls by themselves faster -- X 8192 x 5120 47 -> 41 us -- but the GEMM behind them, which reads the codes as they are, slower by
 // more: training step 4096 x 5120 x 5120 289 -> 302 us.)
+// What bounds it: up to one round of workgroups the chain load - rotate - maximum - codes - store of one patch, beyond that memory (8192 x 20480
+// 523 MB in 129 us, 4.1 TB/s) and with stochastic rounding the vector pipe.  A lane used to own all 32 rows of 8 columns (171 - 188 registers, two
+// wavefronts per SIMD; now 110 - 128 and four), us per call: X 4096 x 5120 28.7 -> 21.4, with stochastic rounding 41.5 -> 28.1; X 8192 x 5120 43.6 -> 34.7,
+// 60.6 -> 47.2; 8192 x 20480 149 -> 129, 198 -> 154; 256 x 512 11.0 -> 7.1, 14.2 -> 9.0.
 //
 // Random draws: the row copy uses the NVFP4 draws (counter (j / 8, i, 0, 0)); the
 // col copy draws its own, counter (i / 8, j, 1, 0), word (i % 8) / 2, low half for
@@ -25,10 +30,8 @@ namespace nvfp4 {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kWaveCols = 512;
-constexpr int kRowsPerWave = 32;
-constexpr int kRowsPerBlock = 128;
-constexpr int kSlot = 65;   // lanes per staging row, padded
+constexpr int kTileCols = 256, kTileRows = 128;
+constexpr int kSlot = 33;   // column octets per staging row, padded
 
 // amax_b / 6 rounded up to a power of two 2^e, e clamped to [-127, 127] (App. B.4).
 // Returns the stored byte e + 127 and the exact encode factor 2^-e.
@@ -83,42 +86,49 @@ __device__ __forceinline__ float elem(const uint4& q, int c) {
   return (c & 1) ? bf16_hi(w) : bf16_lo(w);
 }
 
+// v of this lane, v of the lane 32 on (or back)
+__device__ __forceinline__ float max_of_halves(float v) {
+  const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(s[0]), __uint_as_float(s[1]));
+}
+
 // kSplit: the two copies are made by two sets of workgroups (blockIdx.z).
 template <bool kRow, bool kCol, bool kRht, bool kSR, bool kSplit>
-__global__ __launch_bounds__(kThreads) void quantize_mx_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
-                                                               int64_t ld, uint32_t sign_mask, uint32_t key0, uint32_t key1,
-                                                               uint8_t* __restrict__ row_codes, uint8_t* __restrict__ row_scales,
-                                                               float* __restrict__ row_ts, uint8_t* __restrict__ col_codes,
-                                                               uint8_t* __restrict__ col_scales, float* __restrict__ col_ts) {
-  __shared__ __attribute__((aligned(16))) uint8_t st_col_codes[8 * 4 * kSlot * 16];   // [column of the lane][wavefront][lane] x 16 bytes
-  __shared__ uint8_t st_col_scales[8 * 4 * 64];                                       // [column of the lane][wavefront][lane]
-  __shared__ __attribute__((aligned(16))) uint8_t st_row_scales[4 * kRowsPerWave * 16];   // [wavefront][row][16 blocks]
+__global__ __launch_bounds__(kThreads, 4) void quantize_mx_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
+                                                                  int64_t ld, uint32_t sign_mask, uint32_t key0, uint32_t key1,
+                                                                  uint8_t* __restrict__ row_codes, uint8_t* __restrict__ row_scales,
+                                                                  float* __restrict__ row_ts, uint8_t* __restrict__ col_codes,
+                                                                  uint8_t* __restrict__ col_scales, float* __restrict__ col_ts) {
+  __shared__ __attribute__((aligned(16))) uint8_t st_col_codes[kCol ? 8 * 4 * kSlot * 16 : 16];   // [column of the lane][wavefront][lane % 32] x 16 bytes, 8 of each half
+  __shared__ uint8_t st_col_scales[kCol ? 8 * 4 * 32 : 16];                                      // [column of the lane][wavefront][lane % 32]
+  __shared__ __attribute__((aligned(16))) uint8_t st_row_scales[kRow ? kTileRows * 8 : 16];      // [row][8 blocks]
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t colblk = static_cast<int64_t>(blockIdx.x) * kWaveCols;
-  const int64_t col0 = colblk + lane * 8;
-  const int64_t rowblk = static_cast<int64_t>(blockIdx.y) * kRowsPerBlock;
-  const int64_t row0 = rowblk + wave * kRowsPerWave;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, half = lane >> 5;
+  const int64_t colblk = static_cast<int64_t>(blockIdx.x) * kTileCols;
+  const int64_t col0 = colblk + l32 * 8;
+  const int64_t rowblk = static_cast<int64_t>(blockIdx.y) * kTileRows;
+  const int row_in = wave * 32 + half * 16;   // the lane's first row within the tile
+  const int64_t row0 = rowblk + row_in;
   if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) {
     // MXFP4 has no tensor-level scale: s_dec = 1; the amax slot is not computed.
     if (kRow) { row_ts[0] = 1.0f; row_ts[1] = 0.0f; }
     if (kCol) { col_ts[0] = 1.0f; col_ts[1] = 0.0f; }
   }
-  const bool active = col0 < cols && row0 < rows;   // cols and rows are multiples of 32: whole patches only
+  const bool active = col0 < cols && row0 < rows;   // cols and rows are multiples of 32: both halves of a block or none
 
-  uint4 raw[32];
+  uint4 raw[16];
   if (active) {
 #pragma unroll
-    for (int r = 0; r < 32; ++r) raw[r] = *reinterpret_cast<const uint4*>(x + (row0 + r) * ld + col0);
+    for (int r = 0; r < 16; ++r) raw[r] = *reinterpret_cast<const uint4*>(x + (row0 + r) * ld + col0);
   } else {
 #pragma unroll
-    for (int r = 0; r < 32; ++r) raw[r] = make_uint4(0u, 0u, 0u, 0u);
+    for (int r = 0; r < 16; ++r) raw[r] = make_uint4(0u, 0u, 0u, 0u);
   }
 
   const bool do_row = kRow && (!kSplit || blockIdx.z == 0), do_col = kCol && (!kSplit || blockIdx.z == 1);
   if (do_row) {
 #pragma unroll   // fully: a partly unrolled loop indexes raw[] at run time, which puts the whole patch in scratch memory
-    for (int r = 0; r < 32; ++r) {
+    for (int r = 0; r < 16; ++r) {
       float v[8];
 #pragma unroll
       for (int c = 0; c < 8; ++c) v[c] = elem(raw[r], c);
@@ -136,62 +146,91 @@ __global__ __launch_bounds__(kThreads) void quantize_mx_kernel(const uint16_t* _
       const uint32_t codes = encode8<kSR>(v, dr);
       if (active) {
         *reinterpret_cast<uint32_t*>(row_codes + (row0 + r) * (cols / 2) + col0 / 2) = codes;
-        if ((lane & 3) == 0) st_row_scales[(wave * kRowsPerWave + r) * 16 + (lane >> 2)] = static_cast<uint8_t>(sc);
+        if ((lane & 3) == 0) st_row_scales[(row_in + r) * 8 + (l32 >> 2)] = static_cast<uint8_t>(sc);
       }
-      // keep the scheduler from interleaving all 32 rows' temporaries on top of the 128 registers of the patch
-      if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+      // keep the scheduler from interleaving all rows' temporaries on top of the registers of the patch
+      if ((r & 3) == 3 || kSR) __builtin_amdgcn_sched_barrier(0);
     }
   }
 
   if (kRow && kCol) {
     // Opaque to the optimiser (no instruction emitted): otherwise it recognises the row pass's unpacked values
-    // in the column pass and keeps all 256 of them alive on top of the 128 registers of the patch.
+    // in the column pass and keeps all of them alive on top of the registers of the patch.
 #pragma unroll
-    for (int r = 0; r < 32; ++r) asm volatile("" : "+v"(raw[r].x), "+v"(raw[r].y), "+v"(raw[r].z), "+v"(raw[r].w));
+    for (int r = 0; r < 16; ++r) asm volatile("" : "+v"(raw[r].x), "+v"(raw[r].y), "+v"(raw[r].z), "+v"(raw[r].w));
   }
   if (do_col) {
+    if (kRht) {   // the sign diagonal, on two columns at a time
+      const uint32_t signs = half ? sign_mask >> 16 : sign_mask;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const uint32_t flip = (0u - (signs >> r & 1u)) & 0x80008000u;
+        raw[r].x ^= flip, raw[r].y ^= flip, raw[r].z ^= flip, raw[r].w ^= flip;
+      }
+    }
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
-      float w[32];
+      // w[0 .. 15]: the lane's rows; with a rotation, after the exchange: w[i], w[i + 8] = rows i and i + 16 (lower half) or i + 8 and i + 24 (upper)
+      float w[16];
 #pragma unroll
-      for (int r = 0; r < 32; ++r) w[r] = elem(raw[r], c);
-      if (kRht) rht32(w, sign_mask);
+      for (int r = 0; r < 16; ++r) w[r] = elem(raw[r], c);
+      if (kRht) {
+#pragma unroll
+        for (int h = 1; h < 16; h <<= 1) {
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            if ((i & h) == 0) {
+              const float a = w[i], b = w[i + h];
+              w[i] = a + b;
+              w[i + h] = a - b;
+            }
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(w[i]), __float_as_uint(w[i + 8]), false, false);
+          const float a = __uint_as_float(s[0]), b = __uint_as_float(s[1]);
+          w[i] = 0.176776695296636893f * (a + b);
+          w[i + 8] = 0.176776695296636893f * (a - b);
+        }
+      }
       float m = 0.0f;
 #pragma unroll
-      for (int r = 0; r < 32; ++r) m = fmaxf(m, fabsf(w[r]));
+      for (int r = 0; r < 16; ++r) m = fmaxf(m, fabsf(w[r]));
+      m = max_of_halves(m);
       float inv;
       const uint32_t sc = ue8m0_scale(m, inv);
-      uint32_t out[4];
+      uint2 out;
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
+      for (int g = 0; g < 2; ++g) {   // eight consecutive rows each: groups half and half + 2 of the block's four, unrotated 2 half and 2 half + 1
         float v[8];
 #pragma unroll
         for (int t = 0; t < 8; ++t) v[t] = w[8 * g + t] * inv;
         uint32_t dr[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        if (kSR) draws8(static_cast<uint32_t>((row0 >> 3) + g), static_cast<uint32_t>(col0 + c), 1u, key0, key1, dr);
-        out[g] = encode8<kSR>(v, dr);
+        const int group = kRht ? half + 2 * g : 2 * half + g;
+        if (kSR) draws8(static_cast<uint32_t>((rowblk >> 3) + wave * 4 + group), static_cast<uint32_t>(col0 + c), 1u, key0, key1, dr);
+        (g ? out.y : out.x) = encode8<kSR>(v, dr);
       }
-      *reinterpret_cast<uint4*>(st_col_codes + ((c * 4 + wave) * kSlot + lane) * 16) = make_uint4(out[0], out[1], out[2], out[3]);
-      st_col_scales[(c * 4 + wave) * 64 + lane] = static_cast<uint8_t>(sc);
+      *reinterpret_cast<uint2*>(st_col_codes + ((c * 4 + wave) * kSlot + l32) * 16 + half * 8) = out;
+      if (half == 0) st_col_scales[(c * 4 + wave) * 32 + l32] = static_cast<uint8_t>(sc);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
   __syncthreads();
 
-  const int tile_cols = static_cast<int>(cols - colblk < kWaveCols ? cols - colblk : kWaveCols);
-  const int tile_groups = static_cast<int>((rows - rowblk < kRowsPerBlock ? rows - rowblk : kRowsPerBlock) / 32);   // 32-row groups in this tile
-  if (do_row) {
-    // 128 rows x (tile_cols / 32) scale bytes; a full tile row is 16 contiguous bytes
-    const int r = tid & 127, half = tid >> 7;   // two threads per row, 8 bytes each
-    const int64_t row = rowblk + r;
+  const int tile_cols = static_cast<int>(cols - colblk < kTileCols ? cols - colblk : kTileCols);
+  const int tile_groups = static_cast<int>((rows - rowblk < kTileRows ? rows - rowblk : kTileRows) / 32);   // 32-row groups in this tile
+  if (do_row && tid < kTileRows) {
+    // 128 rows x (tile_cols / 32) scale bytes; a full tile row is 8 contiguous bytes
+    const int64_t row = rowblk + tid;
     if (row < rows) {
-      const uint8_t* src = st_row_scales + r * 16 + half * 8;
-      uint8_t* dst = row_scales + row * (cols / 32) + colblk / 32 + half * 8;
-      const int nb = tile_cols / 32 - half * 8;
-      if (nb >= 8 && ((cols / 32) & 7) == 0) {
+      const uint8_t* src = st_row_scales + tid * 8;
+      uint8_t* dst = row_scales + row * (cols / 32) + colblk / 32;
+      const int nb = tile_cols / 32;
+      if (nb == 8 && ((cols / 32) & 7) == 0) {
         *reinterpret_cast<uint2*>(dst) = *reinterpret_cast<const uint2*>(src);
       } else {
-        for (int b = 0; b < nb && b < 8; ++b) dst[b] = src[b];
+        for (int b = 0; b < nb; ++b) dst[b] = src[b];
       }
     }
   }
@@ -199,12 +238,13 @@ __global__ __launch_bounds__(kThreads) void quantize_mx_kernel(const uint16_t* _
     const int64_t code_ld = rows / 2, scale_ld = rows / 32;
     const bool wide = (code_ld & 15) == 0;
 #pragma unroll 1
-    for (int i = 0; i < 8; ++i) {
-      const int q = i * kThreads + tid;   // 2048 pieces of 16 bytes: column j, 32-row group g
+    for (int i = 0; i < 4; ++i) {
+      const int q = i * kThreads + tid;   // 1024 pieces of 16 bytes: column j, 32-row group g
       const int j = q >> 2, g = q & 3;
       if (j >= tile_cols || g >= tile_groups) continue;
       const int lj = j >> 3, c = j & 7;
-      const uint4 v = *reinterpret_cast<const uint4*>(st_col_codes + ((c * 4 + g) * kSlot + lj) * 16);
+      uint4 v = *reinterpret_cast<const uint4*>(st_col_codes + ((c * 4 + g) * kSlot + lj) * 16);
+      if (kRht) v = make_uint4(v.x, v.z, v.y, v.w);   // staged as groups 0, 2 | 1, 3
       uint8_t* dst = col_codes + (colblk + j) * code_ld + (rowblk + 32 * g) / 2;
       if (wide) {
         *reinterpret_cast<uint4*>(dst) = v;
@@ -215,23 +255,31 @@ __global__ __launch_bounds__(kThreads) void quantize_mx_kernel(const uint16_t* _
         reinterpret_cast<uint32_t*>(dst)[3] = v.w;
       }
     }
-#pragma unroll 1
-    for (int i = 0; i < 2; ++i) {
-      const int j = i * kThreads + tid;   // one column: up to 4 scale bytes
-      if (j >= tile_cols) continue;
-      const int lj = j >> 3, c = j & 7;
-      uint8_t* dst = col_scales + (colblk + j) * scale_ld + rowblk / 32;
-      for (int g = 0; g < tile_groups; ++g) dst[g] = st_col_scales[(c * 4 + g) * 64 + lj];
+    if (tid < tile_cols) {   // one column: up to 4 scale bytes
+      const int lj = tid >> 3, c = tid & 7;
+      uint8_t* dst = col_scales + (colblk + tid) * scale_ld + rowblk / 32;
+      uint8_t sc[4];
+#pragma unroll
+      for (int g = 0; g < 4; ++g) sc[g] = st_col_scales[(c * 4 + g) * 32 + lj];
+      if (tile_groups == 4 && (scale_ld & 3) == 0) {
+        *reinterpret_cast<uint32_t*>(dst) = sc[0] | (sc[1] << 8) | (sc[2] << 16) | (static_cast<uint32_t>(sc[3]) << 24);
+      } else {
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          if (g < tile_groups) dst[g] = sc[g];
+      }
     }
   }
 }
 
 template <bool kRow, bool kCol, bool kRht>
 void dispatch(const QuantizeArgs& a, dim3 grid, hipStream_t s) {
-  // Up to 256 workgroups (one per CU) the call takes as long as one patch does: each copy gets workgroups of its own, though the
-  // patch is then read twice.  us, one set / two: X 256 x 512 15.8 / 12.7, X 1024 x 2048 16.4 / 12.4, dY SR 1024 x 2048 23.1 / 14.0.
+  // Up to 768 workgroups (of the 1024 that are resident at once) the call takes as long as a patch or two do: each copy gets workgroups of its own, though
+  // the patch is then read twice.  us, one set / two: X 4096 x 4096 (512) 18.8 / 17.4, X 4096 x 5120 (640) 23.3 / 21.4, with stochastic rounding 32.6 /
+  // 28.2; X 8192 x 5120 (1280) 34.7 / 41.2, 47.1 / 50.3.
   constexpr bool kBoth = kRow && kCol;
-  const bool split = kBoth && static_cast<int64_t>(grid.x) * grid.y <= 256;
+  constexpr int64_t kTwoSets = 768;
+  const bool split = kBoth && static_cast<int64_t>(grid.x) * grid.y <= kTwoSets;
   if (split) grid.z = 2;
   const auto kernel = a.sr ? (split ? &quantize_mx_kernel<kRow, kCol, kRht, true, kBoth> : &quantize_mx_kernel<kRow, kCol, kRht, true, false>)
                            : (split ? &quantize_mx_kernel<kRow, kCol, kRht, false, kBoth> : &quantize_mx_kernel<kRow, kCol, kRht, false, false>);
@@ -242,8 +290,8 @@ void dispatch(const QuantizeArgs& a, dim3 grid, hipStream_t s) {
 }  // namespace
 
 hipError_t launch_quantize_mx(const QuantizeArgs& a, hipStream_t s) {
-  const dim3 grid(static_cast<unsigned>((a.cols + kWaveCols - 1) / kWaveCols),
-                  static_cast<unsigned>((a.rows + kRowsPerBlock - 1) / kRowsPerBlock));
+  const dim3 grid(static_cast<unsigned>((a.cols + kTileCols - 1) / kTileCols),
+                  static_cast<unsigned>((a.rows + kTileRows - 1) / kTileRows));
   if (a.want_row && a.want_col) {
     if (a.rht) dispatch<true, true, true>(a, grid, s); else dispatch<true, true, false>(a, grid, s);
   } else if (a.want_row) {
