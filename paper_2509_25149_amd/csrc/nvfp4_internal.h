@@ -50,6 +50,12 @@ struct QuantizeArgs {
 hipError_t launch_quantize(const QuantizeArgs& a, hipStream_t s);
 // NVFP4 with a 32- or 128-point rotation of the col copy (rotation groups span several 16-row groups)
 hipError_t launch_quantize_wide(const QuantizeArgs& a, hipStream_t s);
+// the two passes for small tensors (quantize_small.hip)
+uint32_t small_amax_workgroups(const QuantizeArgs& a);
+template <int kRht>
+void launch_amax_small(const QuantizeArgs& a, hipStream_t s);
+template <bool kRow, bool kCol, int kRht>
+void launch_cast_small(const QuantizeArgs& a, const uint32_t* maxima, uint32_t n_maxima, hipStream_t s);
 // NVFP4 with the row copy rotated as well (row_rht; the col copy absent, plain or rotated with d = 16)
 hipError_t launch_quantize_rowrot(const QuantizeArgs& a, hipStream_t s);
 // MXFP4 mode (1x32 blocks, UE8M0 scales, one pass, no workspace); sign_mask holds 32 bits

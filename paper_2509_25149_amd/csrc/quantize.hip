@@ -315,40 +315,54 @@ static AmaxWork amax_work(const QuantizeArgs& a) {
   return w;
 }
 
+// Up to 176 tiles of 128 x 256 the kernels with less work per lane (quantize_small.hip): a call takes as long as one lane's chain does.  us per call, this
+// cast pass / those: X 256 x 512 10.5 / 6.8, X 2048 x 2048 (128 tiles) 11.5 / 9.8, X 4096 x 1040 (160) 13.7 / 12.8, X 2048 x 4096 (256) 14.1 / 16.4;
+// stochastic rounding 12.7 / 7.7, 13.6 / 12.4, 17.2 / 16.2, 17.7 / 20.8; the row copy alone 64 x 5120 8.1 / 5.9, 2048 x 4096 10.6 / 11.0.
+static bool is_small(const QuantizeArgs& a) { return ((a.cols + 255) / 256) * ((a.rows + 127) / 128) <= 176; }
+
 template <bool kRow, bool kCol, int kRht, bool kSR, bool k2D>
-static void launch_cast(const QuantizeArgs& a, hipStream_t s) {
+static void launch_cast(const QuantizeArgs& a, const uint32_t* maxima, uint32_t n_maxima, hipStream_t s) {
   using T = CastTile<kCachedLoads>;   // the tile is the same for all
   const unsigned gx = static_cast<unsigned>((a.cols + T::kCols - 1) / T::kCols), gy = static_cast<unsigned>((a.rows / 16 + T::kGroups - 1) / T::kGroups);
   // Up to 256 workgroups (one per CU) the call takes as long as one patch does: each copy gets workgroups of its own, though the
-  // patch is then read twice.  us, one set / two: X 256 x 512 12.9 / 10.6, dY SR 256 x 512 15.7 / 11.9, X 2048 x 4096 (256 workgroups)
-  // 15.0 / 12.9, dY 4096 x 4096 (512) 28.4 / 31.8.  16x16 blocks have little work per patch: 2048 x 4096 10.3 / 10.8.
+  // patch is then read twice.  us, one set / two: X 2048 x 4096 (256 workgroups) 15.0 / 12.9, dY 4096 x 4096 (512) 28.4 / 31.8.  16x16 blocks have
+  // little work per patch: 2048 x 4096 10.3 / 10.8.
   const dim3 grid(gx, gy, kRow && kCol && !k2D && static_cast<int64_t>(gx) * gy <= 256 ? 2 : 1);
-  const uint32_t* maxima = a.do_amax ? a.ws + kWsHeader : a.ws;
   const CastMemory m = cast_memory(a);
   const auto kernel = m == kCachedLoads     ? &cast_kernel<kRow, kCol, kRht, kSR, k2D, kCachedLoads>
                       : m == kStreamedLoads ? &cast_kernel<kRow, kCol, kRht, kSR, k2D, kStreamedLoads>
                                             : &cast_kernel<kRow, kCol, kRht, kSR, k2D, kStreamedLoadsCachedStores>;
   hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s,
-                     static_cast<const uint16_t*>(a.x), a.rows, a.cols, a.ld, maxima, a.do_amax ? amax_work(a).workgroups : 1u, a.sign_mask, a.key0,
+                     static_cast<const uint16_t*>(a.x), a.rows, a.cols, a.ld, maxima, n_maxima, a.sign_mask, a.key0,
                      a.key1, a.row_codes, a.row_scales, a.row_ts, a.col_codes, a.col_scales, a.col_ts, cast_walk(a));
 }
 
 template <bool kRow, bool kCol, int kRht>
 static void launch_passes(const QuantizeArgs& a, hipStream_t s) {
+  uint32_t n_maxima = 1;
   if (a.do_amax) {
-    const AmaxWork w = amax_work(a);
-    hipLaunchKernelGGL((amax_kernel<kRht>), dim3(w.workgroups), dim3(kThreads), 0, s, static_cast<const uint16_t*>(a.x), a.rows, a.cols,
-                       a.ld, a.sign_mask, w.lane_bits, w.col_blocks, w.pieces, a.ws);
+    if (is_small(a) && a.cols >= 128) {   // (its wavefronts span 128 columns)
+      n_maxima = small_amax_workgroups(a);
+      launch_amax_small<kRht>(a, s);
+    } else {
+      const AmaxWork w = amax_work(a);
+      n_maxima = w.workgroups;
+      hipLaunchKernelGGL((amax_kernel<kRht>), dim3(w.workgroups), dim3(kThreads), 0, s, static_cast<const uint16_t*>(a.x), a.rows, a.cols,
+                         a.ld, a.sign_mask, w.lane_bits, w.col_blocks, w.pieces, a.ws);
+    }
     // the cast pass folds the maxima itself; only a caller of the amax alone needs them folded
-    if (!a.do_cast) hipLaunchKernelGGL(amax_finalize_kernel, dim3(1), dim3(1024), 0, s, a.ws, w.workgroups, a.amax_copy);
+    if (!a.do_cast) hipLaunchKernelGGL(amax_finalize_kernel, dim3(1), dim3(1024), 0, s, a.ws, n_maxima, a.amax_copy);
   }
   if (!a.do_cast) return;
+  const uint32_t* maxima = a.do_amax ? a.ws + kWsHeader : a.ws;
   if (a.block2d) {
-    if (a.sr) launch_cast<kRow, kCol, 0, true, true>(a, s);
-    else launch_cast<kRow, kCol, 0, false, true>(a, s);
+    if (a.sr) launch_cast<kRow, kCol, 0, true, true>(a, maxima, n_maxima, s);
+    else launch_cast<kRow, kCol, 0, false, true>(a, maxima, n_maxima, s);
+  } else if (is_small(a)) {
+    launch_cast_small<kRow, kCol, kRht>(a, maxima, n_maxima, s);
   } else {
-    if (a.sr) launch_cast<kRow, kCol, kRht, true, false>(a, s);
-    else launch_cast<kRow, kCol, kRht, false, false>(a, s);
+    if (a.sr) launch_cast<kRow, kCol, kRht, true, false>(a, maxima, n_maxima, s);
+    else launch_cast<kRow, kCol, kRht, false, false>(a, maxima, n_maxima, s);
   }
 }
 
