@@ -109,7 +109,9 @@ def _check(status: int) -> None:
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    """The current device's current stream.  (torch.cuda.current_stream() builds a Stream object for it: 2.8 us of the 11.5 that a small
+    call takes on the host; this 0.2.)"""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def quantized_sizes(rows: int, cols: int):
