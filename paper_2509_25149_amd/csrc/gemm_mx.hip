@@ -65,6 +65,13 @@ __device__ __forceinline__ void load4_to_lds(uint32_t lane_offset, const uint8_t
                : "memory", "m0");
 }
 
+// The same with M0 left as the previous call set it: the instruction's immediate offset is added to the LDS address and to the global
+// address alike, so the caller passes an address that is kOff too low.
+template <int kOff>
+__device__ __forceinline__ void load16_to_lds_next(uint32_t lane_offset, const uint8_t* base) {
+  asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2" ::"v"(lane_offset), "s"(base), "n"(kOff) : "memory");
+}
+
 // LDS reads; asynchronous, the caller waits (lgkmcnt) before the values are used.
 template <int kOff>
 __device__ __forceinline__ void lds_read16(int4v& dst, uint32_t addr) {
@@ -263,8 +270,14 @@ __global__ __launch_bounds__(kThreads) void gemm_mx_kernel_any_k(Operand A, Oper
 //           swizzle chunk c of row r -> position c ^ ((r >> 1) & 7) so that fragment reads stay conflict-free;
 //           the two steps of an iteration are the two 64-byte halves of a stage
 //   scales  16 bytes of each scale row = four K steps = two iterations per load instruction, in a ring of
-//           two 8 KiB slots; a lane reads its row's dword of the step and gathers bytes as before
-// a third of the line requests for the same bytes.  The pipeline is the one described at the top.
+//           two 8 KiB slots; a wavefront reads 64 rows' 16 bytes at once and transposes them between its lanes (ChunkScales)
+// a third of the line requests for the same bytes.  The pipeline is the one described at the top, with two barriers per stage instead of one: when
+// everybody has read the stage out (a little more than half way through its first 64 MFMAs) the loads that refill its buffer begin, spread from there
+// to the end of the stage; four wavefronts' 16 loads behind the second 64 alone kept the address path busy throughout.
+// What bounds it (parts taken out, results wrong, accesses in bounds; 4096 x 5120 x 5120 bf16, 64.7 us): without the loads 52.2, without waiting for
+// them 61.7, without the fragment reads 63.5, without the output stage of the first of two tiles 61.4; 8192 x 20480 x 5120 416 us: 335, 400, 402 and
+// 342.  us, one barrier and scales by dwords -> now: 4096 x 5120 x 5120 bf16 68.8 -> 64.3, FP32 73.6 -> 70.4; 512 x 5120 x 5120 25.0 -> 23.3; 8192 x 20480 x
+// 5120 436 -> 421 (4.1 PFLOP/s).
 constexpr int kWideRowBytes = 128;
 constexpr int kWideOperandBytes = TM * kWideRowBytes;       // 32 KiB
 constexpr int kWideStageBytes = 2 * kWideOperandBytes;      // 64 KiB
@@ -274,22 +287,42 @@ constexpr int kWideLdsBytes = 2 * kWideStageBytes + 2 * kWideScaleSlotBytes;   /
 
 __device__ __forceinline__ int swz128(int row, int chunk) { return row * kWideRowBytes + ((chunk ^ ((row >> 1) & 7)) << 4); }
 
-// two dwords, kOff0 and kOff1 times 256 bytes past addr
-template <int kOff0, int kOff1>
-__device__ __forceinline__ void lds_read_2x4_st64(int2v& dst, uint32_t addr) {
-  asm volatile("ds_read2st64_b32 %0, %1 offset0:%2 offset1:%3" : "=&v"(dst) : "v"(addr), "n"(kOff0), "n"(kOff1));
+// Read number q of the 8 + kNB of a fragment set: 8 of A codes, kNB of B codes (16-row blocks are 2 KiB apart).
+template <int q, int kNB>
+__device__ __forceinline__ void read_frag_wide(Frags& f, uint32_t a_codes, uint32_t b_codes) {
+  if constexpr (q < 8) lds_read16<q * 16 * kWideRowBytes>(f.a[q], a_codes);
+  else lds_read16<(q - 8) * 16 * kWideRowBytes>(f.b[q - 8], b_codes);
 }
 
-// Read number q of the 16 + kNB of a fragment set: 8 of A codes, kNB of B codes (16-row blocks are 2 KiB apart), 4 of A
-// scales, 4 of B scales (16-row blocks are 256 bytes apart; for kNB < 8 some of them read rows that count for nothing).
-template <int q, int kNB>
-__device__ __forceinline__ void read_frag_wide(Frags& f, RawScales& r, uint32_t a_codes, uint32_t b_codes, uint32_t a_scales,
-                                               uint32_t b_scales) {
-  constexpr int s = q - 8 - kNB;
-  if constexpr (q < 8) lds_read16<q * 16 * kWideRowBytes>(f.a[q], a_codes);
-  else if constexpr (q < 8 + kNB) lds_read16<(q - 8) * 16 * kWideRowBytes>(f.b[q - 8], b_codes);
-  else if constexpr (s < 4) lds_read_2x4_st64<s * 2, s * 2 + 1>(r.a[s], a_scales);
-  else lds_read_2x4_st64<(s - 4) * 2, (s - 4) * 2 + 1>(r.b[s - 4], b_scales);
+// The scales of a chunk (four K steps) as read from LDS: lane l has the 16 bytes of row l & 15 of 16-row block 4 h + (l >> 4), h = 0, 1 of A, then of B: a
+// read is 1 KiB of consecutive LDS.  Element e: the four scales of K step e.  (For kNB < 8 some of B's are of rows that count for nothing.)
+// Read as a dword per row and step, by all four lanes of a row, they took a third of the LDS's time: 8 instructions a step, two rows to a bank.
+struct ChunkScales {
+  int4v s[4];
+};
+template <int q>
+__device__ __forceinline__ void read_chunk_scales(ChunkScales& c, uint32_t a_scales, uint32_t b_scales) {
+  lds_read16<(q & 1) * 64 * 16>(c.s[q], q < 2 ? a_scales : b_scales);
+}
+// The reads are back: from here on (no instruction) the compiler may use the values.
+__device__ __forceinline__ void chunk_scales_back(ChunkScales& c) {
+  asm volatile("" : "+v"(c.s[0]), "+v"(c.s[1]), "+v"(c.s[2]), "+v"(c.s[3]));
+}
+// Byte t of the result = this lane's scale (block l >> 4 of the step) of 16-row block 4 h + t: a 4 x 4 transposition of bytes over the four lanes that
+// hold a row number's dwords: half-wavefronts exchanged and two bytes of each kept, then 16-lane rows and one byte of each.
+__device__ __forceinline__ int transpose_scales(int v, uint32_t sel_half, uint32_t sel_row) {
+  const auto h = __builtin_amdgcn_permlane32_swap(static_cast<uint32_t>(v), static_cast<uint32_t>(v), false, false);
+  const uint32_t u = __builtin_amdgcn_perm(h[1], h[0], sel_half);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return static_cast<int>(__builtin_amdgcn_perm(r[1], r[0], sel_row));
+}
+template <int e>
+__device__ __forceinline__ void set_scales(Frags& f, const ChunkScales& c, uint32_t sel_half, uint32_t sel_row) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    f.pa[h] = transpose_scales(c.s[h][e], sel_half, sel_row);
+    f.pb[h] = transpose_scales(c.s[2 + h][e], sel_half, sel_row);
+  }
 }
 
 // Spreads `total` things evenly over the `slots` places between MFMAs: the number of the one that place n takes, or -1.
@@ -326,7 +359,9 @@ template <bool kBf16Out, int kNB>
 __global__ __launch_bounds__(kThreads) void gemm_mx_kernel_k512(Operand A, Operand B, int64_t K, void* __restrict__ Dv,
                                                                 int64_t ldd, bool accumulate, int tiles_m, int tiles_n) {
   constexpr int kTN = 32 * kNB;                  // columns of a tile: two wavefronts of kNB 16-column blocks
-  constexpr int kReads = 16 + kNB, kLoads = 8 + kNB, kMfmas = 8 * kNB;
+  constexpr int kReads = 8 + kNB, kLoads = 8 + kNB, kMfmas = 8 * kNB;
+  constexpr int kFree = 2 * kReads + 2;   // of a stage's first kMfmas: before it everybody has read the stage out
+  constexpr int kLoadPlaces = 2 * kMfmas - kFree, kEarlyLoads = (kMfmas - kFree) * kLoads / kLoadPlaces;   // the loads go behind these; so many of them behind the first kMfmas
   extern __shared__ __attribute__((aligned(16))) char lds[];
 
   const int num_tiles = tiles_m * tiles_n;
@@ -348,7 +383,7 @@ __global__ __launch_bounds__(kThreads) void gemm_mx_kernel_k512(Operand A, Opera
   // its bit 2 for odd q).  Scale loads: one instruction = 64 tile rows x 16 bytes (four K steps).
   uint32_t lane_even = 0, lane_odd = 0, lane_srow = 0;
   uint32_t a_lo = 0, a_hi = 0, b_lo = 0, b_hi = 0, a_scales = 0, b_scales = 0;   // fragment addresses: stage buffer 0 / scale slot 0, step 0
-  int sel01 = 0;
+  uint32_t sel_half = 0, sel_row = 0;   // of transpose_scales
   auto lane_setup = [&]() {
     const int lane = lane_id();
     const int r0 = wave * 64 + (lane >> 3);
@@ -362,9 +397,10 @@ __global__ __launch_bounds__(kThreads) void gemm_mx_kernel_k512(Operand A, Opera
     a_hi = lds0 + swz128(arow, 4 + kb);
     b_lo = lds0 + kWideOperandBytes + swz128(brow, kb);
     b_hi = lds0 + kWideOperandBytes + swz128(brow, 4 + kb);
-    a_scales = scales0 + arow * 16;
-    b_scales = scales0 + kWideScaleOperandBytes + brow * 16;
-    sel01 = kb | ((4 + kb) << 8);
+    a_scales = scales0 + ((wave >> 1) * 128 + lane) * 16;
+    b_scales = scales0 + kWideScaleOperandBytes + ((wave & 1) * (16 * kNB) + lane) * 16;
+    sel_half = kb < 2 ? 0x05040100u : 0x07060302u;
+    sel_row = (kb & 1) == 0 ? 0x06020400u : 0x07030501u;
   };
   lane_setup();
   // Load addresses: a wave-uniform 64-bit base per operand (codes, scales), which holds the tile and the stage /
@@ -380,29 +416,31 @@ __global__ __launch_bounds__(kThreads) void gemm_mx_kernel_k512(Operand A, Opera
   // Point the loads at stage `stage` and scale chunk `chunk` of tile (tm, tn).
   auto aim = [&](int tm, int tn, int stage, int chunk) {
     const int64_t m_first = static_cast<int64_t>(tm) * TM, n_first = static_cast<int64_t>(tn) * kTN;
-    base_a = A.codes + m_first * code_ld + stage * kWideRowBytes;
-    base_b = B.codes + n_first * code_ld + stage * kWideRowBytes;
+    base_a = A.codes + m_first * code_ld + stage * kWideRowBytes - 3072;
+    base_b = B.codes + n_first * code_ld + stage * kWideRowBytes - 3072;
     base_sa = A.scales + m_first * scale_ld + chunk * 16;
     base_sb = B.scales + n_first * scale_ld + chunk * 16;
     const uint32_t last_a = static_cast<uint32_t>(A.outer - 8 - m_first), last_b = static_cast<uint32_t>(B.outer - 8 - n_first);
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
       const uint32_t r = static_cast<uint32_t>(wave * 64 + q * 8);
-      voff[q] = ((q & 1) ? lane_odd : lane_even) + min(r, last_a) * static_cast<uint32_t>(code_ld);
+      voff[q] = ((q & 1) ? lane_odd : lane_even) + min(r, last_a) * static_cast<uint32_t>(code_ld) + (3 - (q & 3)) * 1024u;
     }
 #pragma unroll
     for (int q = 0; q < kNB; ++q) {
       const uint32_t blk = static_cast<uint32_t>(wave * kNB + q);
-      voff[8 + q] = ((blk & 1) ? lane_odd : lane_even) + min(blk * 8u, last_b) * static_cast<uint32_t>(code_ld);
+      voff[8 + q] = ((blk & 1) ? lane_odd : lane_even) + min(blk * 8u, last_b) * static_cast<uint32_t>(code_ld) + (3 - (q & 3)) * 1024u;
     }
     vsa = min(lane_srow, last_a + 7) * static_cast<uint32_t>(scale_ld);
     vsb = min(lane_srow, last_b + 7) * static_cast<uint32_t>(scale_ld);
   };
-  // load number q of a stage into stage buffer `buf`: 0..7 A, then B
+  // Load number q of a stage into stage buffer `buf`: 0..7 A, then B.  M0 is set once per four loads: three of them reach the next KiB by the immediate
+  // offset, which moves the global address too: the bases sit 3 KiB low, the lane's offsets make up for what the immediate does not add.
   auto issue_codes = [&](auto qc, int buf) {
     constexpr int q = decltype(qc)::value;
-    const uint32_t dst = lds0 + buf * kWideStageBytes + (q < 8 ? wave * 8192 + q * 1024 : kWideOperandBytes + (wave * kNB + q - 8) * 1024);
-    load16_to_lds(voff[q], q < 8 ? base_a : base_b, dst);
+    const uint8_t* base = q < 8 ? base_a : base_b;
+    if constexpr ((q & 3) == 0) load16_to_lds(voff[q], base, lds0 + buf * kWideStageBytes + (q < 8 ? wave * 8192 + q * 1024 : kWideOperandBytes + (wave * kNB + q - 8) * 1024));
+    else load16_to_lds_next<(q & 3) * 1024>(voff[q], base);
   };
   // the two loads of a scale chunk (four K steps) into ring slot `slot`
   auto issue_scales = [&](int slot) {
@@ -425,7 +463,7 @@ __global__ __launch_bounds__(kThreads) void gemm_mx_kernel_k512(Operand A, Opera
   __builtin_amdgcn_s_barrier();
 
   Frags f0, f1;
-  RawScales raw;
+  ChunkScales chunk;
   float4v acc[8][kNB];
   uint32_t gst = 0;             // stages done so far, over all tiles (even at every tile's start)
   bool stores_behind = false;   // the previous tile's stores were issued after the loads now in flight
@@ -434,27 +472,28 @@ __global__ __launch_bounds__(kThreads) void gemm_mx_kernel_k512(Operand A, Opera
     // read again so that the output stage had their registers to work with.)
     {
       const uint32_t cur = (gst & 1) * kWideStageBytes, sc = ((gst >> 1) & 1) * kWideScaleSlotBytes;
-      static_for<0, kReads>([&](auto q) { read_frag_wide<decltype(q)::value, kNB>(f0, raw, a_lo + cur, b_lo + cur, a_scales + sc, b_scales + sc); });
+      static_for<0, kReads>([&](auto q) { read_frag_wide<decltype(q)::value, kNB>(f0, a_lo + cur, b_lo + cur); });
+      static_for<0, 4>([&](auto q) { read_chunk_scales<decltype(q)::value>(chunk, a_scales + sc, b_scales + sc); });
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      pack_scales(f0, raw, sel01);
+      chunk_scales_back(chunk);
+      set_scales<0>(f0, chunk, sel_half, sel_row);
     }
     const int next_item = item + static_cast<int>(gridDim.x);
     const bool has_next = next_item < num_tiles;
     int next_tm = 0, next_tn = 0;
     if (has_next) locate(next_item, next_tm, next_tn);
 
-    // One stage = two K steps; kFirst: the tile's first.  The loads run two stages ahead of the MFMAs, the scale
+    // One stage = two K steps; kFirst: the tile's first; kOdd: the second stage of a scale chunk.  The loads run two stages ahead of the MFMAs, the scale
     // loads (every other stage) one chunk ahead of the stage that reads it.
-    auto stage_step = [&](auto first_tag, int st) {
-      constexpr bool kFirst = decltype(first_tag)::value;
-      const uint32_t cur = (gst & 1) * kWideStageBytes, nxt = cur ^ kWideStageBytes;
-      // scale addresses: this stage's second step; the next stage's first step (ring slot of its chunk)
-      const uint32_t sc1 = ((gst >> 1) & 1) * kWideScaleSlotBytes + (gst & 1) * 8 + 4;
-      const uint32_t sc2 = (((gst + 1) >> 1) & 1) * kWideScaleSlotBytes + ((gst + 1) & 1) * 8;
+    auto stage_step = [&](auto first_tag, auto odd_tag, int st) {
+      constexpr bool kFirst = decltype(first_tag)::value, kOdd = decltype(odd_tag)::value;
+      constexpr int kStep = kOdd ? 2 : 0;   // the stage's first K step within the chunk
+      const uint32_t cur = kOdd ? kWideStageBytes : 0, nxt = cur ^ kWideStageBytes;   // (gst is even at every tile's start)
+      const uint32_t next_chunk = (((gst + 1) >> 1) & 1) * kWideScaleSlotBytes;       // ring slot of the chunk after an odd stage's
       // Where the loads go next: on within the tile, or to the next tile's first stage and chunk, or, with nothing
       // to follow, nowhere (the last stage and chunk are fetched again into buffers nobody reads any more).
       uint32_t code_advance = kWideRowBytes;
-      if ((st & 1) == 0 && (st >> 1) + 1 < chunks) {
+      if (!kOdd && (st >> 1) + 1 < chunks) {
         base_sa += 16;
         base_sb += 16;
       }
@@ -466,38 +505,50 @@ __global__ __launch_bounds__(kThreads) void gemm_mx_kernel_k512(Operand A, Opera
       }
       static_for<0, kMfmas>([&](auto ic) {
         constexpr int n = decltype(ic)::value, i = n / kNB, j = n % kNB, rd = read_at(n, kReads, kMfmas, 1);
+        if constexpr (n == kFree) {
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+          __builtin_amdgcn_s_barrier();
+        }
         if constexpr (kFirst)
           mfma_first<(j & 3), (i & 3)>(acc[i][j], f0.b[j], f0.a[i], f0.pb[j >> 2], f0.pa[i >> 2]);
         else
           mfma<(j & 3), (i & 3)>(acc[i][j], f0.b[j], f0.a[i], f0.pb[j >> 2], f0.pa[i >> 2]);
-        if constexpr (rd >= 0)
-          read_frag_wide<rd, kNB>(f1, raw, a_hi + cur, b_hi + cur, a_scales + sc1, b_scales + sc1);
+        if constexpr (rd >= 0) read_frag_wide<rd, kNB>(f1, a_hi + cur, b_hi + cur);
         if constexpr (n == 2) {
           base_a += code_advance;
           base_b += code_advance;
         }
+        if constexpr (n >= kFree) {
+          constexpr int ld = spread(n - kFree, kLoads, kLoadPlaces);
+          if constexpr (ld >= 0) issue_codes(std::integral_constant<int, ld>{}, kOdd ? 1 : 0);
+        }
       });
-      if (kFirst && stores_behind) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(kTileStoresMx<kBf16Out, kNB>) : "memory");
-      else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+      set_scales<kStep + 1>(f1, chunk, sel_half, sel_row);
+      if (kFirst && stores_behind) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kTileStoresMx<kBf16Out, kNB> + kEarlyLoads) : "memory");
+      else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kEarlyLoads) : "memory");
       __builtin_amdgcn_s_barrier();
-      pack_scales(f1, raw, sel01);
       static_for<0, kMfmas>([&](auto ic) {
         constexpr int n = decltype(ic)::value, i = n / kNB, j = n % kNB;
-        constexpr int rd = read_at(n, kReads, kMfmas, 0), ld = spread(n, kLoads, kMfmas);
+        constexpr int rd = read_at(n, kReads + (kOdd ? 4 : 0), kMfmas, 0), ld = spread(kMfmas - kFree + n, kLoads, kLoadPlaces);
         mfma<(j & 3), (i & 3)>(acc[i][j], f1.b[j], f1.a[i], f1.pb[j >> 2], f1.pa[i >> 2]);
-        if constexpr (rd >= 0)
-          read_frag_wide<rd, kNB>(f0, raw, a_lo + nxt, b_lo + nxt, a_scales + sc2, b_scales + sc2);
-        if constexpr (ld >= 0) issue_codes(std::integral_constant<int, ld>{}, static_cast<int>(gst & 1));
+        if constexpr (rd >= 0 && rd < kReads) read_frag_wide<rd, kNB>(f0, a_lo + nxt, b_lo + nxt);
+        if constexpr (rd >= kReads) read_chunk_scales<rd - kReads>(chunk, a_scales + next_chunk, b_scales + next_chunk);
+        if constexpr (ld >= 0) issue_codes(std::integral_constant<int, ld>{}, kOdd ? 1 : 0);
       });
       // even stages also fetch the scales of the chunk after the next stage's, into the slot its predecessor left
       // at this stage's barrier
-      if ((gst & 1) == 0) issue_scales(static_cast<int>(((gst >> 1) + 1) & 1));
+      if (!kOdd) issue_scales(static_cast<int>(((gst >> 1) + 1) & 1));
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      pack_scales(f0, raw, sel01);
+      if (kOdd) chunk_scales_back(chunk);
+      set_scales<kOdd ? 0 : 2>(f0, chunk, sel_half, sel_row);
       ++gst;
     };
-    stage_step(std::true_type{}, 0);
-    for (int st = 1; st < stages; ++st) stage_step(std::false_type{}, st);
+    stage_step(std::true_type{}, std::false_type{}, 0);
+    stage_step(std::false_type{}, std::true_type{}, 1);
+    for (int st = 2; st < stages; st += 2) {
+      stage_step(std::false_type{}, std::false_type{}, st);
+      stage_step(std::false_type{}, std::true_type{}, st + 1);
+    }
 
     // Everything below is computed here, per tile (see lane_setup).
     int wm = wave >> 1, wn = wave & 1;
