@@ -5,7 +5,7 @@
 // copy's K-contiguous storage -- per logical row for the row copy, per logical column (in the rotated space, App. C)
 // for the col copy.  Eq. 1 is evaluated per row with that row's amax; Eq. 2-4 are unchanged.
 //
-//   row copy alone    ONE pass over the tensor: a wavefront (rows of up to 8192 columns) or a workgroup (up to 32768)
+//   row copy alone    ONE pass over the tensor: a wavefront (rows of up to 1024 columns, or 2048) or a workgroup (up to 32768)
 //                     owns one row, holds all of it in registers, reduces the row's amax and encodes from the
 //                     registers.  The bf16 tensor crosses HBM once.
 //   col copy (+ row)  a column's amax spans every row of the tensor (all tokens), far more than a workgroup can hold,
@@ -43,13 +43,13 @@ __device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b) {
 // ---------------------------------------------------------------- row copy alone: one pass
 // One workgroup per row; thread t holds the eight columns (ch * 256 + t) * 8 .. + 7 of every chunk ch < kNCH.
 template <bool kSR, int kNCH>
-__global__ __launch_bounds__(256) void rowscale_row_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
+__global__ __launch_bounds__(256) void rowscale_row_kernel(const uint16_t* __restrict__ x, int64_t first_row, int64_t rows, int64_t cols,
                                                            int64_t ld, uint32_t key0, uint32_t key1,
                                                            uint8_t* __restrict__ row_codes, uint8_t* __restrict__ row_scales,
                                                            float* __restrict__ row_ts) {
   __shared__ uint32_t red[4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t row = blockIdx.x;
+  const int64_t row = first_row + blockIdx.x;
   const uint16_t* xr = x + row * ld;
 
   uint4 raw[kNCH];
@@ -105,7 +105,7 @@ __global__ __launch_bounds__(256) void rowscale_row_kernel(const uint16_t* __res
   }
 }
 
-// Rows of up to 8192 columns: one WAVEFRONT per row (four rows per workgroup), lane l holds the eight columns
+// Short rows (see launch_quantize_rowscale): one WAVEFRONT per row (four rows per workgroup), lane l holds the eight columns
 // (ch * 64 + l) * 8 .. + 7 of every chunk ch < kNCH.  No LDS and no barrier, and several 16-byte loads in flight
 // per lane: for short rows the workgroup-per-row form above spends its time on launches and its one barrier.
 template <bool kSR, int kNCH>
@@ -387,8 +387,12 @@ __global__ __launch_bounds__(kThreads, 2) void rowscale_cast_kernel(
 
 template <bool kSR, int kNCH>
 void launch_row(const QuantizeArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL((rowscale_row_kernel<kSR, kNCH>), dim3(static_cast<unsigned>(a.rows)), dim3(256), 0, s,
-                     static_cast<const uint16_t*>(a.x), a.rows, a.cols, a.ld, a.key0, a.key1, a.row_codes, a.row_scales, a.row_ts);
+  constexpr int64_t kRowsPerLaunch = int64_t{1} << 23;   // a launch has fewer than 2^32 threads
+  for (int64_t first = 0; first < a.rows; first += kRowsPerLaunch) {
+    const int64_t n = a.rows - first < kRowsPerLaunch ? a.rows - first : kRowsPerLaunch;
+    hipLaunchKernelGGL((rowscale_row_kernel<kSR, kNCH>), dim3(static_cast<unsigned>(n)), dim3(256), 0, s, static_cast<const uint16_t*>(a.x), first, a.rows,
+                       a.cols, a.ld, a.key0, a.key1, a.row_codes, a.row_scales, a.row_ts);
+  }
 }
 
 template <bool kSR, int kNCH>
@@ -422,18 +426,16 @@ void launch_two_pass(const QuantizeArgs& a, hipStream_t s) {
 size_t quantize_rowscale_workspace_words(int64_t rows, int64_t cols) { return static_cast<size_t>(2 * (rows + cols)); }
 
 hipError_t launch_quantize_rowscale(const QuantizeArgs& a, hipStream_t s) {
-  if (a.want_row && !a.want_col && a.cols <= 8192) {         // the row fits a wavefront's registers: one pass
-    const int64_t nch = (a.cols + 511) / 512;
+  // A row to a wavefront up to 1024 columns, and with enough rows up to 2048; longer ones to a workgroup, whose lanes have a quarter of the row's chain of
+  // blocks, each with its division.  us, wavefront / workgroup: 512 x 1024 3.2 / 3.3, 2048 x 1024 3.6 / 4.1; 512 x 2048 3.7 / 3.4, 1024 x 2048 3.8 / 3.7, 2048 x
+  // 2048 4.2 / 4.6; 64 x 5120 5.1 / 3.6, 512 x 5120 5.3 / 4.1, 2048 x 5120 7.2 / 7.3, 8192 x 5120 23.7 / 19.4, 512 x 8192 6.9 / 4.4; stochastic rounding alike
+  // (512 x 5120 6.5 / 4.7, 8192 x 5120 28.2 / 25.8).
+  if (a.want_row && !a.want_col && a.cols <= (a.rows > 1024 ? 2048 : 1024)) {
+    const bool two = a.cols <= 1024;
     if (a.sr) {
-      if (nch <= 2) launch_row_wave<true, 2>(a, s);
-      else if (nch <= 4) launch_row_wave<true, 4>(a, s);
-      else if (nch <= 10) launch_row_wave<true, 10>(a, s);
-      else launch_row_wave<true, 16>(a, s);
+      if (two) launch_row_wave<true, 2>(a, s); else launch_row_wave<true, 4>(a, s);
     } else {
-      if (nch <= 2) launch_row_wave<false, 2>(a, s);
-      else if (nch <= 4) launch_row_wave<false, 4>(a, s);
-      else if (nch <= 10) launch_row_wave<false, 10>(a, s);
-      else launch_row_wave<false, 16>(a, s);
+      if (two) launch_row_wave<false, 2>(a, s); else launch_row_wave<false, 4>(a, s);
     }
     return hipGetLastError();
   }
