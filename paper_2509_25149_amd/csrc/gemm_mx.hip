@@ -65,11 +65,12 @@ __device__ __forceinline__ void load4_to_lds(uint32_t lane_offset, const uint8_t
                : "memory", "m0");
 }
 
-// The same with M0 left as the previous call set it: the instruction's immediate offset is added to the LDS address and to the global
-// address alike, so the caller passes an address that is kOff too low.
+// The same kOff bytes on: the instruction's immediate offset is added to the LDS address and to the global address alike, so the
+// caller passes a global address that is kOff too low.  M0 is an operand: where a following load has the same lds_dst the compiler sets it once for
+// both, and whatever else it may put into M0 in between it undoes.  (s_nop: the wait state that M0 needs when it has just been set.)
 template <int kOff>
-__device__ __forceinline__ void load16_to_lds_next(uint32_t lane_offset, const uint8_t* base) {
-  asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2" ::"v"(lane_offset), "s"(base), "n"(kOff) : "memory");
+__device__ __forceinline__ void load16_to_lds_at(uint32_t lane_offset, const uint8_t* base, uint32_t lds_dst) {
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%2" ::"v"(lane_offset), "s"(base), "n"(kOff), "{m0}"(lds_dst) : "memory");
 }
 
 // LDS reads; asynchronous, the caller waits (lgkmcnt) before the values are used.
@@ -434,13 +435,12 @@ __global__ __launch_bounds__(kThreads) void gemm_mx_kernel_k512(Operand A, Opera
     vsa = min(lane_srow, last_a + 7) * static_cast<uint32_t>(scale_ld);
     vsb = min(lane_srow, last_b + 7) * static_cast<uint32_t>(scale_ld);
   };
-  // Load number q of a stage into stage buffer `buf`: 0..7 A, then B.  M0 is set once per four loads: three of them reach the next KiB by the immediate
+  // Load number q of a stage into stage buffer `buf`: 0..7 A, then B.  One LDS address (M0) serves four loads: three of them reach the next KiB by the immediate
   // offset, which moves the global address too: the bases sit 3 KiB low, the lane's offsets make up for what the immediate does not add.
   auto issue_codes = [&](auto qc, int buf) {
-    constexpr int q = decltype(qc)::value;
-    const uint8_t* base = q < 8 ? base_a : base_b;
-    if constexpr ((q & 3) == 0) load16_to_lds(voff[q], base, lds0 + buf * kWideStageBytes + (q < 8 ? wave * 8192 + q * 1024 : kWideOperandBytes + (wave * kNB + q - 8) * 1024));
-    else load16_to_lds_next<(q & 3) * 1024>(voff[q], base);
+    constexpr int q = decltype(qc)::value, first = q & ~3;
+    load16_to_lds_at<(q - first) * 1024>(voff[q], q < 8 ? base_a : base_b,
+                                         lds0 + buf * kWideStageBytes + (q < 8 ? wave * 8192 + first * 1024 : kWideOperandBytes + (wave * kNB + first - 8) * 1024));
   };
   // the two loads of a scale chunk (four K steps) into ring slot `slot`
   auto issue_scales = [&](int slot) {
