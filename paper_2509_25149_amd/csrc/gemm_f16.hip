@@ -167,17 +167,14 @@ __device__ __forceinline__ void read_frag(Frags& f, uint32_t a_addr, uint32_t b_
   else lds_read16<(q - 8) * kPieceBytes>(f.b[q - 8], b_addr);
 }
 
-// 64 lanes x 16 bytes from global memory (wave-uniform base + per-lane 32-bit offset) straight into
-// 1 KiB of consecutive LDS starting at the wave-uniform LDS address `lds_dst`.  Asynchronous (vmcnt).
-__device__ __forceinline__ void load_1k_to_lds(uint32_t lane_offset, const char* base, uint32_t lds_dst) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_dst), "v"(lane_offset), "s"(base)
-               : "memory", "m0");
-}
-// The same with M0 (the LDS destination) left as the previous call set it: the instruction's immediate offset kOff is
-// added to the LDS address and to the global address alike, so the caller passes a base that is kOff too low.
+// 64 lanes x 16 bytes from global memory (wave-uniform base + per-lane 32-bit offset) straight into 1 KiB of consecutive LDS
+// starting at the wave-uniform LDS address lds_dst + kOff.  Asynchronous (vmcnt).  kOff is the instruction's immediate offset, which is added to the LDS
+// address and to the global address alike, so the caller passes a base that is kOff too low.  M0, the LDS address, is an operand: where a
+// following load has the same lds_dst the compiler sets it once for both, and whatever else it may put into M0 in between it undoes.  (s_nop: the wait
+// state that M0 needs when it has just been set.)
 template <int kOff>
-__device__ __forceinline__ void load_1k_to_lds_next(uint32_t lane_offset, const char* base_minus_off) {
-  asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2" ::"v"(lane_offset), "s"(base_minus_off), "n"(kOff) : "memory");
+__device__ __forceinline__ void load_1k_to_lds(uint32_t lane_offset, const char* base_minus_off, uint32_t lds_dst) {
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%2" ::"v"(lane_offset), "s"(base_minus_off), "n"(kOff), "{m0}"(lds_dst) : "memory");
 }
 
 // The first MFMA of an accumulator in a work item: C = 0, so the 256 accumulation registers are never cleared.
@@ -281,9 +278,7 @@ __global__ __launch_bounds__(kThreads) void gemm_f16_kernel(const _Float16* __re
   // load q of the wavefront's that fill ring buffer `buf`
   auto issue = [&](auto qc, uint32_t buf) {
     constexpr int q = decltype(qc)::value;
-    const char* base = q < 4 ? base_a : base_b;
-    if constexpr ((q & 3) == 0) load_1k_to_lds(voff[q], base, (q < 4 ? fill_a : fill_b) + buf * kStageBytes);
-    else load_1k_to_lds_next<(q & 3) * 1024>(voff[q], base);
+    load_1k_to_lds<(q & 3) * 1024>(voff[q], q < 4 ? base_a : base_b, (q < 4 ? fill_a : fill_b) + buf * kStageBytes);
   };
 
   const int KT = static_cast<int>(K / TK);

@@ -22,7 +22,7 @@ def asm_statements(text):
         yield text[m.end():i - 1]
 
 
-@pytest.mark.parametrize("name", ["gemm_mx.hip"])
+@pytest.mark.parametrize("name", ["gemm_f16.hip", "gemm_mx.hip"])
 def test_lds_loads_name_their_lds_address(name):
     # a global -> LDS load takes its LDS address from M0: the statement sets it itself or has it as an operand
     with open(os.path.join(CSRC, name)) as fh:
