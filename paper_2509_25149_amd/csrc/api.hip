@@ -398,6 +398,17 @@ int nvfp4_gemm(const nvfp4_qtensor* a, const nvfp4_qtensor* b, int op, void* d, 
   return e == hipSuccess ? NVFP4_OK : NVFP4_ERR_HIP;
 }
 
+// For the tests, not part of the ABI: nvfp4_gemm of two NVFP4 operands in the direct kernel's shape of this number, whatever the library's own choice
+// would be.  What the shape cannot do is refused, as an unknown number is.
+int nvfp4_internal_gemm_direct(const nvfp4_qtensor* a, const nvfp4_qtensor* b, int op, void* d, int out_dtype, int64_t ldd, int shape,
+                               nvfp4_stream_t stream) {
+  GemmArgs g;
+  const int rc = plan_gemm(a, b, op, d, out_dtype, ldd, nullptr, 0, &g);
+  if (rc != NVFP4_OK) return rc;
+  if (g.mx) return NVFP4_ERR_INVALID_ARG;
+  return launch_gemm_direct(g, shape, static_cast<hipStream_t>(stream)) == hipSuccess ? NVFP4_OK : NVFP4_ERR_HIP;
+}
+
 // ---------------------------------------------------------------- one linear layer (Sec. 4.1, Fig. 3)
 
 int nvfp4_linear_workspace_bytes(int64_t tokens, int64_t d_in, int64_t d_out, size_t* workspace_bytes) {

@@ -447,3 +447,15 @@ extern "C" void nvfp4_internal_direct_shape(int64_t M, int64_t N, int64_t K, int
   g.K = K;
   nvfp4::direct_shape(nvfp4::pick_direct_shape(g, own != 0).shape, out);
 }
+
+// Likewise: that of the direct kernel's shape of this number; 0: there is none.
+extern "C" int nvfp4_internal_direct_shape_at(int shape, int* out) { return nvfp4::direct_shape(shape, out); }
+
+// Likewise: whether that shape can do such a product.
+extern "C" int nvfp4_internal_direct_fits(int64_t M, int64_t N, int64_t K, int shape) {
+  nvfp4::GemmArgs g{};
+  g.a.outer = M;
+  g.b.outer = N;
+  g.K = K;
+  return nvfp4::direct_shape_fits(g, shape);
+}

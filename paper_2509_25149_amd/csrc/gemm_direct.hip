@@ -170,24 +170,20 @@ __global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, MB * NB > 16 ? 1 : 2) void
 #pragma unroll
     for (int i = 0; i < S::kBlocks; ++i) load_block(i, k, co, so);
   };
-  // A window that is not there whole (K shorter than it): a lane's chunk is whole, half there or absent; what is absent is read from the
-  // row's first bytes and gets scale 0.
+  // A window that is not there whole (K shorter than it; windows of 128 only, see fits): a lane's chunk is whole, half there or absent; what is absent is
+  // read from the row's first bytes and gets scale 0.
   auto load_short = [&]() {
     const bool in0 = chunk * 32 < K, in1 = chunk * 32 + 16 < K;
 #pragma unroll
     for (int i = 0; i < S::kBlocks; ++i) {
       const uint8_t* p = cp[i] + (in0 ? code_off : code_off - chunk * 16);
-#pragma unroll
-      for (int h = 0; h < kSteps; ++h) {
-        const uint8_t* ph = p + h * kLoadRows * code_ld;
-        const uint2 lo = *reinterpret_cast<const uint2*>(ph), hi = *reinterpret_cast<const uint2*>(ph + (in1 ? 8 : 0));
-        ld[i].c[h] = make_uint4(lo.x, lo.y, hi.x, hi.y);
-      }
+      const uint2 lo = *reinterpret_cast<const uint2*>(p), hi = *reinterpret_cast<const uint2*>(p + (in1 ? 8 : 0));
+      ld[i].c[0] = make_uint4(lo.x, lo.y, hi.x, hi.y);
       const uint8_t* ps = sp[i] + srow * scale_ld;
       ld[i].s = 0u;
 #pragma unroll
-      for (int b = 0; b < 2 * kSteps; ++b) {
-        const int block = spart * 2 * kSteps + b;
+      for (int b = 0; b < 2; ++b) {
+        const int block = spart * 2 + b;
         const bool in = block * 16 < K;
         const uint32_t v = ps[in ? block : 0];
         ld[i].s |= in ? v << (8 * b) : 0u;
@@ -288,11 +284,12 @@ __global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, MB * NB > 16 ? 1 : 2) void
     }
   };
   // The rest comes last, as a window that ends where K does: its k are those from lo on (K shorter than a window: it starts at 0, with zeros above K).
-  const int total = windows + (rest ? 1 : 0), k_rest = K >= kWindowK ? K - kWindowK : 0;
+  const bool whole = kSteps == 2 || K >= kWindowK;
+  const int total = windows + (rest ? 1 : 0), k_rest = whole ? K - kWindowK : 0;
   if (total) {
     auto k_of = [&](int n) { return n < windows ? (wk + n * WK) * kWindowK : k_rest; };
-    if (K >= kWindowK) load(k_of(0));
-    else load_short();
+    if (whole) load(k_of(0));
+    else if constexpr (kSteps == 1) load_short();
 #pragma unroll
     for (int i = 0; i < S::kBlocks; ++i) stage(i);
     wavefront_exchange();
@@ -315,8 +312,8 @@ __global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, MB * NB > 16 ? 1 : 2) void
       if (!rest) run_window(std::false_type{}, 0, {}, 0u);
     }
     if (rest) {
-      const int lo = K >= kWindowK ? kWindowK - rest : 0;
-      int hi = K >= kWindowK ? kWindowK : (K + 31) & ~31;
+      const int lo = whole ? kWindowK - rest : 0;
+      int hi = whole ? kWindowK : (K + 31) & ~31;
       if (static_cast<unsigned>(hi - lo - 1) % 64 < 32) {
         hi -= 32;
         rest_piece(hi, lo, 0);
@@ -415,11 +412,13 @@ static int64_t direct_tiles(int64_t M, int64_t N) {
   return ((M + tm - 1) / tm) * ((N + tn - 1) / tn);
 }
 
-// What the kernel's 32-bit rows, byte offsets within a 16-row block and launch size allow; others take other kernels.
+// What the kernel's 32-bit rows, byte offsets within a 16-row block and launch size allow, and at least one window where it has 256 k (a shorter
+// contraction leaves most of such a wavefront's loads empty); others take other kernels.
 template <int I>
 static bool fits(int64_t M, int64_t N, int64_t K) {
-  constexpr int wk = kDirectShapes[I].wk;
-  return M <= 0x7fffffff && N <= 0x7fffffff && K <= (int64_t{1} << 27) && direct_tiles<I>(M, N) * (wk == 1 ? 256 : wk * 64) <= 0xffffffff;
+  constexpr DirectShape d = kDirectShapes[I];
+  return M <= 0x7fffffff && N <= 0x7fffffff && K <= (int64_t{1} << 27) && (d.steps == 1 || K >= 128 * d.steps) &&
+         direct_tiles<I>(M, N) * (d.wk == 1 ? 256 : d.wk * 64) <= 0xffffffff;
 }
 
 // Steps (128 k) of the wavefront that has most of them; a rest counts half a step more than its k: nothing of it overlaps.
@@ -429,7 +428,7 @@ static double wavefront_steps(int64_t K) {
   constexpr int window = 128 * d.steps;
   const int64_t full = K / window, rest = K - full * window, each = full / d.wk;
   const double whole = static_cast<double>((each + (full > each * d.wk)) * d.steps);
-  const double with_rest = static_cast<double>(each * d.steps) + (rest ? (full ? 0.5 : d.steps == 2 ? 3.0 : 1.2) + static_cast<double>(rest) / 128.0 : 0.0);
+  const double with_rest = static_cast<double>(each * d.steps) + (rest ? (full ? 0.5 : 1.2) + static_cast<double>(rest) / 128.0 : 0.0);
   return whole > with_rest ? whole : with_rest;
 }
 
@@ -452,9 +451,11 @@ static DirectPick pick_shape(const GemmArgs& g, bool own, std::integer_sequence<
 
 DirectPick pick_direct_shape(const GemmArgs& g, bool own_tiles) { return pick_shape(g, own_tiles, AllShapes{}); }
 
-void direct_shape(int shape, int* out) {
+bool direct_shape(int shape, int* out) {
+  if (shape < 0 || shape >= kNumDirectShapes) return false;
   const DirectShape& d = kDirectShapes[shape];
   out[0] = d.mb, out[1] = d.nb, out[2] = d.wk, out[3] = d.steps;
+  return true;
 }
 
 template <int I, bool kBf16Out>
@@ -483,8 +484,10 @@ static bool fits_shape(const GemmArgs& g, int shape, std::integer_sequence<int, 
   return ((shape == I && fits<I>(g.a.outer, g.b.outer, g.K)) || ...);
 }
 
+bool direct_shape_fits(const GemmArgs& g, int shape) { return fits_shape(g, shape, AllShapes{}); }
+
 hipError_t launch_gemm_direct(const GemmArgs& g, int shape, hipStream_t s) {
-  if (!fits_shape(g, shape, AllShapes{})) return hipErrorInvalidValue;   // beyond its offsets or a launch
+  if (!direct_shape_fits(g, shape)) return hipErrorInvalidValue;
   return g.out_bf16 ? launch_direct<true>(g, shape, s, AllShapes{}) : launch_direct<false>(g, shape, s, AllShapes{});
 }
 

@@ -103,7 +103,8 @@ struct DirectPick {
   double us;             // expected
 };
 DirectPick pick_direct_shape(const GemmArgs& g, bool own_tiles);   // the best of the shapes that split K, or of those whose wavefronts own different tiles
-void direct_shape(int shape, int* out);   // MB, NB, WK, steps of a shape, for the tests
+bool direct_shape(int shape, int* out);   // MB, NB, WK, steps of a shape, for the tests; false: no such shape
+bool direct_shape_fits(const GemmArgs& g, int shape);   // whether it can do this product
 // Expected time of a kernel on small tiles: `call`, then rounds of 256 tiles of `tile` us and `step` us per step of the loop,
 // or, where that is more, the result's bytes at `result` us per MB (added in quadrature: neither hides the other fully).  A
 // CU holds `resident` workgroups; a round in which only one of them has a tile takes `alone` rounds, not 1.

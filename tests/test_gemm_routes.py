@@ -131,3 +131,30 @@ def test_workspace_without_room_for_partial_tiles_still_serves_the_two_pass_rout
     assert plan(M, N, K, decoded=3) == (TWO_PASS, units, 0, 1)
     assert plan(M, N, K, workspace=16 * 8 * 2 ** 18, decoded=3) == (TWO_PASS, 8, 16, 8)
     assert plan(M, N, K, workspace=N * K * 2, decoded=1)[0] == TWO_PASS
+
+
+def direct_shapes():
+    """The direct kernel's tile shapes by number: (16-row blocks, 16-column blocks, wavefronts that split K, steps of 128 k to a window)."""
+    out, shapes = (ctypes.c_int * 4)(), []
+    while nv.load_library().nvfp4_internal_direct_shape_at(len(shapes), out):
+        shapes.append(tuple(out))
+    return shapes
+
+
+def fits(shape, M, N, K):
+    i64 = ctypes.c_int64
+    return bool(nv.load_library().nvfp4_internal_direct_fits(i64(M), i64(N), i64(K), shape))
+
+
+def test_what_a_direct_shape_can_do():
+    shapes = direct_shapes()
+    assert len(set(shapes)) == len(shapes) and {s[3] for s in shapes} == {1, 2}
+    for i, (mb, nb, wk, steps) in enumerate(shapes):
+        assert fits(i, 16, 16, 16) == fits(i, 4096, 4096, 240) == (steps == 1)       # less than a window of 256 k: windows of 128 only
+        assert fits(i, 16, 16, 256) and fits(i, 16, 16, 2 ** 27) and not fits(i, 16, 16, 2 ** 27 + 16)
+        assert not fits(i, 16, 2 ** 31, 256)
+        own = 2 if wk == 1 else 1
+        rows = 2 ** 32 // (wk * own * own * 64) * mb * own * 16                      # a column of tiles of 2^32 threads
+        if rows < 2 ** 31:
+            assert not fits(i, rows, 16, 256) and fits(i, rows - mb * own * 16, 16, 256)
+    assert not fits(-1, 16, 16, 256) and not fits(len(shapes), 16, 16, 256)
