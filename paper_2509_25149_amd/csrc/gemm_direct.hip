@@ -135,7 +135,9 @@ __global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, MB * NB > 16 ? 1 : 2) void
   // The wavefront's part of K: every WK-th window, and one of them the rest.  (A stretch of K to each, as even as 64 k allow, was slower, also where
   // the windows do not come out even: neighbouring lines then go to one wavefront one after the other.  512 x 5120 x 5120 29.1 / 28.4 us, 1040 x 1296 x
   // 2064 13.7 / 13.1; with windows of 128, half a line, 32 x 5120 x 5120 7.6 / 7.1.)
-  const int full = K / kWindowK, windows = (full - wk + WK - 1) / WK, rest = full % WK == wk ? K - full * kWindowK : 0;
+  // K shorter than a window is one all the same, with zeros above K (4096 x 304 x 112 6.0 us as a rest, 5.5 so).
+  const bool whole = kSteps == 2 || K >= kWindowK;
+  const int full = whole ? K / kWindowK : 1, windows = (full - wk + WK - 1) / WK, rest = whole && full % WK == wk ? K - full * kWindowK : 0;
 
   float4v acc[MB][NB];
 #pragma unroll
@@ -170,25 +172,21 @@ __global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, MB * NB > 16 ? 1 : 2) void
 #pragma unroll
     for (int i = 0; i < S::kBlocks; ++i) load_block(i, k, co, so);
   };
-  // A window that is not there whole (K shorter than it; windows of 128 only, see fits): a lane's chunk is whole, half there or absent; what is absent is
-  // read from the row's first bytes and gets scale 0.
+  // A window that is not there whole (K shorter than it; windows of 128 only, see fits): a lane's chunk, and its two scales, are there whole, half or not
+  // at all; what is not is read from the row's first bytes, and its scales are 0.  The offsets and the mask are opaque (no instruction): knowing that they go
+  // together the compiler jumps around each block's scales and waits for them there, one block after the other (4096 x 304 x 112 5.5 us, 4.9 so).
   auto load_short = [&]() {
     const bool in0 = chunk * 32 < K, in1 = chunk * 32 + 16 < K;
+    uint32_t lo = static_cast<uint32_t>(crow * code_ld) + (in0 ? chunk * 16 : 0), hi = lo + (in1 ? 8 : 0);
+    uint32_t s0 = static_cast<uint32_t>(crow * scale_ld) + (in0 ? chunk * 2 : 0), s1 = s0 + (in1 ? 1 : 0), mask = (in0 ? 0xFFu : 0u) | (in1 ? 0xFF00u : 0u);
+    asm volatile("" : "+v"(lo), "+v"(hi), "+v"(s0), "+v"(s1), "+v"(mask));
 #pragma unroll
     for (int i = 0; i < S::kBlocks; ++i) {
-      const uint8_t* p = cp[i] + (in0 ? code_off : code_off - chunk * 16);
-      const uint2 lo = *reinterpret_cast<const uint2*>(p), hi = *reinterpret_cast<const uint2*>(p + (in1 ? 8 : 0));
-      ld[i].c[0] = make_uint4(lo.x, lo.y, hi.x, hi.y);
-      const uint8_t* ps = sp[i] + srow * scale_ld;
-      ld[i].s = 0u;
-#pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const int block = spart * 2 + b;
-        const bool in = block * 16 < K;
-        const uint32_t v = ps[in ? block : 0];
-        ld[i].s |= in ? v << (8 * b) : 0u;
-      }
+      const uint2 c_lo = *reinterpret_cast<const uint2*>(cp[i] + lo), c_hi = *reinterpret_cast<const uint2*>(cp[i] + hi);
+      ld[i].c[0] = make_uint4(c_lo.x, c_lo.y, c_hi.x, c_hi.y);
+      ld[i].s = (sp[i][s0] | static_cast<uint32_t>(sp[i][s1]) << 8) & mask;
     }
+    asm volatile("");   // (or the loads are merged with load()'s, in pieces and with addresses in vector registers)
   };
   // The window in hand through LDS: stored as loaded, but chunk c of row r at position c ^ swizzle(r), read back in the MFMA's lane order: a
   // lane takes chunks kSteps q .. of its row, one in each step, of which each MFMA of the step takes 8 codes, and their scales.
@@ -283,11 +281,10 @@ __global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, MB * NB > 16 ? 1 : 2) void
       f[t][i] = decode8_f16(w, e4m3_decode_f16x2(block * 16 >= lo ? s : 0u));
     }
   };
-  // The rest comes last, as a window that ends where K does: its k are those from lo on (K shorter than a window: it starts at 0, with zeros above K).
-  const bool whole = kSteps == 2 || K >= kWindowK;
-  const int total = windows + (rest ? 1 : 0), k_rest = whole ? K - kWindowK : 0;
+  // The rest comes last, as a window that ends where K does: its k are those from lo on.
+  const int total = windows + (rest ? 1 : 0);
   if (total) {
-    auto k_of = [&](int n) { return n < windows ? (wk + n * WK) * kWindowK : k_rest; };
+    auto k_of = [&](int n) { return n < windows ? (wk + n * WK) * kWindowK : K - kWindowK; };
     if (whole) load(k_of(0));
     else if constexpr (kSteps == 1) load_short();
 #pragma unroll
@@ -312,8 +309,8 @@ __global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, MB * NB > 16 ? 1 : 2) void
       if (!rest) run_window(std::false_type{}, 0, {}, 0u);
     }
     if (rest) {
-      const int lo = whole ? kWindowK - rest : 0;
-      int hi = whole ? kWindowK : (K + 31) & ~31;
+      const int lo = kWindowK - rest;
+      int hi = kWindowK;
       if (static_cast<unsigned>(hi - lo - 1) % 64 < 32) {
         hi -= 32;
         rest_piece(hi, lo, 0);
@@ -421,14 +418,14 @@ static bool fits(int64_t M, int64_t N, int64_t K) {
          direct_tiles<I>(M, N) * (d.wk == 1 ? 256 : d.wk * 64) <= 0xffffffff;
 }
 
-// Steps (128 k) of the wavefront that has most of them; a rest counts half a step more than its k: nothing of it overlaps.
+// Steps (128 k) of the wavefront that has most of them; a rest counts half a step more than its k: nothing of it overlaps.  K below 128 is a step.
 template <int I>
 static double wavefront_steps(int64_t K) {
   constexpr DirectShape d = kDirectShapes[I];
   constexpr int window = 128 * d.steps;
   const int64_t full = K / window, rest = K - full * window, each = full / d.wk;
   const double whole = static_cast<double>((each + (full > each * d.wk)) * d.steps);
-  const double with_rest = static_cast<double>(each * d.steps) + (rest ? (full ? 0.5 : 1.2) + static_cast<double>(rest) / 128.0 : 0.0);
+  const double with_rest = static_cast<double>(each * d.steps) + (rest ? (full ? 0.5 + static_cast<double>(rest) / 128.0 : 1.0) : 0.0);
   return whole > with_rest ? whole : with_rest;
 }
 
