@@ -135,9 +135,7 @@ __global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, MB * NB > 16 ? 1 : 2) void
   // The wavefront's part of K: every WK-th window, and one of them the rest.  (A stretch of K to each, as even as 64 k allow, was slower, also where
   // the windows do not come out even: neighbouring lines then go to one wavefront one after the other.  512 x 5120 x 5120 29.1 / 28.4 us, 1040 x 1296 x
   // 2064 13.7 / 13.1; with windows of 128, half a line, 32 x 5120 x 5120 7.6 / 7.1.)
-  // K shorter than a window is one all the same, with zeros above K (4096 x 304 x 112 6.0 us as a rest, 5.5 so).
-  const bool whole = kSteps == 2 || K >= kWindowK;
-  const int full = whole ? K / kWindowK : 1, windows = (full - wk + WK - 1) / WK, rest = whole && full % WK == wk ? K - full * kWindowK : 0;
+  const int full = K / kWindowK, windows = (full - wk + WK - 1) / WK, rest = full % WK == wk ? K - full * kWindowK : 0;
 
   float4v acc[MB][NB];
 #pragma unroll
@@ -172,9 +170,17 @@ __global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, MB * NB > 16 ? 1 : 2) void
 #pragma unroll
     for (int i = 0; i < S::kBlocks; ++i) load_block(i, k, co, so);
   };
-  // A window that is not there whole (K shorter than it; windows of 128 only, see fits): a lane's chunk, and its two scales, are there whole, half or not
-  // at all; what is not is read from the row's first bytes, and its scales are 0.  The offsets and the mask are opaque (no instruction): knowing that they go
-  // together the compiler jumps around each block's scales and waits for them there, one block after the other (4096 x 304 x 112 5.5 us, 4.9 so).
+  // The rest of K as a window of 128 that ends where K does, whose scales are 0 for what is not the rest's.
+  auto load_rest = [&]() {
+    load(K - kWindowK);
+    const int first = (kWindowK - rest) / 16 - spart * 2;   // block of the rest's first k, counted from the lane's
+    const uint32_t mask = first <= 0 ? 0xFFFFu : first == 1 ? 0xFF00u : 0u;
+#pragma unroll
+    for (int i = 0; i < S::kBlocks; ++i) ld[i].s &= mask;
+  };
+  // K shorter than a window of 128: a lane's chunk, and its two scales, are there whole, half or not at all; what is not is read from the row's first
+  // bytes, and its scales are 0.  The offsets and the mask are opaque (no instruction): knowing that they go together the compiler jumps around each
+  // block's scales and waits for them there, one block after the other (4096 x 304 x 112 5.5 us, 4.9 so).
   auto load_short = [&]() {
     const bool in0 = chunk * 32 < K, in1 = chunk * 32 + 16 < K;
     uint32_t lo = static_cast<uint32_t>(crow * code_ld) + (in0 ? chunk * 16 : 0), hi = lo + (in1 ? 8 : 0);
@@ -281,16 +287,24 @@ __global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, MB * NB > 16 ? 1 : 2) void
       f[t][i] = decode8_f16(w, e4m3_decode_f16x2(block * 16 >= lo ? s : 0u));
     }
   };
-  // The rest comes last, as a window that ends where K does: its k are those from lo on.
+  // The rest: the first of the wavefront's windows, or the last, in pieces of 32 k of which nothing overlaps: with windows of 256, and up to 64 k in the
+  // larger tiles, where a window would leave more than half of it empty.  us, window / pieces: 64 x 64 tiles of 320 x 2560 x 368 5.1 / 5.4, 64 x 48 of 448 x
+  // 1456 x 368 4.6 / 4.9, 16 x 32 of 48 x 768 x 4272 5.7 / 5.8; own 64 x 64 of 304 x 20224 x 144 12.2 / 11.4, 64 x 64 of 1344 x 1536 x 192 6.3 / 6.0.
+  constexpr bool kAlwaysFirst = kSteps == 1 && MB * NB <= 4;
+  const bool rest_first = kAlwaysFirst || (kSteps == 1 && (rest > 64 || full == 0)), pieces = !rest_first && rest;
   const int total = windows + (rest ? 1 : 0);
   if (total) {
-    auto k_of = [&](int n) { return n < windows ? (wk + n * WK) * kWindowK : K - kWindowK; };
-    if (whole) load(k_of(0));
-    else if constexpr (kSteps == 1) load_short();
+    const int first = rest_first && rest ? wk - WK : wk;   // number of the window that would be the first if all were whole
+    auto k_of = [&](int n) { return n < windows || !pieces ? (first + n * WK) * kWindowK : K - kWindowK; };
+    if (!rest_first || !rest) load(k_of(0));
+    else if constexpr (kSteps == 1) {
+      if (full) load_rest();
+      else load_short();
+    }
 #pragma unroll
     for (int i = 0; i < S::kBlocks; ++i) stage(i);
     wavefront_exchange();
-    if (windows) {
+    if (kAlwaysFirst || windows || !pieces) {
       if (total > 1) load(k_of(1));
 #pragma unroll
       for (int i = 0; i < S::kBlocks; ++i) {
@@ -306,9 +320,9 @@ __global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, MB * NB > 16 ? 1 : 2) void
         offsets(next + 1 < total, co, so);
         run_window(std::true_type{}, k_of(min(next + 1, total - 1)), co, so);
       }
-      if (!rest) run_window(std::false_type{}, 0, {}, 0u);
+      if (kAlwaysFirst || !pieces) run_window(std::false_type{}, 0, {}, 0u);
     }
-    if (rest) {
+    if (!kAlwaysFirst && pieces) {
       const int lo = kWindowK - rest;
       int hi = kWindowK;
       if (static_cast<unsigned>(hi - lo - 1) % 64 < 32) {
@@ -418,14 +432,15 @@ static bool fits(int64_t M, int64_t N, int64_t K) {
          direct_tiles<I>(M, N) * (d.wk == 1 ? 256 : d.wk * 64) <= 0xffffffff;
 }
 
-// Steps (128 k) of the wavefront that has most of them; a rest counts half a step more than its k: nothing of it overlaps.  K below 128 is a step.
+// Steps (128 k) of the wavefront that has most of them.  A rest that is worked in pieces counts half a step more than its k.
 template <int I>
 static double wavefront_steps(int64_t K) {
   constexpr DirectShape d = kDirectShapes[I];
   constexpr int window = 128 * d.steps;
   const int64_t full = K / window, rest = K - full * window, each = full / d.wk;
   const double whole = static_cast<double>((each + (full > each * d.wk)) * d.steps);
-  const double with_rest = static_cast<double>(each * d.steps) + (rest ? (full ? 0.5 + static_cast<double>(rest) / 128.0 : 1.0) : 0.0);
+  const bool a_window = d.steps == 1 && (d.mb * d.nb <= 4 || rest > 64 || full == 0);
+  const double with_rest = static_cast<double>(each * d.steps) + (rest ? (a_window ? 1.0 : 0.5 + static_cast<double>(rest) / 128.0) : 0.0);
   return whole > with_rest ? whole : with_rest;
 }
 
