@@ -328,15 +328,15 @@ __global__ __launch_bounds__(kBigThreads) void gemm_kernel_256(Operand A, Operan
 
 }  // namespace
 
-// Expected time of the 256 x 256 fused kernel: rounds of 256 tiles at 10.8 us and 25.2 ns per k (31 with the chip full for long, at a lower
-// clock).  Fitted to 95 calls; 5th and 95th percentile 0.89 and 1.17 of the measured time.
+// Expected time of the 256 x 256 fused kernel: rounds of 256 tiles at 12.2 us and 25.2 ns per k (31 with the chip full for long, at a lower
+// clock).  5th and 95th percentile over 183 calls 0.83 and 1.26 of the measured time.
 static double fused_us(int64_t M, int64_t N, int64_t K) {
   const int64_t tiles = ((M + TM - 1) / TM) * ((N + TN - 1) / TN);
-  return 1.4 + static_cast<double>((tiles + 255) / 256) * (10.8 + static_cast<double>(K) * (tiles > 1024 ? 0.031 : 0.0252));
+  return 1.4 + static_cast<double>((tiles + 255) / 256) * (12.2 + static_cast<double>(K) * (tiles > 1024 ? 0.031 : 0.0252));
 }
 
 // The 128 x 128 kernel, in the same terms (steps of 64 k; three workgroups fit a CU).
-static constexpr SmallTileCost kTile128Cost{3, 3.9, 1.52, 0.365, 0.759, 0.203};
+static constexpr SmallTileCost kTile128Cost{3, 1.49, 1.37, 0.817};
 
 static hipError_t launch_tile128(const GemmArgs& g, hipStream_t s) {
   const dim3 grid(static_cast<unsigned>((g.b.outer + BN - 1) / BN), static_cast<unsigned>((g.a.outer + BM - 1) / BM));
@@ -369,36 +369,40 @@ struct GemmPlan {
   TwoPassPlan two_pass;  // kTwoPass
 };
 
-// The kernel that is expected to be the fastest, with a margin where the estimates are known to lean one way.  Over the same 1080 products the
-// calls take 1.5 % more than with the best kernel each.  us, direct / two-pass: 512 x 5120 x 5120 28 / 82, 4352 x 1280 x 5376 63 / 80, 2048 x 5120 x 5120 95 / 94,
-// 4352 x 4096 x 4096 155 / 133, 8192 x 20480 x 5120 1474 / 1152.
+// The kernel with the smallest expected time: the two-pass route where the workspace allows it; the 256 x 256 kernel for whole K steps of 64 and 16-byte
+// aligned code rows; 128 x 128 tiles, whose workgroups decode them once, for large results of a short contraction (three of them per CU keep more stores in
+// flight, steps of 64 waste less); the direct kernel with K split among a workgroup's wavefronts or with a tile to each.  The estimates
+// are fitted to measured times (profiles/gemm_routes_us.csv); over its products the calls take 1.5 % more than with the best kernel each.  us,
+// direct / two-pass: 512 x 5120 x 5120 28 / 82, 4352 x 1280 x 5376 63 / 80, 2048 x 5120 x 5120 95 / 94, 4352 x 4096 x 4096 155 / 133, 8192 x 20480 x 5120 1474 /
+// 1152; own tiles / 128 x 128: 5120 x 20480 x 16 (FP32) 87 / 80, x 208 103 / 107.
 static GemmPlan plan_route(const GemmArgs& g) {
-  // The direct kernel: its best shape, with K split among a workgroup's wavefronts or a tile to each
-  const DirectPick split = pick_direct_shape(g, false), own = pick_direct_shape(g, true);
-  const double direct_us = split.us < own.us ? split.us : own.us;
-  // With a workspace: decode pass + FP16 GEMM.  The direct kernel takes up to 15 % longer than its estimate in long products, the clock being lower.
-  const TwoPassPlan two_pass = plan_two_pass(g);
-  const double power = direct_us > 30.0 ? 0.0022 * (direct_us - 30.0) : 0.0;
-  if (two_pass.usable && two_pass.us <= direct_us * (1.0 + (power < 0.15 ? power : 0.15))) return {kTwoPass, {}, two_pass};
-  // Without: the fused kernel -- it needs whole K steps of 64 and 16-byte aligned code rows.
-  const bool big = (g.K % TK == 0) && (reinterpret_cast<uintptr_t>(g.a.codes) % 16 == 0) &&
-                   (reinterpret_cast<uintptr_t>(g.b.codes) % 16 == 0);
-  if (big && fused_us(g.a.outer, g.b.outer, g.K) <= direct_us) return {kFused256, {}, {}};
-  // Large results of a short contraction: 128 x 128 tiles of workgroups that decode them once (three of them per CU keep more stores in flight,
-  // steps of 64 waste less), against the direct kernel with a tile per wavefront.  us, own / 128 x 128: 5120 x 20480 x 16 (FP32) 87 / 80, x 208 103 / 107.
-  // Where K ends in a partial step of 128, own tiles have to promise 8 %: nearer than that the estimates do not tell the two apart.  Accumulated
-  // results move that line (and the choice is one for all, see SmallTileCost): where a large result is read too, two workgroups per CU hide that worse
-  // than three (5120 x 20480 x 400 324 / 290, 4096 x 5120 x 400 75 / 73), so from 3e7 elements on own tiles have to promise 17 % (K of some 800).
   const double elements = static_cast<double>(g.a.outer) * static_cast<double>(g.b.outer);
+  // Small results of a step or less always split K: a wavefront has a step at the most either way, and where the result is read too the others lose (768 x
+  // 2128 x 64 accumulated 8.0 us split, 10.9 in own tiles), and the choice is one for all output types.
+  const bool split_only = g.K <= 128 && elements <= 2097152.0;
+  const DirectPick direct = pick_direct_shape(g, split_only);
+  GemmPlan plan{kDirect, direct, {}};
+  double us = direct.us;
   const int64_t tiles128 = ((g.a.outer + BM - 1) / BM) * ((g.b.outer + BN - 1) / BN);
-  const double tile128 = g.a.outer > int64_t{65535} * BM ? HUGE_VAL   // its tile rows are the launch's second dimension
-                                                         : small_tile_us(kTile128Cost, tiles128, elements, static_cast<double>((g.K + BK - 1) / BK));
-  const bool take_own = own.us < (elements > 3e7 ? 0.83 : g.K % 128 ? 0.92 : 1.02) * tile128;
-  const double other_us = take_own ? own.us : tile128;
-  // Split K against these: small results of a step or less keep it while the estimate, which is too high there (768 x 2128 x 64 8.6 for 6.6 us), is not far
-  // off: where the result is read too, the others lose more (8.0 us split, 10.9 in own tiles).  From K = 1024 on they have to promise 8 %.
-  if (split.us <= (g.K <= 128 && elements <= 2097152.0 ? 1.45 : g.K >= 1024 ? 1.08 : 1.0) * other_us) return {kDirect, split, {}};
-  return take_own ? GemmPlan{kDirect, own, {}} : GemmPlan{kTile128, {}, {}};
+  const double tile128 = small_tile_us(kTile128Cost, tiles128, elements, static_cast<double>((g.K + BK - 1) / BK));
+  if (!split_only && tile128 < us && g.a.outer <= int64_t{65535} * BM) {   // (its tile rows are the launch's second dimension)
+    plan.route = kTile128;
+    us = tile128;
+  }
+  const bool big = (g.K % TK == 0) && (reinterpret_cast<uintptr_t>(g.a.codes) % 16 == 0) && (reinterpret_cast<uintptr_t>(g.b.codes) % 16 == 0);
+  const double fused = fused_us(g.a.outer, g.b.outer, g.K);
+  if (big && (fused < us || direct.us == HUGE_VAL)) {
+    plan.route = kFused256;
+    us = fused;
+  }
+  // The direct kernel takes up to 15 % longer than its estimate in long products, the clock being lower: 3072 x 4352 x 18272 600 us, 517 two-pass.
+  const double power = plan.route == kDirect && us > 30.0 ? 0.0022 * (us - 30.0) : 0.0;
+  const TwoPassPlan two_pass = plan_two_pass(g);
+  if (two_pass.usable && two_pass.us <= us * (1.0 + (power < 0.15 ? power : 0.15))) {
+    plan.route = kTwoPass;
+    plan.two_pass = two_pass;
+  }
+  return plan;
 }
 
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
@@ -439,16 +443,7 @@ extern "C" void nvfp4_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int bf
   }
 }
 
-// Likewise: {MB, NB, WK, steps} of the shape in which the direct kernel takes such a product.  own: without a split of K.
-extern "C" void nvfp4_internal_direct_shape(int64_t M, int64_t N, int64_t K, int own, int* out) {
-  nvfp4::GemmArgs g{};
-  g.a.outer = M;
-  g.b.outer = N;
-  g.K = K;
-  nvfp4::direct_shape(nvfp4::pick_direct_shape(g, own != 0).shape, out);
-}
-
-// Likewise: that of the direct kernel's shape of this number; 0: there is none.
+// Likewise: {MB, NB, WK, steps} of the direct kernel's shape of this number; 0: there is none.
 extern "C" int nvfp4_internal_direct_shape_at(int shape, int* out) { return nvfp4::direct_shape(shape, out); }
 
 // Likewise: whether that shape can do such a product.

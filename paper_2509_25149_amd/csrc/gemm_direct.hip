@@ -11,7 +11,7 @@
 //   - What bounds it is the issue of vector instructions: a 16 x 32 fragment takes 8 of them (4 cvt, 4 pk_mul) and serves MB or
 //     NB MFMAs.  Measured, cycles per MFMA with V such instructions beside it: 8 + 4.5 V (16 alone), whichever wavefront of the SIMD they
 //     are from, so that 4 x 4 blocks (V = 4) cannot do better than 26 and 8 x 5 (2.6) reach 20: the large shapes have one wavefront per SIMD
-//     and 460 registers.
+//     and 320 to 512 registers.
 //   - One wavefront per SIMD has nobody to fill its waits, so the loop is pipelined: behind a row of MFMAs go the decode of the next row's
 //     fragment, the LDS reads of the next step, the stores of the next window into LDS and the loads of the window after it, each
 //     an instruction or two behind an MFMA (interleave).  64 x 80 tiles of 64 x 20480 x 8192: 30.7 us with the same parts in turn, 25.5 so;
@@ -386,31 +386,31 @@ __global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, MB * NB > 16 ? 1 : 2) void
 }  // namespace
 
 // The tile shapes the kernel comes in: MB x NB blocks per wavefront, WK wavefronts that split K, steps of 128 k to a window.  `kind` (for the
-// tests): 0 16 x 32 tiles, 1 32 rows, 2 64 x 48 and 80 columns, 3 64 x 64 and 128 rows, 4 a tile to each wavefront.  Which of them: `us`, fitted to
-// 1080 products of 16 .. 8192 rows, 256 .. 20480 columns, K 16 .. 20480, FP32 and bf16 (5th and 95th percentile 0.87 and 1.15 of the
-// measured time); the shapes taken by it need 0.9 % more than the best ones do.  Large tiles decode less per product, small ones fill the chip; without a
+// tests): 0 16 x 32 tiles, 1 32 rows, 2 64 x 48 and 80 columns, 3 64 x 64 and 128 rows, 4 a tile to each wavefront.  Which of them: the smallest `us`, fitted,
+// three constants to a shape, to products of 16 .. 8192 rows, 256 .. 20480 columns, K 16 .. 20480 (profiles/gemm_routes_us.csv; 5th and 95th
+// percentile 0.83 and 1.16 of the measured time).  Large tiles decode less per product, small ones fill the chip; without a
 // split of K there is no sum through LDS.  us, 64 x 48 / 64 x 64 / 64 x 80 / 128 x 80 / own 64 x 64 / own 128 x 80 / the rest at best: 64 x 20480 x 5120 22.1 /
 // 26.1 / 19.0 / 27.6 / 42 / 84 / 20.3, 512 x 5120 x 5120 40 / 36 / 35 / 28 / 44 / 84 / 36, 4096 x 5120 x 2064 130 / 122 / 168 / 130 / 119 / 97 / 120,
-// 1024 x 1024 x 1024 7.2 / 6.1 / 6.9 / 10 / 12 / - / 7.5, 32 x 5120 x 5120 12 / 13 / 16 / 24 / 41 / - / 7.1 (32 x 32).
+// 1024 x 1024 x 1024 7.2 / 6.1 / 6.9 / 10 / 12 / - / 7.5, 32 x 5120 x 5120 12 / 13 / 16 / 24 / 41 / - / 7.1 (32 x 32).  What a shape earns, over the products
+// of that table: without it they take so many % longer, the worst that many times as long (64 x 48 with windows of 256, 0.01 % and 1.12, went).
 struct DirectShape {
   int mb, nb, wk, steps, kind;
   SmallTileCost us;
 };
 constexpr DirectShape kDirectShapes[] = {
-    {4, 4, 4, 1, 3, {2, 3.58, 1, 0.285, 1.15, 0.341}},
-    {2, 2, 8, 1, 1, {2, 3.11, 1, 0, 0.867, 0.6}},
-    {4, 3, 4, 1, 2, {2, 3.23, 1, 0.387, 1.01, 0.341}},
-    {4, 3, 4, 2, 2, {2, 3.38, 1.07, 0.198, 0.904, 0.382}},
-    {1, 2, 4, 1, 0, {5, 3.15, 1.29, 0, 0.309, 0.368}},
-    {1, 2, 4, 2, 0, {5, 3.09, 1.41, 0, 0.268, 0}},
-    {1, 2, 8, 1, 0, {3, 3.12, 1.02, 0, 0.594, 0.6}},
-    {2, 4, 8, 1, 1, {1, 1.57, 1, 1.59, 1.44, 0.147}},
-    {4, 5, 4, 2, 2, {1, 1.69, 1, 2.22, 1.4, 0.528}},
-    {5, 5, 4, 2, 2, {1, 1.6, 1, 2.52, 1.61, 0.468}},
-    {8, 5, 4, 2, 3, {1, 1.51, 1, 3.87, 2.26, 0.221}},
-    {4, 4, 1, 1, 4, {2, 3.96, 1, 0.608, 1.1, 0.218}},
-    {8, 5, 1, 2, 4, {1, 2.99, 1, 5.99, 2, 0.24}},
-    {6, 4, 1, 2, 4, {1, 2.42, 1, 3.44, 1.42, 0.292}},
+    {4, 4, 4, 1, 3, {2, 1.12, 0.99, 1.06}},    // 1.16 %, 1.52
+    {2, 2, 8, 1, 1, {2, 1.03, 0.27, 0.806}},   // 0.70 %, 1.62
+    {4, 3, 4, 1, 2, {2, 1.13, 0.64, 0.934}},   // 0.81 %, 1.43
+    {1, 2, 4, 1, 0, {5, 1.38, 0.08, 0.285}},   // 0.50 %, 1.45
+    {1, 2, 4, 2, 0, {5, 1.53, 0.03, 0.26}},    // 0.18 %, 1.17
+    {1, 2, 8, 1, 0, {3, 1.15, 0.11, 0.545}},   // 0.80 %, 1.32
+    {2, 4, 8, 1, 1, {1, 1.0, 0.72, 1.46}},     // 0.34 %, 1.29
+    {4, 5, 4, 2, 2, {1, 1.0, 1.89, 1.39}},     // 0.25 %, 1.43
+    {5, 5, 4, 2, 2, {1, 1.0, 2.26, 1.6}},      // 0.20 %, 1.39
+    {8, 5, 4, 2, 3, {1, 1.0, 3.51, 2.29}},     // 0.25 %, 1.34
+    {4, 4, 1, 1, 4, {2, 1.08, 2.0, 1.03}},     // 0.98 %, 1.42
+    {8, 5, 1, 2, 4, {1, 1.0, 8.07, 2.0}},      // 0.18 %, 1.57
+    {6, 4, 1, 2, 4, {1, 1.0, 5.02, 1.38}},     // 0.17 %, 1.32
 };
 constexpr int kNumDirectShapes = sizeof(kDirectShapes) / sizeof(kDirectShapes[0]);
 using AllShapes = std::make_integer_sequence<int, kNumDirectShapes>;
@@ -444,24 +444,28 @@ static double wavefront_steps(int64_t K) {
   return whole > with_rest ? whole : with_rest;
 }
 
+// A tile to each wavefront and one workgroup to a CU: large results wait more for their stores, and accumulated ones for their loads, than two
+// workgroups do: us, 64 x 64 / 128 x 80: 4096 x 8192 x 1040 93 / 114, accumulated 111 / 165; 6560 x 8320 x 1056 accumulated 189 / 223.
 template <int I>
 static double shape_us(const GemmArgs& g) {
   if (!fits<I>(g.a.outer, g.b.outer, g.K)) return HUGE_VAL;
-  return small_tile_us(kDirectShapes[I].us, direct_tiles<I>(g.a.outer, g.b.outer), static_cast<double>(g.a.outer) * static_cast<double>(g.b.outer),
-                       wavefront_steps<I>(g.K));
+  constexpr DirectShape d = kDirectShapes[I];
+  const double elements = static_cast<double>(g.a.outer) * static_cast<double>(g.b.outer);
+  const double us = small_tile_us(d.us, direct_tiles<I>(g.a.outer, g.b.outer), elements, wavefront_steps<I>(g.K));
+  return d.wk == 1 && d.us.resident == 1 && elements > 3e7 ? 1.1 * us : us;
 }
 
 template <int... I>
-static DirectPick pick_shape(const GemmArgs& g, bool own, std::integer_sequence<int, I...>) {
+static DirectPick pick_shape(const GemmArgs& g, bool split_only, std::integer_sequence<int, I...>) {
   DirectPick best{0, 0, HUGE_VAL};
-  auto consider = [&](int shape, double us) {   // (nearer than 5 % the estimates do not tell two shapes apart)
-    if (us < 0.95 * best.us) best = DirectPick{shape, kDirectShapes[shape].kind, us};
+  auto consider = [&](int shape, double us) {
+    if (us < best.us) best = DirectPick{shape, kDirectShapes[shape].kind, us};
   };
-  ((own == (kDirectShapes[I].wk == 1) ? consider(I, shape_us<I>(g)) : void()), ...);
+  (((split_only && kDirectShapes[I].wk == 1) ? void() : consider(I, shape_us<I>(g))), ...);
   return best;
 }
 
-DirectPick pick_direct_shape(const GemmArgs& g, bool own_tiles) { return pick_shape(g, own_tiles, AllShapes{}); }
+DirectPick pick_direct_shape(const GemmArgs& g, bool split_only) { return pick_shape(g, split_only, AllShapes{}); }
 
 bool direct_shape(int shape, int* out) {
   if (shape < 0 || shape >= kNumDirectShapes) return false;

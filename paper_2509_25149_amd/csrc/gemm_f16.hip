@@ -521,10 +521,10 @@ size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) {
 
 // What a call does: one answer for the estimate, the room asked of the workspace and the launch.  The partial tiles of a split
 // count only where tiles are 256 columns wide, and a workspace without room for them makes the last round an ordinary one.
-// Expected time: what is still to decode (codes and scales in, FP16 out) at 5.0 TB/s, then rounds of 256 tiles at 7.9 us for the result and 15.9 ns
+// Expected time: what is still to decode (codes and scales in, FP16 out) at 5.0 TB/s, then rounds of 256 tiles at 9.2 us for the result and 15.9 ns
 // per k while there are fewer (3072 x 5120 x 5120, 240 tiles: 130 us in all), 18.6 when the chip is full (the clock drops with the matrix
-// pipes busy) -- of a plain result, for all output types (see SmallTileCost).  Fitted to 177 calls of 12 us to 1.3 ms; 5th and 95th
-// percentile 0.81 and 1.18 of the measured time, from 200 us on 0.88 .. 1.09.
+// pipes busy) -- of a plain result, for all output types (see SmallTileCost).  5th and 95th percentile over 269 calls of 12 us to
+// 1.3 ms 0.76 and 1.17 of the measured time.
 TwoPassPlan plan_two_pass(const GemmArgs& g) {
   TwoPassPlan plan{false, HUGE_VAL, 8, 0, 1};
   const int64_t M = g.a.outer, N = g.b.outer;
@@ -536,7 +536,7 @@ TwoPassPlan plan_two_pass(const GemmArgs& g) {
   if (operands + partial_bytes(tail) > g.workspace_bytes) tail = TailPlan{0, 1};
   Width w = pick_width(M, N, tail, false);
   plan.us = 7.4 + static_cast<double>(rows) * static_cast<double>(g.K) * 2.5625 / 5.0e6 +
-            w.rounds * (7.9 + static_cast<double>(g.K) * (w.tiles >= kCUs ? 0.0186 : 0.0159));
+            w.rounds * (9.2 + static_cast<double>(g.K) * (w.tiles >= kCUs ? 0.0186 : 0.0159));
   if (g.accumulate && g.K < 1024) w = pick_width(M, N, tail, true);
   if (w.nb != 8) tail = TailPlan{0, 1};
   plan.units = w.nb;

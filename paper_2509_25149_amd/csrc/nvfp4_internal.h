@@ -102,25 +102,26 @@ struct DirectPick {
   int shape, kind;       // its number in the kernel's list; the kind of tile (see there)
   double us;             // expected
 };
-DirectPick pick_direct_shape(const GemmArgs& g, bool own_tiles);   // the best of the shapes that split K, or of those whose wavefronts own different tiles
+DirectPick pick_direct_shape(const GemmArgs& g, bool split_only);   // the best of them, or of those that split K; none can do it: HUGE_VAL
 bool direct_shape(int shape, int* out);   // MB, NB, WK, steps of a shape, for the tests; false: no such shape
 bool direct_shape_fits(const GemmArgs& g, int shape);   // whether it can do this product
-// Expected time of a kernel on small tiles: `call`, then rounds of 256 tiles of `tile` us and `step` us per step of the loop,
-// or, where that is more, the result's bytes at `result` us per MB (added in quadrature: neither hides the other fully).  A
+// Expected time of a kernel on small tiles: that of a call, then rounds of 256 tiles of `tile` us and `step` us per step of the loop,
+// or, where that is more, of the result's bytes (added in quadrature: neither hides the other fully).  A
 // CU holds `resident` workgroups; a round in which only one of them has a tile takes `alone` rounds, not 1.
 // Bytes of an FP32 result, whatever leaves: the choice of the kernel must not depend on the output type, since bf16 and accumulated
 // results are defined by the FP32 ones, to the last bit of whose sums the order of summation counts.
 struct SmallTileCost {
   int resident;
-  double call, alone, tile, step, result;
+  double alone, tile, step;
 };
+constexpr double kCallUs = 2.6, kResultUsPerMB = 0.15;
 // (Always inlined with constants: a launch that takes 7 us to issue should not spend one on divisions by tile sizes.)
 __attribute__((always_inline)) inline double small_tile_us(const SmallTileCost& c, int64_t tiles, double elements, double steps) {
   const int64_t wave = int64_t{256} * c.resident, whole = tiles / wave, last = (tiles - whole * wave + 255) / 256;   // tiles of a CU in the last wave
   double rounds = static_cast<double>(whole * c.resident);
   if (last) rounds += c.resident == 1 ? 1.0 : c.alone + static_cast<double>(last - 1) * (c.resident - c.alone) / (c.resident - 1);
-  const double loop = rounds * (c.tile + c.step * steps), result = c.result * elements * 4e-6;
-  return c.call + __builtin_sqrt(loop * loop + result * result);
+  const double loop = rounds * (c.tile + c.step * steps), result = kResultUsPerMB * elements * 4e-6;
+  return kCallUs + __builtin_sqrt(loop * loop + result * result);
 }
 // Decodes one operand (codes [outer, K/2], scales [outer, K/16]) to FP16 [outer, K]
 hipError_t launch_predecode(const Operand& op, int64_t K, void* fp16_out, hipStream_t s);

@@ -15,12 +15,12 @@ pytestmark = pytest.mark.gpu
 # tile shape the dispatch takes for it: 16x32 tiles (8 wavefronts; 4 for many tiles), 32x32, 64x48, 64x64 with K split among the
 # wavefronts; 128x128 with a tile per wavefront; the 128x128 kernel.
 # K: shorter than a step of 128; a step and a rest of one 16-block; whole steps; more steps than wavefronts, with a rest (every
-# wavefront stages, reads back and stages again, and the sums of all of them are added).  The last six: many rounds of tiles.
+# wavefront stages, reads back and stages again, and the sums of all of them are added).  The last seven: many rounds of tiles.
 @pytest.mark.parametrize("M,N,K,kernel", [
-    (16, 16, 16, (DIRECT, 0)), (48, 80, 112, (DIRECT, 0)), (16, 16400, 272, (DIRECT, 0)), (32, 5136, 400, (DIRECT, 1)),
+    (16, 16, 16, (DIRECT, 0)), (48, 80, 112, (DIRECT, 0)), (16, 16400, 272, (DIRECT, 0)), (32, 5136, 400, (DIRECT, 0)), (32, 5136, 528, (DIRECT, 1)),
     (64, 9232, 128, (DIRECT, 2)), (80, 8208, 144, (DIRECT, 0)), (144, 5200, 1040, (DIRECT, 3)), (32, 5136, 2192, (DIRECT, 1)),
-    (64, 9232, 1168, (DIRECT, 2)), (16, 16400, 1040, (DIRECT, 0)), (528, 5136, 1104, (DIRECT, 3)),
-    (2064, 8208, 16, (TILE_128, 0)), (2064, 4112, 80, (TILE_128, 0)), (1040, 8208, 208, (TILE_128, 0)),
+    (64, 9232, 1168, (DIRECT, 2)), (16, 16400, 1040, (DIRECT, 0)), (528, 5136, 1104, (DIRECT, OWN_TILES)), (272, 5136, 1104, (DIRECT, 3)),
+    (2064, 8208, 16, (TILE_128, 0)), (2064, 4112, 80, (TILE_128, 0)), (1040, 8208, 208, (DIRECT, OWN_TILES)), (1040, 8208, 176, (TILE_128, 0)),
     (2064, 8208, 528, (DIRECT, OWN_TILES)), (4112, 4112, 528, (DIRECT, OWN_TILES)), (2064, 2064, 128, (DIRECT, OWN_TILES))])
 @pytest.mark.parametrize("per_row", [False, True], ids=["tensor_scale", "row_scales"])
 def test_direct_gemm(M, N, K, kernel, per_row):

@@ -13,7 +13,7 @@ from test_gpu_parity import GEMM_TOL, check_quantize, to_dev
 
 pytestmark = pytest.mark.gpu
 
-NUM_SHAPES = 14      # test_every_shape_is_named
+NUM_SHAPES = 13      # test_every_shape_is_named
 
 
 def force(shape, a, b, out, out_dtype):

@@ -142,7 +142,7 @@ def test_gemm_with_row_scales_all_ops(mnk):
 @pytest.mark.parametrize("scales_on", ["A", "B", "both"])
 @pytest.mark.parametrize("M,N,K,with_ws,without", [
     (4112, 4368, 128, (DIRECT, 4, 0, 1), (DIRECT, 4, 0, 1)),
-    (4352, 4096, 1024, (TWO_PASS, 5, 0, 1), (DIRECT, 3, 0, 1)),
+    (4352, 4096, 1024, (TWO_PASS, 5, 0, 1), (DIRECT, 4, 0, 1)),
     (4080, 8176, 192, (TWO_PASS, 8, 0, 1), (FUSED_256, 0, 0, 1)),
     (8176, 5104, 1088, (TWO_PASS, 8, 128, 2), None),
     (4336, 4080, 4096, (TWO_PASS, 8, 16, 8), None)])
