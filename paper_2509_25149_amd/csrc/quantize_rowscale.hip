@@ -5,7 +5,7 @@
 // copy's K-contiguous storage -- per logical row for the row copy, per logical column (in the rotated space, App. C)
 // for the col copy.  Eq. 1 is evaluated per row with that row's amax; Eq. 2-4 are unchanged.
 //
-//   row copy alone    ONE pass over the tensor: a wavefront (rows of up to 1024 columns, or 2048) or a workgroup (up to 32768)
+//   row copy alone    ONE pass over the tensor: a wavefront (short rows, see launch_quantize_rowscale) or a workgroup (up to 32768 columns)
 //                     owns one row, holds all of it in registers, reduces the row's amax and encodes from the
 //                     registers.  The bf16 tensor crosses HBM once.
 //   col copy (+ row)  a column's amax spans every row of the tensor (all tokens), far more than a workgroup can hold,
@@ -426,16 +426,25 @@ void launch_two_pass(const QuantizeArgs& a, hipStream_t s) {
 size_t quantize_rowscale_workspace_words(int64_t rows, int64_t cols) { return static_cast<size_t>(2 * (rows + cols)); }
 
 hipError_t launch_quantize_rowscale(const QuantizeArgs& a, hipStream_t s) {
-  // A row to a wavefront up to 1024 columns, and with enough rows up to 2048; longer ones to a workgroup, whose lanes have a quarter of the row's chain of
-  // blocks, each with its division.  us, wavefront / workgroup: 512 x 1024 3.2 / 3.3, 2048 x 1024 3.6 / 4.1; 512 x 2048 3.7 / 3.4, 1024 x 2048 3.8 / 3.7, 2048 x
-  // 2048 4.2 / 4.6; 64 x 5120 5.1 / 3.6, 512 x 5120 5.3 / 4.1, 2048 x 5120 7.2 / 7.3, 8192 x 5120 23.7 / 19.4, 512 x 8192 6.9 / 4.4; stochastic rounding alike
-  // (512 x 5120 6.5 / 4.7, 8192 x 5120 28.2 / 25.8).
-  if (a.want_row && !a.want_col && a.cols <= (a.rows > 1024 ? 2048 : 1024)) {
-    const bool two = a.cols <= 1024;
+  // A row to a wavefront or to a workgroup, whose lanes have a quarter of the row's chain of blocks, each with its division, and which fills its chunks of 2048
+  // columns less well.  The chain counts in short calls and in long rows; where many rows hide it, the wavefronts' fewer barriers and fuller chunks do, until
+  // memory bounds both.  us, wavefront / workgroup, RNE: 512 x 1024 3.2 / 3.3, 2048 x 1024 3.6 / 4.1; 512 x 2048 3.7 / 3.4, 1024 x 2048 3.8 / 3.7,
+  // 2048 x 2048 4.2 / 4.6; 1536 x 2064 3.9 / 3.9, 2048 x 2064 4.1 / 4.4, 4096 x 2064 6.0 / 6.9, 6144 x 2560 8.6 / 9.1, 7168 x 2320 10.6 / 10.3; 2048 x
+  // 3072 4.5 / 4.6, 4096 x 3072 6.9 / 7.4, 6144 x 3072 11.3 / 10.0; 4096 x 3328 8.4 / 7.8, 4096 x 5120 13.5 / 11.5, 64 x 5120 5.1 / 3.6, 8192 x 5120 22.8 /
+  // 18.7 (only 1920 .. 2048 rows of 4112 .. 4608 columns, one round of wavefronts, lose: 2048 x 4112 5.8 / 6.3); SR: 2048 x 2064 5.2 / 5.4, 4096 x 2064 8.2 / 9.0, 2048 x 3072 5.9 / 5.9, 4096 x 3072 9.5 / 9.9, 6144 x 3072 15.2 / 13.7.
+  const bool short_row = a.cols <= 1024 || (a.cols <= 2048 && a.rows > 1024) || (a.cols <= 3072 && a.rows >= 2048 && a.rows * a.cols <= 16000000);
+  if (a.want_row && !a.want_col && short_row) {
+    const int64_t nch = (a.cols + 511) / 512;
     if (a.sr) {
-      if (two) launch_row_wave<true, 2>(a, s); else launch_row_wave<true, 4>(a, s);
+      if (nch <= 2) launch_row_wave<true, 2>(a, s);
+      else if (nch <= 4) launch_row_wave<true, 4>(a, s);
+      else if (nch <= 5) launch_row_wave<true, 5>(a, s);
+      else launch_row_wave<true, 6>(a, s);
     } else {
-      if (two) launch_row_wave<false, 2>(a, s); else launch_row_wave<false, 4>(a, s);
+      if (nch <= 2) launch_row_wave<false, 2>(a, s);
+      else if (nch <= 4) launch_row_wave<false, 4>(a, s);
+      else if (nch <= 5) launch_row_wave<false, 5>(a, s);
+      else launch_row_wave<false, 6>(a, s);
     }
     return hipGetLastError();
   }
