@@ -274,12 +274,12 @@ __global__ __launch_bounds__(kThreads, 4) void quantize_mx_kernel(const uint16_t
 
 template <bool kRow, bool kCol, bool kRht>
 void dispatch(const QuantizeArgs& a, dim3 grid, hipStream_t s) {
-  // Up to 768 workgroups (of the 1024 that are resident at once) the call takes as long as a patch or two do: each copy gets workgroups of its own, though
-  // the patch is then read twice.  us, one set / two: X 4096 x 4096 (512) 18.8 / 17.4, X 4096 x 5120 (640) 23.3 / 21.4, with stochastic rounding 32.6 /
-  // 28.2; X 8192 x 5120 (1280) 34.7 / 41.2, 47.1 / 50.3.
+  // Up to 640 workgroups (768 with stochastic rounding; 1024 are resident at once) the call takes as long as a patch or two do: each copy gets workgroups of its
+  // own, though the patch is then read twice.  us, one set / two: X 4096 x 4096 (512) 17.7 / 16.4, X 4096 x 5120 (640) 22.4 / 20.7, without rotation 18.7 /
+  // 17.1; X 4192 x 5120 (660) 24.3 / 26.3, 22.1 / 27.8; X 4096 x 6144 (768) 24.2 / 25.8, 20.5 / 23.7; with stochastic rounding 4096 x 5120 31.4 / 27.0, 4192 x
+  // 5120 33.6 / 33.0, 4096 x 6144 32.9 / 32.0, 5120 x 6144 (960) 40.1 / 40.4.
   constexpr bool kBoth = kRow && kCol;
-  constexpr int64_t kTwoSets = 768;
-  const bool split = kBoth && static_cast<int64_t>(grid.x) * grid.y <= kTwoSets;
+  const bool split = kBoth && static_cast<int64_t>(grid.x) * grid.y <= (a.sr ? 768 : 640);
   if (split) grid.z = 2;
   const auto kernel = a.sr ? (split ? &quantize_mx_kernel<kRow, kCol, kRht, true, kBoth> : &quantize_mx_kernel<kRow, kCol, kRht, true, false>)
                            : (split ? &quantize_mx_kernel<kRow, kCol, kRht, false, kBoth> : &quantize_mx_kernel<kRow, kCol, kRht, false, false>);
