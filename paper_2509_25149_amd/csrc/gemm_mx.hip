@@ -277,8 +277,8 @@ __global__ __launch_bounds__(kThreads) void gemm_mx_kernel_any_k(Operand A, Oper
 // to the end of the stage; four wavefronts' 16 loads behind the second 64 alone kept the address path busy throughout.
 // What bounds it (parts taken out, results wrong, accesses in bounds; 4096 x 5120 x 5120 bf16, 64.7 us): without the loads 52.2, without waiting for
 // them 61.7, without the fragment reads 63.5, without the output stage of the first of two tiles 61.4; 8192 x 20480 x 5120 416 us: 335, 400, 402 and
-// 342.  us, one barrier and scales by dwords -> now: 4096 x 5120 x 5120 bf16 68.8 -> 64.3, FP32 73.6 -> 70.4; 512 x 5120 x 5120 25.0 -> 23.3; 8192 x 20480 x
-// 5120 436 -> 421 (4.1 PFLOP/s).
+// 342.  One barrier and scales by dwords -> now, us per call from a graph: 4096 x 5120 x 5120 bf16 61.6 -> 58.4, FP32 68.0 -> 64.7; 512 x 5120 x 5120 bf16
+// 24.7 -> 23.2; 8192 x 20480 x 5120 bf16 426 -> 395 (4.3 PFLOP/s).
 constexpr int kWideRowBytes = 128;
 constexpr int kWideOperandBytes = TM * kWideRowBytes;       // 32 KiB
 constexpr int kWideStageBytes = 2 * kWideOperandBytes;      // 64 KiB
@@ -587,13 +587,14 @@ static hipError_t launch_mx(Kernel kernel, PerDeviceOnce& once, int lds_bytes, c
 }
 
 // Width of the k512 kernel's tiles: 32 kNB columns.  256 x 256 tiles move the fewest bytes per product, but a product of a few
-// hundred of them leaves CUs idle: a tile of 5 / 8 of the width takes 0.80 of the time (K = 5120: 37.6, 35.4, 31.5, 26.4 us for kNB =
-// 8, 7, 5, 4), so the width with the smallest rounds-of-256-tiles x time is taken, the wider one at a tie.  Measured, us, at
-// kNB = 8 / 7 / 5 / 4: 4096 x 5120 x 5120 75 / 70 / 63 / 79, 5120 x 5120 x 4096 (FP32) 69.5 / 67 / 80 / 92, 512 x 5120 x 5120 33 / 33 / 27 /
-// 24, 1024 x 1024 x 1024 12.9 / 12.2 / 10.3 / 9.0, 8192 x 20480 x 5120 422 / 461 / 531 / 608.
+// hundred of them leaves CUs idle: a round of tiles of 5 / 8 of the width takes 0.76 of the time (medians over 115 products: 0.93, 0.76, 0.66 for kNB = 7, 5, 4; four rounds of the last of
+// long K take more: 2272 x 14464 x 5120 112 us against 106 in three of kNB = 7, so it counts 0.70),
+// so the width with the smallest rounds-of-256-tiles x time is taken, the wider one at a tie; over 158 products it was the best of the four but for two by more
+// than 2 %.  us per call from a graph at kNB = 8 / 7 / 5 / 4: 4096 x 5120 x 5120 bf16 70.7 / 65.3 / 58.4 / 72.5, 5120 x 5120 x 4096 FP32 67.9 / 65.2 / 74.5 / 86.0,
+// 512 x 5120 x 5120 bf16 34.2 / 32.2 / 25.9 / 23.2, 1024 x 1024 x 1024 bf16 13.7 / 12.9 / 10.8 / 9.5, 8192 x 20480 x 5120 bf16 400 / 444 / 497 / 568.
 static int pick_mx_width(int64_t M, int64_t N) {
   constexpr int kWidths[4] = {8, 7, 5, 4};
-  constexpr double kTime[4] = {1.0, 0.94, 0.80, 0.71};
+  constexpr double kTime[4] = {1.0, 0.93, 0.76, 0.70};
   int best = 8;
   double best_time = 0.0;
   for (int i = 0; i < 4; ++i) {
