@@ -318,16 +318,23 @@ static AmaxWork amax_work(const QuantizeArgs& a) {
 // Up to 176 tiles of 128 x 256 the kernels with less work per lane (quantize_small.hip): a call takes as long as one lane's chain does.  us per call, this
 // cast pass / those: X 256 x 512 10.5 / 6.8, X 2048 x 2048 (128 tiles) 11.5 / 9.8, X 4096 x 1040 (160) 13.7 / 12.8, X 2048 x 4096 (256) 14.1 / 16.4;
 // stochastic rounding 12.7 / 7.7, 13.6 / 12.4, 17.2 / 16.2, 17.7 / 20.8; the row copy alone 64 x 5120 8.1 / 5.9, 2048 x 4096 10.6 / 11.0.
-static bool is_small(const QuantizeArgs& a) { return ((a.cols + 255) / 256) * ((a.rows + 127) / 128) <= 176; }
+static int64_t cast_tiles(const QuantizeArgs& a) {
+  using T = CastTile<kCachedLoads>;   // the tile is the same for all
+  return ((a.cols + T::kCols - 1) / T::kCols) * ((a.rows / 16 + T::kGroups - 1) / T::kGroups);
+}
+static bool use_cast_small(const QuantizeArgs& a) { return cast_tiles(a) <= 176 && !a.block2d; }
+static bool use_amax_small(const QuantizeArgs& a) { return cast_tiles(a) <= 176 && a.cols >= 128; }   // (its wavefronts span 128 columns)
+
+// Up to 256 workgroups (one per CU) the call takes as long as one patch does: each copy gets workgroups of its own, though the
+// patch is then read twice.  us, one set / two: X 2048 x 4096 (256 workgroups) 15.0 / 12.9, dY 4096 x 4096 (512) 28.4 / 31.8.  16x16 blocks have
+// little work per patch: 2048 x 4096 10.3 / 10.8.
+static unsigned cast_sets(const QuantizeArgs& a) { return a.want_row && a.want_col && !a.block2d && cast_tiles(a) <= 256 ? 2 : 1; }
 
 template <bool kRow, bool kCol, int kRht, bool kSR, bool k2D>
 static void launch_cast(const QuantizeArgs& a, const uint32_t* maxima, uint32_t n_maxima, hipStream_t s) {
   using T = CastTile<kCachedLoads>;   // the tile is the same for all
   const unsigned gx = static_cast<unsigned>((a.cols + T::kCols - 1) / T::kCols), gy = static_cast<unsigned>((a.rows / 16 + T::kGroups - 1) / T::kGroups);
-  // Up to 256 workgroups (one per CU) the call takes as long as one patch does: each copy gets workgroups of its own, though the
-  // patch is then read twice.  us, one set / two: X 2048 x 4096 (256 workgroups) 15.0 / 12.9, dY 4096 x 4096 (512) 28.4 / 31.8.  16x16 blocks have
-  // little work per patch: 2048 x 4096 10.3 / 10.8.
-  const dim3 grid(gx, gy, kRow && kCol && !k2D && static_cast<int64_t>(gx) * gy <= 256 ? 2 : 1);
+  const dim3 grid(gx, gy, cast_sets(a));
   const CastMemory m = cast_memory(a);
   const auto kernel = m == kCachedLoads     ? &cast_kernel<kRow, kCol, kRht, kSR, k2D, kCachedLoads>
                       : m == kStreamedLoads ? &cast_kernel<kRow, kCol, kRht, kSR, k2D, kStreamedLoads>
@@ -341,7 +348,7 @@ template <bool kRow, bool kCol, int kRht>
 static void launch_passes(const QuantizeArgs& a, hipStream_t s) {
   uint32_t n_maxima = 1;
   if (a.do_amax) {
-    if (is_small(a) && a.cols >= 128) {   // (its wavefronts span 128 columns)
+    if (use_amax_small(a)) {
       n_maxima = small_amax_workgroups(a);
       launch_amax_small<kRht>(a, s);
     } else {
@@ -358,7 +365,7 @@ static void launch_passes(const QuantizeArgs& a, hipStream_t s) {
   if (a.block2d) {
     if (a.sr) launch_cast<kRow, kCol, 0, true, true>(a, maxima, n_maxima, s);
     else launch_cast<kRow, kCol, 0, false, true>(a, maxima, n_maxima, s);
-  } else if (is_small(a)) {
+  } else if (use_cast_small(a)) {
     launch_cast_small<kRow, kCol, kRht>(a, maxima, n_maxima, s);
   } else {
     if (a.sr) launch_cast<kRow, kCol, kRht, true, false>(a, maxima, n_maxima, s);
@@ -386,3 +393,22 @@ hipError_t launch_quantize(const QuantizeArgs& a, hipStream_t s) {
 }
 
 }  // namespace nvfp4
+
+// For the tests, not part of the ABI: which kernels nvfp4_quantize takes for a contiguous tensor of these sizes (1x16 or 16x16 blocks, rotation up to 16, one scale
+// per tensor).  out: cast pass (0 cast_kernel, 1 cast_small_kernel), amax pass (likewise), cast_kernel's walk (kWalkReverse | kWalkBands), sets of its workgroups,
+// log2 of amax_kernel's lanes across.
+extern "C" void nvfp4_internal_quantize_plan(int64_t rows, int64_t cols, int want_row, int want_col, int block2d, int* out) {
+  using namespace nvfp4;
+  QuantizeArgs a{};
+  a.rows = rows;
+  a.cols = a.ld = cols;
+  a.want_row = want_row;
+  a.want_col = want_col;
+  a.block2d = block2d;
+  a.do_amax = a.do_cast = true;
+  out[0] = use_cast_small(a);
+  out[1] = use_amax_small(a);
+  out[2] = cast_walk(a);
+  out[3] = static_cast<int>(cast_sets(a));
+  out[4] = amax_work(a).lane_bits;
+}

@@ -1,5 +1,8 @@
 """GPU parity of the quantizer at the edges of its workgroup tiles (cast pass 128 rows x 256 columns, amax pass 64 rows x 512
-columns or more rows of a narrower tensor) and where an amax workgroup takes several pieces, bit for bit against the oracle."""
+columns or more rows of a narrower tensor) and where an amax workgroup takes several pieces, bit for bit against the oracle: tensors of more than 176
+tiles for these kernels; smaller ones, here too, have others."""
+import ctypes
+
 import pytest
 import torch
 
@@ -12,13 +15,28 @@ pytestmark = pytest.mark.gpu
 RC = nv.LAYOUT_ROW | nv.LAYOUT_COL
 
 
+def kernels(rows, cols, layout=RC, block2d=False):
+    """(cast pass of small tensors, amax pass of small tensors, reverse 1 and bands 2, sets of workgroups, log2 of the amax pass's lanes across)"""
+    out, i64 = (ctypes.c_int * 5)(), ctypes.c_int64
+    nv.load_library().nvfp4_internal_quantize_plan(i64(rows), i64(cols), layout & nv.LAYOUT_ROW, layout & nv.LAYOUT_COL, int(block2d), out)
+    return tuple(out)
+
+
 # inside one tile; exactly one; a 16-row and a 16-column remainder of a second; several tiles, odd scale rows (unaligned
 # scale pieces); tensors so narrow that 2, 8 or 32 lanes of a wavefront span them in the amax pass, with a remainder of its row groups;
-# more pieces of its work than workgroups, with few and with many column blocks (272 of them, 530)
-@pytest.mark.parametrize("rows,cols", [(112, 240), (128, 256), (144, 272), (656, 784), (32784, 16), (2064, 48), (4112, 176),
-                                       (144, 139024), (32, 271120)])
+# more pieces of its work than workgroups, with few and with many column blocks (272 of them, 530).  The first group the same in tensors of more than 176 tiles:
+# one row of tiles, inside it and exactly; a remainder each way; so many that both copies share a set of workgroups; 2, 8 and 32 lanes across
+SMALL = [(112, 240), (128, 256), (144, 272), (656, 784), (2064, 48), (4112, 176)]
+LARGE = [(112, 45296), (128, 45312), (144, 22800), (2064, 4112), (32784, 16), (22576, 48), (22672, 176), (144, 139024), (32, 271120)]
+
+
+@pytest.mark.parametrize("rows,cols", SMALL + LARGE)
 @pytest.mark.parametrize("mode", ["activation", "weight", "gradient", "row_only"])
 def test_tile_edges(rows, cols, mode):
+    small, amax_small, _, sets, lane_bits = kernels(rows, cols, nv.LAYOUT_ROW if mode == "row_only" else RC, mode == "weight")
+    assert small == ((rows, cols) in SMALL and mode != "weight") and amax_small == ((rows, cols) in SMALL and cols >= 128)
+    assert sets == (2 if mode in ("activation", "gradient") and -(-rows // 128) * -(-cols // 256) <= 256 else 1)
+    assert lane_bits == {16: 1, 48: 3, 176: 5, 240: 5, 256: 5}.get(cols, 6)
     xb = synth.student_t3(rows, cols, 1e-3, rows + cols) if mode == "gradient" else \
         synth.normal_with_outliers(rows, cols, 1.0, rows + cols, frac=0.01)
     xb[-16:, -16:] = 0                                   # an all-zero 16x16 tile: stored scale 0
@@ -36,8 +54,9 @@ def test_tile_edges(rows, cols, mode):
 
 
 # a row copy alone whose rows do not start on 128-byte lines: tiles dealt out in bands, one per XCD, with a remainder of the 8 and without
-@pytest.mark.parametrize("rows,cols", [(1040, 2064), (1024, 2064), (2064, 784)])
+@pytest.mark.parametrize("rows,cols", [(2064, 2832), (2048, 2832), (11536, 528)])
 def test_row_copy_in_bands(rows, cols):
+    assert kernels(rows, cols, nv.LAYOUT_ROW)[:3] == (0, 0, 2)
     check_quantize(synth.normal_with_outliers(rows, cols, 1.0, 8100 + rows, frac=0.01), nv.LAYOUT_ROW)
 
 
