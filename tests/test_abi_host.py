@@ -261,11 +261,14 @@ def test_no_kernel_keeps_arrays_in_scratch_memory():
         pytest.skip("libnvfp4_hip.resources.json is written by build(); run it first")
     res = json.load(open(build.RESOURCES))
     assert len(res) >= 60
+    strict = ("quantize_mx_kernel", "cast_kernel", "amax_kernel", "cast_small", "amax_small", "cast_wide", "amax_wide", "decode_f16", "dequantize", "rowscale_",
+              "gemm_f16_kernel", "gemm_direct_kernel")
+    for k in strict + ("splitk_sum", "gemm_mx_kernel"):
+        assert any(k in name for name in res), k
     for name, r in res.items():
         assert r["Dynamic Stack"] == "False", name
         assert r["ScratchSize"] <= 32, (name, r["ScratchSize"])
-        if any(k in name for k in ("quantize_mx_kernel", "cast_kernel", "amax_kernel", "cast_wide", "amax_wide", "decode_f16",
-                                   "dequantize", "rowscale_", "gemm_f16_kernel")):
+        if any(k in name for k in strict):
             assert r["ScratchSize"] == 0 and r["VGPRs Spill"] == 0, (name, r)
         if "splitk_sum" in name:
             assert r["ScratchSize"] == 0, (name, r)   # (values parked in unused accumulation registers are no memory traffic)
