@@ -246,11 +246,6 @@ __device__ __forceinline__ void flip_signs32(float v[32], uint32_t sign_mask) {
   for (int i = 0; i < 32; ++i) v[i] = __uint_as_float(__float_as_uint(v[i]) ^ (((sign_mask >> i) & 1u) << 31));
 }
 
-__device__ __forceinline__ void rht32(float v[32], uint32_t sign_mask) {
-  flip_signs32(v, sign_mask);
-  hadamard32(v);
-}
-
 // H32 is symmetric and orthogonal: x = s .* (H32 y)
 __device__ __forceinline__ void rht32_inverse(float y[32], uint32_t sign_mask) {
   hadamard32(y);
