@@ -15,11 +15,14 @@ program directly after `--`:
   rocprofv3 --pmc SQ_LDS_BANK_CONFLICT SQ_LDS_IDX_ACTIVE SQ_INSTS_LDS SQ_INSTS_VALU SQ_ACTIVE_INST_VALU SQ_WAVE_CYCLES \
             SQ_WAIT_INST_ANY SQ_WAVES GRBM_GUI_ACTIVE -d $P/sq -o bench -- $B
 
+  for c in quantize_x_small forward_small forward_few_tokens forward_row_scales step_ragged step_mx; do
+    rocprofv3 --kernel-trace --stats -d $P/case_$c -o case -- python3 $R/bench_profile.py --run-case $c; done
+
 then, anywhere the databases are (they are large; on the GPU machine itself is simplest):
 
   python3 bench_profile.py $P [--out DIR] [--commit ID]     # DIR defaults to profiles/
 
-Only this file, bench.py and the library are involved.  Nothing here runs on the GPU.
+Only this file, bench.py, perf/cases.py and the library are involved.  Nothing here runs on the GPU but --run-case: 200 passes of one case.
 """
 from __future__ import annotations
 
@@ -48,6 +51,22 @@ COMMANDS = {
 }
 
 
+CASES = ("quantize_x_small", "forward_small", "forward_few_tokens", "forward_row_scales", "step_ragged", "step_mx")   # what the 12B layer's run does not reach
+CASE_PASSES = 200
+
+
+def run_case(name: str) -> int:
+    sys.path.insert(0, ROOT)
+    import torch
+    from perf import cases
+    state = cases.prepare(next(c for c in cases.listed() if c["name"] == name), 1)
+    for _ in range(CASE_PASSES):
+        cases.run(state)
+    torch.cuda.synchronize()
+    print(name, "done")
+    return 0
+
+
 def find_db(directory: str):
     hits = sorted(glob.glob(os.path.join(directory, "**", "*_results.db"), recursive=True))
     return hits[-1] if hits else None
@@ -64,6 +83,9 @@ def short_name(n: str) -> str:
         return "nvfp4::splitk_sum_kernel<%s>" % ", ".join("true" if g == "1" else "false" for g in m.groups())
     if "decode_f16_kernel" in n:
         return "nvfp4::decode_f16_kernel"
+    m = re.search(r"gemm_direct_kernelILi(\d)ELi(\d)ELi(\d)ELi(\d)ELb(\d)E", n)
+    if m:      # 16-row and 16-column blocks of a wavefront, wavefronts that split K, steps of 128 k to a window; bf16 output
+        return "nvfp4::gemm_direct_kernel<%s, %s, %s, %s, %s>" % (*m.groups()[:4], "true" if m.group(5) == "1" else "false")
     n = re.sub(r"\(.*", "", n.replace("void ", "").replace("(anonymous namespace)::", ""))
     return n[:110]
 
@@ -141,6 +163,8 @@ def git_head() -> str:
 def main() -> int:
     global OUT_DIR
     argv = sys.argv[1:]
+    if argv[:1] == ["--run-case"]:
+        return run_case(argv[1])
     commit = git_head()
     if "--commit" in argv:                            # where the tree is not a git checkout (the GPU machine)
         i = argv.index("--commit")
@@ -175,6 +199,20 @@ def main() -> int:
             for n, k, s, a, mi, ma, pct in rows:
                 fh.write(f"{k:6d} {s:12.1f} {a:10.1f} {mi:10.1f} {ma:10.1f} {pct:6.1f}  {n}\n")
         measured["kernel_avg_us"] = {n: a for n, k, s, a, mi, ma, pct in rows}
+
+    case_dbs = [(c, find_db(os.path.join(base, "case_" + c))) for c in CASES]
+    if any(db for _, db in case_dbs):
+        with open(os.path.join(OUT_DIR, "cases_kernel_trace.txt"), "w") as fh:
+            fh.write("rocprofv3 kernel-trace summary: cases of perf/cases.py that the 12B layer's run does not reach, one run each, one MI355X.\n"
+                     f"Tree at commit {commit}.  Run from /tmp with TMPDIR=/tmp, R = repository root, P = a scratch directory.  Command (c the case):\n"
+                     "  rocprofv3 --kernel-trace --stats -d $P/case_$c -o case -- python3 $R/bench_profile.py --run-case $c\n"
+                     f"{CASE_PASSES} passes on the same inputs; what prepares them (a weight quantized once) is in the counts.  Durations in microseconds.\n")
+            for c, db in case_dbs:
+                if not db:
+                    continue
+                fh.write(f"\n{c}\n{'calls':>6} {'total_us':>12} {'avg_us':>10} {'min_us':>10} {'max_us':>10}  kernel\n")
+                for n, k, s, a, mi, ma, _ in kernel_trace(db):
+                    fh.write(f"{k:6d} {s:12.1f} {a:10.2f} {mi:10.2f} {ma:10.2f}  {n}\n")
 
     traffic = {}
     if dbs["fetch"] and dbs["write"]:
