@@ -108,10 +108,16 @@ def _check(status: int) -> None:
         raise NVFP4Error(status)
 
 
-def _stream() -> int:
-    """The current device's current stream.  (torch.cuda.current_stream() builds a Stream object for it: 2.8 us of the 11.5 that a small
-    call takes on the host; this 0.2.)"""
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+def _stream_getter(c=torch._C):
+    """What returns the current device's current stream.  (torch.cuda.current_stream() builds a Stream object for it: 2.8 us of the 11.5 that a small
+    call takes on the host; torch's own two functions beneath it 0.2, and where they are not there it is used after all.)"""
+    raw, device = getattr(c, "_cuda_getCurrentRawStream", None), getattr(c, "_cuda_getDevice", None)
+    if raw is None or device is None:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    return lambda: raw(device())
+
+
+_stream = _stream_getter()
 
 
 def quantized_sizes(rows: int, cols: int):
