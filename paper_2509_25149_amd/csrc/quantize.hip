@@ -323,7 +323,12 @@ static int64_t cast_tiles(const QuantizeArgs& a) {
   return ((a.cols + T::kCols - 1) / T::kCols) * ((a.rows / 16 + T::kGroups - 1) / T::kGroups);
 }
 static bool use_cast_small(const QuantizeArgs& a) { return cast_tiles(a) <= 176 && !a.block2d; }
-static bool use_amax_small(const QuantizeArgs& a) { return cast_tiles(a) <= 176 && a.cols >= 128; }   // (its wavefronts span 128 columns)
+// Its wavefronts span 128 columns.  What one workgroup of amax_kernel covers, unrotated, has no long chain and is left to it: a second workgroup costs more than
+// the shorter loads gain (us, amax_kernel / amax_small_kernel: 64 x 256 3.7 / 3.9, a weight's call 7.5 / 7.9; 64 x 1024 4.1 / 3.9; rotated 64 x 256 4.9 / 4.2).
+static bool use_amax_small(const QuantizeArgs& a) {
+  const bool rotated = a.want_col && a.rht_dim != 0;
+  return cast_tiles(a) <= 176 && a.cols >= 128 && (rotated || amax_work(a).pieces > 1);
+}
 
 // Up to 256 workgroups (one per CU) the call takes as long as one patch does: each copy gets workgroups of its own, though the
 // patch is then read twice.  us, one set / two: X 2048 x 4096 (256 workgroups) 15.0 / 12.9, dY 4096 x 4096 (512) 28.4 / 31.8.  16x16 blocks have
@@ -395,9 +400,9 @@ hipError_t launch_quantize(const QuantizeArgs& a, hipStream_t s) {
 }  // namespace nvfp4
 
 // For the tests, not part of the ABI: which kernels nvfp4_quantize takes for a contiguous tensor of these sizes (1x16 or 16x16 blocks, rotation up to 16, one scale
-// per tensor).  out: cast pass (0 cast_kernel, 1 cast_small_kernel), amax pass (likewise), cast_kernel's walk (kWalkReverse | kWalkBands), sets of its workgroups,
+// per tensor; rotated: the col copy is).  out: cast pass (0 cast_kernel, 1 cast_small_kernel), amax pass (likewise), cast_kernel's walk (kWalkReverse | kWalkBands), sets of its workgroups,
 // log2 of amax_kernel's lanes across.
-extern "C" void nvfp4_internal_quantize_plan(int64_t rows, int64_t cols, int want_row, int want_col, int block2d, int* out) {
+extern "C" void nvfp4_internal_quantize_plan(int64_t rows, int64_t cols, int want_row, int want_col, int rotated, int block2d, int* out) {
   using namespace nvfp4;
   QuantizeArgs a{};
   a.rows = rows;
@@ -405,6 +410,7 @@ extern "C" void nvfp4_internal_quantize_plan(int64_t rows, int64_t cols, int wan
   a.want_row = want_row;
   a.want_col = want_col;
   a.block2d = block2d;
+  a.rht_dim = rotated ? 16 : 0;
   a.do_amax = a.do_cast = true;
   out[0] = use_cast_small(a);
   out[1] = use_amax_small(a);
