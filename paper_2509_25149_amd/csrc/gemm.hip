@@ -382,16 +382,17 @@ static GemmPlan plan_route(const GemmArgs& g) {
   const bool split_only = g.K <= 128 && elements <= 2097152.0;
   const DirectPick direct = pick_direct_shape(g, split_only);
   GemmPlan plan{kDirect, direct, {}};
-  double us = direct.us;
+  double loop = direct.loop;
   const int64_t tiles128 = ((g.a.outer + BM - 1) / BM) * ((g.b.outer + BN - 1) / BN);
-  const double tile128 = small_tile_us(kTile128Cost, tiles128, elements, static_cast<double>((g.K + BK - 1) / BK));
-  if (!split_only && tile128 < us && g.a.outer <= int64_t{65535} * BM) {   // (its tile rows are the launch's second dimension)
+  const double tile128 = loop_us(kTile128Cost, tiles128, static_cast<double>((g.K + BK - 1) / BK));
+  if (!split_only && tile128 < loop && g.a.outer <= int64_t{65535} * BM) {   // (its tile rows are the launch's second dimension)
     plan.route = kTile128;
-    us = tile128;
+    loop = tile128;
   }
+  double us = small_tile_us(loop, elements);
   const bool big = (g.K % TK == 0) && (reinterpret_cast<uintptr_t>(g.a.codes) % 16 == 0) && (reinterpret_cast<uintptr_t>(g.b.codes) % 16 == 0);
   const double fused = fused_us(g.a.outer, g.b.outer, g.K);
-  if (big && (fused < us || direct.us == HUGE_VAL)) {
+  if (big && (fused < us || direct.loop == HUGE_VAL)) {
     plan.route = kFused256;
     us = fused;
   }

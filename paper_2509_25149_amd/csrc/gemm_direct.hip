@@ -447,21 +447,21 @@ static double wavefront_steps(int64_t K) {
 // A tile to each wavefront and one workgroup to a CU: large results wait more for their stores, and accumulated ones for their loads, than two
 // workgroups do: us, 64 x 64 / 128 x 80: 4096 x 8192 x 1040 93 / 114, accumulated 111 / 165; 6560 x 8320 x 1056 accumulated 189 / 223.
 template <int I>
-static double shape_us(const GemmArgs& g) {
+static double shape_loop_us(const GemmArgs& g, double elements) {
   if (!fits<I>(g.a.outer, g.b.outer, g.K)) return HUGE_VAL;
   constexpr DirectShape d = kDirectShapes[I];
-  const double elements = static_cast<double>(g.a.outer) * static_cast<double>(g.b.outer);
-  const double us = small_tile_us(d.us, direct_tiles<I>(g.a.outer, g.b.outer), elements, wavefront_steps<I>(g.K));
+  const double us = loop_us(d.us, direct_tiles<I>(g.a.outer, g.b.outer), wavefront_steps<I>(g.K));
   return d.wk == 1 && d.us.resident == 1 && elements > 3e7 ? 1.1 * us : us;
 }
 
 template <int... I>
 static DirectPick pick_shape(const GemmArgs& g, bool split_only, std::integer_sequence<int, I...>) {
+  const double elements = static_cast<double>(g.a.outer) * static_cast<double>(g.b.outer);
   DirectPick best{0, 0, HUGE_VAL};
   auto consider = [&](int shape, double us) {
-    if (us < best.us) best = DirectPick{shape, kDirectShapes[shape].kind, us};
+    if (us < best.loop) best = DirectPick{shape, kDirectShapes[shape].kind, us};
   };
-  (((split_only && kDirectShapes[I].wk == 1) ? void() : consider(I, shape_us<I>(g))), ...);
+  (((split_only && kDirectShapes[I].wk == 1) ? void() : consider(I, shape_loop_us<I>(g, elements))), ...);
   return best;
 }
 

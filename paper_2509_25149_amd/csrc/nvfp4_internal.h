@@ -100,14 +100,15 @@ hipError_t launch_gemm_two_pass(const GemmArgs& g, const TwoPassPlan& plan, hipS
 hipError_t launch_gemm_direct(const GemmArgs& g, int shape, hipStream_t s);
 struct DirectPick {
   int shape, kind;       // its number in the kernel's list; the kind of tile (see there)
-  double us;             // expected
+  double loop;           // us, expected (see SmallTileCost)
 };
 DirectPick pick_direct_shape(const GemmArgs& g, bool split_only);   // the best of them, or of those that split K; none can do it: HUGE_VAL
 bool direct_shape(int shape, int* out);   // MB, NB, WK, steps of a shape, for the tests; false: no such shape
 bool direct_shape_fits(const GemmArgs& g, int shape);   // whether it can do this product
-// Expected time of a kernel on small tiles: that of a call, then rounds of 256 tiles of `tile` us and `step` us per step of the loop,
+// Expected time of a kernel on small tiles (small_tile_us): that of a call, then rounds of 256 tiles of `tile` us and `step` us per step of the loop (`loop_us`),
 // or, where that is more, of the result's bytes (added in quadrature: neither hides the other fully).  A
 // CU holds `resident` workgroups; a round in which only one of them has a tile takes `alone` rounds, not 1.
+// The call and the bytes are the same for all such kernels, so the one with the shortest loop has the smallest time: one root per call, not one per shape.
 // Bytes of an FP32 result, whatever leaves: the choice of the kernel must not depend on the output type, since bf16 and accumulated
 // results are defined by the FP32 ones, to the last bit of whose sums the order of summation counts.
 struct SmallTileCost {
@@ -116,11 +117,14 @@ struct SmallTileCost {
 };
 constexpr double kCallUs = 2.6, kResultUsPerMB = 0.15;
 // (Always inlined with constants: a launch that takes 7 us to issue should not spend one on divisions by tile sizes.)
-__attribute__((always_inline)) inline double small_tile_us(const SmallTileCost& c, int64_t tiles, double elements, double steps) {
+__attribute__((always_inline)) inline double loop_us(const SmallTileCost& c, int64_t tiles, double steps) {
   const int64_t wave = int64_t{256} * c.resident, whole = tiles / wave, last = (tiles - whole * wave + 255) / 256;   // tiles of a CU in the last wave
   double rounds = static_cast<double>(whole * c.resident);
   if (last) rounds += c.resident == 1 ? 1.0 : c.alone + static_cast<double>(last - 1) * (c.resident - c.alone) / (c.resident - 1);
-  const double loop = rounds * (c.tile + c.step * steps), result = kResultUsPerMB * elements * 4e-6;
+  return rounds * (c.tile + c.step * steps);
+}
+inline double small_tile_us(double loop, double elements) {
+  const double result = kResultUsPerMB * elements * 4e-6;
   return kCallUs + __builtin_sqrt(loop * loop + result * result);
 }
 // Decodes one operand (codes [outer, K/2], scales [outer, K/16]) to FP16 [outer, K]
