@@ -295,7 +295,7 @@ __global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, MB * NB > 16 ? 1 : 2) void
   const int total = windows + (rest ? 1 : 0);
   if (total) {
     const int first = rest_first && rest ? wk - WK : wk;   // number of the window that would be the first if all were whole
-    auto k_of = [&](int n) { return n < windows || !pieces ? (first + n * WK) * kWindowK : K - kWindowK; };
+    auto k_of = [&](int n) { return rest_first || n < windows ? (first + n * WK) * kWindowK : K - kWindowK; };
     if (!rest_first || !rest) load(k_of(0));
     else if constexpr (kSteps == 1) {
       if (full) load_rest();
@@ -304,7 +304,7 @@ __global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, MB * NB > 16 ? 1 : 2) void
 #pragma unroll
     for (int i = 0; i < S::kBlocks; ++i) stage(i);
     wavefront_exchange();
-    if (kAlwaysFirst || windows || !pieces) {
+    if (rest_first || windows) {
       if (total > 1) load(k_of(1));
 #pragma unroll
       for (int i = 0; i < S::kBlocks; ++i) {
