@@ -74,10 +74,10 @@ def find_db(directory: str):
 
 def short_name(n: str) -> str:
     """A readable kernel name: template arguments kept, parameter list and namespaces of no interest dropped."""
-    m = re.search(r"gemm_f16_kernelILb(\d)ELb(\d)ELb(\d)ELi(\d)E", n)
+    m = re.search(r"gemm_f16_kernelILb(\d)ELb(\d)ELb(\d)ELi(\d+)ELi(\d+)E", n)
     if m:      # template arguments: bf16 output, per-row tensor scales, split-K partial tiles as output; 32-column units of a tile
         flags = ", ".join("true" if g == "1" else "false" for g in m.groups()[:3])
-        return f"nvfp4::gemm_f16_kernel<{flags}>" + ("" if m.group(4) == "8" else f" {32 * int(m.group(4))} columns")
+        return f"nvfp4::gemm_f16_kernel<{flags}>" + f" {32 * int(m.group(4))}x{32 * int(m.group(5))}"
     m = re.search(r"splitk_sum_kernelILb(\d)ELb(\d)E", n)
     if m:
         return "nvfp4::splitk_sum_kernel<%s>" % ", ".join("true" if g == "1" else "false" for g in m.groups())
@@ -276,7 +276,7 @@ def main() -> int:
                     if kern in mops and mops[kern][1] > 0:
                         fh.write(f"; MOPS_F16 x 512 = {mops[kern][1] * 512:.4e} flop per dispatch (avg)")
                     fh.write("\n")
-                    if "gemm_f16_kernel<true, false, false>" in kern:
+                    if "gemm_f16_kernel<true, false, false> 256x320" in kern:
                         measured["gemm_f16_kernel_mfma_busy_frac"] = frac
                     if "gemm_mx_kernel_k512" in kern:
                         measured.setdefault("gemm_mx_kernel_mfma_busy_frac", frac)

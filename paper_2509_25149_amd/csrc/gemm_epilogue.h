@@ -1,6 +1,6 @@
-// What the 4-wavefront GEMM kernels for gfx950 share besides their loops: the walk over the 256 x 256 tiles, and the
-// output stage: one wavefront's 128 x 128 block of FP32 sums,
-// held as 8 x 8 results of 16x16 MFMAs (acc[i][j][r] = D[m = 16 i + (lane & 15)][n = 16 j + 4 (lane >> 4) + r]),
+// What the 4-wavefront GEMM kernels for gfx950 share besides their loops: the walk over the tiles, and the
+// output stage: one wavefront's block of FP32 sums (128 x 128, say),
+// held as 8 x 8 results of 16x16 MFMAs, or kMB x kNB of them (acc[i][j][r] = D[m = 16 i + (lane & 15)][n = 16 j + 4 (lane >> 4) + r]),
 // times the tensor-level decode scales (App. B.3, after Eq. 5), to FP32 (optionally added into D) or bf16.
 // Device code only.
 #pragma once
@@ -34,7 +34,7 @@ __device__ __forceinline__ int lane_id() {
   return lane;
 }
 
-// Tile number pid of the 256x256 tiling -> tile row and column: the tiles are walked in bands of 8 tile rows, column by
+// Tile number pid of the tiling -> tile row and column: the tiles are walked in bands of 8 tile rows, column by
 // column within a band.
 __device__ __forceinline__ void tile_coordinates(int pid, int tiles_m, int tiles_n, int& tm, int& tn) {
   constexpr int kBand = 8;
@@ -148,24 +148,24 @@ struct WaveBlockStore {
 // A wavefront's whole 128 x 128 block.  (A variant without the predicates for blocks that exist whole measured no
 // faster.)  A kernel should contain this once: where a second use of the sums sits in another branch, the compiler
 // reads all 256 out of the accumulation registers ahead of the branch, into registers it does not have.
-template <bool kBf16Out, bool kVec, int kNB = 8>
-__device__ __forceinline__ void store_wave_block_impl(float4v (&acc)[8][kNB], const TensorScales ts, void* __restrict__ Dv, int64_t ldd,
+template <bool kBf16Out, bool kVec, int kMB, int kNB>
+__device__ __forceinline__ void store_wave_block_impl(float4v (&acc)[kMB][kNB], const TensorScales ts, void* __restrict__ Dv, int64_t ldd,
                                                       bool accumulate, int64_t row0, int64_t col0, int rows, int cols, int lane) {
   const WaveBlockStore<kBf16Out, kVec, kNB> out(ts, Dv, ldd, accumulate, row0, col0, rows, cols, lane);
-  float sa[kVec ? 8 : 1] = {};
+  float sa[kVec ? kMB : 1] = {};
   if (kVec) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) sa[kVec ? i : 0] = out.row_scale(ts, row0, i);
+    for (int i = 0; i < kMB; ++i) sa[kVec ? i : 0] = out.row_scale(ts, row0, i);
   }
 #pragma unroll
-  for (int i = 0; i < 8; ++i) out.store_rows(acc[i], i, sa[kVec ? i : 0]);
+  for (int i = 0; i < kMB; ++i) out.store_rows(acc[i], i, sa[kVec ? i : 0]);
 }
 
 // The per-tensor form, for kernels that have no other.
 template <bool kBf16Out, int kNB = 8>
 __device__ __forceinline__ void store_wave_block(float4v (&acc)[8][kNB], const TensorScales ts, void* __restrict__ Dv, int64_t ldd,
                                                  bool accumulate, int64_t row0, int64_t col0, int rows, int cols, int lane) {
-  store_wave_block_impl<kBf16Out, false, kNB>(acc, ts, Dv, ldd, accumulate, row0, col0, rows, cols, lane);
+  store_wave_block_impl<kBf16Out, false, 8, kNB>(acc, ts, Dv, ldd, accumulate, row0, col0, rows, cols, lane);
 }
 
 }  // namespace nvfp4

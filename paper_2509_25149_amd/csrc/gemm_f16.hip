@@ -98,45 +98,28 @@ __global__ __launch_bounds__(256) void decode_f16_kernel(const uint8_t* __restri
 }
 
 // ---------------------------------------------------------------- pass 2: FP16 GEMM
-// 256 x 256 outputs per workgroup, 256 threads = 4 wavefronts (2 x 2), one per SIMD,
-// each 128 x 128 outputs as 8 x 8 MFMA 16x16 blocks: 256 accumulator registers, which live in
-// the accumulation half of the register file, and 16 fragment loads per 64 MFMAs (a 128 x 64
-// wave tile needs 12 per 32).  LDS is a ring of four stages of 32 k: (A tile, B tile) as 16 + 16 pieces of
-// 16 rows x 32 k, 32 KiB a stage.  A stage is filled by direct global->LDS loads: one instruction moves 64 lanes x 16
-// bytes, one piece of the decoded operand, into 1 KiB of consecutive LDS, which is one MFMA fragment in lane order.
+// 32 kMB x 32 kNB outputs per workgroup, 256 threads = 4 wavefronts (2 x 2), one per SIMD, each 16 kMB x 16 kNB outputs as
+// kMB x kNB MFMA 16x16 blocks: up to 400 accumulator registers, 256 of them in the accumulation half of the register file.
+// LDS is a ring of four stages of 32 k, (A tile, B tile) as 2 kMB + 2 kNB pieces of 16 rows x 32 k.  A stage is
+// filled by direct global->LDS loads: one instruction moves 64 lanes x 16 bytes, one piece of the decoded operand, into 1 KiB of consecutive LDS,
+// which is one MFMA fragment in lane order.
 //
-// With one wavefront per SIMD nothing else can fill the matrix pipe while this one waits, so the
-// loop is software-pipelined and its instruction order is fixed by hand (inline
-// assembly keeps the compiler from regrouping it; measured 1.18 against 1.06 PFLOP/s for the
-// 8-wavefront form on the same operands, at a lower clock: the chip's power limit sets the speed,
-// and this form moves a third less data from LDS per flop).  Stage g:
-//   64 MFMAs on the fragments read during stage g - 1; after every fourth, one of the 16 fragment loads of stage
-//   g + 1; after every eighth, one of the wavefront's 8 global->LDS loads of stage g + 4 into the buffer of stage g,
-//   which nobody reads any more
-//   wait      own fragment loads back; own global->LDS loads of stage g + 2 landed (those of g + 3 and g + 4 may
-//             still be on their way); barrier: every wavefront holds stage g + 1 in registers, stage g + 2 is complete
-// so a load has three to four stages -- some 1.5 us -- to arrive in.
-constexpr int TM = 256, TN = 256, TK = 64;       // TK: the unit K is split and counted in, two stages
+// With one wavefront per SIMD nothing else can fill the matrix pipe while this one waits, so the loop is software-pipelined and its
+// instruction order is fixed by hand (inline assembly keeps the compiler from regrouping it).  A stage runs the upper half of the
+// wavefront's blocks column by column (down one, up the next: consecutive MFMAs share an operand; down every one took 1-2 % longer), then the lower half, and a fragment's registers take its next values as soon as its last MFMA has
+// been issued: no second set of fragments, which is what leaves room for 160 x 160 outputs per wavefront.  Stage g, kMB / 2 * kNB MFMAs each:
+//   upper half   behind them the reads of the lower half's A fragments of this stage, and the second half of the loads of stage g + 3
+//   wait         own reads back (nobody needs this stage's buffer any more); own loads of stage g + 1 landed (those of g + 2 and g + 3 may
+//                still be on their way); barrier
+//   lower half   behind them the reads of the next stage's upper A fragments and of each B fragment as its column is done,
+//                and the first half of the loads of stage g + 4, into the buffer of stage g
+// so a load has two to three stages -- some 1.5 us -- to arrive in, and a fragment kMB / 2 * (kNB - 1) MFMAs, seven times what a read takes.
+constexpr int TM = 256, TN = 256, TK = 64;       // TK: the unit K is split and counted in, two stages; TM, TN: the tiles of a split last round
 constexpr int kThreads = 256;
 constexpr int kStageK = 32;
 constexpr int kPieceBytes = 16 * kStageK * 2;           // what one load instruction moves: 16 rows x 32 k, 1 KiB, contiguous in the decoded operand
-constexpr int kOperandBytes = (TM / 16) * kPieceBytes;  // 16 KiB
-constexpr int kStageBytes = 2 * kOperandBytes;          // 32 KiB
 constexpr int kStages = 4;
-constexpr int kLdsBytes = kStages * kStageBytes;
-
-// Spreads `total` things evenly over the `slots` places between MFMAs, half a distance in: the number of the one that
-// place n takes, or -1.
-constexpr int spread(int n, int total, int slots) {
-  const int at = n * total + slots / 2;
-  return (at + total) / slots > at / slots ? at / slots : -1;
-}
-
-// Fragments of one 32-wide half of a K step for a 128 x 128 wave tile.  A 16x16x32 MFMA operand
-// is 16 rows x 32 k: lane l holds the 8 consecutive k of 16-byte chunk (l >> 4) of row (l & 15).
-struct Frags {
-  half8v a[8], b[8];
-};
+constexpr int stage_bytes(int mb, int nb) { return (2 * mb + (2 * nb + 3) / 4 * 4) * kPieceBytes; }   // (B's pieces rounded up to four wavefronts' loads)
 
 template <int kBegin, int kEnd, class F>
 __device__ __forceinline__ void static_for(F&& f) {
@@ -148,23 +131,30 @@ __device__ __forceinline__ void static_for(F&& f) {
 
 // The MFMA's M index is the B row (n), its N index the A row (m): lane l ends up with the 4
 // consecutive n = (l >> 4) * 4 .. + 3 of m = l & 15, which makes the output stores 64/128-bit.
-// The accumulator is pinned to the accumulation registers ("a"): 256 of them leave the 256
-// ordinary registers to fragments and addresses.
+// kAcc: the accumulator is pinned to the accumulation registers ("a"), which leaves the 256 ordinary registers to fragments, addresses and
+// the accumulators beyond the 64th.  kFirst: the first of a work item, C = 0, so the accumulators are never cleared.
+template <bool kFirst, bool kAcc>
 __device__ __forceinline__ void mfma(float4v& acc, const half8v& b, const half8v& a) {
-  asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(b), "v"(a));
+  if constexpr (kFirst && kAcc) asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, 0" : "=a"(acc) : "v"(b), "v"(a));
+  else if constexpr (kFirst) asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, 0" : "=v"(acc) : "v"(b), "v"(a));
+  else if constexpr (kAcc) asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(b), "v"(a));
+  else asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+v"(acc) : "v"(b), "v"(a));
 }
 
-// 16 bytes of LDS at addr + kOff.  Asynchronous: the caller waits (lgkmcnt) before the value is used.
-template <int kOff>
+// No instruction: the value is used here / comes from here.
+__device__ __forceinline__ void keep(const half8v& f) { asm volatile("" ::"v"(f)); }
+template <bool kAcc>
+__device__ __forceinline__ void settled(float4v& acc) {
+  if constexpr (kAcc) asm volatile("" : "+a"(acc));
+  else asm volatile("" : "+v"(acc));
+}
+
+// 16 bytes of LDS at addr + kOff.  Asynchronous: the caller waits (lgkmcnt) before the value is used.  kNew: into any registers; else
+// into those that the fragment has (an operand in and out).
+template <int kOff, bool kNew = false>
 __device__ __forceinline__ void lds_read16(half8v& dst, uint32_t addr) {
-  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(dst) : "v"(addr), "n"(kOff));
-}
-
-// Fragment q of a set: 0..7 = A rows i * 16, the others B rows j * 16: one piece each.
-template <int q>
-__device__ __forceinline__ void read_frag(Frags& f, uint32_t a_addr, uint32_t b_addr) {
-  if constexpr (q < 8) lds_read16<q * kPieceBytes>(f.a[q], a_addr);
-  else lds_read16<(q - 8) * kPieceBytes>(f.b[q - 8], b_addr);
+  if constexpr (kNew) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(dst) : "v"(addr), "n"(kOff));
+  else asm volatile("ds_read_b128 %0, %1 offset:%2" : "+v"(dst) : "v"(addr), "n"(kOff));
 }
 
 // 64 lanes x 16 bytes from global memory (wave-uniform base + per-lane 32-bit offset) straight into 1 KiB of consecutive LDS
@@ -177,23 +167,51 @@ __device__ __forceinline__ void load_1k_to_lds(uint32_t lane_offset, const char*
   asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%2" ::"v"(lane_offset), "s"(base_minus_off), "n"(kOff), "{m0}"(lds_dst) : "memory");
 }
 
-// The first MFMA of an accumulator in a work item: C = 0, so the 256 accumulation registers are never cleared.
-__device__ __forceinline__ void mfma_first(float4v& acc, const half8v& b, const half8v& a) {
-  asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, 0" : "=a"(acc) : "v"(b), "v"(a));
-}
-
-// A wavefront's output stage issues 8 ceil(kNB / 2) (bf16) or 8 kNB (FP32) stores for a full tile (store_wave_block: 16 bytes
+// A wavefront's output stage issues kMB ceil(kNB / 2) (bf16) or kMB kNB (FP32) stores for a full tile (store_wave_block: 16 bytes
 // per lane and instruction).  Three quarters of them: the number of its memory operations that may still be
 // outstanding when the loads issued before it are needed, with a margin against a store more or less.
-template <bool kBf16Out, int kNB>
-constexpr int kTileStores = kBf16Out ? 6 * ((kNB + 1) / 2) : 6 * kNB;
+template <bool kBf16Out, int kMB, int kNB>
+constexpr int kTileStores = (kMB * 3 / 4) * (kBf16Out ? (kNB + 1) / 2 : kNB);
 
-// Tiles [tile_begin, tile_begin + tile_count) of the 256x256 tiling are covered.
+// What goes behind the MFMAs of a stage.  kR = kMB / 2 rows of blocks a half; MFMA n of a half is column n / kR, row n % kR.
+template <int kMB, int kNB>
+struct Schedule {
+  static constexpr int kR = kMB / 2, kHalf = kR * kNB;
+  static constexpr int kALoads = kMB / 2, kBLoads = (2 * kNB + 3) / 4, kLoads = kALoads + kBLoads;   // a wavefront's loads per stage (some of the last wavefront's of B are not needed)
+  static constexpr int kEarly = (kLoads + 1) / 2;   // of them in the lower half, the rest in the upper half of the following stage
+  // upper half: which A fragment of the lower half is read behind MFMA n, or -1; the last of them is back when the half ends
+  static constexpr int kGap = kHalf - 16 >= 2 * kR ? (kHalf - 16) / kR : 1;
+  static constexpr int upper_read(int n) { return n >= 1 && (n - 1) % kGap == 0 && (n - 1) / kGap < kR ? kR + (n - 1) / kGap : -1; }
+  // lower half: which upper A fragment of the next stage (all of them before the last two of B), and which B fragment
+  static constexpr int kGapA = 2 + kR * (kR - 1) < kR * (kNB - 2) ? kR : 3;
+  static_assert(2 + kGapA * (kR - 1) < kR * (kNB - 2), "the last two reads of a stage are of B");
+  static constexpr int lower_read_a(int n) { return n >= 2 && (n - 2) % kGapA == 0 && (n - 2) / kGapA < kR ? (n - 2) / kGapA : -1; }
+  static constexpr int lower_read_b(int n) { return n >= kR && n % kR == 0 ? n / kR - 1 : -1; }   // (the last column's: behind the next stage's first MFMA)
+  static constexpr int lower_reads_behind_a() {   // of B
+    int r = 0;
+    for (int k = 2 + kGapA * (kR - 1); k < kHalf; ++k) r += lower_read_b(k) >= 0;
+    return r;
+  }
+  // how many of the upper half's reads of A are behind the MFMAs before n
+  static constexpr int upper_reads_before(int n) {
+    int r = 0;
+    for (int k = 0; k < n; ++k) r += upper_read(k) >= 0;
+    return r;
+  }
+  static_assert(upper_reads_before(kHalf) == kR, "");
+  // which of `count` loads goes behind MFMA n: evenly spread, half a distance in
+  static constexpr int load(int n, int count) {
+    const int at = n * count + kHalf / 2;
+    return (at + count) / kHalf > at / kHalf ? at / kHalf : -1;
+  }
+};
+
+// Tiles [tile_begin, tile_begin + tile_count) of the tiling are covered.
 //
 // k_splits == 1: a workgroup takes tiles blockIdx.x, blockIdx.x + gridDim.x, ... of the launch (the host launches one
 // workgroup per CU when there are more tiles than CUs) and runs them as ONE stream of stages: the loads issued during a
 // tile's last four stages already fetch the next tile's first four, so that the pipeline neither drains nor refills at
-// a tile boundary -- what remains there is reading the 256 sums out, scaling, converting and issuing the stores,
+// a tile boundary -- what remains there is reading the sums out, scaling, converting and issuing the stores,
 // which then drain under the next tile's MFMAs (measured with timestamps in the one-tile-per-workgroup form: 4.2 us
 // of pipeline fill, 5.5 us of output stage, most of it waiting for the stores of all CUs at once, and 0.6 us between
 // workgroups, per 118 us of main loop at K = 5120).  Needs K >= 4 stages (2 K steps of 64); the host launches one workgroup per tile
@@ -208,17 +226,17 @@ constexpr int kTileStores = kBf16Out ? 6 * ((kNB + 1) / 2) : 6 * kNB;
 // 1 MiB that four XCDs had written 50 -- with 16 loads in flight per thread, and 90 with 64.)
 // kRowScales: an operand carries a tensor-level scale per row (uniform over a launch, and a different output stage).
 // kSplit: k_splits > 1; the output stage is the store of the partial tile (kBf16Out and kRowScales are false then).
-// kNB: 16-column blocks per wavefront; a tile is 256 rows x 32 kNB columns (8: the 256 x 256 of the description above).  The
-// narrower tiles are for products whose rounds of 256 x 256 tiles come out badly (see pick_width).
-template <bool kBf16Out, bool kRowScales, bool kSplit, int kNB>
+// kMB, kNB: 16-row and 16-column blocks per wavefront; which tile a product takes: pick_tile.
+template <bool kBf16Out, bool kRowScales, bool kSplit, int kMB, int kNB>
 __global__ __launch_bounds__(kThreads) void gemm_f16_kernel(const _Float16* __restrict__ A, const _Float16* __restrict__ B,
                                                             int64_t M, int64_t N, int64_t K, const float* __restrict__ a_ts,
                                                             const float* __restrict__ b_ts, void* __restrict__ Dv,
                                                             int64_t ldd, bool accumulate, int tiles_m, int tiles_n,
                                                             int tile_begin, int tile_count, int k_splits, float* partials,
                                                             bool a_ts_per_row, bool b_ts_per_row) {
-  constexpr int kTN = 32 * kNB, kMfmas = 8 * kNB, kReads = 8 + kNB;
-  constexpr int kBLoads = (2 * kNB + 3) / 4, kLoads = 4 + kBLoads;   // a wavefront's loads per stage: 4 pieces of A, 2 - 4 of B's 2 kNB (some of the last wavefront's are not needed)
+  using S = Schedule<kMB, kNB>;
+  constexpr int kTM = 32 * kMB, kTN = 32 * kNB, kStageBytes = stage_bytes(kMB, kNB);
+  constexpr int kR = S::kR, kHalf = S::kHalf, kALoads = S::kALoads, kBLoads = S::kBLoads, kLoads = S::kLoads, kEarly = S::kEarly;
   extern __shared__ __attribute__((aligned(16))) char lds[];
 
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
@@ -232,16 +250,16 @@ __global__ __launch_bounds__(kThreads) void gemm_f16_kernel(const _Float16* __re
     return wg;   // the tile's number within the launch
   };
 
-  // Direct-load sources: instruction q of wavefront w fills rows w * 64 + 16 q .. + 15 of a tile, which the decoded
+  // Direct-load sources: load q of wavefront w fills 16 rows of a tile (block w * kALoads + q of A's, w * kBLoads + q of B's), which the decoded
   // operand holds as 1 KiB of consecutive bytes per stage, in LDS order (lane l: bytes 16 l .. 16 l + 15).  An address
   // is a wave-uniform 64-bit base per operand, which holds the tile and the stage being fetched, plus a per-lane
-  // 32-bit offset per instruction (256 rows of K * 2 bytes: K < 2^21, checked on the host), which holds the 16-row
+  // 32-bit offset per instruction (320 rows of K * 2 bytes: K < 2^21, checked on the host), which holds the 16-row
   // block and does not change within a tile: moving on by a stage is two scalar additions per operand.  (Every
   // vector instruction between two MFMAs costs: with the stage added to the 8 per-lane offsets instead, the three
   // 12B GEMM calls took 2 % longer.)  A block past the end of an operand is replaced by the operand's last block
   // (rows come in multiples of 16); it only feeds outputs that are never stored.
   // One instruction per load inside the loop (a single wavefront per SIMD issues in order: what it spends on anything
-  // else, the matrix pipe waits): M0, the LDS destination, is written once per four loads; loads q % 4 = 1, 2, 3 reach
+  // else, the matrix pipe waits): M0, the LDS destination, is written once per four loads of an operand; the others reach
   // the next KiB through the instruction's immediate offset, which moves the LDS and the global address alike, so
   // the bases sit 3 KiB low and the offsets make up for what the immediate does not add.
   //
@@ -250,35 +268,35 @@ __global__ __launch_bounds__(kThreads) void gemm_f16_kernel(const _Float16* __re
   // registers itself, and end up in scratch memory, to be fetched back inside the K steps.
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
   uint32_t lane_bytes = 0;          // the lane's part of a load offset
-  uint32_t a_frag = 0, b_frag = 0;  // the lane's 16 bytes of the wavefront's first A / B fragment in ring buffer 0
-  auto lane_setup = [&]() {
+  uint32_t a_frag = 0, b_frag = 0;  // the lane's 16 bytes of the wavefront's first A / B fragment in the buffer that is read from
+  auto lane_setup = [&](uint32_t buf) {
     lane_bytes = static_cast<uint32_t>(lane_id()) * 16u;
-    a_frag = lds0 + (wave >> 1) * (8 * kPieceBytes) + lane_bytes;
-    b_frag = lds0 + kOperandBytes + (wave & 1) * (kNB * kPieceBytes) + lane_bytes;
+    a_frag = lds0 + buf * kStageBytes + (wave >> 1) * (kMB * kPieceBytes) + lane_bytes;
+    b_frag = lds0 + buf * kStageBytes + 2 * kMB * kPieceBytes + (wave & 1) * (kNB * kPieceBytes) + lane_bytes;
   };
-  lane_setup();
+  lane_setup(0);
   const char* base_a = nullptr;
   const char* base_b = nullptr;
-  uint32_t voff[kLoads];   // q 0..3 A, then B
+  uint32_t voff[kLoads];   // A's, then B's
   // Point the loads at stage st (32 k) of tile (tm, tn).
   auto aim = [&](int tm, int tn, int st) {
-    const int64_t m_first = static_cast<int64_t>(tm) * TM, n_first = static_cast<int64_t>(tn) * kTN;
+    const int64_t m_first = static_cast<int64_t>(tm) * kTM, n_first = static_cast<int64_t>(tn) * kTN;
     base_a = reinterpret_cast<const char*>(A) + m_first * K * 2 + (st - 3) * kPieceBytes;
     base_b = reinterpret_cast<const char*>(B) + n_first * K * 2 + (st - 3) * kPieceBytes;
     // 16-row blocks counted from the tile's first; a block's stages are K / 32 KiB
     const uint32_t last_a = static_cast<uint32_t>(M - 16 - m_first) >> 4, last_b = static_cast<uint32_t>(N - 16 - n_first) >> 4;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const uint32_t fixed = static_cast<uint32_t>(3 - q) * 1024u;
-      voff[q] = lane_bytes + min(static_cast<uint32_t>(wave * 4 + q), last_a) * static_cast<uint32_t>(K * 32) + fixed;
-      if (q < kBLoads) voff[4 + q] = lane_bytes + min(static_cast<uint32_t>(wave * kBLoads + q), last_b) * static_cast<uint32_t>(K * 32) + fixed;
-    }
+    for (int q = 0; q < kALoads; ++q)
+      voff[q] = lane_bytes + min(static_cast<uint32_t>(wave * kALoads + q), last_a) * static_cast<uint32_t>(K * 32) + static_cast<uint32_t>(3 - (q & 3)) * 1024u;
+#pragma unroll
+    for (int q = 0; q < kBLoads; ++q)
+      voff[kALoads + q] = lane_bytes + min(static_cast<uint32_t>(wave * kBLoads + q), last_b) * static_cast<uint32_t>(K * 32) + static_cast<uint32_t>(3 - (q & 3)) * 1024u;
   };
-  const uint32_t fill_a = lds0 + wave * (4 * kPieceBytes), fill_b = lds0 + kOperandBytes + wave * (kBLoads * kPieceBytes);   // this wavefront's pieces of each operand tile
+  const uint32_t fill_a = lds0 + wave * (kALoads * kPieceBytes), fill_b = lds0 + (2 * kMB + wave * kBLoads) * kPieceBytes;   // this wavefront's pieces of each operand tile
   // load q of the wavefront's that fill ring buffer `buf`
   auto issue = [&](auto qc, uint32_t buf) {
-    constexpr int q = decltype(qc)::value;
-    load_1k_to_lds<(q & 3) * 1024>(voff[q], q < 4 ? base_a : base_b, (q < 4 ? fill_a : fill_b) + buf * kStageBytes);
+    constexpr int q = decltype(qc)::value, o = q < kALoads ? q : q - kALoads;
+    load_1k_to_lds<(o & 3) * 1024>(voff[q], q < kALoads ? base_a : base_b, (q < kALoads ? fill_a : fill_b) + (o & ~3) * kPieceBytes + buf * kStageBytes);
   };
 
   const int KT = static_cast<int>(K / TK);
@@ -287,51 +305,70 @@ __global__ __launch_bounds__(kThreads) void gemm_f16_kernel(const _Float16* __re
   int tm = 0, tn = 0;
   const int split = item % k_splits;   // k_splits > 1: one work item per workgroup
   const int tile_local = locate(item / k_splits, tm, tn);
-  int kt_begin = static_cast<int>(static_cast<int64_t>(KT) * split / k_splits);
-  int kt_end = static_cast<int>(static_cast<int64_t>(KT) * (split + 1) / k_splits);   // > kt_begin: KT >= k_splits
-  // The stage the loads were last pointed at: they run four stages ahead of the MFMAs.
+  const int kt_begin = static_cast<int>(static_cast<int64_t>(KT) * split / k_splits);
+  const int kt_end = static_cast<int>(static_cast<int64_t>(KT) * (split + 1) / k_splits);   // > kt_begin: KT >= k_splits
+  const int stages = 2 * (kt_end - kt_begin), st_end = 2 * kt_end;   // of an item (with k_splits == 1 the same for every tile)
+  // The stage the loads were last pointed at: they run up to four stages ahead of the MFMAs.
   int fetch_st = 2 * kt_begin;
   aim(tm, tn, fetch_st);
   static_for<0, kLoads>([&](auto q) { issue(q, 0); });
 #pragma unroll
   for (uint32_t buf = 1; buf < kStages; ++buf) {
-    if (fetch_st + 1 < 2 * kt_end) {   // (an item of two stages fetches its last three times)
+    if (fetch_st + 1 < st_end) {   // (an item of two stages fetches its last three times)
       ++fetch_st;
       base_a += kPieceBytes;
       base_b += kPieceBytes;
     }
-    static_for<0, kLoads>([&](auto q) { issue(q, buf); });
+    // (the last stage's second half: behind the first MFMAs, as in every later stage)
+    static_for<0, kLoads>([&](auto q) {
+      if (buf + 1 < kStages || decltype(q)::value < kEarly) issue(q, buf);
+    });
   }
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kLoads) : "memory");   // the first two stages
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kLoads + kEarly) : "memory");   // the first stage
   __builtin_amdgcn_s_barrier();
 
-  Frags f0, f1;
-  float4v acc[8][kNB];
+  half8v fa[kMB], fb[kNB];
+  float4v acc[kMB][kNB];
   uint32_t g = 0;               // stages done so far; stage g lives in ring buffer g % 4
   bool stores_behind = false;   // the previous tile's kTileStores stores were issued after the loads now in flight
   for (;;) {
     // The tile's first fragments.  (After a tile of the same stream its last stage has read them already; they are read
-    // again so that the output stage had their registers to work with.)  The barrier: the first stage loads into the
-    // buffer these came from.
-    {
-      const uint32_t cur = (g & 3u) * kStageBytes;
-      static_for<0, kReads>([&](auto q) { read_frag<decltype(q)::value>(f0, a_frag + cur, b_frag + cur); });
-    }
+    // again so that the output stage had their registers to work with.)
+    static_for<0, kR>([&](auto q) { lds_read16<decltype(q)::value * kPieceBytes, true>(fa[decltype(q)::value], a_frag); });
+    static_for<0, kNB>([&](auto q) { lds_read16<decltype(q)::value * kPieceBytes, true>(fb[decltype(q)::value], b_frag); });
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
     // The next tile of this workgroup, if any: its stages follow this tile's without a break (k_splits == 1 then).
     const int next_item = item + static_cast<int>(gridDim.x);
     const bool has_next = next_item < items;
     int next_tm = 0, next_tn = 0;
     if (has_next) locate(next_item, next_tm, next_tn);
-    const int st_end = 2 * kt_end;
 
-    // One stage on the fragments in `fc`, reading the next stage's into `fn`.  kFirst: the item's first (accumulators
+    // One stage.  kFirst: the item's first (accumulators
     // start from zero); kRelaxed: one of its first two (the stores of the tile before may still be in flight behind
     // the loads this stage waits for).
-    auto stage = [&](auto first_tag, auto relaxed_tag, Frags& fc, Frags& fn) {
+    auto stage = [&](auto first_tag, auto relaxed_tag) {
       constexpr bool kFirst = decltype(first_tag)::value, kRelaxed = decltype(relaxed_tag)::value;
-      const uint32_t buf = g & 3u, nxt = ((g + 1u) & 3u) * kStageBytes;
+      const uint32_t buf = g & 3u, before = (g - 1u) & 3u;
+      static_for<0, kHalf>([&](auto nc) {
+        constexpr int n = decltype(nc)::value, j = n / kR, i = (j & 1) ? kR - 1 - n % kR : n % kR, rd = S::upper_read(n), ld = S::load(n, kLoads - kEarly);
+        // Every third column: the B fragments of it and of the next two are back.  Behind them only the later ones, the last column's (read behind the
+        // first MFMA) and A's have been issued.
+        if constexpr (n % kR == 0 && j % 3 == 0 && !kFirst) {
+          constexpr int last = j + 2 < kNB - 1 ? j + 2 : kNB - 1;
+          constexpr int behind = n == 0 && S::lower_reads_behind_a() < kNB - 2 - last ? S::lower_reads_behind_a() : kNB - 2 - last + (n > 0);
+          asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(last == kNB - 1 ? S::upper_reads_before(n) : behind + S::upper_reads_before(n)) : "memory");
+        }
+        mfma<kFirst, i * kNB + j < 64>(acc[i][j], fb[j], fa[i]);
+        if constexpr (n == 0 && !kFirst) lds_read16<(kNB - 1) * kPieceBytes>(fb[kNB - 1], b_frag);
+        if constexpr (rd >= 0) lds_read16<(rd >= 0 ? rd : 0) * kPieceBytes, kFirst>(fa[rd >= 0 ? rd : 0], a_frag);
+        if constexpr (ld >= 0) issue(std::integral_constant<int, kEarly + (ld >= 0 ? ld : 0)>{}, before);
+      });
+      // Memory operations complete in issue order.  Behind the loads of stage g + 1 this wavefront has issued those of
+      // g + 2 and g + 3, kLoads each, and, across a tile boundary, the stores of the tile before.
+      if (kRelaxed && stores_behind)
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * kLoads + kTileStores<kBf16Out, kMB, kNB> > 63 ? 63 : 2 * kLoads + kTileStores<kBf16Out, kMB, kNB>) : "memory");
+      else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * kLoads) : "memory");
+      __builtin_amdgcn_s_barrier();
       // The loads move on one stage: within the tile, or to the next tile's stage 0, or, with nothing to follow, not at
       // all (the last stage is fetched again, into a buffer nobody reads any more: no branches around the loads).
       uint32_t advance = kPieceBytes;
@@ -344,28 +381,38 @@ __global__ __launch_bounds__(kThreads) void gemm_f16_kernel(const _Float16* __re
           aim(next_tm, next_tn, 0);
         }
       }
-      static_for<0, kMfmas>([&](auto ic) {
-        constexpr int n = decltype(ic)::value, i = n / kNB, j = n % kNB, rd = spread(n, kReads, kMfmas), ld = spread(n, kLoads, kMfmas);
-        if constexpr (kFirst) mfma_first(acc[i][j], fc.b[j], fc.a[i]);
-        else mfma(acc[i][j], fc.b[j], fc.a[i]);
-        if constexpr (rd >= 0) read_frag<rd>(fn, a_frag + nxt, b_frag + nxt);
-        if constexpr (ld == 0) base_a += advance;
-        if constexpr (ld == 4) base_b += advance;
+      const uint32_t to_next = buf == kStages - 1 ? static_cast<uint32_t>(-(kStages - 1) * kStageBytes) : static_cast<uint32_t>(kStageBytes);
+      static_for<0, kHalf>([&](auto nc) {
+        constexpr int n = decltype(nc)::value, j = n / kR, i = kR + ((j & 1) ? kR - 1 - n % kR : n % kR), ra = S::lower_read_a(n), rb = S::lower_read_b(n), ld = S::load(n, kEarly);
+        mfma<kFirst, i * kNB + j < 64>(acc[i][j], fb[j], fa[i]);
+        if constexpr (n == 0) {
+          a_frag += to_next;
+          b_frag += to_next;
+          base_a += advance;
+          base_b += advance;
+        }
+        if constexpr (ra >= 0) lds_read16<(ra >= 0 ? ra : 0) * kPieceBytes>(fa[ra >= 0 ? ra : 0], a_frag);
+        if constexpr (rb >= 0) lds_read16<(rb >= 0 ? rb : 0) * kPieceBytes>(fb[rb >= 0 ? rb : 0], b_frag);
         if constexpr (ld >= 0) issue(std::integral_constant<int, ld>{}, buf);
       });
-      // Memory operations complete in issue order.  Behind the loads of stage g + 2 this wavefront has issued those of
-      // g + 3 and g + 4, kLoads each, and, across a tile boundary, the stores of the tile before.
-      if (kRelaxed && stores_behind)
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * kLoads + kTileStores<kBf16Out, kNB> > 63 ? 63 : 2 * kLoads + kTileStores<kBf16Out, kNB>) : "memory");
-      else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * kLoads) : "memory");
-      __builtin_amdgcn_s_barrier();
       ++g;
     };
-    stage(std::true_type{}, std::true_type{}, f0, f1);
-    stage(std::false_type{}, std::true_type{}, f1, f0);
-    for (int kt = kt_begin + 1; kt < kt_end; ++kt) {
-      stage(std::false_type{}, std::false_type{}, f0, f1);
-      stage(std::false_type{}, std::false_type{}, f1, f0);
+    stage(std::true_type{}, std::true_type{});
+    stage(std::false_type{}, std::true_type{});
+    for (int st = 2; st < stages; ++st) stage(std::false_type{}, std::false_type{});
+
+    // The MFMA results must have left the pipe before ordinary instructions read the accumulators (the compiler
+    // cannot see into the assembly statements to insert these wait states itself), and the reads behind the last stage must have arrived before
+    // their registers serve anything else: the statements without an instruction keep the fragments until then and let the sums be used only from then on.
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+    static_for<0, kMB>([&](auto i) { keep(fa[decltype(i)::value]); });
+    static_for<0, kNB>([&](auto j) { keep(fb[decltype(j)::value]); });
+    static_for<0, kMB * kNB>([&](auto n) { settled<(decltype(n)::value < 64)>(acc[decltype(n)::value / kNB][decltype(n)::value % kNB]); });
+    // With nothing to follow, the trailing global->LDS loads must have landed before the wavefront ends; otherwise the next
+    // tile's first stage is in LDS by now and three more on their way there.
+    if (!has_next) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
     }
 
     // Everything below is computed here, per tile: were the compiler to move the output stage's loop-invariant
@@ -376,22 +423,12 @@ __global__ __launch_bounds__(kThreads) void gemm_f16_kernel(const _Float16* __re
     const int lane = lane_id(), tid = (wm * 2 + wn) * 64 + lane;
     // Tensor-level decode scales on the finished sums (App. B.3, after Eq. 5).
     const TensorScales out_scale{a_ts, b_ts, a_ts_per_row, b_ts_per_row};
-    const int64_t m0 = static_cast<int64_t>(tm) * TM, n0 = static_cast<int64_t>(tn) * kTN;
-    const int Mt = static_cast<int>(M - m0 < TM ? M - m0 : TM);
+    const int64_t m0 = static_cast<int64_t>(tm) * kTM, n0 = static_cast<int64_t>(tn) * kTN;
+    const int Mt = static_cast<int>(M - m0 < kTM ? M - m0 : kTM);
     const int Nt = static_cast<int>(N - n0 < kTN ? N - n0 : kTN);
-    // The MFMA results must have left the pipe before ordinary instructions read the accumulators (the compiler
-    // cannot see into the assembly statements to insert these wait states itself).  With nothing to follow, the
-    // trailing global->LDS loads must have landed before the wavefront ends; otherwise the next
-    // tile's first two stages are in LDS by now and two more on their way there.
-    if (has_next) {
-      asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-    } else {
-      asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
-      __syncthreads();
-    }
 
     if constexpr (kSplit) {   // has_next is false
-      static_assert(kNB == 8, "the partial tiles are 256 x 256");
+      static_assert(kMB == 8 && kNB == 8, "the partial tiles are 256 x 256");
       // Partial tile in fragment order: float4 number (i * 8 + j) * 256 + tid.
       float4v* mine = reinterpret_cast<float4v*>(partials) +
                       (static_cast<int64_t>(tile_local) * k_splits + split) * (TM * TN / 4) + tid;
@@ -401,17 +438,15 @@ __global__ __launch_bounds__(kThreads) void gemm_f16_kernel(const _Float16* __re
         for (int j = 0; j < kNB; ++j) mine[(i * kNB + j) * kThreads] = acc[i][j];
       return;
     } else {
-      store_wave_block_impl<kBf16Out, kRowScales, kNB>(acc, out_scale, Dv, ldd, accumulate, m0 + wm * 128, n0 + wn * (16 * kNB),
-                                                       Mt - wm * 128, Nt - wn * (16 * kNB), lane);
+      store_wave_block_impl<kBf16Out, kRowScales, kMB, kNB>(acc, out_scale, Dv, ldd, accumulate, m0 + wm * (16 * kMB), n0 + wn * (16 * kNB),
+                                                            Mt - wm * (16 * kMB), Nt - wn * (16 * kNB), lane);
     }
     if (!has_next) break;
-    stores_behind = Mt == TM && Nt == kTN;   // every lane stored every block: the count is known
+    stores_behind = Mt == kTM && Nt == kTN;   // every lane stored every block: the count is known
     item = next_item;
     tm = next_tm;
     tn = next_tn;
-    kt_begin = 0;
-    kt_end = KT;
-    lane_setup();
+    lane_setup(g & 3u);
     aim(tm, tn, fetch_st);
   }
 }
@@ -476,7 +511,7 @@ static TailPlan plan_tail(int64_t M, int64_t N, int64_t K) {
   return p;
 }
 
-// Tile width (32 nb columns) of the whole product, and how long it takes in rounds of 256 x 256 tiles.  A narrower tile takes
+// Tile width (32 nb columns) of the whole product in tiles of 256 rows and at most 256 columns, and how long it takes in rounds of 256 x 256 tiles.  A narrower tile takes
 // 0.90, 0.80, 0.68 of the time for nb = 7, 6, 5 (fewer products per byte moved), but rounds come out better for some
 // products; the widest wins a tie.  A split last round costs its share of a round and 0.15 for the partial tiles.  Measured,
 // us per call with nb = 8 / 7 / 6 / 5: 5120 x 5120 x 4096 (FP32) 192 / 179 / 216 / 193, 2048 x 5120 x 5120 113 / 104 / 95 / 93, 4096 x 5120 x 5120
@@ -504,6 +539,46 @@ static Width pick_width(int64_t M, int64_t N, const TailPlan& p, bool reluctant)
   return best;
 }
 
+// What a product takes in tiles of 32 mb x 32 nb, us, without the decode pass: rounds of 256 tiles at `result` us and `k` of the 256 x 256 tile's time per k, which is
+// 14.9 ns while there are fewer tiles than CUs and 17.0 when the chip is full (the clock drops with the matrix pipes busy).  Fitted to 780 times (130 products of
+// 12 us to 1.3 ms, six tiles each), which it meets within 6.5 % (standard deviation).
+struct TileTime {
+  int mb, nb;
+  double result, k;
+};
+constexpr TileTime kTileTimes[] = {{8, 8, 7.8, 1.0}, {8, 7, 7.1, 0.912}, {8, 6, 6.3, 0.80}, {8, 5, 5.4, 0.692}, {8, 10, 8.6, 1.242}, {10, 10, 9.9, 1.51}};
+static double tile_us(const TileTime& t, int64_t tiles, double rounds, int64_t K) {
+  return rounds * (t.result + static_cast<double>(K) * t.k * (tiles >= kCUs ? 0.0170 : 0.0149));
+}
+static double rounds_of(int64_t tiles) { return static_cast<double>((tiles + kCUs - 1) / kCUs); }
+
+// The tile of a product, starting from its width among the tiles of 256 rows: 256 x 320 and 320 x 320 where they take less.  A byte that is loaded or read from LDS serves
+// 1.11 and 1.25 times the MFMAs of a 256 x 256 tile, and for many products rounds come out better.  us per call, the best of the others / 256 x 320 / 320 x 320:
+// 8192 x 20480 x 5120 bf16 1131 / 1112 / 1137, 8192 x 5120 x 20480 1200 / 1152 / 1251, 5120 x 20480 x 8192 FP32 1243 / 1201 / 1127, 5120 x 5120 x 4096 FP32 188 / 217 / 154,
+// 4096 x 15360 x 2048 bf16 192 / 178 / 207.  Over the 130 products the tile with the smallest estimate takes 0.1 % more than the best one.
+// A larger tile has no round split, and tiles without a split sum in the same order.
+// (320 x 320 with a scale per row: the output stage has too few registers for the scales.)
+struct Tile {
+  int mb, nb;
+  double us;
+};
+static Tile pick_tile(int64_t M, int64_t N, int64_t K, const Width& w, const TailPlan& tail, bool row_scales) {
+  Tile best{8, w.nb, HUGE_VAL};
+  for (const TileTime& t : kTileTimes) {
+    const int64_t tiles = ((M + 32 * t.mb - 1) / (32 * t.mb)) * ((N + 32 * t.nb - 1) / (32 * t.nb));
+    double rounds = rounds_of(tiles);
+    if (t.nb <= 8) {
+      if (t.nb != w.nb) continue;
+      if (w.nb == 8 && tail.tail) rounds = static_cast<double>((tiles - tail.tail) / kCUs) + 1.0 / tail.splits + 0.3;   // (the partial tiles)
+    } else if (row_scales && t.mb == 10) {
+      continue;
+    }
+    const double us = tile_us(t, tiles, rounds, K);
+    if (us < best.us) best = Tile{t.mb, t.nb, us};
+  }
+  return best;
+}
+
 // FP16 bytes of the operands that still have to be decoded into the workspace (rows_a / rows_b: 0 for an operand the
 // caller has decoded beforehand)
 static size_t operand_bytes(int64_t rows_a, int64_t rows_b, int64_t K) {
@@ -521,12 +596,9 @@ size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) {
 
 // What a call does: one answer for the estimate, the room asked of the workspace and the launch.  The partial tiles of a split
 // count only where tiles are 256 columns wide, and a workspace without room for them makes the last round an ordinary one.
-// Expected time: what is still to decode (codes and scales in, FP16 out) at 5.0 TB/s, then rounds of 256 tiles at 9.2 us for the result and 15.9 ns
-// per k while there are fewer (3072 x 5120 x 5120, 240 tiles: 130 us in all), 18.6 when the chip is full (the clock drops with the matrix
-// pipes busy) -- of a plain result, for all output types (see SmallTileCost).  5th and 95th percentile over 269 calls of 12 us to
-// 1.3 ms 0.76 and 1.17 of the measured time.
+// Expected time: what is still to decode (codes and scales in, FP16 out) at 5.0 TB/s, then the tiles -- of a plain result, for all output types (see SmallTileCost).
 TwoPassPlan plan_two_pass(const GemmArgs& g) {
-  TwoPassPlan plan{false, HUGE_VAL, 8, 0, 1};
+  TwoPassPlan plan{false, HUGE_VAL, 8, 0, 1, 8, 8};
   const int64_t M = g.a.outer, N = g.b.outer;
   if (g.K % TK != 0 || g.K >= (int64_t{1} << 21)) return plan;   // (the kernel's 32-bit byte offsets inside a 256-row tile)
   const int64_t rows = (g.a.fp16 ? 0 : M) + (g.b.fp16 ? 0 : N);
@@ -535,11 +607,13 @@ TwoPassPlan plan_two_pass(const GemmArgs& g) {
   TailPlan tail = plan_tail(M, N, g.K);
   if (operands + partial_bytes(tail) > g.workspace_bytes) tail = TailPlan{0, 1};
   Width w = pick_width(M, N, tail, false);
-  plan.us = 7.4 + static_cast<double>(rows) * static_cast<double>(g.K) * 2.5625 / 5.0e6 +
-            w.rounds * (9.2 + static_cast<double>(g.K) * (w.tiles >= kCUs ? 0.0186 : 0.0159));
+  const Tile t = pick_tile(M, N, g.K, w, tail, g.a.ts_per_row != 0 || g.b.ts_per_row != 0);
+  plan.us = 7.4 + static_cast<double>(rows) * static_cast<double>(g.K) * 2.5625 / 5.0e6 + t.us;
   if (g.accumulate && g.K < 1024) w = pick_width(M, N, tail, true);
   if (w.nb != 8) tail = TailPlan{0, 1};
   plan.units = w.nb;
+  plan.mb = t.mb;
+  plan.nb = t.nb > 8 ? t.nb : w.nb;
   plan.tail = tail.tail;
   plan.splits = tail.splits;
   // (With both operands decoded beforehand nothing is needed of the workspace.)
@@ -550,18 +624,19 @@ TwoPassPlan plan_two_pass(const GemmArgs& g) {
   return plan;
 }
 
-#define NVFP4_LAUNCH_F16(BF16, ROWSCALES, SPLIT, NB)                                                                  \
+#define NVFP4_LAUNCH_F16(BF16, ROWSCALES, SPLIT, MB, NB)                                                              \
   do {                                                                                                            \
     static PerDeviceOnce once;                                                                                    \
-    const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&gemm_f16_kernel<BF16, ROWSCALES, SPLIT, NB>), kLdsBytes, once); \
+    constexpr int lds_bytes = kStages * stage_bytes(MB, NB);                                                      \
+    const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&gemm_f16_kernel<BF16, ROWSCALES, SPLIT, MB, NB>), lds_bytes, once); \
     if (e != hipSuccess) return e;                                                                                \
-    hipLaunchKernelGGL((gemm_f16_kernel<BF16, ROWSCALES, SPLIT, NB>), dim3(wgs), dim3(kThreads), kLdsBytes, s, a16, b16, \
+    hipLaunchKernelGGL((gemm_f16_kernel<BF16, ROWSCALES, SPLIT, MB, NB>), dim3(wgs), dim3(kThreads), lds_bytes, s, a16, b16, \
                        g.a.outer, g.b.outer, g.K, g.a.ts, g.b.ts, g.d, g.ldd, g.accumulate, tiles_m, tiles_n,     \
                        tile_begin, tile_count, k_splits, partials, g.a.ts_per_row != 0, g.b.ts_per_row != 0);      \
   } while (0)
 
 // Tiles [tile_begin, tile_begin + tile_count); k_splits > 1: each shared by that many workgroups, summed by a second launch.
-template <int kNB>
+template <int kMB, int kNB>
 static hipError_t launch_f16(bool bf16_out, const _Float16* a16, const _Float16* b16, const GemmArgs& g, int tiles_m,
                              int tiles_n, int tile_begin, int tile_count, int k_splits, float* partials, hipStream_t s) {
   // More whole tiles than CUs: one workgroup per CU, each running its tiles as one stream of K steps.
@@ -569,7 +644,7 @@ static hipError_t launch_f16(bool bf16_out, const _Float16* a16, const _Float16*
   if (k_splits == 1 && g.K / TK >= 2 && wgs > static_cast<unsigned>(kCUs)) wgs = kCUs;
   const bool row_scales = g.a.ts_per_row != 0 || g.b.ts_per_row != 0;
   if (k_splits > 1) {
-    NVFP4_LAUNCH_F16(false, false, true, 8);
+    NVFP4_LAUNCH_F16(false, false, true, 8, 8);
     const dim3 grid(static_cast<unsigned>(tile_count) * 32);   // tile, 128 x 128 block, 16 rows
 #define NVFP4_LAUNCH_SUM(BF16, ROWSCALES)                                                                              \
   hipLaunchKernelGGL((splitk_sum_kernel<BF16, ROWSCALES>), grid, dim3(64), 0, s, partials, k_splits, g.a.outer, g.b.outer, \
@@ -582,9 +657,13 @@ static hipError_t launch_f16(bool bf16_out, const _Float16* a16, const _Float16*
     }
 #undef NVFP4_LAUNCH_SUM
   } else if (row_scales) {
-    if (bf16_out) NVFP4_LAUNCH_F16(true, true, false, kNB); else NVFP4_LAUNCH_F16(false, true, false, kNB);
+    if constexpr (kMB == 8) {
+      if (bf16_out) NVFP4_LAUNCH_F16(true, true, false, kMB, kNB); else NVFP4_LAUNCH_F16(false, true, false, kMB, kNB);
+    } else {
+      return hipErrorInvalidValue;   // (pick_tile offers none)
+    }
   } else {
-    if (bf16_out) NVFP4_LAUNCH_F16(true, false, false, kNB); else NVFP4_LAUNCH_F16(false, false, false, kNB);
+    if (bf16_out) NVFP4_LAUNCH_F16(true, false, false, kMB, kNB); else NVFP4_LAUNCH_F16(false, false, false, kMB, kNB);
   }
   return hipGetLastError();
 }
@@ -608,11 +687,11 @@ hipError_t launch_predecode(const Operand& op, int64_t K, void* fp16_out, hipStr
   return hipGetLastError();
 }
 
-// Every tile in one launch of the kernel with 32 kNB columns per tile.
-template <int kNB>
-static hipError_t launch_all(const GemmArgs& g, const _Float16* a16, const _Float16* b16, int tiles_m, hipStream_t s) {
-  const int tiles_n = static_cast<int>((g.b.outer + 32 * kNB - 1) / (32 * kNB));
-  return launch_f16<kNB>(g.out_bf16, a16, b16, g, tiles_m, tiles_n, 0, tiles_m * tiles_n, 1, nullptr, s);
+// Every tile in one launch of the kernel with tiles of 32 kMB x 32 kNB.
+template <int kMB, int kNB>
+static hipError_t launch_all(const GemmArgs& g, const _Float16* a16, const _Float16* b16, hipStream_t s) {
+  const int tiles_m = static_cast<int>((g.a.outer + 32 * kMB - 1) / (32 * kMB)), tiles_n = static_cast<int>((g.b.outer + 32 * kNB - 1) / (32 * kNB));
+  return launch_f16<kMB, kNB>(g.out_bf16, a16, b16, g, tiles_m, tiles_n, 0, tiles_m * tiles_n, 1, nullptr, s);
 }
 
 hipError_t launch_gemm_two_pass(const GemmArgs& g, const TwoPassPlan& plan, hipStream_t s) {
@@ -632,21 +711,23 @@ hipError_t launch_gemm_two_pass(const GemmArgs& g, const TwoPassPlan& plan, hipS
     hipLaunchKernelGGL(decode_f16_kernel, grid, dim3(256), 0, s, g.a.codes, g.a.scales, static_cast<int>(rows_a / 16), a_ws,
                        g.b.codes, g.b.scales, static_cast<int>(rows_b / 16), b_ws, K);
   }
+  if (plan.mb == 10) return launch_all<10, 10>(g, a16, b16, s);
+  switch (plan.nb) {
+    case 10: return launch_all<8, 10>(g, a16, b16, s);
+    case 7: return launch_all<8, 7>(g, a16, b16, s);
+    case 6: return launch_all<8, 6>(g, a16, b16, s);
+    case 5: return launch_all<8, 5>(g, a16, b16, s);
+    default: break;
+  }
   const int tiles_m = static_cast<int>((M + TM - 1) / TM), tiles_n = static_cast<int>((N + TN - 1) / TN);
   const int tiles = tiles_m * tiles_n;
   // One 256x256 tile keeps one CU busy (its LDS fits one workgroup).  Whole rounds of kCUs tiles
   // run as they are; a last partial round that fills at most half the chip is split along K.
-  switch (plan.units) {
-    case 7: return launch_all<7>(g, a16, b16, tiles_m, s);
-    case 6: return launch_all<6>(g, a16, b16, tiles_m, s);
-    case 5: return launch_all<5>(g, a16, b16, tiles_m, s);
-    default: break;
-  }
   const int full = tiles - plan.tail;
   hipError_t e = hipSuccess;
-  if (full > 0) e = launch_f16<8>(g.out_bf16, a16, b16, g, tiles_m, tiles_n, 0, full, 1, nullptr, s);
+  if (full > 0) e = launch_f16<8, 8>(g.out_bf16, a16, b16, g, tiles_m, tiles_n, 0, full, 1, nullptr, s);
   if (e == hipSuccess && plan.tail > 0)
-    e = launch_f16<8>(g.out_bf16, a16, b16, g, tiles_m, tiles_n, full, plan.tail, plan.splits, partials, s);
+    e = launch_f16<8, 8>(g.out_bf16, a16, b16, g, tiles_m, tiles_n, full, plan.tail, plan.splits, partials, s);
   return e;
 }
 
