@@ -11,7 +11,7 @@
 // plus that block's scale byte; the 16x16 result puts D[(l >> 4) * 4 + i][l & 15]
 // in register i of lane l, rows taken from the first operand.
 //
-// 256 x 256 outputs per workgroup, K step 128 (one instruction deep), 256 threads = 4 wavefronts
+// The kernel for any K: 256 x 256 outputs per workgroup, K step 128 (one instruction deep), 256 threads = 4 wavefronts
 // (2 x 2), one per SIMD, of 128 x 128 outputs each: 8 x 8 instructions per K step, 256 accumulator
 // registers in the accumulation half of the register file.  LDS holds two buffers of two K steps,
 // a step being (A codes, B codes, A scales, B scales) = 34 KiB, filled by direct global->LDS
@@ -266,103 +266,117 @@ __global__ __launch_bounds__(kThreads) void gemm_mx_kernel_any_k(Operand A, Oper
 // ---------------------------------------------------------------- K a multiple of 512
 // The kernel above asks the memory system for many small pieces: per K step a 64-byte piece of every code row
 // and a 4-byte piece of every scale row, each its own cache-line request (measured: about one request per
-// clock and CU, which is what bounds it).  When K is a multiple of 512 the same loop runs on fuller lines:
+// clock and CU, which is what bounds it).  When K is a multiple of 512 this one runs on fuller lines:
 //   codes   a stage is two K steps = 128 bytes of each row, 8 rows per load instruction, stored with the XOR
 //           swizzle chunk c of row r -> position c ^ ((r >> 1) & 7) so that fragment reads stay conflict-free;
-//           the two steps of an iteration are the two 64-byte halves of a stage
-//   scales  16 bytes of each scale row = four K steps = two iterations per load instruction, in a ring of
-//           two 8 KiB slots; a wavefront reads 64 rows' 16 bytes at once and transposes them between its lanes (ChunkScales)
-// a third of the line requests for the same bytes.  The pipeline is the one described at the top, with two barriers per stage instead of one: when
-// everybody has read the stage out (a little more than half way through its first 64 MFMAs) the loads that refill its buffer begin, spread from there
-// to the end of the stage; four wavefronts' 16 loads behind the second 64 alone kept the address path busy throughout.
-// What bounds it (parts taken out, results wrong, accesses in bounds; 4096 x 5120 x 5120 bf16, 64.7 us): without the loads 52.2, without waiting for
-// them 61.7, without the fragment reads 63.5, without the output stage of the first of two tiles 61.4; 8192 x 20480 x 5120 416 us: 335, 400, 402 and
-// 342.  One barrier and scales by dwords -> now, us per call from a graph: 4096 x 5120 x 5120 bf16 61.6 -> 58.4, FP32 68.0 -> 64.7; 512 x 5120 x 5120 bf16
-// 24.7 -> 23.2; 8192 x 20480 x 5120 bf16 426 -> 395 (4.3 PFLOP/s).
+//           the two steps of a stage are the two 64-byte halves of its rows
+//   scales  16 bytes of each scale row = four K steps = two stages per load instruction; a wavefront reads 64 rows' 16 bytes at once and transposes them
+//           between its lanes, a step's while the step before runs (behind its MFMAs: bunched between two steps 20 of these instructions cost 90 cycles)
+// a third of the line requests for the same bytes.  What bounds it is loading: a CU takes in 64 bytes a clock, which for 256 x 160 tiles is two thirds of the time that
+// the MFMAs on them take, for 256 x 320 less than half.  So the loop keeps one set of fragments, which leaves room for 128 x 160 outputs per wavefront (320 accumulators): a
+// step runs the upper half of the wavefront's blocks column by column, then the lower half, and a fragment's registers take its next values once its last MFMA
+// has been issued.  The stage's last reads are those of the second step's lower A fragments, at the start of it; the loads that refill the buffer go
+// behind the rest of that step, and have landed in the middle of the next stage's second step.
+// us per call, two sets of fragments in tiles of up to 256 columns -> now: 4096 x 5120 x 5120 bf16 62.8 -> 53.1 (256 x 320; 256 x 160 60.4), 5120 x 5120 x 4096 FP32 69.3 -> 68.2
+// (256 x 224), 8192 x 20480 x 5120 bf16 431 -> 401 (4.3 PFLOP/s), 2048 x 5120 x 5120 33.5 -> 32.2.  Over 120 products of 0.3 to 170 million outputs 4 % less time.
 constexpr int kWideRowBytes = 128;
-constexpr int kWideOperandBytes = TM * kWideRowBytes;       // 32 KiB
-constexpr int kWideStageBytes = 2 * kWideOperandBytes;      // 64 KiB
-constexpr int kWideScaleOperandBytes = TM * 16;             // 4 KiB: 256 rows x 4 steps x 4 blocks
-constexpr int kWideScaleSlotBytes = 2 * kWideScaleOperandBytes;
-constexpr int kWideLdsBytes = 2 * kWideStageBytes + 2 * kWideScaleSlotBytes;   // 144 KiB
+constexpr int wide_stage_bytes(int nb) { return (TM + 32 * nb) * kWideRowBytes; }
+constexpr int wide_lds_bytes(int nb) { return 2 * wide_stage_bytes(nb) + (TM + 32 * nb) * 16 + 768; }   // two stages, one chunk of scales (read in whole KiBs: up to 48 rows past the end)
 
 __device__ __forceinline__ int swz128(int row, int chunk) { return row * kWideRowBytes + ((chunk ^ ((row >> 1) & 7)) << 4); }
 
-// Read number q of the 8 + kNB of a fragment set: 8 of A codes, kNB of B codes (16-row blocks are 2 KiB apart).
-template <int q, int kNB>
-__device__ __forceinline__ void read_frag_wide(Frags& f, uint32_t a_codes, uint32_t b_codes) {
-  if constexpr (q < 8) lds_read16<q * 16 * kWideRowBytes>(f.a[q], a_codes);
-  else lds_read16<(q - 8) * 16 * kWideRowBytes>(f.b[q - 8], b_codes);
-}
-
-// The scales of a chunk (four K steps) as read from LDS: lane l has the 16 bytes of row l & 15 of 16-row block 4 h + (l >> 4), h = 0, 1 of A, then of B: a
-// read is 1 KiB of consecutive LDS.  Element e: the four scales of K step e.  (For kNB < 8 some of B's are of rows that count for nothing.)
-// Read as a dword per row and step, by all four lanes of a row, they took a third of the LDS's time: 8 instructions a step, two rows to a bank.
-struct ChunkScales {
-  int4v s[4];
-};
-template <int q>
-__device__ __forceinline__ void read_chunk_scales(ChunkScales& c, uint32_t a_scales, uint32_t b_scales) {
-  lds_read16<(q & 1) * 64 * 16>(c.s[q], q < 2 ? a_scales : b_scales);
-}
-// The reads are back: from here on (no instruction) the compiler may use the values.
-__device__ __forceinline__ void chunk_scales_back(ChunkScales& c) {
-  asm volatile("" : "+v"(c.s[0]), "+v"(c.s[1]), "+v"(c.s[2]), "+v"(c.s[3]));
-}
 // Byte t of the result = this lane's scale (block l >> 4 of the step) of 16-row block 4 h + t: a 4 x 4 transposition of bytes over the four lanes that
 // hold a row number's dwords: half-wavefronts exchanged and two bytes of each kept, then 16-lane rows and one byte of each.
-__device__ __forceinline__ int transpose_scales(int v, uint32_t sel_half, uint32_t sel_row) {
+__device__ __forceinline__ uint32_t transpose_half(int v, uint32_t sel_half) {
   const auto h = __builtin_amdgcn_permlane32_swap(static_cast<uint32_t>(v), static_cast<uint32_t>(v), false, false);
-  const uint32_t u = __builtin_amdgcn_perm(h[1], h[0], sel_half);
+  return __builtin_amdgcn_perm(h[1], h[0], sel_half);
+}
+__device__ __forceinline__ int transpose_row(uint32_t u, uint32_t sel_row) {
   const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
   return static_cast<int>(__builtin_amdgcn_perm(r[1], r[0], sel_row));
 }
-template <int e>
-__device__ __forceinline__ void set_scales(Frags& f, const ChunkScales& c, uint32_t sel_half, uint32_t sel_row) {
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    f.pa[h] = transpose_scales(c.s[h][e], sel_half, sel_row);
-    f.pb[h] = transpose_scales(c.s[2 + h][e], sel_half, sel_row);
-  }
+
+// 16 bytes of LDS at addr + kOff, kNew: into any registers; else into those that the fragment has (an operand in and out).
+template <int kOff, bool kNew>
+__device__ __forceinline__ void lds_read_frag(int4v& dst, uint32_t addr) {
+  if constexpr (kNew) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(dst) : "v"(addr), "n"(kOff));
+  else asm volatile("ds_read_b128 %0, %1 offset:%2" : "+v"(dst) : "v"(addr), "n"(kOff));
+}
+// No instruction: the value is used here / comes from here.
+__device__ __forceinline__ void keep(const int4v& f) { asm volatile("" ::"v"(f)); }
+__device__ __forceinline__ void arrived(int4v& f) { asm volatile("" : "+v"(f)); }
+template <bool kAcc>
+__device__ __forceinline__ void settled(float4v& acc) {
+  if constexpr (kAcc) asm volatile("" : "+a"(acc));
+  else asm volatile("" : "+v"(acc));
 }
 
-// Spreads `total` things evenly over the `slots` places between MFMAs: the number of the one that place n takes, or -1.
-constexpr int spread(int n, int total, int slots) {
-  return (n + 1) * total / slots > n * total / slots ? n * total / slots : -1;
-}
-// Fragment reads: every second place, so that the last are back before the wait that follows (evenly, the 256-column tile
-// is 1-2 % slower), or evenly where there are not enough places.  odd: which of two places.
-constexpr int read_at(int n, int total, int slots, int odd) {
-  if (2 * total > slots) return spread(n, total, slots);
-  return (n & 1) == odd && (n >> 1) < total ? n >> 1 : -1;
-}
-
-// The first instruction on an accumulator in a tile: C = 0, so the 256 accumulation registers are never cleared.
-template <int kSelB, int kSelA>
-__device__ __forceinline__ void mfma_first(float4v& acc, const int4v& b, const int4v& a, int sb, int sa) {
-  asm volatile("v_mfma_scale_f32_16x16x128_f8f6f4 %0, %1, %2, 0, %3, %4 op_sel:[%5,%6,0] op_sel_hi:[%7,%8,0] cbsz:4 blgp:4"
-               : "=a"(acc)
-               : "v"(b), "v"(a), "v"(sb), "v"(sa), "n"(kSelB & 1), "n"(kSelA & 1), "n"(kSelB >> 1), "n"(kSelA >> 1));
+// The instruction as above; kAcc: accumulator in the accumulation registers; kFirst: the first on an accumulator in a tile, C = 0, so they are never cleared.
+template <bool kFirst, bool kAcc, int kSelB, int kSelA>
+__device__ __forceinline__ void mfma_wide(float4v& acc, const int4v& b, const int4v& a, int sb, int sa) {
+#define NVFP4_MFMA_MX(DST, C)                                                                                                          \
+  asm volatile("v_mfma_scale_f32_16x16x128_f8f6f4 %0, %1, %2, " C ", %3, %4 op_sel:[%5,%6,0] op_sel_hi:[%7,%8,0] cbsz:4 blgp:4"        \
+               : DST(acc)                                                                                                              \
+               : "v"(b), "v"(a), "v"(sb), "v"(sa), "n"(kSelB & 1), "n"(kSelA & 1), "n"(kSelB >> 1), "n"(kSelA >> 1))
+  if constexpr (kFirst && kAcc) NVFP4_MFMA_MX("=a", "0");
+  else if constexpr (kFirst) NVFP4_MFMA_MX("=v", "0");
+  else if constexpr (kAcc) NVFP4_MFMA_MX("+a", "%0");
+  else NVFP4_MFMA_MX("+v", "%0");
+#undef NVFP4_MFMA_MX
 }
 
 // A wavefront's output stage issues 8 ceil(kNB / 2) (bf16) or 8 kNB (FP32) stores for a full tile; three quarters of them may still be
 // outstanding when the loads issued before it are needed (memory operations complete in issue order).
 template <bool kBf16Out, int kNB>
-constexpr int kTileStoresMx = kBf16Out ? 6 * ((kNB + 1) / 2) : 6 * kNB;
+constexpr int kTileStoresMx = 6 * (kBf16Out ? (kNB + 1) / 2 : kNB);
+
+// What goes behind the MFMAs of a K step.  kR rows of blocks a half; MFMA n of a half is in column n / kR.
+template <int kNB>
+struct Schedule {
+  static constexpr int kMB = 8, kR = kMB / 2, kHalf = kR * kNB;
+  static constexpr int kLoads = kMB + kNB;            // a wavefront's code loads per stage
+  static constexpr int kA = kMB / 4, kB = (kNB + 3) / 4;   // registers of packed scales; reads of a chunk's scales
+  static constexpr int kFree = kR + 6 < kHalf - 4 ? kR + 6 : kHalf - 4;   // in the upper half of a stage's second step: before it everybody has read the stage out
+  static constexpr int kLoadPlaces = 2 * kHalf - kFree;
+  static constexpr int spread(int n, int total, int slots) { return (n + 1) * total / slots > n * total / slots ? n * total / slots : -1; }
+  static constexpr int load(int n) { return spread(n, kLoads, kLoadPlaces); }   // n counts from kFree on
+  static constexpr int kEarlyLoads = (kHalf - kFree) * kLoads / kLoadPlaces;    // of them in the upper half
+  // upper half: which A fragment of the lower half is read behind MFMA n (at once: the stage's second step frees the buffer then)
+  static constexpr int upper_read(int n) { return n >= 1 && n <= kR ? kR + n - 1 : -1; }
+  static constexpr int upper_reads_before(int n) { return n <= 1 ? 0 : n - 1 < kR ? n - 1 : kR; }
+  // lower half: which upper A fragment of the next step (all of them before the last two of B), and which B fragment
+  static constexpr int kGapA = 2 + kR * (kR - 1) < kR * (kNB - 2) ? kR : 2 + 3 * (kR - 1) < kR * (kNB - 2) ? 3 : 1;
+  static_assert(2 + kGapA * (kR - 1) < kR * (kNB - 2), "the last two reads of a step are of B");
+  static constexpr int lower_read_a(int n) { return n >= 2 && (n - 2) % kGapA == 0 && (n - 2) / kGapA < kR ? (n - 2) / kGapA : -1; }
+  static constexpr int lower_read_b(int n) { return n >= kR && n % kR == 0 ? n / kR - 1 : -1; }   // (the last column's: behind the next step's first MFMA)
+  static constexpr int lower_reads_behind_a() {   // of B
+    int r = 0;
+    for (int k = 2 + kGapA * (kR - 1); k < kHalf; ++k) r += lower_read_b(k) >= 0;
+    return r;
+  }
+  static constexpr int lower_reads_before(int n) {
+    int r = 0;
+    for (int k = 0; k < n; ++k) r += (lower_read_a(k) >= 0) + (lower_read_b(k) >= 0);
+    return r;
+  }
+  // lower half: the next step's scales are turned in 2 (kA + kB) pieces, one behind each of some MFMAs of the second half of it
+  static constexpr int kTurnFrom = kHalf / 2;
+  static constexpr int turn(int n) { return n >= kTurnFrom ? spread(n - kTurnFrom, 2 * (kA + kB), kHalf - kTurnFrom) : -1; }
+  static_assert(2 * (kA + kB) <= kHalf - kHalf / 2, "a piece of the turn behind each MFMA at the most");
+};
 
 // With more tiles than CUs the host launches one workgroup per CU, which takes tiles blockIdx.x, blockIdx.x +
 // gridDim.x, ... and runs them as ONE stream of stages, as the FP16 kernel of the NVFP4 route does: the loads issued
 // during a tile's last two stages fetch the next tile's first two (and its first scale chunk), so the pipeline
 // neither drains nor refills at a tile boundary.  K is a multiple of 512, so every tile is an even number of stages
-// and a whole number of scale chunks: the stage buffers and the scale ring simply keep turning (`gst` below counts
-// stages over all tiles).  The output stage's stores are not waited for.
+// and a whole number of scale chunks: the stage buffers simply keep turning.  The output stage's stores are not waited for.
+// kNB: 16-column blocks per wavefront (2 x 2 wavefronts of 8 16-row blocks).
 template <bool kBf16Out, int kNB>
 __global__ __launch_bounds__(kThreads) void gemm_mx_kernel_k512(Operand A, Operand B, int64_t K, void* __restrict__ Dv,
                                                                 int64_t ldd, bool accumulate, int tiles_m, int tiles_n) {
-  constexpr int kTN = 32 * kNB;                  // columns of a tile: two wavefronts of kNB 16-column blocks
-  constexpr int kReads = 8 + kNB, kLoads = 8 + kNB, kMfmas = 8 * kNB;
-  constexpr int kFree = 2 * kReads + 2;   // of a stage's first kMfmas: before it everybody has read the stage out
-  constexpr int kLoadPlaces = 2 * kMfmas - kFree, kEarlyLoads = (kMfmas - kFree) * kLoads / kLoadPlaces;   // the loads go behind these; so many of them behind the first kMfmas
+  using S = Schedule<kNB>;
+  constexpr int kMB = S::kMB, kTM = TM, kTN = 32 * kNB, kStageBytes = wide_stage_bytes(kNB), kOperandBytes = kTM * kWideRowBytes;
+  constexpr int kR = S::kR, kHalf = S::kHalf;
   extern __shared__ __attribute__((aligned(16))) char lds[];
 
   const int num_tiles = tiles_m * tiles_n;
@@ -376,77 +390,78 @@ __global__ __launch_bounds__(kThreads) void gemm_mx_kernel_k512(Operand A, Opera
   };
 
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds));
-  const uint32_t scales0 = lds0 + 2 * kWideStageBytes;
+  const uint32_t scales0 = lds0 + 2 * kStageBytes;
   // What depends on the lane is worked out once per tile, from a lane number asked for on the spot (values kept from
   // before the first tile would have to live through every output stage and end up in scratch memory).
-  // Code loads: instruction q (0..7) of wavefront w fills tile rows w * 64 + 8 q .. + 7 (lane -> row lane / 8,
-  // position lane % 8, i.e. chunk (lane % 8) ^ ((row >> 1) & 7); 8 q leaves that term alone for even q and flips
-  // its bit 2 for odd q).  Scale loads: one instruction = 64 tile rows x 16 bytes (four K steps).
+  // Code loads: instruction q of wavefront w fills 8 rows of a tile, rows 8 (w kMB + q) of A's, 8 (w kNB + q) of B's (lane -> row lane / 8,
+  // position lane % 8, i.e. chunk (lane % 8) ^ ((row >> 1) & 7), which an odd 8-row block flips bit 2 of).  Scale loads: one instruction = 64 tile rows x 16 bytes (four K steps).
   uint32_t lane_even = 0, lane_odd = 0, lane_srow = 0;
-  uint32_t a_lo = 0, a_hi = 0, b_lo = 0, b_hi = 0, a_scales = 0, b_scales = 0;   // fragment addresses: stage buffer 0 / scale slot 0, step 0
-  uint32_t sel_half = 0, sel_row = 0;   // of transpose_scales
+  uint32_t a_lo = 0, a_hi = 0, b_lo = 0, b_hi = 0, a_scales = 0, b_scales = 0;   // fragment addresses: stage buffer 0, step 0 / 1
+  uint32_t sel_half = 0, sel_row = 0;   // of the turn of the scales
   auto lane_setup = [&]() {
     const int lane = lane_id();
-    const int r0 = wave * 64 + (lane >> 3);
-    const uint32_t c0 = static_cast<uint32_t>((lane & 7) ^ ((r0 >> 1) & 7)) * 16u;
+    const uint32_t c0 = static_cast<uint32_t>((lane & 7) ^ ((lane >> 4) & 7)) * 16u;
     lane_even = static_cast<uint32_t>(lane >> 3) * static_cast<uint32_t>(code_ld) + c0;
     lane_odd = static_cast<uint32_t>(lane >> 3) * static_cast<uint32_t>(code_ld) + (c0 ^ 64u);
-    lane_srow = static_cast<uint32_t>(wave * 64 + lane);
+    lane_srow = static_cast<uint32_t>(lane);
     const int l16 = lane & 15, kb = lane >> 4;
-    const int arow = (wave >> 1) * 128 + l16, brow = (wave & 1) * (16 * kNB) + l16;
+    const int arow = (wave >> 1) * (16 * kMB) + l16, brow = (wave & 1) * (16 * kNB) + l16;
     a_lo = lds0 + swz128(arow, kb);
     a_hi = lds0 + swz128(arow, 4 + kb);
-    b_lo = lds0 + kWideOperandBytes + swz128(brow, kb);
-    b_hi = lds0 + kWideOperandBytes + swz128(brow, 4 + kb);
-    a_scales = scales0 + ((wave >> 1) * 128 + lane) * 16;
-    b_scales = scales0 + kWideScaleOperandBytes + ((wave & 1) * (16 * kNB) + lane) * 16;
+    b_lo = lds0 + kOperandBytes + swz128(brow, kb);
+    b_hi = lds0 + kOperandBytes + swz128(brow, 4 + kb);
+    a_scales = scales0 + ((wave >> 1) * (16 * kMB) + lane) * 16;
+    b_scales = scales0 + kTM * 16 + ((wave & 1) * (16 * kNB) + lane) * 16;
     sel_half = kb < 2 ? 0x05040100u : 0x07060302u;
     sel_row = (kb & 1) == 0 ? 0x06020400u : 0x07030501u;
   };
   lane_setup();
   // Load addresses: a wave-uniform 64-bit base per operand (codes, scales), which holds the tile and the stage /
   // scale chunk being fetched, plus per-lane 32-bit offsets, which hold the row and the chunk and do not change
-  // within a tile (256 rows of K / 2 bytes: K < 2^24, checked on the host): moving the loads on is scalar work.  An 8-row block past the end of an operand is replaced by the operand's last block (rows come in
+  // within a tile (320 rows of K / 2 bytes: K < 2^24, checked on the host): moving the loads on is scalar work.  An 8-row block past the end of an operand is replaced by the operand's last block (rows come in
   // multiples of 32); it only feeds outputs that are never stored.  Scale rows are clamped per lane.
   const uint8_t* base_a = nullptr;
   const uint8_t* base_b = nullptr;
   const uint8_t* base_sa = nullptr;
   const uint8_t* base_sb = nullptr;
-  uint32_t voff[8 + kNB];   // q 0..7 A, then B
-  uint32_t vsa = 0, vsb = 0;
+  uint32_t last_a = 0, last_b = 0;   // rows that a load of 8 may start at the most
+  uint32_t voff[kMB + kNB];          // A's, then B's
   // Point the loads at stage `stage` and scale chunk `chunk` of tile (tm, tn).
   auto aim = [&](int tm, int tn, int stage, int chunk) {
-    const int64_t m_first = static_cast<int64_t>(tm) * TM, n_first = static_cast<int64_t>(tn) * kTN;
+    const int64_t m_first = static_cast<int64_t>(tm) * kTM, n_first = static_cast<int64_t>(tn) * kTN;
     base_a = A.codes + m_first * code_ld + stage * kWideRowBytes - 3072;
     base_b = B.codes + n_first * code_ld + stage * kWideRowBytes - 3072;
     base_sa = A.scales + m_first * scale_ld + chunk * 16;
     base_sb = B.scales + n_first * scale_ld + chunk * 16;
-    const uint32_t last_a = static_cast<uint32_t>(A.outer - 8 - m_first), last_b = static_cast<uint32_t>(B.outer - 8 - n_first);
+    last_a = static_cast<uint32_t>(A.outer - 8 - m_first), last_b = static_cast<uint32_t>(B.outer - 8 - n_first);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const uint32_t r = static_cast<uint32_t>(wave * 64 + q * 8);
-      voff[q] = ((q & 1) ? lane_odd : lane_even) + min(r, last_a) * static_cast<uint32_t>(code_ld) + (3 - (q & 3)) * 1024u;
+    for (int q = 0; q < kMB; ++q) {
+      const uint32_t blk = static_cast<uint32_t>(wave * kMB + q);
+      voff[q] = ((blk & 1) ? lane_odd : lane_even) + min(blk * 8u, last_a) * static_cast<uint32_t>(code_ld) + (3 - (q & 3)) * 1024u;
     }
 #pragma unroll
     for (int q = 0; q < kNB; ++q) {
       const uint32_t blk = static_cast<uint32_t>(wave * kNB + q);
-      voff[8 + q] = ((blk & 1) ? lane_odd : lane_even) + min(blk * 8u, last_b) * static_cast<uint32_t>(code_ld) + (3 - (q & 3)) * 1024u;
+      voff[kMB + q] = ((blk & 1) ? lane_odd : lane_even) + min(blk * 8u, last_b) * static_cast<uint32_t>(code_ld) + (3 - (q & 3)) * 1024u;
     }
-    vsa = min(lane_srow, last_a + 7) * static_cast<uint32_t>(scale_ld);
-    vsb = min(lane_srow, last_b + 7) * static_cast<uint32_t>(scale_ld);
   };
-  // Load number q of a stage into stage buffer `buf`: 0..7 A, then B.  One LDS address (M0) serves four loads: three of them reach the next KiB by the immediate
+  // Load number q of a stage into stage buffer `buf`: A's, then B's.  One LDS address (M0) serves four loads: three of them reach the next KiB by the immediate
   // offset, which moves the global address too: the bases sit 3 KiB low, the lane's offsets make up for what the immediate does not add.
   auto issue_codes = [&](auto qc, int buf) {
-    constexpr int q = decltype(qc)::value, first = q & ~3;
-    load16_to_lds_at<(q - first) * 1024>(voff[q], q < 8 ? base_a : base_b,
-                                         lds0 + buf * kWideStageBytes + (q < 8 ? wave * 8192 + first * 1024 : kWideOperandBytes + (wave * kNB + first - 8) * 1024));
+    constexpr int q = decltype(qc)::value, o = q < kMB ? q : q - kMB;
+    load16_to_lds_at<(o & 3) * 1024>(voff[q], q < kMB ? base_a : base_b,
+                                     lds0 + buf * kStageBytes + (q < kMB ? wave * (kMB * 1024) : kOperandBytes + wave * (kNB * 1024)) + (o & ~3) * 1024);
   };
-  // the two loads of a scale chunk (four K steps) into ring slot `slot`
-  auto issue_scales = [&](int slot) {
-    const uint32_t dst = scales0 + slot * kWideScaleSlotBytes + wave * 1024;
-    load16_to_lds(vsa, base_sa, dst);
-    load16_to_lds(vsb, base_sb, dst + kWideScaleOperandBytes);
+  // The loads of a scale chunk (four K steps): 64 rows each, a wavefront's own of the first 256 (in a narrower tile some rows come twice, the same
+  // bytes), and of a wider tile the last 64 by every wavefront (the count of its loads is one for all).
+  auto issue_scales = [&]() {
+    auto rows = [&](uint32_t first, int count, uint32_t last, const uint8_t* base, uint32_t dst) {
+      const uint32_t r = static_cast<uint32_t>(min(static_cast<int>(first), count - 64));
+      load16_to_lds(min(r + lane_srow, last + 7) * static_cast<uint32_t>(scale_ld), base, dst + r * 16);
+    };
+    rows(wave * 64, kTM, last_a, base_sa, scales0);
+    rows(wave * 64, kTN, last_b, base_sb, scales0 + kTM * 16);
+    if (kTN > 256) rows(256, kTN, last_b, base_sb, scales0 + kTM * 16);
   };
 
   const int stages = static_cast<int>(K / 256), chunks = static_cast<int>(K / 512);   // stages = 2 chunks >= 2
@@ -454,119 +469,155 @@ __global__ __launch_bounds__(kThreads) void gemm_mx_kernel_k512(Operand A, Opera
   int tm = 0, tn = 0;
   locate(item, tm, tn);
   aim(tm, tn, 0, 0);
-  static_for<0, kLoads>([&](auto q) { issue_codes(q, 0); });
+  static_for<0, S::kLoads>([&](auto q) { issue_codes(q, 0); });
   base_a += kWideRowBytes;
   base_b += kWideRowBytes;
-  static_for<0, kLoads>([&](auto q) { issue_codes(q, 1); });
-  issue_scales(0);
+  static_for<0, S::kLoads>([&](auto q) { issue_codes(q, 1); });
+  issue_scales();
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __builtin_amdgcn_s_barrier();
 
-  Frags f0, f1;
-  ChunkScales chunk;
-  float4v acc[8][kNB];
-  uint32_t gst = 0;             // stages done so far, over all tiles (even at every tile's start)
+  int4v fa[kMB], fb[kNB];
+  // The scales of a chunk as read from LDS: lane l has the 16 bytes of row l & 15 of 16-row block 4 h + (l >> 4), h = 0 .. kA - 1 of A, then of B: a
+  // read is 1 KiB of consecutive LDS.  Element e: the four scales of K step e.  (Some are of rows that count for nothing.)
+  // Read as a dword per row and step, by all four lanes of a row, they took a third of the LDS's time: 8 instructions a step, two rows to a bank.
+  int4v chunk[S::kA + S::kB];
+  int scale[S::kA + S::kB];     // of the step that runs: byte t of number h: block 4 h + t of A; then of B
+  float4v acc[kMB][kNB];
   bool stores_behind = false;   // the previous tile's stores were issued after the loads now in flight
+  auto read_chunk = [&](auto qc) {
+    constexpr int q = decltype(qc)::value;
+    if constexpr (q < S::kA) lds_read_frag<q * 64 * 16, true>(chunk[q], a_scales);
+    else lds_read_frag<(q - S::kA) * 64 * 16, true>(chunk[q], b_scales);
+  };
   for (;;) {
-    // The tile's first fragments.  (After a tile of the same stream its last stage has read them already; they are
+    // The tile's first fragments and scales.  (After a tile of the same stream its last stage has read them already; they are
     // read again so that the output stage had their registers to work with.)
-    {
-      const uint32_t cur = (gst & 1) * kWideStageBytes, sc = ((gst >> 1) & 1) * kWideScaleSlotBytes;
-      static_for<0, kReads>([&](auto q) { read_frag_wide<decltype(q)::value, kNB>(f0, a_lo + cur, b_lo + cur); });
-      static_for<0, 4>([&](auto q) { read_chunk_scales<decltype(q)::value>(chunk, a_scales + sc, b_scales + sc); });
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      chunk_scales_back(chunk);
-      set_scales<0>(f0, chunk, sel_half, sel_row);
-    }
+    static_for<0, S::kA + S::kB>(read_chunk);
+    static_for<0, kR>([&](auto q) { lds_read_frag<decltype(q)::value * 16 * kWideRowBytes, true>(fa[decltype(q)::value], a_lo); });
+    static_for<0, kNB>([&](auto q) { lds_read_frag<decltype(q)::value * 16 * kWideRowBytes, true>(fb[decltype(q)::value], b_lo); });
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    static_for<0, S::kA + S::kB>([&](auto q) {
+      arrived(chunk[decltype(q)::value]);
+      scale[decltype(q)::value] = transpose_row(transpose_half(chunk[decltype(q)::value][0], sel_half), sel_row);
+    });
     const int next_item = item + static_cast<int>(gridDim.x);
     const bool has_next = next_item < num_tiles;
     int next_tm = 0, next_tn = 0;
     if (has_next) locate(next_item, next_tm, next_tn);
 
-    // One stage = two K steps; kFirst: the tile's first; kOdd: the second stage of a scale chunk.  The loads run two stages ahead of the MFMAs, the scale
-    // loads (every other stage) one chunk ahead of the stage that reads it.
-    auto stage_step = [&](auto first_tag, auto odd_tag, int st) {
-      constexpr bool kFirst = decltype(first_tag)::value, kOdd = decltype(odd_tag)::value;
-      constexpr int kStep = kOdd ? 2 : 0;   // the stage's first K step within the chunk
-      const uint32_t cur = kOdd ? kWideStageBytes : 0, nxt = cur ^ kWideStageBytes;   // (gst is even at every tile's start)
-      const uint32_t next_chunk = (((gst + 1) >> 1) & 1) * kWideScaleSlotBytes;       // ring slot of the chunk after an odd stage's
-      // Where the loads go next: on within the tile, or to the next tile's first stage and chunk, or, with nothing
-      // to follow, nowhere (the last stage and chunk are fetched again into buffers nobody reads any more).
-      uint32_t code_advance = kWideRowBytes;
-      if (!kOdd && (st >> 1) + 1 < chunks) {
-        base_sa += 16;
-        base_sb += 16;
-      }
-      if (st + 2 == stages) {
-        code_advance = 0;
-        if (has_next) aim(next_tm, next_tn, 0, 0);
-      } else if (st + 2 > stages && !has_next) {
-        code_advance = 0;
-      }
-      static_for<0, kMfmas>([&](auto ic) {
-        constexpr int n = decltype(ic)::value, i = n / kNB, j = n % kNB, rd = read_at(n, kReads, kMfmas, 1);
-        if constexpr (n == kFree) {
+    // One K step, number kS of its chunk (two stages of two steps).  The loads run two stages ahead of the MFMAs: a stage's buffer is free early in its second
+    // step, and from there to the end of the step the loads of the stage after the next go into it; they have landed in the middle of the next stage's second step.  The scales of the
+    // next chunk are loaded at the end of a chunk's first stage, into the place of its own, which are in registers.
+    auto step = [&](auto first_tag, auto step_tag, int st) __attribute__((always_inline)) {
+      constexpr bool kFirst = decltype(first_tag)::value;
+      constexpr int kS = decltype(step_tag)::value, kBuf = kS >> 1;
+      constexpr bool kSecond = kS & 1;
+      constexpr uint32_t kCur = kBuf * kStageBytes, kNext = (kSecond ? kBuf ^ 1 : kBuf) * kStageBytes;
+      const uint32_t a_cur = (kSecond ? a_hi : a_lo) + kCur, b_cur = (kSecond ? b_hi : b_lo) + kCur;
+      const uint32_t a_nxt = (kSecond ? a_lo : a_hi) + kNext, b_nxt = (kSecond ? b_lo : b_hi) + kNext;
+      static_for<0, kHalf>([&](auto nc) {
+        constexpr int n = decltype(nc)::value, j = n / kR, i = (j & 1) ? kR - 1 - n % kR : n % kR, rd = S::upper_read(n);
+        // Every third column: the B fragments of it and of the next two are back.  Behind them only the later ones, the last column's (read behind the
+        // first MFMA) and A's have been issued.
+        if constexpr (n % kR == 0 && j % 3 == 0 && !kFirst) {
+          constexpr int last = j + 2 < kNB - 1 ? j + 2 : kNB - 1;
+          constexpr int behind = n == 0 && S::lower_reads_behind_a() < kNB - 2 - last ? S::lower_reads_behind_a() : kNB - 2 - last + (n > 0);
+          asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(last == kNB - 1 ? S::upper_reads_before(n) : behind + S::upper_reads_before(n)) : "memory");
+        }
+        if constexpr (kSecond && n == S::kFree) {
           asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
           __builtin_amdgcn_s_barrier();
         }
-        if constexpr (kFirst)
-          mfma_first<(j & 3), (i & 3)>(acc[i][j], f0.b[j], f0.a[i], f0.pb[j >> 2], f0.pa[i >> 2]);
-        else
-          mfma<(j & 3), (i & 3)>(acc[i][j], f0.b[j], f0.a[i], f0.pb[j >> 2], f0.pa[i >> 2]);
-        if constexpr (rd >= 0) read_frag_wide<rd, kNB>(f1, a_hi + cur, b_hi + cur);
-        if constexpr (n == 2) {
-          base_a += code_advance;
-          base_b += code_advance;
+        mfma_wide<kFirst, i * kNB + j < 64, (j & 3), (i & 3)>(acc[i][j], fb[j], fa[i], scale[S::kA + (j >> 2)], scale[i >> 2]);
+        if constexpr (n == 0 && !kFirst) lds_read_frag<(kNB - 1) * 16 * kWideRowBytes, false>(fb[kNB - 1], b_cur);
+        if constexpr (rd >= 0) lds_read_frag<(rd >= 0 ? rd : 0) * 16 * kWideRowBytes, kFirst>(fa[rd >= 0 ? rd : 0], a_cur);
+        if constexpr (kSecond && n == 1) {
+          // Where the loads go next: on within the tile, or to the next tile's first stage and chunk, or, with nothing
+          // to follow, nowhere (the last stage and chunk are fetched again into buffers nobody reads any more).
+          uint32_t advance = kWideRowBytes;
+          if (kBuf == 0 && (st >> 1) + 1 < chunks) {
+            base_sa += 16;
+            base_sb += 16;
+          }
+          if (st + 2 == stages) {
+            advance = 0;
+            if (has_next) aim(next_tm, next_tn, 0, 0);
+          } else if (st + 2 > stages && !has_next) {
+            advance = 0;
+          }
+          base_a += advance;
+          base_b += advance;
         }
-        if constexpr (n >= kFree) {
-          constexpr int ld = spread(n - kFree, kLoads, kLoadPlaces);
-          if constexpr (ld >= 0) issue_codes(std::integral_constant<int, ld>{}, kOdd ? 1 : 0);
+        if constexpr (kSecond && n >= S::kFree) {
+          constexpr int ld = S::load(n - S::kFree);
+          if constexpr (ld >= 0) issue_codes(std::integral_constant<int, ld>{}, kBuf);
         }
       });
-      set_scales<kStep + 1>(f1, chunk, sel_half, sel_row);
-      if (kFirst && stores_behind) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kTileStoresMx<kBf16Out, kNB> + kEarlyLoads) : "memory");
-      else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kEarlyLoads) : "memory");
-      __builtin_amdgcn_s_barrier();
-      static_for<0, kMfmas>([&](auto ic) {
-        constexpr int n = decltype(ic)::value, i = n / kNB, j = n % kNB;
-        constexpr int rd = read_at(n, kReads + (kOdd ? 4 : 0), kMfmas, 0), ld = spread(kMfmas - kFree + n, kLoads, kLoadPlaces);
-        mfma<(j & 3), (i & 3)>(acc[i][j], f1.b[j], f1.a[i], f1.pb[j >> 2], f1.pa[i >> 2]);
-        if constexpr (rd >= 0 && rd < kReads) read_frag_wide<rd, kNB>(f0, a_lo + nxt, b_lo + nxt);
-        if constexpr (rd >= kReads) read_chunk_scales<rd - kReads>(chunk, a_scales + next_chunk, b_scales + next_chunk);
-        if constexpr (ld >= 0) issue_codes(std::integral_constant<int, ld>{}, kOdd ? 1 : 0);
+      // The lower half's A fragments are back; in a stage's second step the next stage has landed (its loads and scales: all but those of this step).
+      if constexpr (kSecond) {
+        if (kS == 1 && stores_behind && st == 0)
+          asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(S::kEarlyLoads + kTileStoresMx<kBf16Out, kNB> > 63 ? 63 : S::kEarlyLoads + kTileStoresMx<kBf16Out, kNB>) : "memory");
+        else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(S::kEarlyLoads) : "memory");
+        __builtin_amdgcn_s_barrier();
+      } else {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      }
+      uint32_t half[S::kA + S::kB];
+      int next_scale[S::kA + S::kB];
+      static_for<0, kHalf>([&](auto nc) {
+        constexpr int n = decltype(nc)::value, j = n / kR, i = kR + ((j & 1) ? kR - 1 - n % kR : n % kR);
+        constexpr int ra = S::lower_read_a(n), rb = S::lower_read_b(n), tr = S::turn(n);
+        if constexpr (kS == 3 && n == S::kTurnFrom) {
+          asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(S::lower_reads_before(n)) : "memory");
+          static_for<0, S::kA + S::kB>([&](auto q) { arrived(chunk[decltype(q)::value]); });
+        }
+        mfma_wide<kFirst, i * kNB + j < 64, (j & 3), (i & 3)>(acc[i][j], fb[j], fa[i], scale[S::kA + (j >> 2)], scale[i >> 2]);
+        if constexpr (kS == 3 && n < 2) static_for<n * 3, (n == 0 && S::kA + S::kB > 3 ? 3 : n * 3 > S::kA + S::kB ? n * 3 : S::kA + S::kB)>(read_chunk);
+        if constexpr (ra >= 0) lds_read_frag<(ra >= 0 ? ra : 0) * 16 * kWideRowBytes, false>(fa[ra >= 0 ? ra : 0], a_nxt);
+        if constexpr (rb >= 0) lds_read_frag<(rb >= 0 ? rb : 0) * 16 * kWideRowBytes, false>(fb[rb >= 0 ? rb : 0], b_nxt);
+        if constexpr (tr >= 0 && tr % 2 == 0) half[tr / 2] = transpose_half(chunk[tr / 2][(kS + 1) & 3], sel_half);
+        if constexpr (tr >= 0 && tr % 2 == 1) next_scale[tr / 2] = transpose_row(half[tr / 2], sel_row);
+        if constexpr (kSecond) {
+          constexpr int ld = S::load(kHalf - S::kFree + n);
+          if constexpr (ld >= 0) issue_codes(std::integral_constant<int, ld>{}, kBuf);
+        }
       });
-      // even stages also fetch the scales of the chunk after the next stage's, into the slot its predecessor left
-      // at this stage's barrier
-      if (!kOdd) issue_scales(static_cast<int>(((gst >> 1) + 1) & 1));
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      if (kOdd) chunk_scales_back(chunk);
-      set_scales<kOdd ? 0 : 2>(f0, chunk, sel_half, sel_row);
-      ++gst;
+      if constexpr (kS == 1) issue_scales();
+#pragma unroll
+      for (int q = 0; q < S::kA + S::kB; ++q) scale[q] = next_scale[q];
     };
-    stage_step(std::true_type{}, std::false_type{}, 0);
-    stage_step(std::false_type{}, std::true_type{}, 1);
-    for (int st = 2; st < stages; st += 2) {
-      stage_step(std::false_type{}, std::false_type{}, st);
-      stage_step(std::false_type{}, std::true_type{}, st + 1);
-    }
+    auto chunk_of_steps = [&](auto first_tag, int st) __attribute__((always_inline)) {
+      step(first_tag, std::integral_constant<int, 0>{}, st);
+      step(std::false_type{}, std::integral_constant<int, 1>{}, st);
+      step(std::false_type{}, std::integral_constant<int, 2>{}, st + 1);
+      step(std::false_type{}, std::integral_constant<int, 3>{}, st + 1);
+    };
+    chunk_of_steps(std::true_type{}, 0);
+    for (int st = 2; st < stages; st += 2) chunk_of_steps(std::false_type{}, st);
+
+    // The MFMA results must have left the pipe before ordinary instructions read the accumulators (the compiler
+    // cannot see into the assembly statements to insert these wait states itself), and the reads behind the last step must have arrived before
+    // their registers serve anything else: the statements without an instruction keep the fragments until then and let the sums be used only from then on.
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+    static_for<0, kMB>([&](auto i) { keep(fa[decltype(i)::value]); });
+    static_for<0, kNB>([&](auto j) { keep(fb[decltype(j)::value]); });
+    static_for<0, kMB * kNB>([&](auto n) { settled<(decltype(n)::value < 64)>(acc[decltype(n)::value / kNB][decltype(n)::value % kNB]); });
+    // With nothing to follow, the trailing global->LDS loads must have landed before the wavefront ends.
+    if (!has_next) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 
     // Everything below is computed here, per tile (see lane_setup).
     int wm = wave >> 1, wn = wave & 1;
     asm volatile("" : "+s"(wm), "+s"(wn));
     const int lane = lane_id();
     const TensorScales out_scale{A.ts, B.ts, false, false};    // both are 1 for MXFP4 (no tensor-level scale)
-    const int64_t m0 = static_cast<int64_t>(tm) * TM, n0 = static_cast<int64_t>(tn) * kTN;
-    const int Mt = static_cast<int>(A.outer - m0 < TM ? A.outer - m0 : TM);
+    const int64_t m0 = static_cast<int64_t>(tm) * kTM, n0 = static_cast<int64_t>(tn) * kTN;
+    const int Mt = static_cast<int>(A.outer - m0 < kTM ? A.outer - m0 : kTM);
     const int Nt = static_cast<int>(B.outer - n0 < kTN ? B.outer - n0 : kTN);
-    // The MFMA results must have left the pipe before ordinary instructions read the accumulators (the compiler
-    // cannot see into the assembly statements to insert these wait states itself).  With nothing to follow, the
-    // trailing global->LDS loads must have landed before the wavefront ends.
-    if (has_next) asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-    else asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
-    store_wave_block<kBf16Out, kNB>(acc, out_scale, Dv, ldd, accumulate, m0 + wm * 128, n0 + wn * (16 * kNB), Mt - wm * 128, Nt - wn * (16 * kNB),
-                               lane);
+    store_wave_block<kBf16Out, kNB>(acc, out_scale, Dv, ldd, accumulate, m0 + wm * (16 * kMB), n0 + wn * (16 * kNB), Mt - wm * (16 * kMB),
+                                                     Nt - wn * (16 * kNB), lane);
     if (!has_next) break;
-    stores_behind = Mt == TM && Nt == kTN;   // every lane stored every block: the count is known
+    stores_behind = Mt == kTM && Nt == kTN;   // every lane stored every block: the count is known
     item = next_item;
     tm = next_tm;
     tn = next_tn;
@@ -586,20 +637,20 @@ static hipError_t launch_mx(Kernel kernel, PerDeviceOnce& once, int lds_bytes, c
   return hipGetLastError();
 }
 
-// Width of the k512 kernel's tiles: 32 kNB columns.  256 x 256 tiles move the fewest bytes per product, but a product of a few
-// hundred of them leaves CUs idle: a round of tiles of 5 / 8 of the width takes 0.76 of the time (medians over 115 products: 0.93, 0.76, 0.66 for kNB = 7, 5, 4; four rounds of the last of
-// long K take more: 2272 x 14464 x 5120 112 us against 106 in three of kNB = 7, so it counts 0.70),
-// so the width with the smallest rounds-of-256-tiles x time is taken, the wider one at a tie; over 158 products it was the best of the four but for two by more
-// than 2 %.  us per call from a graph at kNB = 8 / 7 / 5 / 4: 4096 x 5120 x 5120 bf16 70.7 / 65.3 / 58.4 / 72.5, 5120 x 5120 x 4096 FP32 67.9 / 65.2 / 74.5 / 86.0,
-// 512 x 5120 x 5120 bf16 34.2 / 32.2 / 25.9 / 23.2, 1024 x 1024 x 1024 bf16 13.7 / 12.9 / 10.8 / 9.5, 8192 x 20480 x 5120 bf16 400 / 444 / 497 / 568.
-static int pick_mx_width(int64_t M, int64_t N) {
-  constexpr int kWidths[4] = {8, 7, 5, 4};
-  constexpr double kTime[4] = {1.0, 0.93, 0.76, 0.70};
+// Width of the k512 kernel's tiles: 256 rows x 32 nb columns.  A wider tile moves fewer bytes per product, but a product of a few
+// hundred of them leaves CUs idle: a round of 256 tiles of nb = 10, 7, 5, 4 takes 1.19, 0.92, 0.75, 0.65 of one of nb = 8, and 0.9 of that where it does not fill the chip (fitted
+// to 120 products), so the width with the smallest rounds x time is taken, the wider one of up to 256 columns at a tie.  Over these products it takes 0.4 % more than the best one.
+// us per call at nb = 8 / 7 / 5 / 10: 4096 x 5120 x 5120 bf16 73.2 / 66.8 / 60.4 / 53.1, 5120 x 5120 x 4096 FP32 70.6 / 68.2 / 77.1 / 83.9, 2048 x 5120 x 5120 bf16 37.6 / 34.7 /
+// 32.2 / 42.2, 8192 x 20480 x 5120 bf16 421 / 450 / 474 / 401.  (320 rows x 160 or 256 columns: no better over them.)
+static int pick_mx_width(int64_t M, int64_t N, int widest) {
+  constexpr int kWidths[5] = {8, 7, 5, 4, 10};
+  constexpr double kTime[5] = {1.0, 0.92, 0.75, 0.65, 1.19};
   int best = 8;
   double best_time = 0.0;
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < 5; ++i) {
+    if (kWidths[i] > widest) continue;
     const int64_t tiles = ((M + TM - 1) / TM) * ((N + 32 * kWidths[i] - 1) / (32 * kWidths[i]));
-    const double t = static_cast<double>((tiles + 255) / 256) * kTime[i];
+    const double t = (tiles < 256 ? 0.9 : static_cast<double>((tiles + 255) / 256)) * kTime[i];
     if (i == 0 || t < best_time) {
       best = kWidths[i];
       best_time = t;
@@ -614,8 +665,9 @@ static hipError_t launch_k512(const GemmArgs& g, int tiles_m, hipStream_t s) {
   const int tiles_n = static_cast<int>((g.b.outer + 32 * kNB - 1) / (32 * kNB));
   const int64_t tiles = static_cast<int64_t>(tiles_m) * tiles_n;
   const dim3 grid(static_cast<unsigned>(tiles < 256 ? tiles : 256));   // one workgroup per CU, each running its tiles as one stream
-  if (g.out_bf16) return launch_mx(gemm_mx_kernel_k512<true, kNB>, once_bf16, kWideLdsBytes, g, grid, tiles_m, tiles_n, s);
-  return launch_mx(gemm_mx_kernel_k512<false, kNB>, once_f32, kWideLdsBytes, g, grid, tiles_m, tiles_n, s);
+  constexpr int lds = wide_lds_bytes(kNB);
+  if (g.out_bf16) return launch_mx(gemm_mx_kernel_k512<true, kNB>, once_bf16, lds, g, grid, tiles_m, tiles_n, s);
+  return launch_mx(gemm_mx_kernel_k512<false, kNB>, once_f32, lds, g, grid, tiles_m, tiles_n, s);
 }
 
 hipError_t launch_gemm_mx(const GemmArgs& g, hipStream_t s) {
@@ -624,10 +676,11 @@ hipError_t launch_gemm_mx(const GemmArgs& g, hipStream_t s) {
   // 16-byte pieces of scale rows need K / 32 to be a multiple of 16 and the scale arrays 16-byte aligned
   const bool wide = g.K % 512 == 0 && reinterpret_cast<uintptr_t>(g.a.scales) % 16 == 0 && reinterpret_cast<uintptr_t>(g.b.scales) % 16 == 0;
   if (wide) {
-    switch (pick_mx_width(g.a.outer, g.b.outer)) {
+    switch (pick_mx_width(g.a.outer, g.b.outer, 10)) {
       case 4: return launch_k512<4>(g, tiles_m, s);
       case 5: return launch_k512<5>(g, tiles_m, s);
       case 7: return launch_k512<7>(g, tiles_m, s);
+      case 10: return launch_k512<10>(g, tiles_m, s);
       default: return launch_k512<8>(g, tiles_m, s);
     }
   }
@@ -639,5 +692,7 @@ hipError_t launch_gemm_mx(const GemmArgs& g, hipStream_t s) {
 
 }  // namespace nvfp4
 
-// For the tests, not part of the ABI: 32-column units of the tile that an MXFP4 product of these sizes takes where K is a multiple of 512.
-extern "C" int nvfp4_internal_mx_gemm_units(int64_t M, int64_t N) { return nvfp4::pick_mx_width(M, N); }
+// For the tests, not part of the ABI: 32-column units of the tile that an MXFP4 product of these sizes takes where K is a multiple of 512, of those of up to 256 columns
+// and of all.
+extern "C" int nvfp4_internal_mx_gemm_units(int64_t M, int64_t N) { return nvfp4::pick_mx_width(M, N, 8); }
+extern "C" int nvfp4_internal_mx_gemm_width(int64_t M, int64_t N) { return nvfp4::pick_mx_width(M, N, 10); }
