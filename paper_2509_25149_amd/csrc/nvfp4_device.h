@@ -100,11 +100,10 @@ __device__ __forceinline__ float block_scale(float amax_b, float s_enc, float s_
 
 // Two scaled values -> one byte of two E2M1 codes written into byte `kSel`
 // of `old` (round to nearest even, saturating; matches the tie rule "even
-// code").  The instruction's scale operand divides by a power of two only; it
-// is held at 1.
-template <int kSel>
+// code").  The instruction's scale operand divides by a power of two only: kDiv = 1, 2 or 4.
+template <int kSel, int kDiv = 1>
 __device__ __forceinline__ uint32_t cvt_rne_pair(uint32_t old, float v0, float v1) {
-  return __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(old, v0, v1, 1.0f, kSel);
+  return __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(old, v0, v1, static_cast<float>(kDiv), kSel);
 }
 
 // Stochastic rounding of one value with a 16-bit random integer placed in the
@@ -125,12 +124,17 @@ __device__ __forceinline__ uint32_t cvt_sr_single(float v, uint32_t rand_hi16) {
 
 // The same conversion written into byte kSel of `acc`, the other three bytes kept: the instruction only writes the byte
 // it is told to, but the builtin does not say so to the compiler (see above), so the accumulating form is spelled in
-// assembly with the destination tied.  Four of these fill a dword without any merging.
-template <int kSel>
+// assembly with the destination tied.  Four of these fill a dword without any merging.  The value is divided by kDiv = 1, 2 or 4.
+template <int kSel, int kDiv = 1>
 __device__ __forceinline__ void cvt_sr_single_into(uint32_t& acc, float v, uint32_t rand_hi16) {
   float2v p;   // the pair's second value is never looked at
   p.x = v;
-  asm("v_cvt_scalef32_sr_pk_fp4_f32 %0, %1, %2, 1.0 op_sel:[0,0,%3,%4]" : "+v"(acc) : "v"(p), "v"(rand_hi16), "n"(kSel & 1), "n"(kSel >> 1));
+#define NVFP4_CVT_SR(SCALE) \
+  asm("v_cvt_scalef32_sr_pk_fp4_f32 %0, %1, %2, " SCALE " op_sel:[0,0,%3,%4]" : "+v"(acc) : "v"(p), "v"(rand_hi16), "n"(kSel & 1), "n"(kSel >> 1))
+  if constexpr (kDiv == 4) NVFP4_CVT_SR("4.0");
+  else if constexpr (kDiv == 2) NVFP4_CVT_SR("2.0");
+  else NVFP4_CVT_SR("1.0");
+#undef NVFP4_CVT_SR
 }
 
 // (a & mask) | (b & ~mask) in one v_bitop3_b32 (truth table: the expression evaluated on

@@ -89,6 +89,8 @@ __global__ __launch_bounds__(kThreads) void amax_kernel(const uint16_t* __restri
 // rows x 256 columns, which is 64 bytes of codes per column of the col copy and 128 per row of the row copy.  (One
 // patch per lane instead of two 16-row groups one after the other: 256 x 512 22.7 -> 13.1 us per call, 1040 x 2064 49 -> 15.7.
 // Wavefronts of 16 rows x 512 columns leave 32-byte pieces of col codes, 8192 x 5120 47 -> 57 us; 64 x 128 no better than this.)
+// A 4- or 16-point rotation's normalisation is left to the conversions, whose scale operand divides by a power of two: 128 multiplications of a patch's 2050 (3100 with
+// stochastic rounding) instructions less; X 8192 x 5120 45.9 -> 45.1 us, dY 8192 x 20480 SR 188.6 -> 185.4.
 // What bounds it: large tensors the memory system (all calls, both passes, bytes over time: W 5120 x 20480 6.2 TB/s where a
 // plain copy of this card runs at 4.6 - 5.1), with stochastic rounding the vector pipe (Philox and one conversion per
 // value), small ones the chain load - amax - scale - table - codes of one patch.
@@ -223,12 +225,9 @@ __global__ __launch_bounds__(kThreads, kSR && kRow && kCol && !k2D ? 3 : 2) void
           }
           float v[16];
           signed_column(p, c, sign_mask, v);
-          if (kRht) {
-            butterfly_rows<kRht>(v);
-#pragma unroll
-            for (int r = 0; r < 16; ++r) v[r] *= rht_norm<kRht>();
-          }
-          emit_column<kSR, k2D, T>(v, c, rnd, lane, gl, s_enc_c, lut_col, s_enc_tile, tile_code, st_col_codes, st_col_scales);
+          butterfly_rows<kRht>(v);
+          normalise<kRht>(v);
+          emit_column<kSR, k2D, T, kRhtDiv<kRht>>(v, c, rnd, lane, gl, s_enc_c, lut_col, s_enc_tile, tile_code, st_col_codes, st_col_scales);
           __builtin_amdgcn_sched_barrier(0);
         }
       } else {
@@ -238,17 +237,12 @@ __global__ __launch_bounds__(kThreads, kSR && kRow && kCol && !k2D ? 3 : 2) void
           // Without a rotation sign_mask is 0 at run time; it is still applied, so that these values are not
           // recognised as the row pass's: keeping all 128 of those alive costs more registers than there are.
           signed_column_pair(p, t, sign_mask, lo, hi);
-          if (kRht) {
-            butterfly_rows<kRht>(lo);
-            butterfly_rows<kRht>(hi);
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              lo[r] *= rht_norm<kRht>();
-              hi[r] *= rht_norm<kRht>();
-            }
-          }
-          emit_column<kSR, k2D, T>(lo, 2 * t, rnd, lane, gl, s_enc_c, lut_col, s_enc_tile, tile_code, st_col_codes, st_col_scales);
-          emit_column<kSR, k2D, T>(hi, 2 * t + 1, rnd, lane, gl, s_enc_c, lut_col, s_enc_tile, tile_code, st_col_codes, st_col_scales);
+          butterfly_rows<kRht>(lo);
+          butterfly_rows<kRht>(hi);
+          normalise<kRht>(lo);
+          normalise<kRht>(hi);
+          emit_column<kSR, k2D, T, kRhtDiv<kRht>>(lo, 2 * t, rnd, lane, gl, s_enc_c, lut_col, s_enc_tile, tile_code, st_col_codes, st_col_scales);
+          emit_column<kSR, k2D, T, kRhtDiv<kRht>>(hi, 2 * t + 1, rnd, lane, gl, s_enc_c, lut_col, s_enc_tile, tile_code, st_col_codes, st_col_scales);
         }
       }
     }

@@ -161,6 +161,7 @@ __global__ __launch_bounds__(kThreads) void cast_small_kernel(
   }
 
   if (kCol) {
+    constexpr int kDiv = kRhtDiv<kRht>;
     const uint32_t wg = kRow ? blockIdx.x - row_wgs : blockIdx.x;
     const uint32_t across = static_cast<uint32_t>((cols + kColTileCols - 1) / kColTileCols), by = wg / across, bx = wg - by * across;
     const int lane = tid & 63, wave = tid >> 6;
@@ -200,14 +201,12 @@ __global__ __launch_bounds__(kThreads) void cast_small_kernel(
       uint32_t code[2];
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
-        if (kRht) {
-          butterfly_rows<kRht>(v[c]);
-#pragma unroll
-          for (int r = 0; r < 16; ++r) v[c][r] *= rht_norm<kRht>();
-        }
+        butterfly_rows<kRht>(v[c]);
+        normalise<kRht>(v[c]);
         float m = 0.0f;
 #pragma unroll
         for (int r = 0; r < 16; r += 2) m = fmaxf(fmaxf(m, fabsf(v[c][r])), fabsf(v[c][r + 1]));
+        if (kDiv != 1) m *= 1.0f / kDiv;
         code[c] = e4m3_encode(div_by_6(m) * s_enc);
         const float s_enc_b = lut[code[c]];
 #pragma unroll
@@ -217,19 +216,19 @@ __global__ __launch_bounds__(kThreads) void cast_small_kernel(
         for (int h = 0; h < 2; ++h) {
           if (!kSR) {
             const uint32_t none[4] = {0, 0, 0, 0};
-            half[h] = encode8<false>(v[c] + 8 * h, none);
+            half[h] = encode8<false, kDiv>(v[c] + 8 * h, none);
           } else {
             const float* u = v[c] + 8 * h;
             auto d = [&](int t) { return c ? draws[8 * h + t] & 0xFFFF0000u : draws[8 * h + t] << 16; };
             uint32_t e = 0u, o = 0u;
-            cvt_sr_single_into<0>(e, u[0], d(0));
-            cvt_sr_single_into<1>(e, u[2], d(2));
-            cvt_sr_single_into<2>(e, u[4], d(4));
-            cvt_sr_single_into<3>(e, u[6], d(6));
-            cvt_sr_single_into<0>(o, u[1], d(1));
-            cvt_sr_single_into<1>(o, u[3], d(3));
-            cvt_sr_single_into<2>(o, u[5], d(5));
-            cvt_sr_single_into<3>(o, u[7], d(7));
+            cvt_sr_single_into<0, kDiv>(e, u[0], d(0));
+            cvt_sr_single_into<1, kDiv>(e, u[2], d(2));
+            cvt_sr_single_into<2, kDiv>(e, u[4], d(4));
+            cvt_sr_single_into<3, kDiv>(e, u[6], d(6));
+            cvt_sr_single_into<0, kDiv>(o, u[1], d(1));
+            cvt_sr_single_into<1, kDiv>(o, u[3], d(3));
+            cvt_sr_single_into<2, kDiv>(o, u[5], d(5));
+            cvt_sr_single_into<3, kDiv>(o, u[7], d(7));
             half[h] = interleave_nibbles(e, o);
           }
         }

@@ -120,6 +120,19 @@ __device__ __forceinline__ constexpr float rht_norm() {
                                                                                         : 0.0883883476483184405f;
 }
 
+// The divisor of the conversions to E2M1 that stands for that normalisation where it is a power of two, else 1: the rotated values then stay as the
+// butterfly leaves them and only a block's maximum is normalised.  Same codes: v / 4 and (v s) / 4 are exact (bf16 sums are multiples of 2^-133), and
+// where the product of v / 4 and s would have been subnormal, both round to a code of 0.  One multiplication per value less: see cast_kernel.
+template <int kRht>
+constexpr int kRhtDiv = kRht == 16 ? 4 : kRht == 4 ? 2 : 1;
+template <int kRht>
+__device__ __forceinline__ void normalise(float (&v)[16]) {   // what the conversions do not
+  if constexpr (kRht != 0 && kRhtDiv<kRht> == 1) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) v[r] *= rht_norm<kRht>();
+  }
+}
+
 // Maximum over the wavefront, valid in lane 63: shifts within rows of 16 lanes, then row 0 -> 1 and 2 -> 3, then the lower half
 // -> the upper (lanes without a source take 0).
 __device__ __forceinline__ uint32_t wave_max_u32_lane63(uint32_t m) {
@@ -136,14 +149,14 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t m) {
 }
 
 // Eight scaled values of one row -> one dword of eight codes.
-template <bool kSR>
+template <bool kSR, int kDiv = 1>
 __device__ __forceinline__ uint32_t encode8(const float v[8], const uint32_t rnd[4]) {
   if (!kSR) {
     uint32_t d = 0;
-    d = cvt_rne_pair<0>(d, v[0], v[1]);
-    d = cvt_rne_pair<1>(d, v[2], v[3]);
-    d = cvt_rne_pair<2>(d, v[4], v[5]);
-    d = cvt_rne_pair<3>(d, v[6], v[7]);
+    d = cvt_rne_pair<0, kDiv>(d, v[0], v[1]);
+    d = cvt_rne_pair<1, kDiv>(d, v[2], v[3]);
+    d = cvt_rne_pair<2, kDiv>(d, v[4], v[5]);
+    d = cvt_rne_pair<3, kDiv>(d, v[6], v[7]);
     return d;
   } else {
     uint32_t e = 0u, o = 0u;   // low nibble of byte t: element 2t (e) / 2t + 1 (o)
@@ -167,21 +180,21 @@ __device__ __forceinline__ uint32_t draw_hi16(const uint32_t rnd[16][4], int r, 
 }
 
 // Eight scaled values of one column (rows r0..r0+7 of the patch) -> one dword.
-template <bool kSR>
+template <bool kSR, int kDiv = 1>
 __device__ __forceinline__ uint32_t encode8_col(const float* v, const uint32_t rnd[16][4], int r0, int c) {
   if (!kSR) {
     const uint32_t none[4] = {0, 0, 0, 0};
-    return encode8<false>(v, none);
+    return encode8<false, kDiv>(v, none);
   } else {
     uint32_t e = 0u, o = 0u;
-    cvt_sr_single_into<0>(e, v[0], draw_hi16(rnd, r0 + 0, c));
-    cvt_sr_single_into<1>(e, v[2], draw_hi16(rnd, r0 + 2, c));
-    cvt_sr_single_into<2>(e, v[4], draw_hi16(rnd, r0 + 4, c));
-    cvt_sr_single_into<3>(e, v[6], draw_hi16(rnd, r0 + 6, c));
-    cvt_sr_single_into<0>(o, v[1], draw_hi16(rnd, r0 + 1, c));
-    cvt_sr_single_into<1>(o, v[3], draw_hi16(rnd, r0 + 3, c));
-    cvt_sr_single_into<2>(o, v[5], draw_hi16(rnd, r0 + 5, c));
-    cvt_sr_single_into<3>(o, v[7], draw_hi16(rnd, r0 + 7, c));
+    cvt_sr_single_into<0, kDiv>(e, v[0], draw_hi16(rnd, r0 + 0, c));
+    cvt_sr_single_into<1, kDiv>(e, v[2], draw_hi16(rnd, r0 + 2, c));
+    cvt_sr_single_into<2, kDiv>(e, v[4], draw_hi16(rnd, r0 + 4, c));
+    cvt_sr_single_into<3, kDiv>(e, v[6], draw_hi16(rnd, r0 + 6, c));
+    cvt_sr_single_into<0, kDiv>(o, v[1], draw_hi16(rnd, r0 + 1, c));
+    cvt_sr_single_into<1, kDiv>(o, v[3], draw_hi16(rnd, r0 + 3, c));
+    cvt_sr_single_into<2, kDiv>(o, v[5], draw_hi16(rnd, r0 + 5, c));
+    cvt_sr_single_into<3, kDiv>(o, v[7], draw_hi16(rnd, r0 + 7, c));
     return interleave_nibbles(e, o);
   }
 }
@@ -269,9 +282,9 @@ __device__ __forceinline__ void row_pass(const Patch& p, const uint32_t (&rnd)[1
   }
 }
 
-// One 1x16 block of the col copy: the 16 (possibly rotated) values of column c of the patch -> scale byte and
+// One 1x16 block of the col copy: the 16 (possibly rotated) values of column c of the patch, times kDiv -> scale byte and
 // eight bytes of codes, staged in LDS.
-template <bool kSR, bool k2D, class T = WideTile>
+template <bool kSR, bool k2D, class T = WideTile, int kDiv = 1>
 __device__ __forceinline__ void emit_column(float (&v)[16], int c, const uint32_t (&rnd)[16][4], int lane, int gl,
                                             float s_enc_c, const float* lut_col, float s_enc_tile, uint32_t tile_code,
                                             uint8_t* st_col_codes, uint8_t* st_col_scales) {
@@ -284,14 +297,15 @@ __device__ __forceinline__ void emit_column(float (&v)[16], int c, const uint32_
     float m = 0.0f;
 #pragma unroll
     for (int r = 0; r < 16; r += 2) m = fmaxf(fmaxf(m, fabsf(v[r])), fabsf(v[r + 1]));
+    if (kDiv != 1) m *= 1.0f / kDiv;
     code = e4m3_encode(div_by_6(m) * s_enc_c);
     s_enc_b = lut_col[code];
   }
 #pragma unroll
   for (int r = 0; r < 16; ++r) v[r] *= s_enc_b;
   uint2 out;
-  out.x = encode8_col<kSR>(v, rnd, 0, c);
-  out.y = encode8_col<kSR>(v + 8, rnd, 8, c);
+  out.x = encode8_col<kSR, kDiv>(v, rnd, 0, c);
+  out.y = encode8_col<kSR, kDiv>(v + 8, rnd, 8, c);
   *reinterpret_cast<uint2*>(st_col_codes + ((c * T::kGroups + gl) * T::kSlot + lane) * 8) = out;
   st_col_scales[(c * T::kGroups + gl) * T::kLanes + lane] = static_cast<uint8_t>(code);
 }
