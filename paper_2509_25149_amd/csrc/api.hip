@@ -460,8 +460,7 @@ int nvfp4_linear_backward(const void* dy, int64_t tokens, int64_t d_out, int64_t
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (launch_quantize(pdy.a, s) != hipSuccess) return NVFP4_ERR_HIP;
   *qdy = pdy.desc;
-  if (launch_gemm(dgrad, s) != hipSuccess) return NVFP4_ERR_HIP;
-  return launch_gemm(wgrad, s) == hipSuccess ? NVFP4_OK : NVFP4_ERR_HIP;
+  return launch_gemm_pair(dgrad, wgrad, s) == hipSuccess ? NVFP4_OK : NVFP4_ERR_HIP;
 }
 
 int nvfp4_dequantize(const nvfp4_qtensor* q, int which_copy, int undo_rht, void* out, int out_dtype,

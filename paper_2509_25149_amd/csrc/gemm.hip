@@ -406,14 +406,26 @@ static GemmPlan plan_route(const GemmArgs& g) {
   return plan;
 }
 
-hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) {
-  const GemmPlan p = plan_route(g);
+static hipError_t launch_planned(const GemmArgs& g, const GemmPlan& p, hipStream_t s) {
   switch (p.route) {
     case kTwoPass: return launch_gemm_two_pass(g, p.two_pass, s);
     case kFused256: return launch_fused256(g, s);
     case kTile128: return launch_tile128(g, s);
     default: return launch_gemm_direct(g, p.direct.shape, s);
   }
+}
+
+hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) { return launch_planned(g, plan_route(g), s); }
+
+static bool pairs(const GemmArgs& g, const GemmPlan& p, const GemmArgs& h, const GemmPlan& q) {
+  return p.route == kDirect && q.route == kDirect && direct_pair_fits(g, p.direct.shape, h, q.direct.shape);
+}
+
+hipError_t launch_gemm_pair(const GemmArgs& g, const GemmArgs& h, hipStream_t s) {
+  const GemmPlan p = plan_route(g), q = plan_route(h);
+  if (pairs(g, p, h, q)) return launch_gemm_direct_pair(g, p.direct.shape, h, q.direct.shape, s);
+  const hipError_t e = launch_planned(g, p, s);
+  return e == hipSuccess ? launch_planned(h, q, s) : e;
 }
 
 }  // namespace nvfp4
@@ -459,6 +471,23 @@ extern "C" int nvfp4_internal_two_pass_tile(int64_t M, int64_t N, int64_t K, int
   out[0] = 32 * p.two_pass.mb;
   out[1] = 32 * p.two_pass.nb;
   return 1;
+}
+
+// Likewise: whether a backward pass of these sizes runs its two products in one launch.
+extern "C" int nvfp4_internal_backward_pairs(int64_t tokens, int64_t d_in, int64_t d_out, size_t workspace_bytes) {
+  using namespace nvfp4;
+  const uint8_t* const some = reinterpret_cast<const uint8_t*>(uintptr_t{4096});
+  auto product = [&](int64_t M, int64_t N, int64_t K) {
+    GemmArgs g{};
+    g.a = Operand{some, some, nullptr, M};
+    g.b = Operand{some, some, nullptr, N};
+    g.K = K;
+    g.workspace = workspace_bytes ? const_cast<uint8_t*>(some) : nullptr;
+    g.workspace_bytes = workspace_bytes;
+    return g;
+  };
+  const GemmArgs dgrad = product(tokens, d_in, d_out), wgrad = product(d_in, d_out, tokens);
+  return pairs(dgrad, plan_route(dgrad), wgrad, plan_route(wgrad));
 }
 
 // Likewise: {MB, NB, WK, steps} of the direct kernel's shape of this number; 0: there is none.

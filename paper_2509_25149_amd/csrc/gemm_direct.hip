@@ -99,9 +99,10 @@ struct Shape {
   static constexpr int kLdsBytes = kWaves * kWaveBytes;
 };
 
-template <int MB, int NB, int WK, int Steps, bool kBf16Out>
-__global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, MB * NB > 16 ? 1 : 2) void gemm_direct_kernel(
-    Operand A, Operand B, int K, void* __restrict__ Dv, int64_t ldd, bool accumulate, int tiles_m, int tiles_n) {
+// Tile number pid of a product of tiles_m x tiles_n of them.  bf16_out: the output type, a constant where a kernel serves one.
+template <int MB, int NB, int WK, int Steps>
+__device__ __forceinline__ void direct_tile(const Operand& A, const Operand& B, const int K, void* __restrict__ Dv, const int64_t ldd, const bool accumulate,
+                                            const bool bf16_out, const int tiles_m, const int tiles_n, int pid) {
   using S = Shape<MB, NB, WK, Steps>;
   constexpr int kSteps = Steps, kWindowK = S::kWindowK, kCodeBytes = S::kCodeBytes, kScaleBytes = S::kScaleBytes;
   constexpr int kChunks = 4 * kSteps, kLoadRows = 64 / kChunks, kRowBytes = 16 * kChunks;   // of a row of a window; rows that a load instruction covers
@@ -109,7 +110,6 @@ __global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, MB * NB > 16 ? 1 : 2) void
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6), wk = WK == 1 ? 0 : wave;
   const int num_tiles = tiles_m * tiles_n;
-  int pid = blockIdx.x;
   if ((num_tiles & 7) == 0) pid = (pid & 7) * (num_tiles >> 3) + (pid >> 3);
   int tm, tn;
   tile_coordinates(pid, tiles_m, tiles_n, tm, tn);
@@ -350,7 +350,7 @@ __global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, MB * NB > 16 ? 1 : 2) void
     const uint32_t m = m0 + i * 16 + l16, n = n0 + j * 16 + q * 4;
     if (m < M && n < N) {
       v *= scale4(ts, out_scale, vec, true, m, n);
-      if (kBf16Out) {
+      if (bf16_out) {
         uint2 o;
         o.x = f32x2_to_bf16(v[0], v[1]);
         o.y = f32x2_to_bf16(v[2], v[3]);
@@ -381,6 +381,33 @@ __global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, MB * NB > 16 ? 1 : 2) void
       store(v, f / NB, f % NB);
     }
   }
+}
+
+template <int MB, int NB, int WK, int Steps, bool kBf16Out>
+__global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, MB * NB > 16 ? 1 : 2) void gemm_direct_kernel(
+    Operand A, Operand B, int K, void* __restrict__ Dv, int64_t ldd, bool accumulate, int tiles_m, int tiles_n) {
+  direct_tile<MB, NB, WK, Steps>(A, B, K, Dv, ldd, accumulate, kBf16Out, tiles_m, tiles_n, static_cast<int>(blockIdx.x));
+}
+
+// Two products that do not depend on each other in one launch (a layer's Dgrad and Wgrad): the first `tiles` workgroups take the first one's tiles.  Apart, a small layer's
+// products leave the chip half empty one after the other: 1040 x 2064 x 1296 has 731 tiles for 512 places, 2064 x 1296 x 1040 187.  Each is worked
+// exactly as by a launch of its own.  The shapes are those of which two workgroups of four wavefronts fit a CU.  Backward calls (quantizer included), us, apart / in one launch:
+// tokens x d_in x d_out 1040 x 2064 x 1296 42.0 / 37.1, 416 x 1280 x 512 16.8 / 13.7, 240 x 2304 x 16384 94.5 / 82.3, 8064 x 1024 x 1024 69.4 / 65.0; geometric mean
+// over 100 sizes 1.09, the worst 3408 x 960 x 6768 197 / 206.  The product with the shorter wavefronts first: 1.07.
+struct DirectProduct {
+  Operand a, b;
+  void* d;
+  int64_t ldd;
+  int K, tiles_m, tiles_n, shape;   // shape: 0 64 x 64 and 1 64 x 48 with K split, 2 64 x 64 to each wavefront
+  bool accumulate, bf16_out;
+};
+__global__ __launch_bounds__(256, 2) void gemm_direct_pair_kernel(DirectProduct first, DirectProduct second) {
+  const int tiles = first.tiles_m * first.tiles_n, id = static_cast<int>(blockIdx.x);
+  const DirectProduct& p = id < tiles ? first : second;
+  const int pid = id < tiles ? id : id - tiles;
+  if (p.shape == 0) direct_tile<4, 4, 4, 1>(p.a, p.b, p.K, p.d, p.ldd, p.accumulate, p.bf16_out, p.tiles_m, p.tiles_n, pid);
+  else if (p.shape == 1) direct_tile<4, 3, 4, 1>(p.a, p.b, p.K, p.d, p.ldd, p.accumulate, p.bf16_out, p.tiles_m, p.tiles_n, pid);
+  else direct_tile<4, 4, 1, 1>(p.a, p.b, p.K, p.d, p.ldd, p.accumulate, p.bf16_out, p.tiles_m, p.tiles_n, pid);
 }
 
 }  // namespace
@@ -431,6 +458,12 @@ static bool fits(int64_t M, int64_t N, int64_t K) {
   return M <= 0x7fffffff && N <= 0x7fffffff && K <= (int64_t{1} << 27) && (d.steps == 1 || K >= 128 * d.steps) &&
          direct_tiles<I>(M, N) * (d.wk == 1 ? 256 : d.wk * 64) <= 0xffffffff;
 }
+
+template <int... I>
+static int64_t tiles_of(const GemmArgs& g, int shape, std::integer_sequence<int, I...>) {
+  return ((shape == I ? direct_tiles<I>(g.a.outer, g.b.outer) : 0) + ...);
+}
+static int64_t tiles_of(const GemmArgs& g, int shape) { return tiles_of(g, shape, AllShapes{}); }
 
 // Steps (128 k) of the wavefront that has most of them.  A rest that is worked in pieces counts half a step more than its k.
 template <int I>
@@ -501,6 +534,41 @@ static bool fits_shape(const GemmArgs& g, int shape, std::integer_sequence<int, 
 }
 
 bool direct_shape_fits(const GemmArgs& g, int shape) { return fits_shape(g, shape, AllShapes{}); }
+
+// The pair kernel's number of a shape, or -1.
+static int pair_shape(int shape) {
+  const DirectShape& d = kDirectShapes[shape];
+  if (d.mb != 4 || d.steps != 1) return -1;
+  if (d.wk == 4) return d.nb == 4 ? 0 : d.nb == 3 ? 1 : -1;
+  return d.wk == 1 && d.nb == 4 ? 2 : -1;
+}
+
+bool direct_pair_fits(const GemmArgs& g, int shape, const GemmArgs& h, int shape2) {
+  if (pair_shape(shape) < 0 || pair_shape(shape2) < 0 || !direct_shape_fits(g, shape) || !direct_shape_fits(h, shape2)) return false;
+  return tiles_of(g, shape) + tiles_of(h, shape2) <= 0xffffffff / 256;   // threads of a launch
+}
+
+// The product whose wavefronts run longer goes first, so that the other's fill the places that it leaves.
+hipError_t launch_gemm_direct_pair(const GemmArgs& g, int shape, const GemmArgs& h, int shape2, hipStream_t s) {
+  if (!direct_pair_fits(g, shape, h, shape2)) return hipErrorInvalidValue;
+  auto product = [](const GemmArgs& x, int sh) {
+    const DirectShape& d = kDirectShapes[sh];
+    const int tm = d.mb * (d.wk == 1 ? 32 : 16), tn = d.nb * (d.wk == 1 ? 32 : 16);
+    return DirectProduct{x.a, x.b, x.d, x.ldd, static_cast<int>(x.K), static_cast<int>((x.a.outer + tm - 1) / tm), static_cast<int>((x.b.outer + tn - 1) / tn),
+                         pair_shape(sh), x.accumulate, x.out_bf16};
+  };
+  auto length = [](const GemmArgs& x, int sh) { return x.K / kDirectShapes[sh].wk * kDirectShapes[sh].nb; };
+  DirectProduct first = product(g, shape), second = product(h, shape2);
+  if (length(h, shape2) > length(g, shape)) std::swap(first, second);
+  constexpr int lds = Shape<4, 4, 4, 1>::kLdsBytes;   // the most of the three
+  static_assert(lds >= Shape<4, 3, 4, 1>::kLdsBytes && lds >= Shape<4, 4, 1, 1>::kLdsBytes, "");
+  static PerDeviceOnce once;
+  const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&gemm_direct_pair_kernel), lds, once);
+  if (e != hipSuccess) return e;
+  const unsigned tiles = static_cast<unsigned>(first.tiles_m * first.tiles_n) + static_cast<unsigned>(second.tiles_m * second.tiles_n);
+  hipLaunchKernelGGL(gemm_direct_pair_kernel, dim3(tiles), dim3(256), lds, s, first, second);
+  return hipGetLastError();
+}
 
 hipError_t launch_gemm_direct(const GemmArgs& g, int shape, hipStream_t s) {
   if (!direct_shape_fits(g, shape)) return hipErrorInvalidValue;

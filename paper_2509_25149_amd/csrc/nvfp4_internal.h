@@ -86,6 +86,8 @@ struct GemmArgs {
   size_t workspace_bytes;
 };
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
+// Two products neither of which reads what the other writes; each as by launch_gemm, in one launch where both are small (see gemm_direct_pair_kernel).
+hipError_t launch_gemm_pair(const GemmArgs& g, const GemmArgs& h, hipStream_t s);
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);
 // What the two-pass route does with a product: in tiles of 256 rows, 32-column units of its tile, how many tiles of the last round are split along K over
 // how many workgroups; the tile that it takes, 32 mb x 32 nb -- that one, or a larger one (nothing is split then); what it is expected to take; usable: shape, alignment and workspace allow it.
@@ -99,6 +101,8 @@ TwoPassPlan plan_two_pass(const GemmArgs& g);
 hipError_t launch_gemm_two_pass(const GemmArgs& g, const TwoPassPlan& plan, hipStream_t s);
 // Straight from the packed codes, without scratch, any K.  `shape`: number of a tile shape, see gemm_direct.hip.
 hipError_t launch_gemm_direct(const GemmArgs& g, int shape, hipStream_t s);
+bool direct_pair_fits(const GemmArgs& g, int shape, const GemmArgs& h, int shape2);
+hipError_t launch_gemm_direct_pair(const GemmArgs& g, int shape, const GemmArgs& h, int shape2, hipStream_t s);
 struct DirectPick {
   int shape, kind;       // its number in the kernel's list; the kind of tile (see there)
   double loop;           // us, expected (see SmallTileCost)
