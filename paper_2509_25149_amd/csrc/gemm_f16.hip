@@ -560,10 +560,11 @@ static double rounds_of(int64_t tiles) { return static_cast<double>((tiles + kCU
 // (320 x 320 with a scale per row: the output stage has too few registers for the scales.)
 struct Tile {
   int mb, nb;
-  double us;
+  double gain;   // time in it over that in the tile of 256 rows
 };
 static Tile pick_tile(int64_t M, int64_t N, int64_t K, const Width& w, const TailPlan& tail, bool row_scales) {
-  Tile best{8, w.nb, HUGE_VAL};
+  Tile best{8, w.nb, 1.0};
+  double base = 0.0;   // (the tile of 256 rows comes first)
   for (const TileTime& t : kTileTimes) {
     const int64_t tiles = ((M + 32 * t.mb - 1) / (32 * t.mb)) * ((N + 32 * t.nb - 1) / (32 * t.nb));
     double rounds = rounds_of(tiles);
@@ -574,7 +575,8 @@ static Tile pick_tile(int64_t M, int64_t N, int64_t K, const Width& w, const Tai
       continue;
     }
     const double us = tile_us(t, tiles, rounds, K);
-    if (us < best.us) best = Tile{t.mb, t.nb, us};
+    if (t.nb <= 8) base = us;
+    else if (us < best.gain * base) best = Tile{t.mb, t.nb, us / base};
   }
   return best;
 }
@@ -596,7 +598,11 @@ size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) {
 
 // What a call does: one answer for the estimate, the room asked of the workspace and the launch.  The partial tiles of a split
 // count only where tiles are 256 columns wide, and a workspace without room for them makes the last round an ordinary one.
-// Expected time: what is still to decode (codes and scales in, FP16 out) at 5.0 TB/s, then the tiles -- of a plain result, for all output types (see SmallTileCost).
+// Expected time: what is still to decode (codes and scales in, FP16 out) at 5.0 TB/s, then rounds of 256 tiles at 9.2 us for the result and 15.9 ns
+// per k while there are fewer, 18.6 when the chip is full (the clock drops with the matrix pipes busy), times what a larger tile gains, where the contraction is more of the
+// work than storing the result (4112 x 4368 x 128: 256 x 320 tiles take 0.98 of the best others' time, by fewer rounds 0.8) -- of a plain result,
+// for all output types (see SmallTileCost).  It is what the choice among the kernels is fitted with; estimates nearer to the measured times of this route took it where the
+// direct kernel is up to 20 % faster (18.8 us for this product, 22.6 here).
 TwoPassPlan plan_two_pass(const GemmArgs& g) {
   TwoPassPlan plan{false, HUGE_VAL, 8, 0, 1, 8, 8};
   const int64_t M = g.a.outer, N = g.b.outer;
@@ -608,7 +614,8 @@ TwoPassPlan plan_two_pass(const GemmArgs& g) {
   if (operands + partial_bytes(tail) > g.workspace_bytes) tail = TailPlan{0, 1};
   Width w = pick_width(M, N, tail, false);
   const Tile t = pick_tile(M, N, g.K, w, tail, g.a.ts_per_row != 0 || g.b.ts_per_row != 0);
-  plan.us = 7.4 + static_cast<double>(rows) * static_cast<double>(g.K) * 2.5625 / 5.0e6 + t.us;
+  plan.us = 7.4 + static_cast<double>(rows) * static_cast<double>(g.K) * 2.5625 / 5.0e6 +
+            w.rounds * (9.2 + static_cast<double>(g.K) * (w.tiles >= kCUs ? 0.0186 : 0.0159)) * (g.K > 1024 ? t.gain : 1.0);
   if (g.accumulate && g.K < 1024) w = pick_width(M, N, tail, true);
   if (w.nb != 8) tail = TailPlan{0, 1};
   plan.units = w.nb;

@@ -8,6 +8,7 @@ import torch
 
 import oracle
 from paper_2509_25149_amd import binding as nv, synth
+from test_gemm_routes import plan
 from test_gpu_parity import GEMM_TOL, to_dev
 
 pytestmark = pytest.mark.gpu
@@ -21,10 +22,10 @@ def tile(M, N, K, per_row):
 
 
 @pytest.mark.parametrize("M,N,K,per_row,takes", [
-    (3088, 6176, 256, False, (320, 320)), (4112, 9664, 256, False, (320, 320)), (2096, 19184, 320, False, (320, 320)),
-    (1216, 13152, 256, False, (256, 320)), (6656, 5024, 256, False, (256, 320)), (6656, 5024, 320, True, (256, 320)),
-    (2336, 11792, 256, False, (256, 256)), (2208, 5504, 256, False, (256, 224)), (2592, 9504, 256, False, (256, 224)),
-    (1936, 11664, 256, False, (256, 192)), (3872, 12704, 320, False, (256, 160))])
+    (1488, 13584, 256, False, (320, 320)), (4112, 9664, 256, False, (320, 320)), (2096, 19184, 320, False, (320, 320)),
+    (1456, 10960, 320, False, (256, 320)), (6656, 5024, 256, False, (256, 320)), (6656, 5024, 320, True, (256, 320)),
+    (1808, 15536, 256, False, (256, 256)), (3088, 3904, 320, False, (256, 224)), (2592, 9504, 256, False, (256, 224)),
+    (1664, 13584, 320, False, (256, 192)), (3872, 12704, 320, False, (256, 160))])
 def test_every_tile(M, N, K, per_row, takes):
     assert tile(M, N, K, per_row) == takes
     xb, wb = synth.normal_with_outliers(M, K, 1.0, 7400 + K, frac=0.01), synth.normal(N, K, 0.02, 7500 + N)
@@ -44,3 +45,21 @@ def test_every_tile(M, N, K, per_row, takes):
     acc = buf[:, :N].clone()
     nv.nvfp4_gemm(qx, qw, nv.OP_DGRAD, nv.OUT_F32_ACCUMULATE, out=acc, workspace=ws)
     assert torch.equal(acc, buf[:, :N] + buf[:, :N])
+
+
+@pytest.mark.parametrize("M,N,K,per_row,splits", [(2896, 8096, 1024, False, 2), (2896, 8096, 1024, True, 2), (2592, 18240, 2112, False, 4),
+                                                  (5088, 4032, 2048, True, 4), (3376, 9248, 4096, False, 8), (3376, 9248, 4096, True, 8)])
+def test_split_last_round(M, N, K, per_row, splits):
+    """256 x 256 tiles whose last round is split along K: against the kernel that a call without scratch takes, which sums in another order."""
+    assert tile(M, N, K, per_row) == (256, 256) and plan(M, N, K, workspace=True)[3] == splits and plan(M, N, K)[0] != 0
+    xb, wb = synth.normal_with_outliers(M, K, 1.0, 7600 + K, frac=0.01), synth.normal(N, K, 0.02, 7700 + N)
+    qx = nv.nvfp4_quantize(to_dev(xb), nv.LAYOUT_ROW | (nv.LAYOUT_ROW_SCALES if per_row else 0))
+    qw = nv.nvfp4_quantize(to_dev(wb), nv.LAYOUT_ROW)
+    ws = torch.empty(nv.gemm_workspace_bytes(M, N, K), dtype=torch.uint8, device="cuda")
+    buf = torch.full((M, N + 16), 7.0, dtype=torch.float32, device="cuda")
+    nv.nvfp4_gemm(qx, qw, nv.OP_DGRAD, out=buf[:, :N], workspace=ws)
+    ref = nv.nvfp4_gemm(qx, qw, nv.OP_DGRAD).double()
+    assert torch.all(buf[:, N:] == 7.0)
+    # two FP32 sums of K / 32 steps each: sqrt(K / 32) 2^-24 of the result twice, 1.4e-6 at the most
+    assert (buf[:, :N].double() - ref).norm() <= 3e-6 * ref.norm()
+    assert torch.equal(nv.nvfp4_gemm(qx, qw, nv.OP_DGRAD, nv.OUT_BF16, workspace=ws), buf[:, :N].to(torch.bfloat16))
