@@ -321,7 +321,7 @@ uint32_t nvfp4_rht_sign_mask(uint64_t rht_seed);
  * [1] FP32->E2M1 SR over a grid of values x all 2^16 random values (the plain
  * and the accumulating form of the conversion),
  * [2] FP32->E4M3 (and back) over all non-negative finite patterns,
- * [3] the division-free x/6 against IEEE division over the same patterns,
+ * [3] the division-free x/6, and the MXFP4 block scale without one, against IEEE division over the same patterns,
  * [4] FP32->bf16 (the GEMM and dequantize outputs) over all finite patterns.
  * Asynchronous like every other call.
  */

@@ -88,6 +88,17 @@ __device__ __forceinline__ half2v e4m3_decode_f16x2(uint32_t code) {
 // wavefront-wide branch to it cut the row and column passes of a patch into 24 pieces that could not overlap.)
 __device__ __forceinline__ float div_by_6(float x) { return static_cast<float>(static_cast<double>(x) * (1.0 / 6.0)); }
 
+// MXFP4: fl(amax_b / 6) rounded up to a power of two 2^e, e clamped to [-127, 127] (App. B.4): the stored byte e + 127.  The rounded quotient is at most 2^e exactly
+// where amax_b is at most 1.5 x 2^(e + 2), so the byte is amax_b's exponent, one more where its significand exceeds 1.5, less 2.  (Two inputs are
+// exceptions, by comparison over all patterns (the self-test): one whose quotient rounds down to the subnormal 2^-127, and infinity.)
+__device__ __forceinline__ uint32_t ue8m0_scale(float amax_b) {
+  const uint32_t bits = __float_as_uint(amax_b);
+  const uint32_t up = bits >= 0x7F800000u ? 256u : (bits - (bits == 0x01400001u) + 0x3FFFFFu) >> 23;
+  return max(up, 2u) - 2u;
+}
+// 2^e as the conversions' scale operand: they look at the exponent field alone, so 2^-127 need not be the subnormal number.
+__device__ __forceinline__ float conversion_scale(uint32_t byte) { return __uint_as_float(byte << 23); }
+
 // Stored block scale and the "real" block encode scale (App. B.2):
 //   code    = e4m3(amax_b / 6 * s_enc)
 //   s_enc_b = 1 / (fp32(code) * s_dec), 0 when the stored scale is 0.
@@ -98,12 +109,21 @@ __device__ __forceinline__ float block_scale(float amax_b, float s_enc, float s_
   return den == 0.0f ? 0.0f : 1.0f / den;
 }
 
-// Two scaled values -> one byte of two E2M1 codes written into byte `kSel`
+// A register whose bits mean nothing yet: the conversions below write it byte by byte, so nothing has to be put into it first.  No instruction.
+// (`near`: any value that is at hand; two such words with the same would be one to the compiler, with a move for the copy.)
+__device__ __forceinline__ uint32_t any_word(float near) {
+  uint32_t w;
+  asm("" : "=v"(w) : "v"(near));
+  return w;
+}
+
+// Two scaled values, divided by `scale`, -> one byte of two E2M1 codes written into byte `kSel`
 // of `old` (round to nearest even, saturating; matches the tie rule "even
-// code").  The instruction's scale operand divides by a power of two only: kDiv = 1, 2 or 4.
-template <int kSel, int kDiv = 1>
-__device__ __forceinline__ uint32_t cvt_rne_pair(uint32_t old, float v0, float v1) {
-  return __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(old, v0, v1, static_cast<float>(kDiv), kSel);
+// code").  The instruction divides by a power of two, exactly: of its scale operand only the exponent field e counts, as 2^(e - 127), e = 0 included (checked
+// for all 255 fields against products with the exact factor, subnormal values too).
+template <int kSel>
+__device__ __forceinline__ uint32_t cvt_rne_pair(uint32_t old, float v0, float v1, float scale = 1.0f) {
+  return __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(old, v0, v1, scale, kSel);
 }
 
 // Stochastic rounding of one value with a 16-bit random integer placed in the
@@ -124,7 +144,7 @@ __device__ __forceinline__ uint32_t cvt_sr_single(float v, uint32_t rand_hi16) {
 
 // The same conversion written into byte kSel of `acc`, the other three bytes kept: the instruction only writes the byte
 // it is told to, but the builtin does not say so to the compiler (see above), so the accumulating form is spelled in
-// assembly with the destination tied.  Four of these fill a dword without any merging.  The value is divided by kDiv = 1, 2 or 4.
+// assembly with the destination tied.  Four of these fill a dword without any merging.  The value is divided by kDiv = 1, 2 or 4, or by `scale` as above.
 template <int kSel, int kDiv = 1>
 __device__ __forceinline__ void cvt_sr_single_into(uint32_t& acc, float v, uint32_t rand_hi16) {
   float2v p;   // the pair's second value is never looked at
@@ -135,6 +155,12 @@ __device__ __forceinline__ void cvt_sr_single_into(uint32_t& acc, float v, uint3
   else if constexpr (kDiv == 2) NVFP4_CVT_SR("2.0");
   else NVFP4_CVT_SR("1.0");
 #undef NVFP4_CVT_SR
+}
+template <int kSel>
+__device__ __forceinline__ void cvt_sr_single_into(uint32_t& acc, float v, uint32_t rand_hi16, float scale) {
+  float2v p;
+  p.x = v;
+  asm("v_cvt_scalef32_sr_pk_fp4_f32 %0, %1, %2, %3 op_sel:[0,0,%4,%5]" : "+v"(acc) : "v"(p), "v"(rand_hi16), "v"(scale), "n"(kSel & 1), "n"(kSel >> 1));
 }
 
 // (a & mask) | (b & ~mask) in one v_bitop3_b32 (truth table: the expression evaluated on

@@ -33,39 +33,26 @@ constexpr int kThreads = 256;
 constexpr int kTileCols = 256, kTileRows = 128;
 constexpr int kSlot = 33;   // column octets per staging row, padded
 
-// amax_b / 6 rounded up to a power of two 2^e, e clamped to [-127, 127] (App. B.4).
-// Returns the stored byte e + 127 and the exact encode factor 2^-e.
-__device__ __forceinline__ uint32_t ue8m0_scale(float amax_b, float& inv) {
-  const uint32_t bits = __float_as_uint(div_by_6(amax_b));
-  const int E = static_cast<int>(bits >> 23), M = static_cast<int>(bits & 0x7FFFFFu);
-  int e;
-  if (E > 0) e = E - 127 + (M != 0 ? 1 : 0);
-  else e = M > 0x400000 ? -126 : -127;   // subnormal quotient (or zero)
-  e = min(e, 127);
-  inv = __uint_as_float(e == 127 ? 0x00400000u : static_cast<uint32_t>(127 - e) << 23);
-  return static_cast<uint32_t>(e + 127);
-}
-
-// Eight values -> one dword of eight codes (value t in nibble t).
+// Eight values, divided by the power of two `scale` -> one dword of eight codes (value t in nibble t).  The division is the conversion's own: one multiplication per value less.
 template <bool kSR>
-__device__ __forceinline__ uint32_t encode8(const float v[8], const uint32_t draws_hi16[8]) {
+__device__ __forceinline__ uint32_t encode8(const float v[8], float scale, const uint32_t draws_hi16[8]) {
   if (!kSR) {
-    uint32_t d = 0;
-    d = cvt_rne_pair<0>(d, v[0], v[1]);
-    d = cvt_rne_pair<1>(d, v[2], v[3]);
-    d = cvt_rne_pair<2>(d, v[4], v[5]);
-    d = cvt_rne_pair<3>(d, v[6], v[7]);
+    uint32_t d = any_word(v[0]);
+    d = cvt_rne_pair<0>(d, v[0], v[1], scale);
+    d = cvt_rne_pair<1>(d, v[2], v[3], scale);
+    d = cvt_rne_pair<2>(d, v[4], v[5], scale);
+    d = cvt_rne_pair<3>(d, v[6], v[7], scale);
     return d;
   } else {
-    uint32_t e = 0u, o = 0u;
-    cvt_sr_single_into<0>(e, v[0], draws_hi16[0]);
-    cvt_sr_single_into<1>(e, v[2], draws_hi16[2]);
-    cvt_sr_single_into<2>(e, v[4], draws_hi16[4]);
-    cvt_sr_single_into<3>(e, v[6], draws_hi16[6]);
-    cvt_sr_single_into<0>(o, v[1], draws_hi16[1]);
-    cvt_sr_single_into<1>(o, v[3], draws_hi16[3]);
-    cvt_sr_single_into<2>(o, v[5], draws_hi16[5]);
-    cvt_sr_single_into<3>(o, v[7], draws_hi16[7]);
+    uint32_t e = any_word(v[0]), o = any_word(v[1]);
+    cvt_sr_single_into<0>(e, v[0], draws_hi16[0], scale);
+    cvt_sr_single_into<1>(e, v[2], draws_hi16[2], scale);
+    cvt_sr_single_into<2>(e, v[4], draws_hi16[4], scale);
+    cvt_sr_single_into<3>(e, v[6], draws_hi16[6], scale);
+    cvt_sr_single_into<0>(o, v[1], draws_hi16[1], scale);
+    cvt_sr_single_into<1>(o, v[3], draws_hi16[3], scale);
+    cvt_sr_single_into<2>(o, v[5], draws_hi16[5], scale);
+    cvt_sr_single_into<3>(o, v[7], draws_hi16[7], scale);
     return interleave_nibbles(e, o);
   }
 }
@@ -137,13 +124,10 @@ __global__ __launch_bounds__(kThreads, 4) void quantize_mx_kernel(const uint16_t
       for (int c = 0; c < 8; ++c) m = fmaxf(m, fabsf(v[c]));
       m = fmaxf(m, lane_xor1(m));   // a 32-column block is four neighbouring lanes
       m = fmaxf(m, lane_xor2(m));
-      float inv;
-      const uint32_t sc = ue8m0_scale(m, inv);
-#pragma unroll
-      for (int c = 0; c < 8; ++c) v[c] *= inv;
+      const uint32_t sc = ue8m0_scale(m);
       uint32_t dr[8] = {0, 0, 0, 0, 0, 0, 0, 0};
       if (kSR) draws8(static_cast<uint32_t>(col0 >> 3), static_cast<uint32_t>(row0 + r), 0u, key0, key1, dr);
-      const uint32_t codes = encode8<kSR>(v, dr);
+      const uint32_t codes = encode8<kSR>(v, conversion_scale(sc), dr);
       if (active) {
         *reinterpret_cast<uint32_t*>(row_codes + (row0 + r) * (cols / 2) + col0 / 2) = codes;
         if ((lane & 3) == 0) st_row_scales[(row_in + r) * 8 + (l32 >> 2)] = static_cast<uint8_t>(sc);
@@ -198,18 +182,17 @@ __global__ __launch_bounds__(kThreads, 4) void quantize_mx_kernel(const uint16_t
 #pragma unroll
       for (int r = 0; r < 16; ++r) m = fmaxf(m, fabsf(w[r]));
       m = max_of_halves(m);
-      float inv;
-      const uint32_t sc = ue8m0_scale(m, inv);
+      const uint32_t sc = ue8m0_scale(m);
       uint2 out;
 #pragma unroll
       for (int g = 0; g < 2; ++g) {   // eight consecutive rows each: groups half and half + 2 of the block's four, unrotated 2 half and 2 half + 1
         float v[8];
 #pragma unroll
-        for (int t = 0; t < 8; ++t) v[t] = w[8 * g + t] * inv;
+        for (int t = 0; t < 8; ++t) v[t] = w[8 * g + t];
         uint32_t dr[8] = {0, 0, 0, 0, 0, 0, 0, 0};
         const int group = kRht ? half + 2 * g : 2 * half + g;
         if (kSR) draws8(static_cast<uint32_t>((rowblk >> 3) + wave * 4 + group), static_cast<uint32_t>(col0 + c), 1u, key0, key1, dr);
-        (g ? out.y : out.x) = encode8<kSR>(v, dr);
+        (g ? out.y : out.x) = encode8<kSR>(v, conversion_scale(sc), dr);
       }
       *reinterpret_cast<uint2*>(st_col_codes + ((c * 4 + wave) * kSlot + l32) * 16 + half * 8) = out;
       if (half == 0) st_col_scales[(c * 4 + wave) * 32 + l32] = static_cast<uint8_t>(sc);

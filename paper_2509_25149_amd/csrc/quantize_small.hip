@@ -220,7 +220,7 @@ __global__ __launch_bounds__(kThreads) void cast_small_kernel(
           } else {
             const float* u = v[c] + 8 * h;
             auto d = [&](int t) { return c ? draws[8 * h + t] & 0xFFFF0000u : draws[8 * h + t] << 16; };
-            uint32_t e = 0u, o = 0u;
+            uint32_t e = any_word(u[0]), o = any_word(u[1]);
             cvt_sr_single_into<0, kDiv>(e, u[0], d(0));
             cvt_sr_single_into<1, kDiv>(e, u[2], d(2));
             cvt_sr_single_into<2, kDiv>(e, u[4], d(4));

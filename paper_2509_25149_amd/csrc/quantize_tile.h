@@ -152,22 +152,22 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t m) {
 template <bool kSR, int kDiv = 1>
 __device__ __forceinline__ uint32_t encode8(const float v[8], const uint32_t rnd[4]) {
   if (!kSR) {
-    uint32_t d = 0;
-    d = cvt_rne_pair<0, kDiv>(d, v[0], v[1]);
-    d = cvt_rne_pair<1, kDiv>(d, v[2], v[3]);
-    d = cvt_rne_pair<2, kDiv>(d, v[4], v[5]);
-    d = cvt_rne_pair<3, kDiv>(d, v[6], v[7]);
+    uint32_t d = any_word(v[0]);
+    d = cvt_rne_pair<0>(d, v[0], v[1], kDiv);
+    d = cvt_rne_pair<1>(d, v[2], v[3], kDiv);
+    d = cvt_rne_pair<2>(d, v[4], v[5], kDiv);
+    d = cvt_rne_pair<3>(d, v[6], v[7], kDiv);
     return d;
   } else {
-    uint32_t e = 0u, o = 0u;   // low nibble of byte t: element 2t (e) / 2t + 1 (o)
-    cvt_sr_single_into<0>(e, v[0], rnd[0] << 16);
-    cvt_sr_single_into<1>(e, v[2], rnd[1] << 16);
-    cvt_sr_single_into<2>(e, v[4], rnd[2] << 16);
-    cvt_sr_single_into<3>(e, v[6], rnd[3] << 16);
-    cvt_sr_single_into<0>(o, v[1], rnd[0] & 0xFFFF0000u);
-    cvt_sr_single_into<1>(o, v[3], rnd[1] & 0xFFFF0000u);
-    cvt_sr_single_into<2>(o, v[5], rnd[2] & 0xFFFF0000u);
-    cvt_sr_single_into<3>(o, v[7], rnd[3] & 0xFFFF0000u);
+    uint32_t e = any_word(v[0]), o = any_word(v[1]);   // low nibble of byte t: element 2t (e) / 2t + 1 (o)
+    cvt_sr_single_into<0, kDiv>(e, v[0], rnd[0] << 16);
+    cvt_sr_single_into<1, kDiv>(e, v[2], rnd[1] << 16);
+    cvt_sr_single_into<2, kDiv>(e, v[4], rnd[2] << 16);
+    cvt_sr_single_into<3, kDiv>(e, v[6], rnd[3] << 16);
+    cvt_sr_single_into<0, kDiv>(o, v[1], rnd[0] & 0xFFFF0000u);
+    cvt_sr_single_into<1, kDiv>(o, v[3], rnd[1] & 0xFFFF0000u);
+    cvt_sr_single_into<2, kDiv>(o, v[5], rnd[2] & 0xFFFF0000u);
+    cvt_sr_single_into<3, kDiv>(o, v[7], rnd[3] & 0xFFFF0000u);
     return interleave_nibbles(e, o);
   }
 }
@@ -186,7 +186,7 @@ __device__ __forceinline__ uint32_t encode8_col(const float* v, const uint32_t r
     const uint32_t none[4] = {0, 0, 0, 0};
     return encode8<false, kDiv>(v, none);
   } else {
-    uint32_t e = 0u, o = 0u;
+    uint32_t e = any_word(v[0]), o = any_word(v[1]);
     cvt_sr_single_into<0, kDiv>(e, v[0], draw_hi16(rnd, r0 + 0, c));
     cvt_sr_single_into<1, kDiv>(e, v[2], draw_hi16(rnd, r0 + 2, c));
     cvt_sr_single_into<2, kDiv>(e, v[4], draw_hi16(rnd, r0 + 4, c));

@@ -124,7 +124,11 @@ __global__ __launch_bounds__(256) void selftest_div6_kernel(unsigned long long* 
   const uint64_t stride = static_cast<uint64_t>(gridDim.x) * blockDim.x;
   for (uint64_t w = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x; w < 0x7F800000ull; w += stride) {
     const float x = __uint_as_float(static_cast<uint32_t>(w));
-    local += __float_as_uint(div_by_6(x)) != __float_as_uint(x / 6.0f);
+    const uint32_t q = __float_as_uint(x / 6.0f);
+    local += __float_as_uint(div_by_6(x)) != q;
+    // the MXFP4 scale byte: the quotient rounded up to a power of two, 2^-127 at the least
+    const uint32_t up = q >= 0x00800000u ? (q >> 23) + ((q & 0x7FFFFFu) != 0) : q > 0x400000u;
+    local += ue8m0_scale(x) != up;
   }
   if (local) atomicAdd(bad, local);
 }
