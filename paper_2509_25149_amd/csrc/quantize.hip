@@ -102,7 +102,7 @@ __global__ __launch_bounds__(kThreads) void amax_kernel(const uint16_t* __restri
 enum CastMemory { kCachedLoads = 0, kStreamedLoads = 1, kStreamedLoadsCachedStores = 2 };
 template <int kMemory>
 using CastTile = Staged<8, 32, kMemory != kStreamedLoadsCachedStores>;
-enum { kWalkReverse = 1, kWalkBands = 2 };   // see cast_walk
+enum { kWalkReverse = 1, kWalkBands = 2, kWalkStrips = 4 };   // see cast_walk
 __device__ __forceinline__ float to_scalar(float v) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v))); }
 
 // kMemory: see cast_memory (a template argument because a branch around the patch's loads makes every one of them wait at
@@ -127,11 +127,17 @@ __global__ __launch_bounds__(kThreads, kSR && kRow && kCol && !k2D ? 3 : 2) void
   const int tid = threadIdx.x, lane = tid & (T::kLanes - 1), wave = tid >> 6;
   const int gl = tid / T::kLanes;                // group index inside the tile
   unsigned bx = blockIdx.x, by = blockIdx.y;
-  if (walk & kWalkBands) {
+  if (walk & (kWalkBands | kWalkStrips)) {
     const unsigned id = by * gridDim.x + bx, band = gridDim.x * gridDim.y >> 3;
     const unsigned to = id < band * 8 ? (id & 7) * band + (id >> 3) : id;
-    by = to / gridDim.x;
-    bx = to - by * gridDim.x;
+    if (walk & kWalkStrips) {
+      const unsigned strip = to / (8 * gridDim.y), in = to - strip * (8 * gridDim.y), width = min(8u, gridDim.x - strip * 8);
+      by = width == 8 ? in >> 3 : in / width;
+      bx = strip * 8 + in - by * width;
+    } else {
+      by = to / gridDim.x;
+      bx = to - by * gridDim.x;
+    }
   }
   if (walk & kWalkReverse) {
     bx = gridDim.x - 1 - bx;
@@ -276,6 +282,11 @@ size_t quantize_workspace_bytes(int64_t rows, int64_t cols) {
 // The row copy alone, rows not on 128-byte lines: neighbouring tiles, which share those lines and the border lines of the codes, go to
 // workgroups of one XCD (they are dealt out round robin), an eighth of the grid to each: 5104 x 20464 91 -> 80 us, 8176 x 5104 38.8 -> 35.1,
 // 1920 x 31504 56 -> 50.  With both copies it loses above 200 MB (5104 x 20464 129 -> 137), with few rows too (272 x 131088 36 -> 37).
+// The others in strips of 8 tiles across, walked downwards, an eighth of the sequence to each XCD: a tile leaves 16 bytes of a row's scales, 8 bytes of a column's and
+// 64 of its codes, which fill lines of 128 together with neighbours to the side and below; from workgroups all over the chip each L2 has its part of such a line and writes it
+// by itself (without the scales W took 6 us less, with them as non-temporal stores 9 to 30 more).  W 5120 x 20480 85.8 -> 82.8 us, 5136 x 20496 125 -> 117, X 4096 x 5120
+// 28.5 -> 27.7, dY 8208 x 16400 186 -> 180, the row copy alone 8192 x 20480 122 -> 117; strips of 4 alike, of 16 84.4 for the first.  Not both copies of an aligned tensor above 256 MB,
+// which the cache holds in part, its last rows: X 8192 x 20480 150 -> 159.
 constexpr int64_t kCacheBytes = int64_t{256} << 20;
 static bool lines_aligned(const QuantizeArgs& a) { return a.ld % 64 == 0 && reinterpret_cast<uintptr_t>(a.x) % 128 == 0; }
 static CastMemory cast_memory(const QuantizeArgs& a) {
@@ -287,7 +298,8 @@ static CastMemory cast_memory(const QuantizeArgs& a) {
 static int cast_walk(const QuantizeArgs& a) {
   const bool reverse = a.do_amax && a.rows * a.cols * 2 > kCacheBytes / 2 && cast_memory(a) == kCachedLoads;
   const bool bands = !a.want_col && !lines_aligned(a) && a.rows >= 1024;
-  return (reverse ? kWalkReverse : 0) | (bands ? kWalkBands : 0);
+  const bool strips = !bands && !(a.want_row && a.want_col && lines_aligned(a) && cast_memory(a) != kCachedLoads);
+  return (reverse ? kWalkReverse : 0) | (bands ? kWalkBands : strips ? kWalkStrips : 0);
 }
 
 // Workgroups of the amax pass, at most 512: two to a CU keep enough loads in flight, and every workgroup of the cast pass
@@ -394,7 +406,7 @@ hipError_t launch_quantize(const QuantizeArgs& a, hipStream_t s) {
 }  // namespace nvfp4
 
 // For the tests, not part of the ABI: which kernels nvfp4_quantize takes for a contiguous tensor of these sizes (1x16 or 16x16 blocks, rotation up to 16, one scale
-// per tensor; rotated: the col copy is).  out: cast pass (0 cast_kernel, 1 cast_small_kernel), amax pass (likewise), cast_kernel's walk (kWalkReverse | kWalkBands), sets of its workgroups,
+// per tensor; rotated: the col copy is).  out: cast pass (0 cast_kernel, 1 cast_small_kernel), amax pass (likewise), cast_kernel's walk (kWalkReverse | kWalkBands | kWalkStrips), sets of its workgroups,
 // log2 of amax_kernel's lanes across.
 extern "C" void nvfp4_internal_quantize_plan(int64_t rows, int64_t cols, int want_row, int want_col, int rotated, int block2d, int* out) {
   using namespace nvfp4;
