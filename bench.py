@@ -377,7 +377,7 @@ def matrix_pipe_context(torch, nv, reps: int = 3, iters: int = 100000):
         b.record()
         torch.cuda.synchronize()
         res[f"register_only_mfma_{name}_TFLOPs"] = flops / (a.elapsed_time(b) * 1e-3) / 1e12
-    # the GEMM kernel's register block: 8 x 8 accumulators, one wavefront per SIMD (64 MFMAs per trip: a eighth of the trips)
+    # the GEMM kernel's register block of a 256 x 256 tile: 8 x 8 accumulators, one wavefront per SIMD (64 MFMAs per trip: a eighth of the trips)
     mfma_rate(torch, 2, iters // 80, buf, gemm_block=True)
     a, b = ev(), ev()
     a.record()
@@ -400,7 +400,7 @@ def matrix_pipe_context(torch, nv, reps: int = 3, iters: int = 100000):
     res["vendor_fp16_gemm_fprop_shape_TFLOPs"] = 10 * 2.0 * TOKENS * D_MODEL * D_FFN / (a.elapsed_time(b) * 1e-3) / 1e12
     res["note"] = ("not part of `value`: v_mfma_f32_16x16x32_f16 in a register-only loop (512 workgroups x 4 wavefronts, 16 "
                    "independent accumulators) per operand kind -- the chip is power-limited, the rate depends on the "
-                   "operand bits; the same with the GEMM kernel's register block (256 workgroups x 4 wavefronts, 8 x 8 "
+                   "operand bits; the same with the GEMM kernel's register block of a 256x256 tile (256 workgroups x 4 wavefronts, 8 x 8 "
                    "accumulators: an operand register serves 8 instructions in a row); and torch.matmul FP16 "
                    "[8192,5120]x[5120,20480] on N(0,1) data")
     return res
@@ -596,9 +596,8 @@ def main() -> int:
                      "note": "call time = amax pass + fold + cast pass; one-pass bytes = bf16 read once + both copies written, "
                              "two-pass bytes = the bf16 tensor counted twice (the second read does cross HBM: see traffic)"},
         "dequantize_ms": sum(a.elapsed_time(b) for a, b in deq_events) / len(deq_events),
-        "roofline": {"kernel": "one nvfp4_gemm call = decode_f16_kernel (A, B) + gemm_f16_kernel (256x256 tiles, one "
-                               "workgroup per CU running its tiles as one stream of K steps; for a partial last round of "
-                               "tiles a split-K launch of it + splitk_sum_kernel)",
+        "roofline": {"kernel": "one nvfp4_gemm call = decode_f16_kernel (A, B) + gemm_f16_kernel (tiles of up to 320x320, "
+                               "one workgroup per CU running its tiles as one stream of K steps)",
                      "bound": "mfma", "achieved": gemm_tflops, "peak": PEAK_MFMA_F16_TFLOPS,
                      "unit": "TFLOP/s", "frac": gemm_tflops / PEAK_MFMA_F16_TFLOPS,
                      "traffic": pc.get("gemm_call_traffic_bytes"),

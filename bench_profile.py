@@ -184,7 +184,7 @@ def main() -> int:
                           "see profiles/bench_linear_layer_12B_*.txt for the commands"}
     head = ("bench.py, one NVFP4 linear layer fwd+bwd at the 12B MLP up-projection shape (8192 tokens, 5120 -> 20480), one MI355X;\n"
             "the MXFP4 comparison block of bench.py runs in the same process (gemm_mx_kernel_*, quantize_mx_kernel).\n"
-            "Run from /tmp with TMPDIR=/tmp on the GPU box, R = repository root, P = a scratch directory.  Summarised by bench_profile.py.\n")
+            "Run from /tmp with TMPDIR=/tmp on the GPU machine, R = repository root, P = a scratch directory.  Summarised by bench_profile.py.\n")
 
     if dbs["trace"]:
         rows = kernel_trace(dbs["trace"])
@@ -192,8 +192,8 @@ def main() -> int:
             fh.write("rocprofv3 kernel-trace summary: " + head)
             fh.write("Command:\n  " + COMMANDS["trace"] + "\n")
             fh.write("5 timed steps + 1 warm-up step + the side blocks are all in the counts.  One nvfp4_gemm call = decode_f16_kernel +\n"
-                     "gemm_f16_kernel<bf16 output, per-row scales, false> (+ for the last partial round of tiles, Dgrad and Wgrad:\n"
-                     "gemm_f16_kernel<false, false, true>, which stores split-K partial tiles, and splitk_sum_kernel, which adds them).\n"
+                     "gemm_f16_kernel<bf16 output, per-row scales, split-K partial tiles> tile; a product whose last round of tiles is split has\n"
+                     "a launch of gemm_f16_kernel<false, false, true> and of splitk_sum_kernel, which adds the partial tiles, beside it.\n"
                      "Durations in microseconds; pct = share of all GPU kernel time in the process (input generation included).\n\n")
             fh.write(f"{'calls':>6} {'total_us':>12} {'avg_us':>10} {'min_us':>10} {'max_us':>10} {'pct':>6}  kernel\n")
             for n, k, s, a, mi, ma, pct in rows:

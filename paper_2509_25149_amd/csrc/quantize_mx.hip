@@ -15,9 +15,11 @@
 // the calls by themselves faster -- X 8192 x 5120 47 -> 41 us -- but the GEMM behind them, which reads the codes as they are, slower by
 // more: training step 4096 x 5120 x 5120 289 -> 302 us.)
 // What bounds it: up to one round of workgroups the chain load - rotate - maximum - codes - store of one patch, beyond that memory (8192 x 20480
-// 523 MB in 129 us, 4.1 TB/s) and with stochastic rounding the vector pipe.  A lane used to own all 32 rows of 8 columns (171 - 188 registers, two
+// 523 MB in 126 us, 4.2 TB/s) and with stochastic rounding the vector pipe.  A lane used to own all 32 rows of 8 columns (171 - 188 registers, two
 // wavefronts per SIMD; now 110 - 128 and four), us per call: X 4096 x 5120 28.7 -> 21.4, with stochastic rounding 41.5 -> 28.1; X 8192 x 5120 43.6 -> 34.7,
-// 60.6 -> 47.2; 8192 x 20480 149 -> 129, 198 -> 154; 256 x 512 11.0 -> 7.1, 14.2 -> 9.0.
+// 60.6 -> 47.2; 8192 x 20480 149 -> 129, 198 -> 154; 256 x 512 11.0 -> 7.1, 14.2 -> 9.0.  A block's power of two as the conversions' scale
+// operand instead of a multiplication per value, and its byte from two integer operations: 4096 x 5120 21.0 -> 19.2, 28.6 -> 26.9; 8192 x 20480 133 -> 126,
+// 157 -> 151.
 //
 // Random draws: the row copy uses the NVFP4 draws (counter (j / 8, i, 0, 0)); the
 // col copy draws its own, counter (i / 8, j, 1, 0), word (i % 8) / 2, low half for
