@@ -2,7 +2,7 @@
 """Turns rocprofv3 result databases of bench.py runs into the short text summaries under profiles/ and into
 profiles/measured_counters.json, which bench.py reads back (HBM-side traffic per call, matrix-pipe utilisation).
 
-rocprofv3 is run on the GPU box (from /tmp with TMPDIR=/tmp; R = repository root, P = any scratch directory), one run per counter group, the
+rocprofv3 is run on the GPU machine (from /tmp with TMPDIR=/tmp; R = repository root, P = any scratch directory), one run per counter group, the
 program directly after `--`:
 
   B="python3 $R/bench.py --steps 2 --warmup 1 --no-cpu-baseline --no-layer-calls --no-row-scales --no-rht-sweep --no-context"
@@ -18,7 +18,7 @@ program directly after `--`:
   for c in quantize_x_small forward_small forward_few_tokens forward_row_scales step_ragged step_mx; do
     rocprofv3 --kernel-trace --stats -d $P/case_$c -o case -- python3 $R/bench_profile.py --run-case $c; done
 
-then, anywhere the databases are (they are large; on the GPU box itself is simplest):
+then, anywhere the databases are (they are large; on the GPU machine itself is simplest):
 
   python3 bench_profile.py $P [--out DIR] [--commit ID]     # DIR defaults to profiles/
 
@@ -166,7 +166,7 @@ def main() -> int:
     if argv[:1] == ["--run-case"]:
         return run_case(argv[1])
     commit = git_head()
-    if "--commit" in argv:                            # where the tree is not a git checkout (the GPU box)
+    if "--commit" in argv:                            # where the tree is not a git checkout (the GPU machine)
         i = argv.index("--commit")
         commit = argv[i + 1]
         del argv[i:i + 2]
