@@ -421,9 +421,25 @@ static bool pairs(const GemmArgs& g, const GemmPlan& p, const GemmArgs& h, const
   return p.route == kDirect && q.route == kDirect && direct_pair_fits(g, p.direct.shape, h, q.direct.shape);
 }
 
+// Whether a product's result lies over something that the other one reads or writes; rows further apart than they are long count as a whole.
+static bool writes_over(const GemmArgs& w, const GemmArgs& other) {
+  auto result_bytes = [](const GemmArgs& x) { return ((x.a.outer - 1) * x.ldd + x.b.outer) * (x.out_bf16 ? 2 : 4); };
+  const uintptr_t lo = reinterpret_cast<uintptr_t>(w.d), hi = lo + result_bytes(w);
+  auto meets = [&](const void* p, int64_t bytes) {
+    const uintptr_t at = reinterpret_cast<uintptr_t>(p);
+    return at < hi && lo < at + bytes;
+  };
+  auto meets_operand = [&](const Operand& o) {
+    return meets(o.codes, o.outer * other.K / 2) || meets(o.scales, o.outer * other.K / 16) || meets(o.ts, o.ts_per_row ? o.outer * 8 : 8);
+  };
+  return meets(other.d, result_bytes(other)) || meets_operand(other.a) || meets_operand(other.b);
+}
+
+// In one launch only what does not depend on the order: a caller that keeps one result where the other product's operands or result were gets
+// what two launches leave there.
 hipError_t launch_gemm_pair(const GemmArgs& g, const GemmArgs& h, hipStream_t s) {
   const GemmPlan p = plan_route(g), q = plan_route(h);
-  if (pairs(g, p, h, q)) return launch_gemm_direct_pair(g, p.direct.shape, h, q.direct.shape, s);
+  if (pairs(g, p, h, q) && !writes_over(g, h) && !writes_over(h, g)) return launch_gemm_direct_pair(g, p.direct.shape, h, q.direct.shape, s);
   const hipError_t e = launch_planned(g, p, s);
   return e == hipSuccess ? launch_planned(h, q, s) : e;
 }

@@ -86,7 +86,8 @@ struct GemmArgs {
   size_t workspace_bytes;
 };
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
-// Two products neither of which reads what the other writes; each as by launch_gemm, in one launch where both are small (see gemm_direct_pair_kernel).
+// Two products, each as by launch_gemm and in this order; in one launch where both are small (see gemm_direct_pair_kernel) and neither's result lies over what the other
+// reads or writes.
 hipError_t launch_gemm_pair(const GemmArgs& g, const GemmArgs& h, hipStream_t s);
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);
 // What the two-pass route does with a product: in tiles of 256 rows, 32-column units of its tile, how many tiles of the last round are split along K over

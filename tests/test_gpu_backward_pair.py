@@ -58,3 +58,20 @@ def test_one_launch_replays_from_a_graph():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(dx, want[0]) and torch.equal(dw, want[1])
+
+
+def test_results_over_each_other_or_over_the_weights_codes():
+    """The order of the calls holds where buffers are shared: dW, computed last, over dX; dW over the codes of W that Dgrad reads."""
+    t, d_in, d_out = 1040, 2064, 1296
+    qx, qw, dy, ws = operands(t, d_in, d_out)
+    dw = torch.empty((d_in, d_out), device="cuda")
+    dx, _ = nv.nvfp4_linear_backward(dy, qx, qw, dw, ws, False, 3)
+    shared = torch.zeros((d_in, d_out), device="cuda")
+    over = shared.view(-1).view(torch.bfloat16)[:t * d_in].view(t, d_in)
+    nv.nvfp4_linear_backward(dy, qx, qw, shared, ws, False, 3, dx=over)
+    assert torch.equal(shared, dw)
+    codes = shared.view(-1).view(torch.uint8)[:qw.row_codes.numel()]
+    codes.copy_(qw.row_codes.view(-1))
+    qw.desc.row_codes = codes.data_ptr()
+    dx2, _ = nv.nvfp4_linear_backward(dy, qx, qw, shared, ws, False, 3)
+    assert torch.equal(dx2, dx) and torch.equal(shared, dw)
