@@ -305,6 +305,7 @@ __device__ __forceinline__ void lds_read_frag(int4v& dst, uint32_t addr) {
 // No instruction: the value is used here / comes from here.
 __device__ __forceinline__ void keep(const int4v& f) { asm volatile("" ::"v"(f)); }
 __device__ __forceinline__ void arrived(int4v& f) { asm volatile("" : "+v"(f)); }
+__device__ __forceinline__ void turned(int& scale) { asm volatile("" : "+v"(scale)); }   // what makes it stays ahead of the statements behind this, what uses it behind it
 template <bool kAcc>
 __device__ __forceinline__ void settled(float4v& acc) {
   if constexpr (kAcc) asm volatile("" : "+a"(acc));
@@ -359,10 +360,11 @@ struct Schedule {
     for (int k = 0; k < n; ++k) r += (lower_read_a(k) >= 0) + (lower_read_b(k) >= 0);
     return r;
   }
-  // lower half: the next step's scales are turned in 2 (kA + kB) pieces, one behind each of some MFMAs of the second half of it
-  static constexpr int kTurnFrom = kHalf / 2;
-  static constexpr int turn(int n) { return n >= kTurnFrom ? spread(n - kTurnFrom, 2 * (kA + kB), kHalf - kTurnFrom) : -1; }
-  static_assert(2 * (kA + kB) <= kHalf - kHalf / 2, "a piece of the turn behind each MFMA at the most");
+  // lower half: the next step's scales are turned in 2 (kA + kB) pieces, one behind each of some MFMAs of the second half of it but the last: an MFMA may read a
+  // vector instruction's result two instructions later at the earliest, and the compiler sees no MFMA in the statements that it could keep apart
+  static constexpr int kTurnFrom = kHalf / 2, kTurnPlaces = kHalf - kTurnFrom - 1;
+  static constexpr int turn(int n) { return n >= kTurnFrom && n < kHalf - 1 ? spread(n - kTurnFrom, 2 * (kA + kB), kTurnPlaces) : -1; }
+  static_assert(2 * (kA + kB) <= kTurnPlaces, "a piece of the turn behind each MFMA at the most");
 };
 
 // With more tiles than CUs the host launches one workgroup per CU, which takes tiles blockIdx.x, blockIdx.x +
@@ -501,6 +503,8 @@ __global__ __launch_bounds__(kThreads) void gemm_mx_kernel_k512(Operand A, Opera
       arrived(chunk[decltype(q)::value]);
       scale[decltype(q)::value] = transpose_row(transpose_half(chunk[decltype(q)::value][0], sel_half), sel_row);
     });
+    static_for<0, S::kA + S::kB>([&](auto q) { turned(scale[decltype(q)::value]); });
+    asm volatile("s_nop 1");   // (see Schedule::turn)
     const int next_item = item + static_cast<int>(gridDim.x);
     const bool has_next = next_item < num_tiles;
     int next_tm = 0, next_tn = 0;
@@ -576,8 +580,15 @@ __global__ __launch_bounds__(kThreads) void gemm_mx_kernel_k512(Operand A, Opera
         if constexpr (kS == 3 && n < 2) static_for<n * 3, (n == 0 && S::kA + S::kB > 3 ? 3 : n * 3 > S::kA + S::kB ? n * 3 : S::kA + S::kB)>(read_chunk);
         if constexpr (ra >= 0) lds_read_frag<(ra >= 0 ? ra : 0) * 16 * kWideRowBytes, false>(fa[ra >= 0 ? ra : 0], a_nxt);
         if constexpr (rb >= 0) lds_read_frag<(rb >= 0 ? rb : 0) * 16 * kWideRowBytes, false>(fb[rb >= 0 ? rb : 0], b_nxt);
-        if constexpr (tr >= 0 && tr % 2 == 0) half[tr / 2] = transpose_half(chunk[tr / 2][(kS + 1) & 3], sel_half);
-        if constexpr (tr >= 0 && tr % 2 == 1) next_scale[tr / 2] = transpose_row(half[tr / 2], sel_row);
+        if constexpr (tr >= 0 && tr % 2 == 0) {
+          int v = chunk[tr / 2][(kS + 1) & 3];
+          turned(v);   // (not ahead of this MFMA)
+          half[tr / 2] = transpose_half(v, sel_half);
+        }
+        if constexpr (tr >= 0 && tr % 2 == 1) {
+          next_scale[tr / 2] = transpose_row(half[tr / 2], sel_row);
+          turned(next_scale[tr / 2]);
+        }
         if constexpr (kSecond) {
           constexpr int ld = S::load(kHalf - S::kFree + n);
           if constexpr (ld >= 0) issue_codes(std::integral_constant<int, ld>{}, kBuf);
