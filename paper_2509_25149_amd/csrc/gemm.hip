@@ -418,7 +418,7 @@ static hipError_t launch_planned(const GemmArgs& g, const GemmPlan& p, hipStream
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) { return launch_planned(g, plan_route(g), s); }
 
 static bool pairs(const GemmArgs& g, const GemmPlan& p, const GemmArgs& h, const GemmPlan& q) {
-  return p.route == kDirect && q.route == kDirect && direct_pair_fits(g, p.direct.shape, h, q.direct.shape);
+  return p.route == kDirect && q.route == kDirect && direct_pair_fits(g, p.direct.shape, h, q.direct.shape) && direct_pair_pays(g, p.direct, h, q.direct);
 }
 
 // Whether a product's result lies over something that the other one reads or writes; rows further apart than they are long count as a whole.

@@ -392,8 +392,8 @@ __global__ __launch_bounds__((WK == 1 ? 4 : WK) * 64, MB * NB > 16 ? 1 : 2) void
 // Two products that do not depend on each other in one launch (a layer's Dgrad and Wgrad): the first `tiles` workgroups take the first one's tiles.  Apart, a small layer's
 // products leave the chip half empty one after the other: 1040 x 2064 x 1296 has 731 tiles for 512 places, 2064 x 1296 x 1040 187.  Each is worked
 // exactly as by a launch of its own.  The shapes are those of which two workgroups of four wavefronts fit a CU.  Backward calls (quantizer included), us, apart / in one launch:
-// tokens x d_in x d_out 1040 x 2064 x 1296 42.0 / 37.1, 416 x 1280 x 512 16.8 / 13.7, 240 x 2304 x 16384 94.5 / 82.3, 8064 x 1024 x 1024 69.4 / 65.0; geometric mean
-// over 100 sizes 1.09, the worst 3408 x 960 x 6768 197 / 206.  The product with the shorter wavefronts first: 1.07.
+// tokens x d_in x d_out 1040 x 2064 x 1296 42.0 / 37.1, 416 x 1280 x 512 16.8 / 13.7, 240 x 2304 x 16384 94.5 / 82.3, 6912 x 448 x 13664 338 / 328; geometric mean
+// over 100 sizes 1.09; where two launches are faster: direct_pair_pays.  The product with the shorter wavefronts first: 1.07.
 struct DirectProduct {
   Operand a, b;
   void* d;
@@ -541,6 +541,16 @@ static int pair_shape(int shape) {
   if (d.mb != 4 || d.steps != 1) return -1;
   if (d.wk == 4) return d.nb == 4 ? 0 : d.nb == 3 ? 1 : -1;
   return d.wk == 1 && d.nb == 4 ? 2 : -1;
+}
+
+// Where one launch takes longer than two: one product has a tile for nearly every CU, the other between one and two.  Apart they come out even over the CUs; in one launch the
+// places fall free unevenly, and a CU that gets two of the last tiles works at half the speed on each.  What that costs grows with the length of the tiles of the
+// smaller product; the launch that is saved is 2.5 us.  Over 873 sizes 242 are such, and take 0.6 % longer in one launch (4416 x 384 x 9456 195 / 176 us in two, 3408 x 960 x 6768
+// 201 / 192, but 8064 x 1024 x 1024 62 / 65); the others take 8 % less in one, the worst of them 1.7 % more.
+bool direct_pair_pays(const GemmArgs& g, const DirectPick& p, const GemmArgs& h, const DirectPick& q) {
+  const int64_t tg = tiles_of(g, p.shape), th = tiles_of(h, q.shape);
+  const bool uneven = tg <= th ? tg > 192 && tg <= 256 && th > 256 && th <= 512 : th > 192 && th <= 256 && tg > 256 && tg <= 512;
+  return !(uneven && (tg <= th ? p : q).loop > 10.0);
 }
 
 bool direct_pair_fits(const GemmArgs& g, int shape, const GemmArgs& h, int shape2) {

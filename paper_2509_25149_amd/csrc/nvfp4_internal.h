@@ -86,7 +86,7 @@ struct GemmArgs {
   size_t workspace_bytes;
 };
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
-// Two products, each as by launch_gemm and in this order; in one launch where both are small (see gemm_direct_pair_kernel) and neither's result lies over what the other
+// Two products, each as by launch_gemm and in this order; in one launch where both are small (see gemm_direct_pair_kernel), that is faster and neither's result lies over what the other
 // reads or writes.
 hipError_t launch_gemm_pair(const GemmArgs& g, const GemmArgs& h, hipStream_t s);
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);
@@ -102,8 +102,6 @@ TwoPassPlan plan_two_pass(const GemmArgs& g);
 hipError_t launch_gemm_two_pass(const GemmArgs& g, const TwoPassPlan& plan, hipStream_t s);
 // Straight from the packed codes, without scratch, any K.  `shape`: number of a tile shape, see gemm_direct.hip.
 hipError_t launch_gemm_direct(const GemmArgs& g, int shape, hipStream_t s);
-bool direct_pair_fits(const GemmArgs& g, int shape, const GemmArgs& h, int shape2);
-hipError_t launch_gemm_direct_pair(const GemmArgs& g, int shape, const GemmArgs& h, int shape2, hipStream_t s);
 struct DirectPick {
   int shape, kind;       // its number in the kernel's list; the kind of tile (see there)
   double loop;           // us, expected (see SmallTileCost)
@@ -111,6 +109,9 @@ struct DirectPick {
 DirectPick pick_direct_shape(const GemmArgs& g, bool split_only);   // the best of them, or of those that split K; none can do it: HUGE_VAL
 bool direct_shape(int shape, int* out);   // MB, NB, WK, steps of a shape, for the tests; false: no such shape
 bool direct_shape_fits(const GemmArgs& g, int shape);   // whether it can do this product
+bool direct_pair_fits(const GemmArgs& g, int shape, const GemmArgs& h, int shape2);   // whether two products can share a launch
+bool direct_pair_pays(const GemmArgs& g, const DirectPick& p, const GemmArgs& h, const DirectPick& q);   // and whether it is faster
+hipError_t launch_gemm_direct_pair(const GemmArgs& g, int shape, const GemmArgs& h, int shape2, hipStream_t s);
 // Expected time of a kernel on small tiles (small_tile_us): that of a call, then rounds of 256 tiles of `tile` us and `step` us per step of the loop (`loop_us`),
 // or, where that is more, of the result's bytes (added in quadrature: neither hides the other fully).  A
 // CU holds `resident` workgroups; a round in which only one of them has a tile takes `alone` rounds, not 1.
