@@ -447,46 +447,27 @@ hipError_t launch_gemm_pair(const GemmArgs& g, const GemmArgs& h, hipStream_t s)
 }  // namespace nvfp4
 
 // For the tests, not part of the ABI: which kernel an NVFP4 product of these sizes takes with aligned operands.  decoded: bit 0 A, bit 1 B
-// decoded beforehand.  out: route (0 two-pass, 1 fused 256 x 256, 2 128 x 128, 3 direct); two-pass: in tiles of 256 rows, 32-column units of a tile, tiles of a split
-// last round, workgroups that share each (unless a larger tile is taken: nvfp4_internal_two_pass_tile); direct: the kind of tile.
-extern "C" void nvfp4_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int bf16_out, int accumulate, size_t workspace_bytes, int decoded, int* out) {
+// decoded beforehand; row_scales: bit 0 A, bit 1 B with a scale per row.  out: route (0 two-pass, 1 fused 256 x 256, 2 128 x 128, 3 direct); two-pass: rows and columns of
+// its tile, tiles of a split last round, workgroups that share each; direct: the kind of tile.
+extern "C" void nvfp4_internal_gemm_plan(int64_t M, int64_t N, int64_t K, int bf16_out, int accumulate, size_t workspace_bytes, int decoded, int row_scales,
+                                         int* out) {
   using namespace nvfp4;
   GemmArgs g{};
   const uint8_t* const some = reinterpret_cast<const uint8_t*>(uintptr_t{4096});
-  g.a = Operand{some, some, nullptr, M, 0, decoded & 1 ? some : nullptr};
-  g.b = Operand{some, some, nullptr, N, 0, decoded & 2 ? some : nullptr};
+  g.a = Operand{some, some, nullptr, M, row_scales & 1, decoded & 1 ? some : nullptr};
+  g.b = Operand{some, some, nullptr, N, row_scales >> 1 & 1, decoded & 2 ? some : nullptr};
   g.K = K;
   g.out_bf16 = bf16_out != 0;
   g.accumulate = accumulate != 0;
   g.workspace = workspace_bytes ? const_cast<uint8_t*>(some) : nullptr;
   g.workspace_bytes = workspace_bytes;
   const GemmPlan p = plan_route(g);
+  const bool two_pass = p.route == kTwoPass;
   out[0] = p.route;
-  out[1] = p.route == kDirect ? p.direct.kind : 0;
-  out[2] = 0;
-  out[3] = 1;
-  if (p.route == kTwoPass) {
-    out[1] = p.two_pass.units;
-    out[2] = p.two_pass.tail;
-    out[3] = p.two_pass.splits;
-  }
-}
-
-// Likewise: rows and columns of the tile that the two-pass route takes for it; 0: it takes another route.
-extern "C" int nvfp4_internal_two_pass_tile(int64_t M, int64_t N, int64_t K, int row_scales, size_t workspace_bytes, int* out) {
-  using namespace nvfp4;
-  GemmArgs g{};
-  const uint8_t* const some = reinterpret_cast<const uint8_t*>(uintptr_t{4096});
-  g.a = Operand{some, some, nullptr, M, row_scales};
-  g.b = Operand{some, some, nullptr, N};
-  g.K = K;
-  g.workspace = workspace_bytes ? const_cast<uint8_t*>(some) : nullptr;
-  g.workspace_bytes = workspace_bytes;
-  const GemmPlan p = plan_route(g);
-  if (p.route != kTwoPass) return 0;
-  out[0] = 32 * p.two_pass.mb;
-  out[1] = 32 * p.two_pass.nb;
-  return 1;
+  out[1] = two_pass ? 32 * p.two_pass.mb : p.route == kDirect ? p.direct.kind : 0;
+  out[2] = two_pass ? 32 * p.two_pass.nb : 0;
+  out[3] = two_pass ? p.two_pass.tail : 0;
+  out[4] = two_pass ? p.two_pass.splits : 1;
 }
 
 // Likewise: whether a backward pass of these sizes runs its two products in one launch.

@@ -17,7 +17,9 @@
 // (measured: the fused kernel runs at 1.0-1.07 PFLOP/s, this route at 1.5-1.6
 // in the GEMM proper, the decode pass adding 5-8 % of its time).
 // The results are identical to the fused kernel's up to FP32 summation order.
+#include <algorithm>
 #include <cmath>
+#include <cstdint>
 #include <type_traits>
 
 #include "nvfp4_internal.h"
@@ -495,7 +497,7 @@ __global__ __launch_bounds__(64) void splitk_sum_kernel(const float* __restrict_
 constexpr int kCUs = 256;
 constexpr size_t kPartialTileBytes = static_cast<size_t>(TM) * TN * sizeof(float);
 
-// How the last, partial round of 256x256 tiles is run: `tail` tiles (0 = there is none to treat
+// How the last, partial round of 256x256 tiles is run where a product takes those: `tail` tiles (0 = there is none to treat
 // specially) shared by `splits` workgroups each.
 struct TailPlan {
   int tail, splits;
@@ -590,41 +592,54 @@ static size_t operand_bytes(int64_t rows_a, int64_t rows_b, int64_t K) {
 
 static size_t partial_bytes(const TailPlan& p) { return static_cast<size_t>(p.tail) * p.splits * kPartialTileBytes; }
 
-// Enough for every way in which the operands may come; a call may use less (plan_two_pass).
-size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) {
-  const TailPlan p = plan_tail(M, N, K);
-  return operand_bytes(M, N, K) + partial_bytes(p);
+// The tile of a product and what goes with it: how many tiles of its last round are split (of 256 x 256 tiles only) and the expected time of its rounds.
+struct TileChoice {
+  int mb, nb;
+  TailPlan tail;
+  double rounds_us;
+};
+static TileChoice choose_tile(int64_t M, int64_t N, int64_t K, bool row_scales, bool accumulate, const TailPlan& tail) {
+  Width w = pick_width(M, N, tail, false);
+  const Tile t = pick_tile(M, N, K, w, tail, row_scales);
+  const double us = w.rounds * (9.2 + static_cast<double>(K) * (w.tiles >= kCUs ? 0.0186 : 0.0159)) * (K > 1024 ? t.gain : 1.0);
+  if (accumulate && K < 1024) w = pick_width(M, N, tail, true);
+  const int nb = t.nb > 8 ? t.nb : w.nb;
+  return TileChoice{t.mb, nb, nb == 8 ? tail : TailPlan{0, 1}, us};
+}
+// The split is chosen if the workspace has the room for its partial tiles; otherwise the last round is an ordinary one.
+static TileChoice choose_tile(int64_t M, int64_t N, int64_t K, bool row_scales, bool accumulate, size_t room_for_partials) {
+  const TileChoice c = choose_tile(M, N, K, row_scales, accumulate, plan_tail(M, N, K));
+  return partial_bytes(c.tail) <= room_for_partials ? c : choose_tile(M, N, K, row_scales, accumulate, TailPlan{0, 1});
 }
 
-// What a call does: one answer for the estimate, the room asked of the workspace and the launch.  The partial tiles of a split
-// count only where tiles are 256 columns wide, and a workspace without room for them makes the last round an ordinary one.
+// Enough for every way in which the operands may come; a call may use less (plan_two_pass).
+size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) {
+  size_t partials = 0;
+  for (const bool row_scales : {false, true}) partials = std::max(partials, partial_bytes(choose_tile(M, N, K, row_scales, false, SIZE_MAX).tail));
+  return operand_bytes(M, N, K) + partials;
+}
+
+// What a call does: one answer for the estimate, the room asked of the workspace and the launch.
 // Expected time: what is still to decode (codes and scales in, FP16 out) at 5.0 TB/s, then rounds of 256 tiles at 9.2 us for the result and 15.9 ns
 // per k while there are fewer, 18.6 when the chip is full (the clock drops with the matrix pipes busy), times what a larger tile gains, where the contraction is more of the
 // work than storing the result (4112 x 4368 x 128: 256 x 320 tiles take 0.98 of the best others' time, by fewer rounds 0.8) -- of a plain result,
 // for all output types (see SmallTileCost).  It is what the choice among the kernels is fitted with; estimates nearer to the measured times of this route took it where the
 // direct kernel is up to 20 % faster (18.8 us for this product, 22.6 here).
 TwoPassPlan plan_two_pass(const GemmArgs& g) {
-  TwoPassPlan plan{false, HUGE_VAL, 8, 0, 1, 8, 8};
+  TwoPassPlan plan{false, HUGE_VAL, 8, 8, 0, 1};
   const int64_t M = g.a.outer, N = g.b.outer;
-  if (g.K % TK != 0 || g.K >= (int64_t{1} << 21)) return plan;   // (the kernel's 32-bit byte offsets inside a 256-row tile)
+  if (g.K % TK != 0 || g.K >= (int64_t{1} << 21)) return plan;   // (the kernel's 32-bit byte offsets inside a tile)
   const int64_t rows = (g.a.fp16 ? 0 : M) + (g.b.fp16 ? 0 : N);
   const size_t operands = operand_bytes(rows, 0, g.K);
   if (operands > g.workspace_bytes) return plan;
-  TailPlan tail = plan_tail(M, N, g.K);
-  if (operands + partial_bytes(tail) > g.workspace_bytes) tail = TailPlan{0, 1};
-  Width w = pick_width(M, N, tail, false);
-  const Tile t = pick_tile(M, N, g.K, w, tail, g.a.ts_per_row != 0 || g.b.ts_per_row != 0);
-  plan.us = 7.4 + static_cast<double>(rows) * static_cast<double>(g.K) * 2.5625 / 5.0e6 +
-            w.rounds * (9.2 + static_cast<double>(g.K) * (w.tiles >= kCUs ? 0.0186 : 0.0159)) * (g.K > 1024 ? t.gain : 1.0);
-  if (g.accumulate && g.K < 1024) w = pick_width(M, N, tail, true);
-  if (w.nb != 8) tail = TailPlan{0, 1};
-  plan.units = w.nb;
-  plan.mb = t.mb;
-  plan.nb = t.nb > 8 ? t.nb : w.nb;
-  plan.tail = tail.tail;
-  plan.splits = tail.splits;
-  // (With both operands decoded beforehand nothing is needed of the workspace.)
-  const bool room = operands + partial_bytes(tail) == 0 || (g.workspace && reinterpret_cast<uintptr_t>(g.workspace) % 256 == 0);
+  const TileChoice c = choose_tile(M, N, g.K, g.a.ts_per_row != 0 || g.b.ts_per_row != 0, g.accumulate, g.workspace_bytes - operands);
+  plan.us = 7.4 + static_cast<double>(rows) * static_cast<double>(g.K) * 2.5625 / 5.0e6 + c.rounds_us;
+  plan.mb = c.mb;
+  plan.nb = c.nb;
+  plan.tail = c.tail.tail;
+  plan.splits = c.tail.splits;
+  // (With both operands decoded beforehand and no round split nothing is needed of the workspace.)
+  const bool room = operands + partial_bytes(c.tail) == 0 || (g.workspace && reinterpret_cast<uintptr_t>(g.workspace) % 256 == 0);
   plan.usable = room && reinterpret_cast<uintptr_t>(g.a.fp16) % 16 == 0 && reinterpret_cast<uintptr_t>(g.b.fp16) % 16 == 0 &&
                 reinterpret_cast<uintptr_t>(g.a.codes) % 16 == 0 && reinterpret_cast<uintptr_t>(g.b.codes) % 16 == 0 &&
                 reinterpret_cast<uintptr_t>(g.a.scales) % 4 == 0 && reinterpret_cast<uintptr_t>(g.b.scales) % 4 == 0;

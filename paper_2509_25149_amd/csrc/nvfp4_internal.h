@@ -90,13 +90,12 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
 // reads or writes.
 hipError_t launch_gemm_pair(const GemmArgs& g, const GemmArgs& h, hipStream_t s);
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);
-// What the two-pass route does with a product: in tiles of 256 rows, 32-column units of its tile, how many tiles of the last round are split along K over
-// how many workgroups; the tile that it takes, 32 mb x 32 nb -- that one, or a larger one (nothing is split then); what it is expected to take; usable: shape, alignment and workspace allow it.
+// What the two-pass route does with a product: tiles of 32 mb x 32 nb, of which the last `tail` (256 x 256 then) are split along K over
+// `splits` workgroups each; what it is expected to take; usable: shape, alignment and workspace allow it.
 struct TwoPassPlan {
   bool usable;
   double us;
-  int units, tail, splits;
-  int mb, nb;
+  int mb, nb, tail, splits;
 };
 TwoPassPlan plan_two_pass(const GemmArgs& g);
 hipError_t launch_gemm_two_pass(const GemmArgs& g, const TwoPassPlan& plan, hipStream_t s);

@@ -151,11 +151,12 @@ def test_gemm_and_dequantize_reject_bad_arguments(lib):
 
 
 def test_gemm_workspace_query(lib):
-    # FP16 copies of both operands (+ FP32 partial tiles when the last round of 256x256 tiles is partial:
-    # 640 tiles -> 128 tiles x 2 splits, 1600 tiles -> 64 tiles x 4 splits)
+    # FP16 copies of both operands (+ FP32 partial tiles where a partial last round of 256x256 tiles is split:
+    # 384 tiles -> 128 tiles x 2 splits, 528 tiles -> 16 tiles x 8 splits)
     assert nv.gemm_workspace_bytes(8192, 20480, 5120) == (8192 + 20480) * 5120 * 2
-    assert nv.gemm_workspace_bytes(8192, 5120, 20480) == (8192 + 5120) * 20480 * 2 + 256 * 256 * 256 * 4
-    assert nv.gemm_workspace_bytes(20480, 5120, 8192) == (20480 + 5120) * 8192 * 2 + 256 * 256 * 256 * 4
+    assert nv.gemm_workspace_bytes(8192, 5120, 20480) == (8192 + 5120) * 20480 * 2
+    assert nv.gemm_workspace_bytes(2944, 8192, 1024) == (2944 + 8192) * 1024 * 2 + 128 * 2 * 256 * 256 * 4
+    assert nv.gemm_workspace_bytes(8256, 4096, 4096) == (8256 + 4096) * 4096 * 2 + 16 * 8 * 256 * 256 * 4
     w = ctypes.c_size_t()
     assert lib.nvfp4_gemm_workspace_bytes(8, 16, 16, ctypes.addressof(w)) == -2
     assert lib.nvfp4_gemm_workspace_bytes(16, 16, 16, None) == -1

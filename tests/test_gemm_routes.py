@@ -18,14 +18,15 @@ def library():
         pytest.skip("libnvfp4_hip.so not built")
 
 
-def plan(M, N, K, bf16=False, accumulate=False, workspace=0, decoded=0):
-    """(route, shape, tiles of a split last round, splits); workspace: bytes, or True for what the library asks for."""
-    out = (ctypes.c_int * 4)()
+def plan(M, N, K, bf16=False, accumulate=False, workspace=0, decoded=0, row_scales=0):
+    """(route, shape, tiles of a split last round, splits) as launched; shape: (rows, columns) of a two-pass tile, the direct kernel's kind of tile;
+    workspace: bytes, or True for what the library asks for; decoded, row_scales: bit 0 A, bit 1 B."""
+    out = (ctypes.c_int * 5)()
     if workspace is True:
         workspace = nv.gemm_workspace_bytes(M, N, K)
     i64 = ctypes.c_int64
-    nv.load_library().nvfp4_internal_gemm_plan(i64(M), i64(N), i64(K), int(bf16), int(accumulate), ctypes.c_size_t(workspace), decoded, out)
-    return tuple(out)
+    nv.load_library().nvfp4_internal_gemm_plan(i64(M), i64(N), i64(K), int(bf16), int(accumulate), ctypes.c_size_t(workspace), decoded, row_scales, out)
+    return out[0], (out[1], out[2]) if out[0] == TWO_PASS else out[1], out[3], out[4]
 
 
 def mx_units(M, N):
@@ -67,10 +68,11 @@ def test_small_results_split_k_while_all_workgroups_are_resident(M, N, K):
             assert route == DIRECT and shape < OWN_TILES
 
 
-@pytest.mark.parametrize("M,N,K,units", [(8192, 20480, 5120, 8), (8192, 5120, 20480, 8), (5120, 20480, 8192, 8), (5120, 5120, 4096, 7),
-                                         (2048, 5120, 5120, 5), (4096, 5120, 5120, 5), (960, 18016, 2560, 5)])
-def test_large_products_take_the_two_pass_route(M, N, K, units):
-    assert plan(M, N, K, workspace=True)[:2] == (TWO_PASS, units)
+@pytest.mark.parametrize("M,N,K,tile", [(8192, 20480, 5120, (256, 320)), (8192, 5120, 20480, (256, 320)), (5120, 20480, 8192, (320, 320)),
+                                        (5120, 5120, 4096, (320, 320)), (2048, 5120, 5120, (256, 160)), (4096, 5120, 5120, (256, 320)),
+                                        (960, 18016, 2560, (256, 320)), (2944, 8192, 1024, (256, 256))])
+def test_large_products_take_the_two_pass_route(M, N, K, tile):
+    assert plan(M, N, K, workspace=True)[:2] == (TWO_PASS, tile)
     assert plan(M, N, K, workspace=0)[0] in (FUSED_256, DIRECT)
 
 
@@ -79,9 +81,11 @@ def test_mxfp4_tile_widths(M, N, units):
     assert mx_units(M, N) == units
 
 
-def test_accumulating_products_keep_the_widest_tile_unless_a_narrower_one_saves_rounds():
-    assert plan(5120, 20480, 256, accumulate=True, workspace=True)[:2] == (TWO_PASS, 8)      # 299 us; 160 columns 313
-    assert plan(5120, 20480, 256, bf16=True, workspace=True)[:2] == (TWO_PASS, 5)            # 83 us; 256 columns 88
+def test_accumulating_products_of_a_short_contraction_keep_a_wide_tile_unless_a_narrower_one_saves_rounds():
+    """1620 tiles of 256 columns are 7 rounds, 2538 of 160 columns 10 of 0.68: 3 % less, not enough where the result is read too."""
+    M, N, K = 13776, 7472, 512
+    assert plan(M, N, K, accumulate=True, workspace=True)[:2] == (TWO_PASS, (256, 256))
+    assert plan(M, N, K, workspace=True)[:2] == (TWO_PASS, (256, 160))
 
 
 @pytest.mark.parametrize("K", [2 ** 27 + 16, 2 ** 29, 2 ** 31 + 16, 2 ** 33 + 64])
@@ -118,19 +122,52 @@ def test_one_kernel_for_all_output_types():
 
 
 def test_workspace_without_room_for_partial_tiles_still_serves_the_two_pass_route():
-    M, N, K = 4352, 4096, 4096                                   # 272 tiles: the last 16 split 8 ways
+    M, N, K = 8256, 4096, 4096                                   # 528 tiles: the last 16 split 8 ways
     operands = (M + N) * K * 2
-    assert plan(M, N, K, workspace=True) == (TWO_PASS, 8, 16, 8)
+    assert plan(M, N, K, workspace=True) == (TWO_PASS, (256, 256), 16, 8)
     assert nv.gemm_workspace_bytes(M, N, K) == operands + 16 * 8 * 2 ** 18
-    route, units, tail, splits = plan(M, N, K, workspace=operands)
-    assert (route, tail, splits) == (TWO_PASS, 0, 1) and units < 8    # two whole rounds of 256 columns or fewer of narrower tiles
+    route, tile, tail, splits = plan(M, N, K, workspace=operands)
+    assert (route, tail, splits) == (TWO_PASS, 0, 1) and tile != (256, 256)    # three whole rounds of 256 columns or fewer of other tiles
     assert plan(M, N, K, workspace=operands - 256)[0] != TWO_PASS
-    # narrower tiles ask for no partial ones: 4096 x 5120 x 5120 (320 tiles) runs 160 columns wide
-    assert plan(4096, 5120, 5120, workspace=(4096 + 5120) * 5120 * 2) == (TWO_PASS, 5, 0, 1)
     # with both operands decoded nothing is needed; with room for the partial tiles alone the split is back
-    assert plan(M, N, K, decoded=3) == (TWO_PASS, units, 0, 1)
-    assert plan(M, N, K, workspace=16 * 8 * 2 ** 18, decoded=3) == (TWO_PASS, 8, 16, 8)
+    assert plan(M, N, K, decoded=3) == (TWO_PASS, tile, 0, 1)
+    assert plan(M, N, K, workspace=16 * 8 * 2 ** 18, decoded=3) == (TWO_PASS, (256, 256), 16, 8)
     assert plan(M, N, K, workspace=N * K * 2, decoded=1)[0] == TWO_PASS
+
+
+@pytest.mark.parametrize("M,N,K", [(4352, 4096, 4096), (8192, 5120, 20480), (5120, 20480, 8192), (4096, 5120, 5120), (2048, 5120, 5120)])
+def test_tiles_without_a_split_ask_for_no_room_for_partial_ones(M, N, K):
+    """Their rounds of 256 x 256 tiles would be partial; they run in others."""
+    operands = (M + N) * K * 2
+    assert nv.gemm_workspace_bytes(M, N, K) == operands
+    with_room = plan(M, N, K, workspace=operands + 2 ** 27)
+    assert with_room[0] == TWO_PASS and with_room[1] != (256, 256) and with_room[2:] == (0, 1)
+    assert plan(M, N, K, workspace=operands) == with_room
+    assert plan(M, N, K, decoded=3) == plan(M, N, K, workspace=2 ** 27, decoded=3) == with_room
+
+
+def test_the_workspace_query_covers_either_kind_of_scales():
+    M, N, K = 5088, 4032, 2048                                   # 320 x 320 tiles, which a scale per row rules out
+    assert plan(M, N, K, workspace=True) == (TWO_PASS, (320, 320), 0, 1)
+    for row_scales in (1, 2, 3):
+        assert plan(M, N, K, workspace=True, row_scales=row_scales) == (TWO_PASS, (256, 256), 64, 4)
+    assert nv.gemm_workspace_bytes(M, N, K) == (M + N) * K * 2 + 64 * 4 * 2 ** 18
+
+
+def test_what_the_query_asks_for_is_enough_and_no_more_than_is_used():
+    """More room changes nothing, and where it asks for partial tiles one of the kinds of scales has them."""
+    rng = random.Random(9)
+    size = lambda: max(256, int(256 * 60 ** rng.random()) // 16 * 16)
+    split = 0
+    for _ in range(3000):
+        M, N, K = size(), size(), size() // 64 * 64
+        need = nv.gemm_workspace_bytes(M, N, K)
+        plans = [plan(M, N, K, workspace=need, decoded=3, row_scales=r) for r in (0, 1, 2, 3)]
+        assert plans == [plan(M, N, K, workspace=2 ** 42, decoded=3, row_scales=r) for r in (0, 1, 2, 3)]
+        partials = need - ((M + N) * K * 2 + 255) // 256 * 256
+        assert partials == max(p[2] * p[3] if p[3] > 1 else 0 for p in plans) * 2 ** 18
+        split += partials > 0
+    assert split > 20
 
 
 def direct_shapes():

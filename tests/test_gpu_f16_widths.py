@@ -6,14 +6,18 @@ import torch
 
 import oracle
 from paper_2509_25149_amd import binding as nv, synth
+from test_gemm_routes import TWO_PASS, plan
 from test_gpu_parity import GEMM_TOL, to_dev
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("M,N,K", [(5072, 5072, 1024), (2032, 6128, 2048), (2016, 5088, 2048), (4080, 5104, 1088)])
+# the last three: more tiles than CUs
+@pytest.mark.parametrize("M,N,K,columns", [(5408, 2192, 320, 224), (2736, 4368, 256, 192), (4624, 1680, 1088, 160), (6160, 3984, 256, 224), (6112, 3984, 256, 192),
+                                           (6432, 7728, 320, 160)])
 @pytest.mark.parametrize("per_row", [False, True], ids=["tensor_scale", "row_scales"])
-def test_two_pass_widths(M, N, K, per_row):
+def test_two_pass_widths(M, N, K, columns, per_row):
+    assert plan(M, N, K, workspace=True, row_scales=int(per_row))[:2] == (TWO_PASS, (256, columns))
     xb, wb = synth.normal_with_outliers(M, K, 1.0, 7200 + K, frac=0.01), synth.normal(N, K, 0.02, 7300 + N)
     qx = nv.nvfp4_quantize(to_dev(xb), nv.LAYOUT_ROW | (nv.LAYOUT_ROW_SCALES if per_row else 0))
     qw = nv.nvfp4_quantize(to_dev(wb), nv.LAYOUT_ROW)

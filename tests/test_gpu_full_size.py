@@ -233,16 +233,14 @@ def test_indexing_beyond_2_31_elements():
     assert float(err) <= 2e-6
 
 
-@pytest.mark.parametrize("M,N,K,splits", [(4352, 4096, 4096, 8), (4208, 4304, 2048, 4), (8192, 5120, 1024, 2),
-                                          (4336, 4080, 4096, 8), (8176, 5104, 1088, 2), (4112, 8176, 2048, 4)])
+@pytest.mark.parametrize("M,N,K,splits", [(8448, 4096, 4096, 8), (2816, 18432, 2048, 4), (2944, 8192, 1024, 2),
+                                          (8240, 4080, 4096, 8), (2896, 8080, 1088, 2), (2592, 18240, 2112, 4)])
 def test_split_k_last_round(M, N, K, splits):
-    """Shapes whose last round of 256x256 tiles is partial (272, 289, 640, 272, 640 and 544 tiles; the last three ragged at both edges): the
+    """Shapes whose last round of 256x256 tiles is partial (528, 792, 384, 528, 384 and 792 tiles; the last three ragged at both edges): the
     split-K launch and the launch that adds its partial tiles against the oracle on a sample, against another kernel's result
-    everywhere, and bit-for-bit against itself (the partial sums are added in a fixed order).  The second runs in narrower
-    tiles instead; what the library asks for as workspace would cover its split."""
-    assert plan(M, N, K, workspace=True)[:2] == (TWO_PASS, 5 if M == 4208 else 8)
-    assert M == 4208 or plan(M, N, K, workspace=True)[3] == splits
+    everywhere, and bit-for-bit against itself (the partial sums are added in a fixed order)."""
     tiles = -(-M // 256) * -(-N // 256)                                        # partial tiles are in the workspace
+    assert plan(M, N, K, workspace=True) == (TWO_PASS, (256, 256), tiles % 256, splits)
     assert nv.gemm_workspace_bytes(M, N, K) == (((M + N) * K * 2 + 255) // 256) * 256 + (tiles % 256) * splits * 2 ** 18
     ab = synth.normal_with_outliers(M, K, 1.0, 901)
     bb = synth.normal(N, K, 0.05, 902)

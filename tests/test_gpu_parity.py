@@ -286,7 +286,7 @@ def test_gemm_with_two_ragged_tiles_per_compute_unit(K):
     as it goes.  K = 128 takes the first of these only with both operands decoded beforehand."""
     M, N = 4080, 8176
     decoded = 3 if K == 128 else 0
-    assert plan(M, N, K, workspace=True, decoded=decoded) == (TWO_PASS, 8, 0, 1) and plan(M, N, K)[0] == FUSED_256
+    assert plan(M, N, K, workspace=True, decoded=decoded) == (TWO_PASS, (256, 256), 0, 1) and plan(M, N, K)[0] == FUSED_256
     xb = synth.normal_with_outliers(M, K, 1.0, 930 + K, frac=0.01)
     wb = synth.normal(K, N, 0.02, 931 + K)
     qx, rx = check_quantize(xb, nv.LAYOUT_ROW)
@@ -359,13 +359,15 @@ def test_linear_layer_calls_equal_the_call_sequence():
     assert e.value.status == -3
 
 
-@pytest.mark.parametrize("tokens,d_in,d_out", [(4352, 1024, 4096), (4352, 4096, 4096)])
+@pytest.mark.parametrize("tokens,d_in,d_out", [(4352, 1024, 4096), (8256, 4096, 4096)])
 def test_layer_step_replays_from_a_hip_graph(tokens, d_in, d_out):
     """A whole layer step (quantize + three GEMMs through the per-layer entry points, caller-owned buffers only) is
     captured into a HIP graph and replayed with eager work in between; every replay must reproduce the eager
-    result bit for bit.  d_in = 1024: narrower tiles and the direct kernel; 4096: a split-K last round."""
-    if d_in == 4096:                                 # Fprop, Dgrad: 17 x 16 = 272 tiles, the last 16 split along K
-        assert plan(tokens, d_out, d_in, bf16=True, workspace=True) == (TWO_PASS, 8, 16, 8)
+    result bit for bit.  d_in = 1024: 320-column tiles and the direct kernel; 4096: a split-K last round."""
+    if d_in == 4096:                                 # Fprop, Dgrad: 33 x 16 = 528 tiles, the last 16 split along K
+        assert plan(tokens, d_out, d_in, bf16=True, workspace=True) == (TWO_PASS, (256, 256), 16, 8)
+    else:
+        assert plan(tokens, d_out, d_in, bf16=True, workspace=True)[:2] == (TWO_PASS, (256, 320))
     wb = synth.normal(d_in, d_out, 0.02, 951)
     xb = synth.normal_with_outliers(tokens, d_in, 1.0, 952)
     dyb = synth.student_t3(tokens, d_out, 1e-3, 953)
@@ -467,18 +469,18 @@ def test_the_two_supplied_maxima_are_independent(raw):
     assert_copy_equal(q.col_codes, q.col_scales, q.col_ts, oracle.quantize(xb, oracle.COL, use_rht=True, rht_seed=5, amax=float(own[1])), "col copy")
 
 
-@pytest.mark.parametrize("tokens,d_in,d_out", [(4352, 1024, 4096), (4352, 4096, 4096)])
+@pytest.mark.parametrize("tokens,d_in,d_out", [(4352, 1024, 4096), (8256, 4096, 4096)])
 def test_predecoded_operands_give_the_same_bits(tokens, d_in, d_out):
     """nvfp4_predecode: a weight decoded to FP16 once serves Fprop and Dgrad of every micro-batch (Sec. 4.3, Sec. 4.1);
     the GEMM on the decoded copy runs the same kernel on the same FP16 values, so the results are identical.  d_in = 4096: all
-    three products on the two-pass route, Fprop and Dgrad with a split-K last round (d_in = 1024: Fprop alone, in narrower tiles; the
+    three products on the two-pass route, Fprop and Dgrad with a split-K last round (d_in = 1024: Fprop alone, in 320-column tiles; the
     others read the codes); a workspace sized only for the operands still to decode must be enough."""
     if d_in == 4096:
         for decoded in (0, 2):
-            assert plan(tokens, d_out, d_in, workspace=True, decoded=decoded) == (TWO_PASS, 8, 16, 8)
-            assert plan(tokens, d_in, d_out, workspace=True, decoded=decoded) == (TWO_PASS, 8, 16, 8)
+            assert plan(tokens, d_out, d_in, workspace=True, decoded=decoded) == (TWO_PASS, (256, 256), 16, 8)
+            assert plan(tokens, d_in, d_out, workspace=True, decoded=decoded) == (TWO_PASS, (256, 256), 16, 8)
         for decoded in (0, 3):
-            assert plan(d_in, d_out, tokens, workspace=True, decoded=decoded) == (TWO_PASS, 8, 0, 1)
+            assert plan(d_in, d_out, tokens, workspace=True, decoded=decoded) == (TWO_PASS, (256, 256), 0, 1)
     wb = synth.normal(d_in, d_out, 0.02, 2101)
     qw = nv.nvfp4_quantize(to_dev(wb), nv.LAYOUT_ROW | nv.LAYOUT_COL, nv.BLOCK_16x16)
     qx = nv.nvfp4_quantize(to_dev(synth.normal_with_outliers(tokens, d_in, 1.0, 2102)), nv.LAYOUT_ROW | nv.LAYOUT_COL,

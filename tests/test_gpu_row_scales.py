@@ -142,16 +142,18 @@ def test_gemm_with_row_scales_all_ops(mnk):
 @pytest.mark.parametrize("scales_on", ["A", "B", "both"])
 @pytest.mark.parametrize("M,N,K,with_ws,without", [
     (4112, 4368, 128, (DIRECT, 4, 0, 1), (DIRECT, 4, 0, 1)),
-    (4352, 4096, 1024, (TWO_PASS, 5, 0, 1), (DIRECT, 4, 0, 1)),
-    (4080, 8176, 192, (TWO_PASS, 8, 0, 1), (FUSED_256, 0, 0, 1)),
-    (8176, 5104, 1088, (TWO_PASS, 8, 128, 2), None),
-    (4336, 4080, 4096, (TWO_PASS, 8, 16, 8), None)])
+    (4352, 4096, 1024, (TWO_PASS, (256, 320), 0, 1), (DIRECT, 4, 0, 1)),
+    (3872, 12704, 320, (TWO_PASS, (256, 160), 0, 1), None),
+    (4080, 8176, 192, (TWO_PASS, (256, 256), 0, 1), (FUSED_256, 0, 0, 1)),
+    (2896, 8096, 1024, (TWO_PASS, (256, 256), 128, 2), None),
+    (3376, 9248, 4096, (TWO_PASS, (256, 256), 6, 8), None)])
 def test_gemm_with_row_scales_and_more_tiles_than_compute_units(M, N, K, with_ws, without, scales_on):
     """The per-row output stage in the launch forms that the small shapes above do not reach, ragged at both edges: the direct kernel
-    with a tile per wavefront; 160-column tiles run as streams by one workgroup per CU; 256-column tiles likewise, and the fused kernel
-    without a workspace; a last round split along K two and eight ways, whose partial tiles the sum launch scales per row."""
-    assert plan(M, N, K, workspace=True) == with_ws
-    assert without is None or plan(M, N, K) == without
+    with a tile per wavefront; 320-column tiles, one to a workgroup; 160-column tiles run as streams by one workgroup per CU; 256-column tiles likewise, and the fused
+    kernel without a workspace; a last round split along K two and eight ways, whose partial tiles the sum launch scales per row."""
+    row_scales = {"A": 1, "B": 2, "both": 3}[scales_on]
+    assert plan(M, N, K, workspace=True, row_scales=row_scales) == with_ws
+    assert without is None or plan(M, N, K, row_scales=row_scales) == without
     def operand(rows, seed, per_row):
         x = synth.bf16_bits_to_f32(synth.normal_with_outliers(rows, K, 1.0, seed, frac=0.01))
         x *= np.exp2(-(np.arange(rows) % 12))[:, None].astype(np.float32)          # rows of different magnitude

@@ -1,24 +1,21 @@
 """GPU parity of the two-pass GEMM in each of its tiles, ragged at both edges, one tile per workgroup and several as one stream, against
 the oracle's binary64 product."""
-import ctypes
-
 import numpy as np
 import pytest
 import torch
 
 import oracle
 from paper_2509_25149_amd import binding as nv, synth
-from test_gemm_routes import plan
+from test_gemm_routes import TWO_PASS, plan
 from test_gpu_parity import GEMM_TOL, to_dev
 
 pytestmark = pytest.mark.gpu
 
 
 def tile(M, N, K, per_row):
-    out = (ctypes.c_int * 2)()
-    i64 = ctypes.c_int64
-    assert nv.load_library().nvfp4_internal_two_pass_tile(i64(M), i64(N), i64(K), int(per_row), ctypes.c_size_t(nv.gemm_workspace_bytes(M, N, K)), out)
-    return tuple(out)
+    route, shape = plan(M, N, K, workspace=True, row_scales=int(per_row))[:2]
+    assert route == TWO_PASS
+    return shape
 
 
 @pytest.mark.parametrize("M,N,K,per_row,takes", [
@@ -51,7 +48,7 @@ def test_every_tile(M, N, K, per_row, takes):
                                                   (5088, 4032, 2048, True, 4), (3376, 9248, 4096, False, 8), (3376, 9248, 4096, True, 8)])
 def test_split_last_round(M, N, K, per_row, splits):
     """256 x 256 tiles whose last round is split along K: against the kernel that a call without scratch takes, which sums in another order."""
-    assert tile(M, N, K, per_row) == (256, 256) and plan(M, N, K, workspace=True)[3] == splits and plan(M, N, K)[0] != 0
+    assert plan(M, N, K, workspace=True, row_scales=int(per_row))[1::2] == ((256, 256), splits) and plan(M, N, K)[0] != TWO_PASS
     xb, wb = synth.normal_with_outliers(M, K, 1.0, 7600 + K, frac=0.01), synth.normal(N, K, 0.02, 7700 + N)
     qx = nv.nvfp4_quantize(to_dev(xb), nv.LAYOUT_ROW | (nv.LAYOUT_ROW_SCALES if per_row else 0))
     qw = nv.nvfp4_quantize(to_dev(wb), nv.LAYOUT_ROW)
@@ -63,3 +60,6 @@ def test_split_last_round(M, N, K, per_row, splits):
     # two FP32 sums of K / 32 steps each: sqrt(K / 32) 2^-24 of the result twice, 1.4e-6 at the most
     assert (buf[:, :N].double() - ref).norm() <= 3e-6 * ref.norm()
     assert torch.equal(nv.nvfp4_gemm(qx, qw, nv.OP_DGRAD, nv.OUT_BF16, workspace=ws), buf[:, :N].to(torch.bfloat16))
+    acc = buf[:, :N].clone()
+    nv.nvfp4_gemm(qx, qw, nv.OP_DGRAD, nv.OUT_F32_ACCUMULATE, out=acc, workspace=ws)
+    assert torch.equal(acc, buf[:, :N] + buf[:, :N])

@@ -1,11 +1,11 @@
 """Which tile the two-pass GEMM takes (host code only)."""
-import ctypes
 import os
 import random
 
 import pytest
 
 from paper_2509_25149_amd import binding as nv
+from test_gemm_routes import TWO_PASS, plan
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -16,10 +16,8 @@ def library():
 
 def tile(M, N, K, per_row=False):
     """Rows and columns, or None where the product takes another route."""
-    out = (ctypes.c_int * 2)()
-    i64 = ctypes.c_int64
-    ok = nv.load_library().nvfp4_internal_two_pass_tile(i64(M), i64(N), i64(K), int(per_row), ctypes.c_size_t(nv.gemm_workspace_bytes(M, N, K)), out)
-    return tuple(out) if ok else None
+    route, shape = plan(M, N, K, workspace=True, row_scales=int(per_row))[:2]
+    return shape if route == TWO_PASS else None
 
 
 @pytest.mark.parametrize("M,N,K,takes", [(8192, 20480, 5120, (256, 320)), (8192, 5120, 20480, (256, 320)), (5120, 20480, 8192, (320, 320)),
