@@ -560,11 +560,22 @@ static double rounds_of(int64_t tiles) { return static_cast<double>((tiles + kCU
 // 4096 x 15360 x 2048 bf16 192 / 178 / 207.  Over the 130 products the tile with the smallest estimate takes 0.1 % more than the best one.
 // A larger tile has no round split, and tiles without a split sum in the same order.
 // (320 x 320 with a scale per row: the output stage has too few registers for the scales.)
+// Where the contraction is short the result is most of the work, which the estimate knows least about: there a larger tile has to promise more, most of all where the
+// result is accumulated (read too).  Measured, time in the tile of 256 rows over that in the larger one, geometric mean and least, by what the estimate promises: accumulated,
+// K < 1024, 256 x 320 under 0.9 1.06, 0.98, from 0.9 on 0.98, 0.88; 320 x 320 under 0.8 1.04, 0.95, from 0.8 on 0.96, 0.84; plain results, K < 400, from 0.95 on
+// 0.95, 0.92 (FP32), 0.98, 0.94 (bf16).  13312 x 1296 x 512 accumulated: 256 x 160 48 us, 320 x 320 56.  And 320 x 320 in the place of 256 x 160, one round of about 215 for two
+// of nearly 256 each, has to promise a tenth: 8448 x 2288 x 1216 accumulated 66 / 74, 6432 x 3008 x 1024 FP32 41.5 / 43.5 with promises of 0.95, 20336 x 2320 x 1024 1.12 times
+// faster with one of 0.83.
+static double promise_needed(int mb, int units, int64_t K, bool accumulate) {
+  if (accumulate && K < 1024) return mb == 8 ? 0.9 : 0.8;
+  if (mb == 10 && units == 5) return 0.9;
+  return K < 400 ? 0.95 : 1.0;
+}
 struct Tile {
   int mb, nb;
   double gain;   // time in it over that in the tile of 256 rows
 };
-static Tile pick_tile(int64_t M, int64_t N, int64_t K, const Width& w, const TailPlan& tail, bool row_scales) {
+static Tile pick_tile(int64_t M, int64_t N, int64_t K, const Width& w, const TailPlan& tail, bool row_scales, bool accumulate) {
   Tile best{8, w.nb, 1.0};
   double base = 0.0;   // (the tile of 256 rows comes first)
   for (const TileTime& t : kTileTimes) {
@@ -578,7 +589,7 @@ static Tile pick_tile(int64_t M, int64_t N, int64_t K, const Width& w, const Tai
     }
     const double us = tile_us(t, tiles, rounds, K);
     if (t.nb <= 8) base = us;
-    else if (us < best.gain * base) best = Tile{t.mb, t.nb, us / base};
+    else if (us < best.gain * base && us < promise_needed(t.mb, w.nb, K, accumulate) * base) best = Tile{t.mb, t.nb, us / base};
   }
   return best;
 }
@@ -600,11 +611,13 @@ struct TileChoice {
 };
 static TileChoice choose_tile(int64_t M, int64_t N, int64_t K, bool row_scales, bool accumulate, const TailPlan& tail) {
   Width w = pick_width(M, N, tail, false);
-  const Tile t = pick_tile(M, N, K, w, tail, row_scales);
+  Tile t = pick_tile(M, N, K, w, tail, row_scales, false);
   const double us = w.rounds * (9.2 + static_cast<double>(K) * (w.tiles >= kCUs ? 0.0186 : 0.0159)) * (K > 1024 ? t.gain : 1.0);
-  if (accumulate && K < 1024) w = pick_width(M, N, tail, true);
-  const int nb = t.nb > 8 ? t.nb : w.nb;
-  return TileChoice{t.mb, nb, nb == 8 ? tail : TailPlan{0, 1}, us};
+  if (accumulate && K < 1024) {
+    w = pick_width(M, N, tail, true);
+    t = pick_tile(M, N, K, w, tail, row_scales, true);
+  }
+  return TileChoice{t.mb, t.nb, t.nb == 8 ? tail : TailPlan{0, 1}, us};
 }
 // The split is chosen if the workspace has the room for its partial tiles; otherwise the last round is an ordinary one.
 static TileChoice choose_tile(int64_t M, int64_t N, int64_t K, bool row_scales, bool accumulate, size_t room_for_partials) {

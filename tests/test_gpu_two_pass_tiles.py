@@ -19,8 +19,8 @@ def tile(M, N, K, per_row):
 
 
 @pytest.mark.parametrize("M,N,K,per_row,takes", [
-    (1488, 13584, 256, False, (320, 320)), (4112, 9664, 256, False, (320, 320)), (2096, 19184, 320, False, (320, 320)),
-    (1456, 10960, 320, False, (256, 320)), (6656, 5024, 256, False, (256, 320)), (6656, 5024, 320, True, (256, 320)),
+    (1424, 13776, 320, False, (320, 320)), (3360, 12128, 256, False, (320, 320)), (2096, 19184, 320, False, (320, 320)),
+    (1456, 10960, 320, False, (256, 320)), (6160, 5808, 256, False, (256, 320)), (2320, 14752, 320, True, (256, 320)),
     (1808, 15536, 256, False, (256, 256)), (3088, 3904, 320, False, (256, 224)), (2592, 9504, 256, False, (256, 224)),
     (1664, 13584, 320, False, (256, 192)), (3872, 12704, 320, False, (256, 160))])
 def test_every_tile(M, N, K, per_row, takes):

@@ -27,6 +27,21 @@ def test_products_take_the_tile_whose_rounds_come_out_best(M, N, K, takes):
     assert tile(M, N, K) == takes
 
 
+# us accumulated in the tile taken / in the larger one of which a round estimate says that it takes less
+@pytest.mark.parametrize("M,N,K,takes", [(4928, 12272, 128, (256, 256)),      # 113 / 132
+                                         (13312, 1296, 512, (256, 160)),      # 48 / 56
+                                         (7088, 12288, 512, (256, 192)),      # 258 / 297
+                                         (17904, 1008, 960, (256, 160)),      # 58 / 67
+                                         (8448, 2288, 1216, (256, 160)),      # 66 / 74
+                                         (8304, 4768, 64, (256, 320)),        # the larger one: 65; 160 columns 73
+                                         (7888, 3088, 960, (320, 320)),       # 72; 224 columns 81
+                                         (5120, 20480, 512, (320, 320))])     # 315; 256 columns 336
+def test_a_larger_tile_has_to_promise_more_where_a_short_contraction_is_accumulated(M, N, K, takes):
+    assert plan(M, N, K, accumulate=True, workspace=True, decoded=3)[:2] == (TWO_PASS, takes)
+    if K == 512 and M == 7088:
+        assert plan(M, N, K, workspace=True, decoded=3)[:2] == (TWO_PASS, (320, 320))
+
+
 def test_a_scale_per_row_never_takes_320_rows():
     rng = random.Random(3)
     size = lambda: max(256, int(256 * 80 ** rng.random()) // 16 * 16)
