@@ -22,7 +22,11 @@ def tile(M, N, K, per_row):
     (1424, 13776, 320, False, (320, 320)), (3360, 12128, 256, False, (320, 320)), (2096, 19184, 320, False, (320, 320)),
     (1456, 10960, 320, False, (256, 320)), (6160, 5808, 256, False, (256, 320)), (2320, 14752, 320, True, (256, 320)),
     (1808, 15536, 256, False, (256, 256)), (3088, 3904, 320, False, (256, 224)), (2592, 9504, 256, False, (256, 224)),
-    (1664, 13584, 320, False, (256, 192)), (3872, 12704, 320, False, (256, 160))])
+    (1664, 13584, 320, False, (256, 192)), (3872, 12704, 320, False, (256, 160)),
+    # two stages of K (a workgroup per tile), and four, the shortest that run as one stream: all that is loaded ahead is the next tile's
+    (11328, 3216, 64, False, (256, 320)), (12848, 2848, 64, True, (256, 320)), (13888, 3216, 64, False, (320, 320)),
+    (12816, 1568, 128, False, (256, 320)), (5520, 5904, 128, False, (256, 320)), (6304, 5184, 128, True, (256, 320)),
+    (8464, 2832, 128, False, (320, 320)), (5424, 7648, 128, False, (320, 320))])
 def test_every_tile(M, N, K, per_row, takes):
     assert tile(M, N, K, per_row) == takes
     xb, wb = synth.normal_with_outliers(M, K, 1.0, 7400 + K, frac=0.01), synth.normal(N, K, 0.02, 7500 + N)
