@@ -653,13 +653,12 @@ static hipError_t launch_mx(Kernel kernel, PerDeviceOnce& once, int lds_bytes, c
 // to 120 products), so the width with the smallest rounds x time is taken, the wider one of up to 256 columns at a tie.  Over these products it takes 0.4 % more than the best one.
 // us per call at nb = 8 / 7 / 5 / 10: 4096 x 5120 x 5120 bf16 73.2 / 66.8 / 60.4 / 53.1, 5120 x 5120 x 4096 FP32 70.6 / 68.2 / 77.1 / 83.9, 2048 x 5120 x 5120 bf16 37.6 / 34.7 /
 // 32.2 / 42.2, 8192 x 20480 x 5120 bf16 421 / 450 / 474 / 401.  (320 rows x 160 or 256 columns: no better over them.)
-static int pick_mx_width(int64_t M, int64_t N, int widest) {
+static int pick_mx_width(int64_t M, int64_t N) {
   constexpr int kWidths[5] = {8, 7, 5, 4, 10};
   constexpr double kTime[5] = {1.0, 0.92, 0.75, 0.65, 1.19};
   int best = 8;
   double best_time = 0.0;
   for (int i = 0; i < 5; ++i) {
-    if (kWidths[i] > widest) continue;
     const int64_t tiles = ((M + TM - 1) / TM) * ((N + 32 * kWidths[i] - 1) / (32 * kWidths[i]));
     const double t = (tiles < 256 ? 0.9 : static_cast<double>((tiles + 255) / 256)) * kTime[i];
     if (i == 0 || t < best_time) {
@@ -687,7 +686,7 @@ hipError_t launch_gemm_mx(const GemmArgs& g, hipStream_t s) {
   // 16-byte pieces of scale rows need K / 32 to be a multiple of 16 and the scale arrays 16-byte aligned
   const bool wide = g.K % 512 == 0 && reinterpret_cast<uintptr_t>(g.a.scales) % 16 == 0 && reinterpret_cast<uintptr_t>(g.b.scales) % 16 == 0;
   if (wide) {
-    switch (pick_mx_width(g.a.outer, g.b.outer, 10)) {
+    switch (pick_mx_width(g.a.outer, g.b.outer)) {
       case 4: return launch_k512<4>(g, tiles_m, s);
       case 5: return launch_k512<5>(g, tiles_m, s);
       case 7: return launch_k512<7>(g, tiles_m, s);
@@ -703,7 +702,5 @@ hipError_t launch_gemm_mx(const GemmArgs& g, hipStream_t s) {
 
 }  // namespace nvfp4
 
-// For the tests, not part of the ABI: 32-column units of the tile that an MXFP4 product of these sizes takes where K is a multiple of 512, of those of up to 256 columns
-// and of all.
-extern "C" int nvfp4_internal_mx_gemm_units(int64_t M, int64_t N) { return nvfp4::pick_mx_width(M, N, 8); }
-extern "C" int nvfp4_internal_mx_gemm_width(int64_t M, int64_t N) { return nvfp4::pick_mx_width(M, N, 10); }
+// For the tests, not part of the ABI: 32-column units of the tile that an MXFP4 product of these sizes takes where K is a multiple of 512.
+extern "C" int nvfp4_internal_mx_gemm_width(int64_t M, int64_t N) { return nvfp4::pick_mx_width(M, N); }

@@ -29,9 +29,10 @@ def plan(M, N, K, bf16=False, accumulate=False, workspace=0, decoded=0, row_scal
     return out[0], (out[1], out[2]) if out[0] == TWO_PASS else out[1], out[3], out[4]
 
 
-def mx_units(M, N):
+def mx_columns(M, N):
+    """Of an MXFP4 product's tile where K is a multiple of 512."""
     i64 = ctypes.c_int64
-    return nv.load_library().nvfp4_internal_mx_gemm_units(i64(M), i64(N))
+    return 32 * nv.load_library().nvfp4_internal_mx_gemm_width(i64(M), i64(N))
 
 
 @pytest.mark.parametrize("M,N", [(2048, 2048), (2048, 8192), (5120, 20480), (4096, 5120), (8176, 1296)])
@@ -76,9 +77,9 @@ def test_large_products_take_the_two_pass_route(M, N, K, tile):
     assert plan(M, N, K, workspace=0)[0] in (FUSED_256, DIRECT)
 
 
-@pytest.mark.parametrize("M,N,units", [(8192, 20480, 8), (4096, 5120, 5), (5120, 5120, 7), (512, 5120, 4)])
-def test_mxfp4_tile_widths(M, N, units):
-    assert mx_units(M, N) == units
+@pytest.mark.parametrize("M,N,columns", [(8192, 20480, 320), (4096, 5120, 320), (5120, 5120, 224), (4096, 4096, 256), (2048, 5120, 160), (512, 5120, 128)])
+def test_mxfp4_tile_widths(M, N, columns):
+    assert mx_columns(M, N) == columns
 
 
 def test_accumulating_products_of_a_short_contraction_keep_a_wide_tile_unless_a_narrower_one_saves_rounds():

@@ -1,13 +1,12 @@
 """GPU parity of the MXFP4 GEMM in each of its tile widths, ragged at both edges, one tile per workgroup and several as one stream, over
 one, two and three chunks of scales, against the oracle's binary64 product."""
-import ctypes
-
 import numpy as np
 import pytest
 import torch
 
 import oracle
 from paper_2509_25149_amd import binding as nv, synth
+from test_gemm_routes import mx_columns
 from test_gpu_parity import GEMM_TOL, to_dev
 
 pytestmark = pytest.mark.gpu
@@ -17,8 +16,7 @@ pytestmark = pytest.mark.gpu
                                            (3104, 4288, 512, 256), (5216, 5440, 1024, 256), (3104, 4960, 512, 320), (4896, 3136, 1536, 320),
                                            (5664, 5696, 1024, 320)])
 def test_every_width(M, N, K, columns):
-    i64 = ctypes.c_int64
-    assert 32 * nv.load_library().nvfp4_internal_mx_gemm_width(i64(M), i64(N)) == columns
+    assert mx_columns(M, N) == columns
     ab, bb = synth.normal_with_outliers(M, K, 1.0, 940 + K, frac=0.01), synth.normal(N, K, 0.05, 941 + N)
     qa = nv.nvfp4_quantize(to_dev(ab), nv.LAYOUT_ROW, nv.BLOCK_MX32)
     qb = nv.nvfp4_quantize(to_dev(bb), nv.LAYOUT_ROW, nv.BLOCK_MX32)

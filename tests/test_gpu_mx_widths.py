@@ -1,4 +1,4 @@
-"""GPU parity of the MXFP4 GEMM's narrower tiles (K a multiple of 512), ragged at both edges and with workgroups that run
+"""GPU parity of the MXFP4 GEMM's tiles (K a multiple of 512), ragged at both edges and with workgroups that run
 several tiles as one stream, against the oracle's binary64 product."""
 import numpy as np
 import pytest
@@ -6,15 +6,17 @@ import torch
 
 import oracle
 from paper_2509_25149_amd import binding as nv, synth
+from test_gemm_routes import mx_columns
 from test_gpu_parity import GEMM_TOL, to_dev
 
 pytestmark = pytest.mark.gpu
 
 
-# 128, 160, 224 and 256 columns per tile: one tile each side of ragged; 512 / 460 tiles on 256 CUs; whole 256 x 256 tiles
-@pytest.mark.parametrize("M,N,K", [(288, 160, 512), (1056, 1056, 1536), (4064, 5088, 512), (2016, 5088, 1536), (5088, 5088, 512),
-                                   (4096, 4096, 1024)])
-def test_mx_gemm_widths(M, N, K):
+# one tile each side of ragged; 256 tiles, 460 on 256 CUs; whole 256 x 256 tiles
+@pytest.mark.parametrize("M,N,K,columns", [(288, 160, 512, 128), (1056, 1056, 1536, 128), (4064, 5088, 512, 320), (2016, 5088, 1536, 160), (5088, 5088, 512, 224),
+                                           (4096, 4096, 1024, 256)])
+def test_mx_gemm_widths(M, N, K, columns):
+    assert mx_columns(M, N) == columns
     ab, bb = synth.normal_with_outliers(M, K, 1.0, 930 + K, frac=0.01), synth.normal(N, K, 0.05, 931 + N)
     qa = nv.nvfp4_quantize(to_dev(ab), nv.LAYOUT_ROW, nv.BLOCK_MX32)
     qb = nv.nvfp4_quantize(to_dev(bb), nv.LAYOUT_ROW, nv.BLOCK_MX32)

@@ -7,7 +7,7 @@ import torch
 
 import oracle
 from paper_2509_25149_amd import binding as nv, synth
-from test_gemm_routes import mx_units
+from test_gemm_routes import mx_columns
 
 pytestmark = pytest.mark.gpu
 RHT_SEED, SR_SEED = 20250929, 0xC0FFEE
@@ -114,12 +114,12 @@ def test_mx_gemm_all_ops(mnk):
 
 
 @pytest.mark.parametrize("K", [512, 1536])
-@pytest.mark.parametrize("M,N,units", [(4128, 4384, 5), (4064, 8160, 8)])
-def test_mx_gemm_with_more_tiles_than_compute_units(M, N, units, K):
-    """17 x 28 tiles of 256 x 160 and 16 x 32 of 256 x 256, the last row and column of them ragged: the kernel for K % 512 == 0 is
-    launched with one workgroup per CU, which runs two tiles as one stream of stages (K = 512: one scale chunk per tile, the
-    shortest tile; K = 1536: an odd number of chunks, so the scale ring's phase differs from tile to tile)."""
-    assert mx_units(M, N) == units
+@pytest.mark.parametrize("M,N,columns", [(4896, 3872, 160), (4640, 4192, 224), (4064, 8160, 256), (5920, 5408, 320)])
+def test_mx_gemm_with_more_tiles_than_compute_units(M, N, columns, K):
+    """500 tiles of 256 x 160, 361 of 256 x 224, 512 of 256 x 256 and 408 of 256 x 320, the last row and column of them ragged: the kernel for K % 512 == 0 is
+    launched with one workgroup per CU, which runs up to two tiles as one stream of stages (K = 512: one scale chunk per tile, the
+    shortest tile; K = 1536: an odd number of chunks)."""
+    assert mx_columns(M, N) == columns and -(-M // 256) * -(-N // columns) > 256
     ab = synth.normal_with_outliers(M, K, 1.0, 920 + K, frac=0.01)
     bb = synth.normal(N, K, 0.05, 921 + K)
     qa = nv.nvfp4_quantize(to_dev(ab), nv.LAYOUT_ROW, nv.BLOCK_MX32)
