@@ -367,9 +367,10 @@ __global__ __launch_bounds__(kThreads) void gemm_f16_kernel(const _Float16* __re
       });
       // Memory operations complete in issue order.  Behind the loads of stage g + 1 this wavefront has issued those of
       // g + 2 and g + 3, kLoads each, and, across a tile boundary, the stores of the tile before.
-      if (kRelaxed && stores_behind)
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * kLoads + kTileStores<kBf16Out, kMB, kNB> > 63 ? 63 : 2 * kLoads + kTileStores<kBf16Out, kMB, kNB>) : "memory");
-      else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * kLoads) : "memory");
+      // (The reads are waited for on every path, whatever is known of the stores.)
+      constexpr int kBehind = 2 * kLoads + (kRelaxed ? kTileStores<kBf16Out, kMB, kNB> : 0);
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(kBehind > 63 ? 63 : kBehind) : "memory");
+      if (kRelaxed && !stores_behind) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kLoads) : "memory");
       __builtin_amdgcn_s_barrier();
       // The loads move on one stage: within the tile, or to the next tile's stage 0, or, with nothing to follow, not at
       // all (the last stage is fetched again, into a buffer nobody reads any more: no branches around the loads).

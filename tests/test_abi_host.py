@@ -263,7 +263,7 @@ def test_no_kernel_keeps_arrays_in_scratch_memory():
     res = json.load(open(build.RESOURCES))
     assert len(res) >= 60
     strict = ("quantize_mx_kernel", "cast_kernel", "amax_kernel", "cast_small", "amax_small", "cast_wide", "amax_wide", "decode_f16", "dequantize", "rowscale_",
-              "gemm_f16_kernel", "gemm_direct_kernel")
+              "gemm_f16_kernel", "gemm_direct_kernel", "gemm_direct_pair_kernel")
     for k in strict + ("splitk_sum", "gemm_mx_kernel"):
         assert any(k in name for name in res), k
     for name, r in res.items():

@@ -87,6 +87,23 @@ def early_mfmas(instructions):
     return bad
 
 
+def touched_in_flight(instructions):
+    """Instructions that read or write a register into which an LDS read may still be on its way.  Reads come back in order, so a wait for
+    all but n operations leaves at most the n latest reads (others that are counted with them, scalar loads, can only make that fewer)."""
+    bad = set()
+
+    def step(pending, x):
+        op, operands, writes, reads = x
+        bad.update((op, operands) for into in pending if into & (writes | reads))
+        if op.startswith("ds_read"):
+            return pending + (writes,)
+        waits = re.search(r"lgkmcnt\((\d+)\)", operands) if op == "s_waitcnt" else None
+        return pending[max(0, len(pending) - int(waits.group(1))):] if waits else pending
+
+    paths(instructions, step, ())
+    return bad
+
+
 @pytest.fixture(scope="module")
 def listings(tmp_path_factory):
     if not os.path.exists(HIPCC):
@@ -119,6 +136,31 @@ def test_the_search_for_early_mfmas_finds_them():
     assert not early_mfmas(made_up("v_perm_b32 v22, v1, v2, v3", mfma))
     # around a loop's back edge
     assert early_mfmas(made_up(".LBB0_1:", mfma, "s_nop 3", perm, "s_cbranch_scc0 .LBB0_1"))
+
+
+def test_the_search_for_reads_in_flight_finds_them():
+    read, use = "ds_read_b128 v[4:7], v1 offset:16", "v_mfma_f32_16x16x32_f16 a[0:3], v[4:7], v[8:11], 0"
+    assert touched_in_flight(made_up(read, use))
+    assert touched_in_flight(made_up(read, "v_mov_b32_e32 v6, v0"))
+    assert not touched_in_flight(made_up(read, "s_waitcnt lgkmcnt(0)", use))
+    later = "ds_read_b128 v[12:15], v1"
+    assert not touched_in_flight(made_up(read, later, "s_waitcnt vmcnt(3) lgkmcnt(1)", use))
+    assert touched_in_flight(made_up(later, read, "s_waitcnt lgkmcnt(1)", use))
+    assert touched_in_flight(made_up(read, "s_waitcnt vmcnt(0)", use))
+    # a wait on one of two ways, and a use on the way back through a loop
+    assert touched_in_flight(made_up(read, "s_cbranch_scc0 .LBB0_1", "s_waitcnt lgkmcnt(0)", ".LBB0_1:", use))
+    assert touched_in_flight(made_up(".LBB0_1:", "v_mov_b32_e32 v20, v7", "s_waitcnt lgkmcnt(0)", read, "s_cbranch_scc0 .LBB0_1"))
+
+
+@pytest.mark.parametrize("name", FILES)
+def test_no_instruction_touches_a_register_that_an_lds_read_is_on_its_way_to(listings, name):
+    """Fragment reads are in flight across the halves of a stage and the loop's back edge; the waits are not tied to the registers, so a copy or a
+    spill that the compiler put there would take old values without a message."""
+    checked = 0
+    for kernel, instructions in listings[name].items():
+        checked += sum(x[0].startswith("ds_read") for x in instructions)
+        assert not touched_in_flight(instructions), kernel
+    assert checked > 500
 
 
 @pytest.mark.parametrize("name", FILES)
