@@ -319,9 +319,11 @@ uint32_t nvfp4_rht_sign_mask(uint64_t rht_seed);
  * mismatches: DEVICE pointer to uint64[5], zeroed by the caller; the kernels
  * add their mismatch counts: [0] FP32->E2M1 RNE over all 2^32 bit patterns,
  * [1] FP32->E2M1 SR over a grid of values x all 2^16 random values (the plain
- * and the accumulating form of the conversion),
+ * and the accumulating form of the conversion), both divided by every power of
+ * two that the conversions can be given, over a sample of values,
  * [2] FP32->E4M3 (and back) over all non-negative finite patterns,
- * [3] the division-free x/6, and the MXFP4 block scale without one, against IEEE division over the same patterns,
+ * [3] the division-free x/6, and the MXFP4 block scale without one, against IEEE division over the same patterns
+ * and infinity,
  * [4] FP32->bf16 (the GEMM and dequantize outputs) over all finite patterns.
  * Asynchronous like every other call.
  */

@@ -90,7 +90,7 @@ __device__ __forceinline__ float div_by_6(float x) { return static_cast<float>(s
 
 // MXFP4: fl(amax_b / 6) rounded up to a power of two 2^e, e clamped to [-127, 127] (App. B.4): the stored byte e + 127.  The rounded quotient is at most 2^e exactly
 // where amax_b is at most 1.5 x 2^(e + 2), so the byte is amax_b's exponent, one more where its significand exceeds 1.5, less 2.  (Two inputs are
-// exceptions, by comparison over all patterns (the self-test): one whose quotient rounds down to the subnormal 2^-127, and infinity.)
+// exceptions, by comparison over all non-negative patterns (the self-test): one whose quotient rounds down to the subnormal 2^-127, and infinity.)
 __device__ __forceinline__ uint32_t ue8m0_scale(float amax_b) {
   const uint32_t bits = __float_as_uint(amax_b);
   const uint32_t up = bits >= 0x7F800000u ? 256u : (bits - (bits == 0x01400001u) + 0x3FFFFFu) >> 23;
@@ -119,8 +119,8 @@ __device__ __forceinline__ uint32_t any_word(float near) {
 
 // Two scaled values, divided by `scale`, -> one byte of two E2M1 codes written into byte `kSel`
 // of `old` (round to nearest even, saturating; matches the tie rule "even
-// code").  The instruction divides by a power of two, exactly: of its scale operand only the exponent field e counts, as 2^(e - 127), e = 0 included (checked
-// for all 255 fields against products with the exact factor, subnormal values too).
+// code").  The instruction divides by a power of two, exactly: of its scale operand only the exponent field e counts, as 2^(e - 127), e = 0 included (the self-test:
+// all 255 fields, 2^16 values each, subnormal ones too, against conversions of the exact quotient).
 template <int kSel>
 __device__ __forceinline__ uint32_t cvt_rne_pair(uint32_t old, float v0, float v1, float scale = 1.0f) {
   return __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(old, v0, v1, scale, kSel);

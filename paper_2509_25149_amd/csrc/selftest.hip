@@ -91,6 +91,31 @@ __global__ __launch_bounds__(256) void selftest_sr_kernel(unsigned long long* ba
   if (local) atomicAdd(bad, local);
 }
 
+// The conversions' division by a power of two: every exponent field e of the scale operand (0 .. 254: 2^(e - 127)) and values whose quotient lies in [2^-24, 2^9), 2^16 of
+// them per field, subnormal ones among them where e is small, against the plain conversion of the quotient, which is exact (in binary64 first); the literal divisors alike.
+__global__ __launch_bounds__(256) void selftest_scale_kernel(unsigned long long* bad_rne, unsigned long long* bad_sr) {
+  unsigned long long rne = 0, sr = 0;
+  const uint32_t stride = gridDim.x * blockDim.x;
+  for (uint32_t w = blockIdx.x * blockDim.x + threadIdx.x; w < 255u << 16; w += stride) {
+    const uint32_t e = w >> 16, hash = w * 0x9E3779B1u, rand_hi16 = (w ^ hash) << 16;
+    const int field = min(max(static_cast<int>(e) + static_cast<int>(w % 33u) - 24, 0), 254);
+    const float v = __uint_as_float((hash & 0x807FFFFFu) | static_cast<uint32_t>(field) << 23);
+    const float quotient = static_cast<float>(static_cast<double>(v) * exp2(static_cast<double>(127 - static_cast<int>(e))));
+    const float scale = conversion_scale(e);
+    rne += (cvt_rne_pair<0>(0u, v, -v, scale) & 0xFFu) != (cvt_rne_pair<0>(0u, quotient, -quotient) & 0xFFu);
+    uint32_t divided = 0u, plain = 0u;
+    cvt_sr_single_into<1>(divided, v, rand_hi16, scale);
+    cvt_sr_single_into<1>(plain, quotient, rand_hi16);
+    sr += ((divided ^ plain) & 0xF00u) != 0u;
+    uint32_t half = 0u, quarter = 0u;
+    cvt_sr_single_into<1, 2>(half, 2.0f * quotient, rand_hi16);
+    cvt_sr_single_into<1, 4>(quarter, 4.0f * quotient, rand_hi16);
+    sr += (((half ^ plain) | (quarter ^ plain)) & 0xF00u) != 0u;
+  }
+  if (rne) atomicAdd(bad_rne, rne);
+  if (sr) atomicAdd(bad_sr, sr);
+}
+
 __global__ __launch_bounds__(256) void selftest_e4m3_kernel(unsigned long long* bad) {
   unsigned long long local = 0;
   const uint64_t stride = static_cast<uint64_t>(gridDim.x) * blockDim.x;
@@ -122,12 +147,12 @@ __global__ __launch_bounds__(256) void selftest_bf16_kernel(unsigned long long* 
 __global__ __launch_bounds__(256) void selftest_div6_kernel(unsigned long long* bad) {
   unsigned long long local = 0;
   const uint64_t stride = static_cast<uint64_t>(gridDim.x) * blockDim.x;
-  for (uint64_t w = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x; w < 0x7F800000ull; w += stride) {
+  for (uint64_t w = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x; w <= 0x7F800000ull; w += stride) {
     const float x = __uint_as_float(static_cast<uint32_t>(w));
     const uint32_t q = __float_as_uint(x / 6.0f);
     local += __float_as_uint(div_by_6(x)) != q;
-    // the MXFP4 scale byte: the quotient rounded up to a power of two, 2^-127 at the least
-    const uint32_t up = q >= 0x00800000u ? (q >> 23) + ((q & 0x7FFFFFu) != 0) : q > 0x400000u;
+    // the MXFP4 scale byte: the quotient rounded up to a power of two, 2^-127 at the least and 2^127 at the most (of infinity)
+    const uint32_t up = q >= 0x00800000u ? min((q >> 23) + ((q & 0x7FFFFFu) != 0), 254u) : q > 0x400000u;
     local += ue8m0_scale(x) != up;
   }
   if (local) atomicAdd(bad, local);
@@ -139,6 +164,7 @@ hipError_t run_selftest(uint64_t* mismatches_dev, hipStream_t s) {
   unsigned long long* dev = reinterpret_cast<unsigned long long*>(mismatches_dev);
   hipLaunchKernelGGL(selftest_rne_kernel, dim3(4096), dim3(256), 0, s, dev + 0);
   hipLaunchKernelGGL(selftest_sr_kernel, dim3(0x40E1u * 5u), dim3(256), 0, s, dev + 1);
+  hipLaunchKernelGGL(selftest_scale_kernel, dim3(4096), dim3(256), 0, s, dev + 0, dev + 1);
   hipLaunchKernelGGL(selftest_e4m3_kernel, dim3(4096), dim3(256), 0, s, dev + 2);
   hipLaunchKernelGGL(selftest_div6_kernel, dim3(4096), dim3(256), 0, s, dev + 3);
   hipLaunchKernelGGL(selftest_bf16_kernel, dim3(4096), dim3(256), 0, s, dev + 4);
