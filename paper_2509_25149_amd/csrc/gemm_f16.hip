@@ -526,7 +526,7 @@ struct Width {
 };
 // A product that is accumulated into its result takes longer over the result the more tiles there are (5120 x 20480, K = 64 / 256 / 512: nb = 8
 // 283 / 299 / 333, nb = 5 306 / 313 / 345): there a narrower tile has to promise 4 % while K is short (`reluctant`; no last round is split
-// then, so the sums are the same).
+// then, so the sums are the same), and a larger one more (promise_needed; 320 x 320 there 287 / 293 / 315).
 static Width pick_width(int64_t M, int64_t N, const TailPlan& p, bool reluctant) {
   constexpr double kTime[4] = {1.0, 0.90, 0.80, 0.68};
   const int64_t tiles_m = (M + TM - 1) / TM;
