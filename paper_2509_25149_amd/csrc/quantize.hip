@@ -285,8 +285,13 @@ size_t quantize_workspace_bytes(int64_t rows, int64_t cols) {
 // The others in strips of 8 tiles across, walked downwards, an eighth of the sequence to each XCD: a tile leaves 16 bytes of a row's scales, 8 bytes of a column's and
 // 64 of its codes, which fill lines of 128 together with neighbours to the side and below; from workgroups all over the chip each L2 has its part of such a line and writes it
 // by itself (without the scales W took 6 us less, with them as non-temporal stores 9 to 30 more).  W 5120 x 20480 85.8 -> 82.8 us, 5136 x 20496 125 -> 117, X 4096 x 5120
-// 28.5 -> 27.7, dY 8208 x 16400 186 -> 180, the row copy alone 8192 x 20480 122 -> 117; strips of 4 alike, of 16 84.4 for the first.  Not both copies of an aligned tensor above 256 MB,
-// which the cache holds in part, its last rows: X 8192 x 20480 150 -> 159.
+// 28.5 -> 27.7, dY 8208 x 16400 186 -> 180, the row copy alone 8192 x 20480 122 -> 117; strips of 4 alike, of 16 84.4 for the first.
+// Some aligned tensors along their rows all the same (along_rows_pays): the cache holds the last rows of a tensor somewhat larger than itself, and where the tiles across are a
+// multiple of 8 (of 4, of 2) an XCD meets every (every second, every fourth) tile of a column that way too.  us, along the rows / in strips: both copies above 256 MB, X 8192 x 20480 150 / 159.
+// One copy of a tensor whose amax is given, which has not just been read: the row copy above 256 MB (163 sizes: 1.09 times the time in strips; 9216 x 19968 86 / 97, 3840 x 65792 114 / 189), with
+// stochastic rounding any (227: 0.99 if the tensor is in the cache, 1.035 if not; 4352 x 10496 48.4 / 50.4); the col copy up to 256 MB with a multiple of 4 tiles across (111: 1.014, 1.04; 13312 x
+// 6144 47.6 / 51.1).  The col copy of 256 to 384 MB, taller than wide, with an even number of tiles across (118: 1.058; 79616 x 2048 119 / 143, 14080 x 12288 125 / 134) or stochastic
+// rounding (76: 1.025; 39680 x 3840 138 / 144); an odd number of tiles 0.967 (19456 x 9984 166 / 155), wider than tall 0.94.
 constexpr int64_t kCacheBytes = int64_t{256} << 20;
 static bool lines_aligned(const QuantizeArgs& a) { return a.ld % 64 == 0 && reinterpret_cast<uintptr_t>(a.x) % 128 == 0; }
 static CastMemory cast_memory(const QuantizeArgs& a) {
@@ -295,10 +300,19 @@ static CastMemory cast_memory(const QuantizeArgs& a) {
   if (!a.do_amax) return bytes > kCacheBytes ? kStreamedLoadsCachedStores : kCachedLoads;
   return bytes > kCacheBytes / 16 * 19 ? kStreamedLoads : kCachedLoads;
 }
+// Of an aligned tensor.
+static bool along_rows_pays(const QuantizeArgs& a) {
+  using T = CastTile<kCachedLoads>;   // the tile is the same for all
+  const int64_t bytes = a.rows * a.cols * 2, across = (a.cols + T::kCols - 1) / T::kCols;
+  const bool large = bytes > kCacheBytes;
+  if (a.want_row && a.want_col) return large;
+  if (a.do_amax) return a.want_col && large && bytes <= kCacheBytes / 2 * 3 && a.rows > a.cols && (across % 2 == 0 || a.sr);
+  return a.want_row ? large || a.sr : !large && across % 4 == 0;
+}
 static int cast_walk(const QuantizeArgs& a) {
   const bool reverse = a.do_amax && a.rows * a.cols * 2 > kCacheBytes / 2 && cast_memory(a) == kCachedLoads;
   const bool bands = !a.want_col && !lines_aligned(a) && a.rows >= 1024;
-  const bool strips = !bands && !(a.want_row && a.want_col && lines_aligned(a) && cast_memory(a) != kCachedLoads);
+  const bool strips = !bands && !(lines_aligned(a) && along_rows_pays(a));
   return (reverse ? kWalkReverse : 0) | (bands ? kWalkBands : strips ? kWalkStrips : 0);
 }
 
@@ -405,19 +419,21 @@ hipError_t launch_quantize(const QuantizeArgs& a, hipStream_t s) {
 
 }  // namespace nvfp4
 
-// For the tests, not part of the ABI: which kernels nvfp4_quantize takes for a contiguous tensor of these sizes (1x16 or 16x16 blocks, rotation up to 16, one scale
-// per tensor; rotated: the col copy is).  out: cast pass (0 cast_kernel, 1 cast_small_kernel), amax pass (likewise), cast_kernel's walk (kWalkReverse | kWalkBands | kWalkStrips), sets of its workgroups,
+// For the tests, not part of the ABI: which kernels nvfp4_quantize takes for a contiguous tensor of these sizes (rotation up to 16, one scale
+// per tensor; rotated: the col copy is; options: 1 16x16 blocks, 2 stochastic rounding, 4 the amax given).  out: cast pass (0 cast_kernel, 1 cast_small_kernel), amax pass (likewise), cast_kernel's walk (kWalkReverse | kWalkBands | kWalkStrips), sets of its workgroups,
 // log2 of amax_kernel's lanes across.
-extern "C" void nvfp4_internal_quantize_plan(int64_t rows, int64_t cols, int want_row, int want_col, int rotated, int block2d, int* out) {
+extern "C" void nvfp4_internal_quantize_plan(int64_t rows, int64_t cols, int want_row, int want_col, int rotated, int options, int* out) {
   using namespace nvfp4;
   QuantizeArgs a{};
   a.rows = rows;
   a.cols = a.ld = cols;
   a.want_row = want_row;
   a.want_col = want_col;
-  a.block2d = block2d;
+  a.block2d = options & 1;
+  a.sr = options & 2;
   a.rht_dim = rotated ? 16 : 0;
-  a.do_amax = a.do_cast = true;
+  a.do_amax = !(options & 4);
+  a.do_cast = true;
   out[0] = use_cast_small(a);
   out[1] = use_amax_small(a);
   out[2] = cast_walk(a);

@@ -18,3 +18,20 @@ def test_walk(rows, cols, layout, walk):
     out, i64 = (ctypes.c_int * 5)(), ctypes.c_int64
     nv.load_library().nvfp4_internal_quantize_plan(i64(rows), i64(cols), layout & nv.LAYOUT_ROW, layout & nv.LAYOUT_COL, 0, 0, out)
     assert out[2] == walk
+
+
+SR, GIVEN = 2, 4   # stochastic rounding; the amax given
+
+
+# Aligned tensors that take longer in strips than along their rows: one copy whose amax is given, a tall col copy somewhat larger than the memory-side cache
+@pytest.mark.skipif(not os.path.exists(nv.LIB_PATH), reason="libnvfp4_hip.so not built")
+@pytest.mark.parametrize("rows,cols,layout,options,walk", [
+    (9216, 19968, nv.LAYOUT_ROW, GIVEN, 0), (3840, 65792, nv.LAYOUT_ROW, GIVEN | SR, 0), (8192, 16384, nv.LAYOUT_ROW, GIVEN, 4), (8192, 16384, nv.LAYOUT_ROW, GIVEN | SR, 0),
+    (13312, 6144, nv.LAYOUT_COL, GIVEN, 0), (13312, 6400, nv.LAYOUT_COL, GIVEN, 4), (8192, 20480, nv.LAYOUT_COL, GIVEN, 4), (13312, 6144, RC, GIVEN, 4),
+    (8192, 20480, RC, GIVEN, 0), (79616, 2048, nv.LAYOUT_COL, 0, 0), (14080, 12288, nv.LAYOUT_COL, 0, 0), (13792, 12160, nv.LAYOUT_COL, 0, 0),
+    (19456, 9984, nv.LAYOUT_COL, 0, 4), (19456, 9984, nv.LAYOUT_COL, SR, 0), (39680, 3840, nv.LAYOUT_COL, SR, 0), (39680, 3840, nv.LAYOUT_COL, 0, 4),
+    (12288, 14080, nv.LAYOUT_COL, 0, 4), (65536, 2048, nv.LAYOUT_COL, 0, 1 | 4), (102400, 2048, nv.LAYOUT_COL, 0, 4)])
+def test_walk_of_tensors_that_strips_slow_down(rows, cols, layout, options, walk):
+    out, i64 = (ctypes.c_int * 5)(), ctypes.c_int64
+    nv.load_library().nvfp4_internal_quantize_plan(i64(rows), i64(cols), layout & nv.LAYOUT_ROW, layout & nv.LAYOUT_COL, 0, options, out)
+    assert out[2] == walk
