@@ -653,6 +653,8 @@ static hipError_t launch_mx(Kernel kernel, PerDeviceOnce& once, int lds_bytes, c
 // to 120 products), so the width with the smallest rounds x time is taken, the wider one of up to 256 columns at a tie.  Over these products it takes 0.4 % more than the best one.
 // us per call at nb = 8 / 7 / 5 / 10: 4096 x 5120 x 5120 bf16 73.2 / 66.8 / 60.4 / 53.1, 5120 x 5120 x 4096 FP32 70.6 / 68.2 / 77.1 / 83.9, 2048 x 5120 x 5120 bf16 37.6 / 34.7 /
 // 32.2 / 42.2, 8192 x 20480 x 5120 bf16 421 / 450 / 474 / 401.  (320 rows x 160 or 256 columns: no better over them.)
+// 320 columns have to promise 2 %: five rounds of them in the place of six of 256, 0.8 % less by this estimate, took 1.02 times the time over 32 products (6656 x 14240 x 3584 bf16 186 us, 256
+// columns 166; 9600 x 9216 x 6656 290 / 273); where they promise more, 0.94 over 368.
 static int pick_mx_width(int64_t M, int64_t N) {
   constexpr int kWidths[5] = {8, 7, 5, 4, 10};
   constexpr double kTime[5] = {1.0, 0.92, 0.75, 0.65, 1.19};
@@ -661,7 +663,7 @@ static int pick_mx_width(int64_t M, int64_t N) {
   for (int i = 0; i < 5; ++i) {
     const int64_t tiles = ((M + TM - 1) / TM) * ((N + 32 * kWidths[i] - 1) / (32 * kWidths[i]));
     const double t = (tiles < 256 ? 0.9 : static_cast<double>((tiles + 255) / 256)) * kTime[i];
-    if (i == 0 || t < best_time) {
+    if (i == 0 || t < (kWidths[i] == 10 ? 0.98 : 1.0) * best_time) {
       best = kWidths[i];
       best_time = t;
     }

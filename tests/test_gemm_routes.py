@@ -82,6 +82,12 @@ def test_mxfp4_tile_widths(M, N, columns):
     assert mx_columns(M, N) == columns
 
 
+@pytest.mark.parametrize("M,N,columns", [(6656, 14240, 256), (9600, 9216, 256), (7328, 11712, 256),     # five rounds of 320 columns, six of 256: 186 / 166 us at K = 3584
+                                         (13824, 12672, 320), (8160, 4992, 320), (4608, 4224, 320)])      # nine and ten; three of 224; two of 160
+def test_mxfp4_widest_tile_has_to_promise_more_than_one_percent(M, N, columns):
+    assert mx_columns(M, N) == columns
+
+
 def test_accumulating_products_of_a_short_contraction_keep_a_wide_tile_unless_a_narrower_one_saves_rounds():
     """1620 tiles of 256 columns are 7 rounds, 2538 of 160 columns 10 of 0.68: 3 % less, not enough where the result is read too."""
     M, N, K = 13776, 7472, 512
