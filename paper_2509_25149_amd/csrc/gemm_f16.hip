@@ -613,7 +613,7 @@ struct TileChoice {
 static TileChoice choose_tile(int64_t M, int64_t N, int64_t K, bool row_scales, bool accumulate, const TailPlan& tail) {
   Width w = pick_width(M, N, tail, false);
   Tile t = pick_tile(M, N, K, w, tail, row_scales, false);
-  const double us = w.rounds * (9.2 + static_cast<double>(K) * (w.tiles >= kCUs ? 0.0186 : 0.0159)) * (K > 1024 ? t.gain : 1.0);
+  const double us = w.rounds * (9.2 + static_cast<double>(K) * (w.tiles >= kCUs ? 0.0186 : 0.0159)) * (K > 1536 && K <= 4096 ? t.gain : 1.0);
   if (accumulate && K < 1024) {
     w = pick_width(M, N, tail, true);
     t = pick_tile(M, N, K, w, tail, row_scales, true);
@@ -635,10 +635,12 @@ size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) {
 
 // What a call does: one answer for the estimate, the room asked of the workspace and the launch.
 // Expected time: what is still to decode (codes and scales in, FP16 out) at 5.0 TB/s, then rounds of 256 tiles at 9.2 us for the result and 15.9 ns
-// per k while there are fewer, 18.6 when the chip is full (the clock drops with the matrix pipes busy), times what a larger tile gains, where the contraction is more of the
-// work than storing the result (4112 x 4368 x 128: 256 x 320 tiles take 0.98 of the best others' time, by fewer rounds 0.8) -- of a plain result,
-// for all output types (see SmallTileCost).  It is what the choice among the kernels is fitted with; estimates nearer to the measured times of this route took it where the
-// direct kernel is up to 20 % faster (18.8 us for this product, 22.6 here).
+// per k while there are fewer, 18.6 when the chip is full (the clock drops with the matrix pipes busy), times what a larger tile gains where the contraction is more of the
+// work than storing the result (4112 x 4368 x 128: 256 x 320 tiles take 0.98 of the best others' time, by fewer rounds 0.8) and not so long that the direct kernel's estimate is stretched
+// already (plan_route).  Were it to count from K = 1024 on, 82 of 60000 drawn products would leave the direct kernel for it; time there over that in the larger tiles, FP32 / bf16 / accumulated:
+// K up to 1536 (56 of them) 0.97 / 1.05 / 0.91 (11648 x 1328 x 1152 accumulated 53 us / 68), up to 4096 (19) 1.04 / 1.11 / 1.00, above (7) 0.94 / 0.96 / 0.88.  All of it is of a plain result, for all output
+// types (see SmallTileCost), and what the choice among the kernels is fitted with; estimates nearer to the measured times of this route took it where the
+// direct kernel is up to 20 % faster (18.8 us for 4112 x 4368 x 128, 22.6 here).
 TwoPassPlan plan_two_pass(const GemmArgs& g) {
   TwoPassPlan plan{false, HUGE_VAL, 8, 8, 0, 1};
   const int64_t M = g.a.outer, N = g.b.outer;

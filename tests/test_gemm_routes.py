@@ -82,6 +82,15 @@ def test_mxfp4_tile_widths(M, N, columns):
     assert mx_columns(M, N) == columns
 
 
+# us in the direct kernel / two-pass, accumulated
+@pytest.mark.parametrize("M,N,K,route", [(11648, 1328, 1152, DIRECT),      # 53 / 68
+                                         (1344, 11248, 1280, DIRECT), (896, 17280, 8960, DIRECT),
+                                         (864, 17504, 2496, TWO_PASS)])    # 1.13 to 1.26 times as fast as the direct kernel
+def test_what_a_larger_tile_gains_counts_for_the_route_in_contractions_of_1536_to_4096(M, N, K, route):
+    for accumulate in (False, True):
+        assert plan(M, N, K, accumulate=accumulate, workspace=True)[0] == route
+
+
 @pytest.mark.parametrize("M,N,columns", [(6656, 14240, 256), (9600, 9216, 256), (7328, 11712, 256),     # five rounds of 320 columns, six of 256: 186 / 166 us at K = 3584
                                          (13824, 12672, 320), (8160, 4992, 320), (4608, 4224, 320)])      # nine and ten; three of 224; two of 160
 def test_mxfp4_widest_tile_has_to_promise_more_than_one_percent(M, N, columns):
